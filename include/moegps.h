@@ -198,6 +198,8 @@ int moe_pack_weights(const void* W1, const void* W3, const void* W2, int dtype,
  * bf16: products accumulate in fp32, the hidden activation is rounded to bf16 between the
  * two products, the output is rounded to bf16.  SwiGLU uses the hardware exponential and
  * reciprocal instructions (about 1 ulp each, far below the bf16 rounding that follows).
+ * With a few rows per expert a product's sums are taken as up to eight parts of the contracted
+ * width, added in a fixed order in fp32.
  * When the second product has only a few tiles per workgroup, its closing tiles are summed as
  * up to four parts of the hidden width (fp32 partial sums held in the workspace, added in the
  * order of the parts, then rounded once); the result does not depend on launch order.
@@ -245,12 +247,16 @@ int moe_grouped_ffn_gather(const void* x, int dtype, int T, int k, const int32_t
  *   MOE_FFN_OPT_SPLIT_K        closing tiles of the second product as parts of K:
  *                              -1 automatic, 0 never, 1 whenever the shapes allow
  *   MOE_FFN_OPT_GROUP_N        N-tiles walked side by side under one run of M-tiles, 0 automatic
+ *   MOE_FFN_OPT_STREAM         weight-streaming kernels for a few rows per expert: -1 automatic,
+ *                              0 never, 1 / 2 their first / second form (a forced tile shape or more
+ *                              than 65536 rows comes first)
  * Returns MOE_ERR_INVALID_ARG for an unknown option or a value out of range.
  */
 #define MOE_FFN_OPT_TILE1    0
 #define MOE_FFN_OPT_TILE2    1
 #define MOE_FFN_OPT_SPLIT_K  2
 #define MOE_FFN_OPT_GROUP_N  3
+#define MOE_FFN_OPT_STREAM   4
 int moe_grouped_ffn_set_option(int option, int value);
 
 /*

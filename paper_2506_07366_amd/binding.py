@@ -337,7 +337,7 @@ def moe_grouped_ffn_gather(x: torch.Tensor, assign_of_row: torch.Tensor, k: int,
     return y
 
 
-FFN_OPT_TILE1, FFN_OPT_TILE2, FFN_OPT_SPLIT_K, FFN_OPT_GROUP_N = 0, 1, 2, 3
+FFN_OPT_TILE1, FFN_OPT_TILE2, FFN_OPT_SPLIT_K, FFN_OPT_GROUP_N, FFN_OPT_STREAM = 0, 1, 2, 3, 4
 
 
 def moe_grouped_ffn_set_option(option: int, value: int) -> None:

@@ -7,10 +7,10 @@
 //   GEMM-1: H[A, ffn]  = swiglu( X[A, d] * [W1|W3]_e )    (gate/up columns interleaved
 //           by 32 in the packed weights, so the SwiGLU happens on the accumulators)
 //   GEMM-2: Y[A, d]    = H[A, ffn] * W2_e
-// Packed weights are stored "column-major" ([N][K], K contiguous), the same shape
-// as the activations, so both operands stream as K-contiguous 16-byte pieces
-// straight from global memory into LDS (global_load_lds_dwordx4) and feed
-// v_mfma_f32_16x16x32_bf16 fragments with one ds_read_b128 each.
+// Packed weights are stored transposed and by MFMA fragment (see packed_index), activations
+// by row; both stream as K-contiguous 16-byte pieces straight from global memory into LDS
+// (global_load_lds_dwordx4) and feed v_mfma_f32_16x16x32_bf16 fragments with one ds_read_b128
+// each.  With a few rows per expert the weights go past LDS into registers (ffn_stream.h).
 //
 // Rows are tiled by EXPERT, not by segment: replicas of an expert hold the same
 // weights, so the rows of all its segments in the launched slot range are listed
@@ -51,7 +51,8 @@ struct MTile {
     int kt0;     // k-tiles [kt0, kt1) of the product belong to this entry; kt1 == 0: all of them
     int kt1;
     int part;    // < 0: results go to the output; else fp32 partial sums go to slab `part`
-    int pad0, pad1;
+    int first;   // whole tiles: the expert's whole tiles are the entries [first, first + n_same)
+    int n_same;
 };
 // An M-tile whose K range is split, for the pass that adds up the partial sums
 struct SplitInfo {
@@ -71,46 +72,68 @@ constexpr int kCntEntries = 0, kCntPass0 = 1, kCntPass1 = 2, kCntSplit = 3, kCnt
 // ---------------------------------------------------------------------------
 // The packed form of a weight matrix is what the GEMM's loads want to find: the transposed
 // matrix W^T [N_out][K_out] cut into tiles of kPackN rows by kPackK columns, tiles of one
-// row block side by side along K, every tile 32 KiB in one piece and laid out exactly as
-// it sits in LDS (row r, 16-byte piece c of the row at piece c ^ swz(r)).  A k-tile of a
-// weight panel is then one contiguous read instead of 256 pieces of 128 bytes a row apart,
-// which the memory system serves a quarter slower at some row lengths (8 KiB among them).
+// row block side by side along K, every tile 32 KiB in one piece.  Inside a tile the matrix is
+// stored by MFMA fragment: the 16 rows x 32 columns one v_mfma_f32_16x16x32_bf16 takes are
+// 1 KiB in one piece, in lane order (lane 16*q + r holds row r, columns 8q .. 8q+7), the two
+// fragments of a 16-row group along K side by side.  So
+//   - a k-tile of a weight panel is one contiguous read instead of 256 pieces of 128 bytes a row
+//     apart, which the memory system serves a quarter slower at some row lengths (8 KiB among
+//     them), and goes to LDS as it comes;
+//   - a fragment in LDS is read at base + 16 * lane: free of bank conflicts, and every
+//     fragment of a stage is the same lane address plus a constant;
+//   - a kernel that streams weights without LDS loads a fragment into registers as one
+//     contiguous kilobyte.
 constexpr int kPackN = 256, kPackK = 64;
-// 16-byte piece `slot` of LDS row `row` holds piece slot ^ swz(row) of the row.  The LDS
+constexpr int kFragElems = 16 * 32;  // one MFMA operand fragment
+__host__ __device__ inline size_t packed_index(int n, int k, int K_out) {
+    const int row = n % kPackN, kk = k % kPackK;
+    const size_t tile = (size_t)(n / kPackN) * (K_out / kPackK) + k / kPackK;
+    const int frag = (row >> 4) * (kPackK / 32) + (kk >> 5);
+    return tile * (kPackN * kPackK) + frag * kFragElems + (((kk >> 3) & 3) * 16 + (row & 15)) * 8 + (kk & 7);
+}
+// Activation tiles keep rows of 128 bytes in LDS: 16-byte piece `slot` of LDS row `row` holds
+// piece slot ^ swz(row) of the row.  The LDS
 // has 64 four-byte banks and serves a ds_read_b128 sixteen lanes at a time, so the
 // 16 consecutive rows one such group touches must land on 16 distinct 16-byte bank
 // groups of a 256-byte span: with 128-byte rows that is (row&1, slot) -> xor with
 // (row>>1)&7.
 __host__ __device__ inline int swz(int row) { return (row >> 1) & 7; }
-__host__ __device__ inline size_t packed_index(int n, int k, int K_out) {
-    const int row = n % kPackN, kk = k % kPackK;
-    const size_t tile = (size_t)(n / kPackN) * (K_out / kPackK) + k / kPackK;
-    return (tile * kPackN + row) * kPackK + (((kk >> 3) ^ swz(row)) << 3) + (kk & 7);
-}
 
 // out[packed_index(n, k)] = in[k][n] for one expert per blockIdx.z, zero where k >= K or
 // n >= N (the output is K_out x N_out, padded); optional interleave of the output row
-// index: rows of W1 go to (n/32)*64 + n%32, rows of W3 32 further.
+// index: rows of W1 go to (n/32)*64 + n%32, rows of W3 32 further.  A workgroup turns 32 k x
+// 64 n through LDS: 16-byte reads along n (VEC: the row length N is a multiple of 8), whole
+// fragments of 1 KiB written by a wavefront each.
+template <bool VEC>
 __global__ __launch_bounds__(256) void pack_transpose_kernel(const bf16_t* __restrict__ in, bf16_t* __restrict__ out,
                                                               int K, int N, int K_out, int N_out,
                                                               size_t in_expert_stride, size_t out_expert_stride,
                                                               int interleave, int sel) {
-    __shared__ bf16_t tile[32][33];
+    constexpr int TK = 32, TN = 64, PITCH = TK + 8;
+    __shared__ __align__(16) bf16_t tile[TN * PITCH];
     const bf16_t* src = in + (size_t)blockIdx.z * in_expert_stride;
     bf16_t* dst = out + (size_t)blockIdx.z * out_expert_stride;
-    const int n0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-    for (int r = ty; r < 32; r += 8) {
-        const int kk = k0 + r, nn = n0 + tx;
-        tile[r][tx] = (kk < K && nn < N) ? src[(size_t)kk * N + nn] : (bf16_t)0;
+    const int n0 = blockIdx.x * TN, k0 = blockIdx.y * TK;
+    const int tid = threadIdx.x;
+    {
+        const int kr = tid >> 3, nc = (tid & 7) * 8;
+        const int kk = k0 + kr, nn = n0 + nc;
+        alignas(16) bf16_t v[8];
+        if (VEC && kk < K && nn < N) {
+            *(uint4*)v = *(const uint4*)(src + (size_t)kk * N + nn);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = (kk < K && nn + i < N) ? src[(size_t)kk * N + nn + i] : (bf16_t)0;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) tile[(nc + i) * PITCH + kr] = v[i];
     }
     __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int nn = n0 + r, kk = k0 + tx;
-        if (nn < N_out && kk < K_out) {
-            const int orow = interleave ? ((nn / 32) * 64 + sel * 32 + (nn % 32)) : nn;
-            dst[packed_index(orow, kk, K_out)] = tile[tx][r];
-        }
+    const int row = (tid >> 6) * 16 + (tid & 15), q = (tid >> 4) & 3;
+    const int nn = n0 + row;
+    if (nn < N_out) {
+        const int orow = interleave ? ((nn / 32) * 64 + sel * 32 + (nn % 32)) : nn;
+        *(uint4*)(dst + packed_index(orow, k0 + 8 * q, K_out)) = *(const uint4*)&tile[row * PITCH + 8 * q];
     }
 }
 
@@ -372,6 +395,11 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             k0 = (int)((long long)ts.kt * part / P);
             k1 = (int)((long long)ts.kt * (part + 1) / P);
         };
+        // whole ragged tiles of the experts below e (each sits right behind its expert's full tiles)
+        for (int e = tid; e < E; e += blockDim.x) e_segs[e] = (e_tail[e] > 0 && e_rank[e] < n_whole_tail) ? 1 : 0;
+        __syncthreads();
+        block_exclusive_scan_2048(e_segs, E, wave_sum);
+        auto whole_tails_below = [&](int e) { return e_segs[e]; };
         auto emit = [&](int list0, int rows, int expert, int whole_index, int split_index) {
             MTile mt;
             mt.list0 = list0;
@@ -379,7 +407,11 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             mt.expert = expert;
             mt.kt0 = mt.kt1 = 0;
             mt.part = -1;
-            mt.pad0 = mt.pad1 = 0;
+            // (full tiles from n_whole_full on are split; entries of the experts below: their whole tiles)
+            const int f0 = e_full[expert] < n_whole_full ? e_full[expert] : n_whole_full;
+            const int f1 = e_full[expert + 1] < n_whole_full ? e_full[expert + 1] : n_whole_full;
+            mt.first = f0 + whole_tails_below(expert);
+            mt.n_same = f1 + whole_tails_below(expert + 1) - mt.first;
             if (split_index < 0) {
                 ts.tiles[whole_index] = mt;
                 return;
@@ -392,11 +424,6 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             ts.splits[split_index].list0 = list0;
             ts.splits[split_index].rows = rows;
         };
-        // whole ragged tiles of the experts below e (each sits right behind its expert's full tiles)
-        for (int e = tid; e < E; e += blockDim.x) e_segs[e] = (e_tail[e] > 0 && e_rank[e] < n_whole_tail) ? 1 : 0;
-        __syncthreads();
-        block_exclusive_scan_2048(e_segs, E, wave_sum);
-        auto whole_tails_below = [&](int e) { return e_segs[e]; };
         if (fits) {
             // full-height tiles: tile t belongs to the expert whose range of tile numbers holds it
             for (int t = tid; t < n_full; t += blockDim.x) {
@@ -775,7 +802,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
             const int tmv16 = rows_w16 <= 0 ? 0 : (rows_w16 >= WTM ? TM16 : (rows_w16 + 15) / 16);
             const int sw16 = swz(l16);  // rows differ by multiples of 16 -> same swizzle
             const unsigned a_base = lds_base + (unsigned)((wm * WTM + l16) * ROW_BYTES);
-            const unsigned b_base = lds_base + (unsigned)(A_BYTES + (wn * WTN + l16) * ROW_BYTES);
+            // weight fragment (16-row group j of this wavefront, step ks) sits at b_base + stage +
+            // (j * 2 + ks) KiB
+            const unsigned b_base = lds_base + (unsigned)(A_BYTES + wn * WTN * ROW_BYTES + lane_k * 16);
             bf16x8 af[TM16], bfr[2][TN16];
             auto piece_of = [&](int kt, int ks) {
                 return (unsigned)((kt % NSTAGE) * STAGE_BYTES + (((ks * 4 + g16) ^ sw16) * 16));
@@ -787,10 +816,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
                 // is the same for every wavefront
                 lds_read_b128<i * 16 * ROW_BYTES>(af[i], a_base + piece);
             };
-            auto read_b_all = [&](int buf, unsigned piece) {
+            auto read_b_all = [&](auto KS, int buf, int kt) {
+                const unsigned base = b_base + (unsigned)((kt % NSTAGE) * STAGE_BYTES);
                 static_for<TN16>([&](auto J) {
                     constexpr int j = decltype(J)::value;
-                    lds_read_b128<j * 16 * ROW_BYTES>(bfr[buf][j], b_base + piece);
+                    lds_read_b128<(j * 2 + decltype(KS)::value) * 1024>(bfr[buf][j], base);
                 });
             };
             auto row_mfmas = [&](auto I, int buf) {
@@ -818,7 +848,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
                     lds_wait<0>();
 #pragma unroll
                 for (int j = 0; j < TN16; ++j) lds_landed(bfr[cur][j]);
-                if constexpr (NEXT && !HANDOVER) read_b_all(nxt, np);
+                if constexpr (NEXT && !HANDOVER) read_b_all(std::integral_constant<int, ks + 1>{}, nxt, kt);
                 static_for<TM16>([&](auto I) {
                     constexpr int i = decltype(I)::value;
                     if constexpr (HANDOVER && i == 0) {
@@ -830,7 +860,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
                         else
                             wait_vmcnt<0>();
                         __builtin_amdgcn_s_barrier();
-                        read_b_all(nxt, np);
+                        read_b_all(std::integral_constant<int, 0>{}, nxt, kt + 1);
                     }
                     if constexpr (i > 0 && NEXT && !HANDOVER)
                         lds_wait<TM16 - 1 + TN16>();  // activation fragment i has landed
@@ -855,7 +885,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
             else
                 wait_vmcnt<0>();
             __builtin_amdgcn_s_barrier();
-            read_b_all(0, piece_of(0, 0));
+            read_b_all(std::integral_constant<int, 0>{}, 0, 0);
             static_for<TM16>([&](auto I) { read_a(I, piece_of(0, 0)); });
             int kt = 0;
             for (; kt + 1 < KT; ++kt) {
@@ -975,6 +1005,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
         }
     }
 }
+
+#include "ffn_stream.h"
 
 // Adds up the fp32 slabs of every split M-tile in the order of the parts and writes the rows
 // as bf16: y[c_rows[list0 + r]] = scale * (((P_0[r] + P_1[r]) + P_2[r]) + ...).  blockIdx.x =
@@ -1122,7 +1154,7 @@ struct FfnWs {
 constexpr int kMinBM = 32;  // the lowest tile shape
 
 // Process-wide overrides of the automatic choices (moe_grouped_ffn_set_option); -1 / 0 = automatic.
-static std::atomic<int> g_opt_tile1{-1}, g_opt_tile2{-1}, g_opt_split{-1}, g_opt_group_n{0};
+static std::atomic<int> g_opt_tile1{-1}, g_opt_tile2{-1}, g_opt_split{-1}, g_opt_group_n{0}, g_opt_stream{-1};
 
 // The bf16 kernels work on a hidden width padded to a multiple of 64: the packed weights
 // carry zero columns (W1, W3) and zero rows (W2) for the padding, so the padded hidden
@@ -1232,9 +1264,7 @@ static GemmVariant make_variant() {
 
 // Tile shapes built into the library: 0 = 256x256x64 with two LDS stages, 1 = 128x256x64 with
 // three (for products with too few 256-row tiles to fill the chip twice), 2 = 32x256x64 with
-// four (for slivers of a few rows per expert, where the product only streams weights: three
-// k-tiles of a weight panel in flight per workgroup instead of two, and an eighth of the
-// activation tile to fetch for rows that are not there).
+// four (by option only; slivers of a few rows per expert are streamed, ffn_stream.h).
 constexpr int kNumVariants = 3;
 static const GemmVariant kGemmSwiglu[kNumVariants] = {make_variant<256, 256, 64, 2, 4, 2, kEpiSwiglu>(),
                                                       make_variant<128, 256, 64, 2, 4, 3, kEpiSwiglu>(),
@@ -1283,6 +1313,53 @@ static int launch_gemm_bf16(const GemmVariant& v, const bf16_t* A, int lda, cons
     return check_launch();
 }
 
+// Whether a product streams its weights through registers (ffn_stream.h): 0 no, else the form.
+// The rule goes by the whole batch (A rows, E experts), not by the launched slot range, so that
+// a row gets the same bits from a launch over some slots as from one over all.
+// Up to 24 rows per expert on average (routing is skewed: up to three times as many per expert that
+// holds any) the streaming forms lead the LDS-staged tiles at every skew measured (both products,
+// 128 experts of 4096 x 1536: 256 tokens 580 -> 506 us, with popularity 0.1 297 -> 273; 64 experts
+// of 2048 x 1408, 250 tokens: 191 -> 162); at 32 the most skewed batches fall behind (512 tokens at
+// popularity 0.1: 329 against 361 us).  A product whose 128 x 256 tiles would not go once
+// round the chip is better off with the finer units up to 64 (16 experts of 4096 x 688, 200
+// tokens, first product: 68 -> 43 us; the second, 352 tiles: 25 against 27).
+// Of the two, form 1 (finer units) leads up to 4 rows per expert, and up to 16 where the 128-column
+// units of form 2 would not go round the 512 workgroups the chip holds (8 experts, 64 tokens,
+// second product: 112 against 130 us; 128 tokens: 178 against 140 the other way); above, form 2
+// reads the activations half as often.
+static int stream_form(int forced_tile, int64_t A, int E, int n_cols) {
+    const int opt = g_opt_stream.load();
+    if (forced_tile >= 0 || opt == 0 || A > 65536) return 0;
+    if (opt > 0) return opt;
+    if (A > (int64_t)24 * E &&
+        (A > (int64_t)64 * E || (ceil_div64(A, 128) + E) * ceil_div(n_cols, 256) > kGemmGrid))
+        return 0;
+    if (A <= (int64_t)4 * E) return 1;
+    return A > (int64_t)16 * E || (int64_t)E * (n_cols / 128) >= 2 * kGemmGrid ? 2 : 1;
+}
+
+template <int EPI>
+static int launch_stream(int form, int64_t A, int E, const bf16_t* X, int lda, const bf16_t* Bp, size_t b_stride,
+                         bf16_t* C, int ldc, const MTile* tiles, const int32_t* counts, int N, int K, const RowMap& rm,
+                         hipStream_t st) {
+    auto go = [&](auto kern, int grid, int threads) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, X, lda, Bp, b_stride, C, ldc, tiles, counts, N, K, rm);
+        return check_launch();
+    };
+    // as many workgroups as the registers let a CU hold
+    if (form == 2) return go(grouped_gemm_stream_shared_kernel<EPI>, 2 * kGemmGrid, 512);
+    // Units of 32 columns where those of 64 would make fewer than three per CU (one token, 8 experts
+    // of 3072 columns: 37 -> 35 us; 16 tokens, 4096 columns over K = 14336: 107 -> 98 us) and the
+    // activation fragments, read for every unit, are few.  A short K is split four ways instead of
+    // eight: three k-tiles per wavefront and less would be mostly prologue (24 k-tiles, 128 experts:
+    // 170 -> 166 us; 64 k-tiles: 307 against 315 us the other way).
+    const int64_t experts = A < E ? A : E;
+    if (A <= (int64_t)8 * E && experts * (N / 64) < 3 * kGemmGrid)
+        return go(grouped_gemm_stream_ksplit_kernel<2, 8, EPI>, 3 * kGemmGrid, 512);
+    if (K / kPackK <= 32) return go(grouped_gemm_stream_ksplit_kernel<4, 4, EPI>, 4 * kGemmGrid, 256);
+    return go(grouped_gemm_stream_ksplit_kernel<4, 8, EPI>, 3 * kGemmGrid, 512);
+}
+
 }  // namespace moegps
 
 extern "C" int moe_grouped_ffn_set_option(int option, int value) {
@@ -1300,6 +1377,10 @@ extern "C" int moe_grouped_ffn_set_option(int option, int value) {
         case MOE_FFN_OPT_GROUP_N:
             if (value < 0) return MOE_ERR_INVALID_ARG;
             g_opt_group_n.store(value);
+            return MOE_OK;
+        case MOE_FFN_OPT_STREAM:
+            if (value < -1 || value > 2) return MOE_ERR_INVALID_ARG;
+            g_opt_stream.store(value);
             return MOE_OK;
         default:
             return MOE_ERR_INVALID_ARG;
@@ -1345,22 +1426,22 @@ static int pack_weights_impl(const void* W1, const void* W3, const void* W2, int
     // W1 (, W3): in[k = d][n = ffn] -> rows n' of the packed matrix, zero rows for n >= ffn and up
     // to whole tiles of rows
     const int rows1 = (int)(packed_rows((size_t)n1 * fp) / n1);  // rows per matrix, padding included
-    dim3 g13(rows1 / 32, d / 32, E);
-    hipLaunchKernelGGL(pack_transpose_kernel, g13, dim3(256), 0, st, (const bf16_t*)W1, p1, d, ffn, d, rows1, es, e1,
-                       W3 ? 1 : 0, 0);
-    int rc = check_launch();
-    if (rc != MOE_OK) return rc;
-    if (W3) {
-        hipLaunchKernelGGL(pack_transpose_kernel, g13, dim3(256), 0, st, (const bf16_t*)W3, p1, d, ffn, d, rows1, es,
-                           e1, 1, 1);
-        if ((rc = check_launch()) != MOE_OK) return rc;
-    }
+    auto pack = [&](const void* W, bf16_t* out, int K, int N, int K_out, int N_out, size_t out_stride, int interleave,
+                    int sel) {
+        const dim3 grid(ceil_div(N_out, 64), K_out / 32, E);
+        if (N % 8 == 0)
+            hipLaunchKernelGGL(pack_transpose_kernel<true>, grid, dim3(256), 0, st, (const bf16_t*)W, out, K, N, K_out,
+                               N_out, es, out_stride, interleave, sel);
+        else
+            hipLaunchKernelGGL(pack_transpose_kernel<false>, grid, dim3(256), 0, st, (const bf16_t*)W, out, K, N, K_out,
+                               N_out, es, out_stride, interleave, sel);
+        return check_launch();
+    };
+    int rc = pack(W1, p1, d, ffn, d, rows1, e1, W3 ? 1 : 0, 0);
+    if (rc == MOE_OK && W3) rc = pack(W3, p1, d, ffn, d, rows1, e1, 1, 1);
     // W2: in[k = ffn][n = d] -> packed [n = d][k = fp], zero for k >= ffn and rows n >= d
-    const int rows2 = (int)packed_rows((size_t)d);
-    dim3 g2(rows2 / 32, fp / 32, E);
-    hipLaunchKernelGGL(pack_transpose_kernel, g2, dim3(256), 0, st, (const bf16_t*)W2, p2, ffn, d, fp, rows2, es, e2,
-                       0, 0);
-    return check_launch();
+    if (rc == MOE_OK) rc = pack(W2, p2, ffn, d, fp, (int)packed_rows((size_t)d), e2, 0, 0);
+    return rc;
 }
 }  // namespace moegps
 
@@ -1448,19 +1529,13 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
         return check_launch();
     }
 
-    // Tile shape per product: 256x256 unless the product has too few such tiles to keep 256
-    // workgroups busy for two rounds, or the segments are slivers of a few rows each
-    // (decode), then 128x256 with three stages.  The tile count is only known on the device;
-    // the host estimates it from the row count.  A product of slivers with few k-tiles per tile
-    // (the second product at the hidden widths of fine-grained experts) takes 32x256 with four
-    // stages: the taller shapes fetch their whole activation tile every k-tile, rows that are
-    // not there as copies of the last one, half as many bytes again as the weights at 128 rows
-    // (decode at 128 experts, 24 k-tiles: 0.201 -> 0.192 ms; 64x256 with four stages stays at
-    // 0.200); on long tiles that does not make up for the extra M-tiles of experts with more
-    // than 32 rows (same batch, first product, 64 k-tiles: 0.369 -> 0.392 ms).
-    auto pick = [&](int forced, int n_cols, int k_tiles) {
+    // Batches of a few rows per expert stream their weights (stream_form); for the rest, tile shape
+    // per product: 256x256 unless the product has too few such tiles to keep 256 workgroups
+    // busy for two rounds, or the segments are slivers, then 128x256 with three stages.  The tile
+    // count is only known on the device; the host estimates it from the row count.  (32x256 is
+    // left to the option: the batches it was ahead on are streamed now.)
+    auto pick = [&](int forced, int n_cols) {
         if (forced >= 0) return forced;
-        if (A < (int64_t)16 * nrange && k_tiles <= 32) return 2;
         if (A < (int64_t)64 * nrange) return 1;
         // fewer than 256 rows per expert on average: most 256-row tiles would be ragged (128
         // experts, 16384 rows: 623 against 683 us for the first product; 64 experts, 12288 rows:
@@ -1477,8 +1552,10 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     };
     const int fp = padded_ffn(ffn, dtype);  // hidden width the kernels see
     const int n1 = relu ? 1 : 2;            // matrices in the first product
-    const int v1 = pick(g_opt_tile1.load(), n1 * fp, d / 64);
-    const int v2 = pick(g_opt_tile2.load(), d, fp / 64);
+    const int v1 = pick(g_opt_tile1.load(), n1 * fp);
+    const int v2 = pick(g_opt_tile2.load(), d);
+    const int s1 = stream_form(g_opt_tile1.load(), A, E, n1 * fp);
+    const int s2 = g_opt_split.load() == 1 ? 0 : stream_form(g_opt_tile2.load(), A, E, d);
     // N-tiles walked side by side under one run of M-tiles.  A run of 32 tiles is 32/g M-tiles
     // under g weight panels; every group streams the activation rows again.  Up to 12 N-tiles
     // are walked together, so the rows are read once.  Wider outputs are walked in groups: of 4
@@ -1498,12 +1575,13 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     };
     const GemmVariant& g1 = relu ? kGemmRelu[v1] : kGemmSwiglu[v1];
     const GemmVariant& g2 = kGemmPlain[v2];
-    const bool split = ws.split_capacity > 0;
     // one launch builds the row list and both tables; the second product shares the first one's
     // table when it has the same tile height and splits nothing
-    const bool own2 = g2.bm != g1.bm || split;
-    TableSpec t1{ws.tiles1, ws.counts, nullptr, g1.bm, ws.capacity, d / g1.bk, 0, 1, kGemmGrid, 0, 0};
-    TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, g2.bm, ws.capacity, fp / g2.bk,
+    const int bm1 = s1 ? kStreamBM : g1.bm, bm2 = s2 ? kStreamBM : g2.bm;
+    const bool split = ws.split_capacity > 0 && !s2;
+    const bool own2 = bm2 != bm1 || split;
+    TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / g1.bk, 0, 1, kGemmGrid, 0, 0};
+    TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / g2.bk,
                  split ? ws.parts : 0, ceil_div(d, g2.bn), kGemmGrid, ws.split_all, ws.split_capacity};
     hipLaunchKernelGGL(build_tables_kernel, dim3(build_grid), dim3(1024), 0, st, seg_offsets, slot_expert, seg_begin,
                        seg_end, E, t1, t2, ws.rowlist, ws.queues, 16);
@@ -1513,13 +1591,25 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     const bf16_t* p13 = (const bf16_t*)packed;
     const bf16_t* p2 = p13 + (size_t)E * packed_elems1(n1, d, fp);
     if (timed) (void)hipEventRecord(g_time_events[0], st);
-    rc = launch_gemm_bf16(g1, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h, fp, ws.tiles1,
-                          ws.counts, ws.queues, n1 * fp, d, group_for(n1 * fp, g1.bn, A * (int64_t)d * 2), rm1, nullptr, st);
+    if (s1) {
+        rc = relu ? launch_stream<kEpiRelu>(s1, A, E, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h,
+                                            fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, st)
+                  : launch_stream<kEpiSwiglu>(s1, A, E, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp),
+                                              (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, st);
+    } else {
+        rc = launch_gemm_bf16(g1, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h, fp, ws.tiles1,
+                              ws.counts, ws.queues, n1 * fp, d, group_for(n1 * fp, g1.bn, A * (int64_t)d * 2), rm1,
+                              nullptr, st);
+    }
     if (timed) (void)hipEventRecord(g_time_events[1], st);
     if (rc != MOE_OK) return rc;
     if (timed) (void)hipEventRecord(g_time_events[2], st);
-    rc = launch_gemm_bf16(g2, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d, tiles2, count2,
-                          ws.queues + 8, d, fp, group_for(d, g2.bn, A * (int64_t)fp * 2), rm2, ws.partials, st);
+    if (s2)
+        rc = launch_stream<kEpiNone>(s2, A, E, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d,
+                                     tiles2, count2, d, fp, rm2, st);
+    else
+        rc = launch_gemm_bf16(g2, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d, tiles2, count2,
+                              ws.queues + 8, d, fp, group_for(d, g2.bn, A * (int64_t)fp * 2), rm2, ws.partials, st);
     if (rc == MOE_OK && split) {
         hipLaunchKernelGGL(add_partials_kernel, dim3(ws.split_capacity < 64 ? ws.split_capacity : 64, 32), dim3(256),
                            0, st, ws.partials, ws.splits, count2, ws.parts, (bf16_t*)y_perm, d, d, rm2);

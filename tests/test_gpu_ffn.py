@@ -382,6 +382,54 @@ def test_ffn_every_tile_variant(tile1, tile2, split, ffn_options):
     assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * scale)
 
 
+@pytest.mark.parametrize("form", [1, 2])
+@pytest.mark.parametrize("d,ffn,relu", [(64, 64, False),      # one k-tile: one half / seven parts of K are empty
+                                        (192, 320, False),    # odd numbers of k-tiles, half a unit at the edge of N
+                                        (576, 1088, True),    # nine and seventeen k-tiles, ReLU
+                                        (2176, 192, False)])  # K above and below 32 k-tiles
+def test_ffn_streaming_forms(form, d, ffn, relu):
+    """The weight-streaming kernels at every count of 16-row groups, with M-tiles of one expert behind
+    each other, empty slots and more experts than rows, in place and through the row gather with
+    gate weights: against the oracle (bf16 tolerance of this file), the same bits twice and from a
+    launch over a part of the slots."""
+    E = 6
+    cfg = wl.MoEConfig("s", T=1, d=d, ffn=ffn, E=E, k=1, G=4, S=3, dtype="bf16", mode=0, seed=41,
+                       act="relu" if relu else "swiglu")
+    seg_sizes = [1, 0, 16, 17, 0, 33, 64, 65, 130, 0, 5, 31]
+    slot_expert = [0, 1, 2, 3, -1, 4, 0, 1, 2, -1, 4, 3]     # expert 5 has no slot
+    A = sum(seg_sizes)
+    rng = np.random.default_rng(43)
+    x = wl.quantize(rng.standard_normal((A, d)).astype(np.float32), "bf16")
+    so = np.concatenate([[0], np.cumsum(seg_sizes)]).astype(np.int32)
+    W1s, W3s, W2s = host_weights(cfg)
+    Wf = [wl.from_storage(w, "bf16") for w in (W1s, W3s, W2s)]
+    packed = B.moe_pack_weights_relu(to_device(W1s, "bf16"), to_device(W2s, "bf16")) if relu \
+        else B.moe_pack_weights(*dev_weights(cfg, (W1s, W3s, W2s)))
+    ref = grouped_ffn(x, so, slot_expert, Wf[0], None if relu else Wf[1], Wf[2])
+    scale = np.max(np.abs(ref))
+    xd = to_device(wl.to_storage(x, "bf16"), "bf16")
+    args = (dev_i32(so), dev_i32(slot_expert), packed, E, ffn)
+    try:
+        B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, form)
+        y = B.moe_grouped_ffn(xd, *args, relu=relu)
+        assert torch.equal(y, B.moe_grouped_ffn(xd, *args, relu=relu))
+        part = B.moe_grouped_ffn(xd, *args, seg_begin=5, seg_end=9, relu=relu)
+        got = to_host_f32(y)
+        assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * scale)
+        assert np.array_equal(to_host_f32(part)[so[5]:so[9]], got[so[5]:so[9]])
+        assert np.all(to_host_f32(part)[:so[5]] == 0) and np.all(to_host_f32(part)[so[9]:] == 0)
+        if not relu:
+            a_of_row = rng.permutation(A).astype(np.int32)
+            src = np.empty_like(x)
+            src[a_of_row] = x
+            w = rng.random((A, 1)).astype(np.float32)
+            yw = B.moe_grouped_ffn_gather(to_device(wl.to_storage(src, "bf16"), "bf16"), dev_i32(a_of_row), 1, *args,
+                                          topk_w=torch.from_numpy(w).cuda())
+            assert np.max(np.abs(to_host_f32(yw) - ref * w[a_of_row])) <= TOL["bf16"] * scale
+    finally:
+        B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, -1)
+
+
 @pytest.mark.parametrize("relu", [False, True])
 def test_ffn_split_k_matches_whole_tiles(relu, ffn_options):
     """Closing tiles computed as parts of K: same result as whole tiles up to the fp32
