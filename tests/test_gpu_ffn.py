@@ -85,6 +85,38 @@ def test_ffn_ragged_segments(dtype, d, ffn):
     assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL[dtype] * scale)
 
 
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("d,ffn,scale", [(4, 4, 1),       # one quarter of a 16-deep step, four columns
+                                         (20, 68, 1),     # ragged steps and columns, 32-row tiles
+                                         (144, 260, 1),   # nine steps (chunks of four), one column tile of four columns
+                                         (36, 2052, 12)]) # enough tiles for the 64-row form
+def test_ffn_f32_tile_edges(d, ffn, scale, relu):
+    """fp32 products at row counts around the 32- and 64-row tiles and at widths that are no multiple
+    of a step or a column tile.  An expert without rows holds inf and nan: nothing of it may show."""
+    cfg = wl.CONFIGS["cfg1_tiny_f32"].replace(d=d, ffn=ffn, seed=17)
+    sizes = [r * scale for r in (1, 31, 32, 33, 0, 64, 65, 127, 2, 0, 63, 16)]
+    slot_expert = np.array([0, 1, 2, 3, 4, 5, 6, 7, 0, -1, 1, 6], dtype=np.int32)
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((int(offs[-1]), d)).astype(np.float32)
+    W1, W3, W2 = [w.copy() for w in host_weights(cfg)]
+    for w in (W1, W3, W2):
+        w[4] = np.inf
+        w[4, ::2] = np.nan
+    dx, so, se = torch.from_numpy(x).cuda(), dev_i32(offs), dev_i32(slot_expert)
+    if relu:
+        packed = B.moe_pack_weights_relu(*[to_device(w, "f32") for w in (W1, W2)])
+    else:
+        packed = B.moe_pack_weights(*[to_device(w, "f32") for w in (W1, W3, W2)])
+    y = to_host_f32(B.moe_grouped_ffn(dx, so, se, packed, cfg.E, ffn, relu=relu))
+    ref = np.zeros((x.shape[0], d))
+    for s_, e in enumerate(slot_expert):
+        lo, hi = offs[s_], offs[s_ + 1]
+        if hi > lo:
+            ref[lo:hi] = ffn_rows_relu(x[lo:hi], W1[e], W2[e]) if relu else ffn_rows(x[lo:hi], W1[e], W3[e], W2[e])
+    assert rel_err(y, ref) <= TOL["f32"]
+
+
 def test_ffn_slot_range_only_touches_its_rows():
     cfg = wl.MoEConfig("f", T=1, d=128, ffn=256, E=5, k=1, G=4, S=3, dtype="bf16", mode=0, seed=21)
     rng = np.random.default_rng(5)
