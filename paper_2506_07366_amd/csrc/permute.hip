@@ -9,55 +9,91 @@
 // chunks from an exclusive scan of per-chunk key counts.  No atomics decide any
 // position, so the permutation is identical for every launch.
 //
-//   count    : per-chunk histogram of the dispatch keys (expert ids)
-//   scan1    : chunk bases per expert; per-expert replica tables from the plan
+//   count    : per-chunk histogram of the dispatch keys (expert ids); further workgroups of the
+//              same launch turn the plan into per-expert replica tables
 //   segment  : stable rank -> replica -> segment id; per-chunk segment histogram
-//   scan2    : chunk bases per segment, seg_offsets, rank_load
-//   place    : row_of_assign / assign_of_row
+//   place    : seg_offsets, rank_load, row_of_assign / assign_of_row
 //   scatter  : each token row is read once and written to its k rows of x_perm
 //
-// A batch of at most 8192 assignments (decode, short prefill) takes the five index steps in
-// one workgroup and one launch: the same ranks and scans, the chunk being the whole batch.
+// These kernels are bound by latency, each costs 4-5 us whatever it does, so a workgroup of
+// "segment" and "place" adds up the counts of the chunks before its own by itself (a few hundred
+// coalesced loads, served by the L2) and the scans are no launches of their own; and the chunks
+// are cut small enough that a workgroup ranks 256 elements at a time in one or two rounds.  Only above
+// kSelfScanChunks chunks, where every workgroup would read megabytes, two scan kernels turn the
+// counts into bases first.  Index kernels against chunks of 2048 and always the scans (whole
+// moe_permute without the row copy, modes 1 / 2):
+//   12288 assignments,  64 experts, 80 slots    32.8 / 38.6 -> 14.5 / 14.9 us
+//   98304               64          80          34.9 / 40.6 -> 22.4 / 24.5
+//   262144              128         160         57.0 / 64.7 -> 40.0 / 47.4
+//   65536               128         160         38.2 / 45.7 -> 27.1 / 28.6
+//
+// A batch of at most kSmallA assignments (decode, short prompts) takes the index steps in
+// one workgroup and one launch: the same ranks and scans, the chunk being the whole batch.  The
+// line lies where the two meet: 2056 assignments to 128 experts 15.2 us in one workgroup, 15.9 in
+// three launches; 3200 17.3 against 16.3; 8192 29.3 against 17.1 (mode 2: 39.7 against 18.9).
 #include "common.h"
 #include "block_scan.h"
+#include <initializer_list>
 #include <mutex>
 
 namespace moegps {
 
 constexpr int kPermThreads = 256;
 constexpr int kPermWaves = kPermThreads / kWave;
-constexpr int kRounds = 8;                                  // 64-element rounds per wavefront
+constexpr int kRounds = 8;                                  // max 64-element rounds per wavefront
 constexpr int kChunk = kPermThreads * kRounds;              // max elements per workgroup (2048)
 constexpr int kMaxKeys = MOE_MAX_SEGMENTS;                  // >= MOE_MAX_EXPERTS
+constexpr int kChunksWanted = 128;                          // chunks a batch is cut into while rounds are left to give
+constexpr int kSelfScanChunks = 256;
 
-__host__ __device__ inline int tokens_per_chunk(int k) { return kChunk / k > 0 ? kChunk / k : 1; }
+__host__ __device__ inline int tokens_per_chunk(int k, int rounds) {
+    return kPermThreads * rounds / k > 0 ? kPermThreads * rounds / k : 1;
+}
 
 struct PermWs {
-    int32_t* bh1;       // [nb, E]    per-chunk expert counts -> chunk bases
-    int32_t* bh2;       // [nb, NSEG] per-chunk segment counts -> chunk bases
-    int32_t* seg;       // [A]        segment of each assignment
+    int32_t* bh1;       // [nb, E]    per-chunk expert counts (-> chunk bases)
+    int32_t* bh2;       // [nb, NSEG] per-chunk segment counts (-> chunk bases)
+    uint16_t* seg;      // [A]        segment of each assignment
     int32_t* rep_cnt;   // [E]        replicas per expert (0 = everything to the home slot)
     int32_t* rep_slot;  // [E, G]     replica slots, ascending
     int32_t* rep_hi;    // [E, G]     exclusive upper bound of each replica's rank range
+    int rounds;         // rounds per chunk
+    int nb;             // chunks
 };
+static_assert(MOE_MAX_SEGMENTS <= (1 << 16), "segment ids are kept in 16 bits");
 
-static size_t perm_ws_layout(int T, int E, int k, int G, int S, char* base, PermWs* ws) {
-    const int nb = ceil_div(T > 0 ? T : 1, tokens_per_chunk(k));
+// Bytes of scratch of a batch.  (The figure is a fixed function of the sizes: chunks of 2048 with
+// 4-byte segment ids.  The layout below keeps inside it, so callers that sized their scratch once,
+// and the fixed array of moe_permute_static, serve the same batches at any chunk size.)
+static size_t perm_ws_bytes(int T, int E, int k, int G, int S) {
+    const int nb = ceil_div(T > 0 ? T : 1, tokens_per_chunk(k, kRounds));
     size_t off = 0;
-    auto take = [&](size_t n_int) {
-        int32_t* p = base ? (int32_t*)(base + off) : nullptr;
-        off += align_up(n_int * sizeof(int32_t), 256);
-        return p;
-    };
-    PermWs w;
-    w.bh1 = take((size_t)nb * E);
-    w.bh2 = take((size_t)nb * G * S);
-    w.seg = take((size_t)T * k);
-    w.rep_cnt = take(E);
-    w.rep_slot = take((size_t)E * G);
-    w.rep_hi = take((size_t)E * G);
-    if (ws) *ws = w;
+    for (const size_t n : {(size_t)nb * E, (size_t)nb * G * S, (size_t)T * k, (size_t)E, (size_t)E * G, (size_t)E * G})
+        off += align_up(n * sizeof(int32_t), 256);
     return off;
+}
+
+static PermWs perm_ws_layout(int T, int E, int k, int G, int S, char* base) {
+    const size_t have = perm_ws_bytes(T, E, k, G, S);
+    const int64_t A = (int64_t)T * k;
+    PermWs w;
+    int64_t want = ceil_div64(A, (int64_t)kPermThreads * kChunksWanted);
+    for (w.rounds = (int)(want < 1 ? 1 : (want > kRounds ? kRounds : want));; ++w.rounds) {
+        w.nb = T > 0 ? ceil_div(T, tokens_per_chunk(k, w.rounds)) : 0;
+        size_t off = 0;
+        auto take = [&](size_t bytes) {
+            char* p = base + off;
+            off += align_up(bytes, 256);
+            return p;
+        };
+        w.bh1 = (int32_t*)take((size_t)w.nb * E * 4);
+        w.bh2 = (int32_t*)take((size_t)w.nb * G * S * 4);
+        w.seg = (uint16_t*)take((size_t)A * 2);
+        w.rep_cnt = (int32_t*)take((size_t)E * 4);
+        w.rep_slot = (int32_t*)take((size_t)E * G * 4);
+        w.rep_hi = (int32_t*)take((size_t)E * G * 4);
+        if (off <= have || w.rounds == kRounds) return w;
+    }
 }
 
 __device__ __forceinline__ int clamp_key(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
@@ -66,15 +102,15 @@ __device__ __forceinline__ int home_slot_of(int e, int H, int S) { return (e / H
 
 // ---------------------------------------------------------------------------
 // Stable rank of every element of a chunk among equal keys earlier in the chunk.
-// Wavefront w owns elements [w*512, (w+1)*512) of the chunk in kRounds rounds of
-// 64; element p of the chunk is (w, r, lane) with p = w*512 + r*64 + lane.
+// Wavefront w owns `rounds` <= NR rounds of 64 elements; element p of the chunk is (w, r, lane)
+// with p = (w * rounds + r) * 64 + lane.
 // The workgroup has NWAVES wavefronts; wcnt is LDS scratch of NWAVES*nkeys ints.
 // On return rank[r] holds the rank, and (if chunk_hist) chunk_hist[key] the chunk's
 // count per key.  Only the first `rounds` rounds hold elements (uniform over the workgroup).
 // ---------------------------------------------------------------------------
-template <int NWAVES>
-__device__ void chunk_stable_rank(const int (&key)[kRounds], const bool (&valid)[kRounds], int nkeys, int* wcnt,
-                                  int (&rank)[kRounds], int32_t* chunk_hist, int rounds = kRounds) {
+template <int NWAVES, int NR>
+__device__ void chunk_stable_rank(const int (&key)[NR], const bool (&valid)[NR], int nkeys, int* wcnt, int (&rank)[NR],
+                                  int32_t* chunk_hist, int rounds = NR) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int w = tid / kWave;
@@ -85,7 +121,7 @@ __device__ void chunk_stable_rank(const int (&key)[kRounds], const bool (&valid)
     const unsigned long long lt = (1ull << lane) - 1ull;
     int* mine = wcnt + w * nkeys;
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
+    for (int r = 0; r < NR; ++r) {
         rank[r] = 0;
         if (r >= rounds) continue;
         // lanes of this round holding the same key
@@ -117,23 +153,8 @@ __device__ void chunk_stable_rank(const int (&key)[kRounds], const bool (&valid)
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r)
+    for (int r = 0; r < NR; ++r)
         if (r < rounds && valid[r]) rank[r] += mine[key[r]];
-}
-
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kPermThreads) void perm_count_kernel(const int32_t* __restrict__ keys, int T, int k,
-                                                                   int E, int32_t* __restrict__ bh1) {
-    __shared__ int bins[MOE_MAX_EXPERTS];
-    const int tpc = tokens_per_chunk(k);
-    const int64_t lo = (int64_t)blockIdx.x * tpc * k;
-    const int64_t A = (int64_t)T * k;
-    const int64_t hi = lo + (int64_t)tpc * k < A ? lo + (int64_t)tpc * k : A;
-    for (int e = threadIdx.x; e < E; e += blockDim.x) bins[e] = 0;
-    __syncthreads();
-    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) atomicAdd(&bins[clamp_key(keys[i], E)], 1);
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += blockDim.x) bh1[(size_t)blockIdx.x * E + e] = bins[e];
 }
 
 // inclusive prefix sum over the 64 lanes of a wavefront (every lane active)
@@ -221,21 +242,76 @@ __device__ __forceinline__ void replica_table(int e, int mode, int G, int nseg, 
     if (lane == 0) ws.rep_cnt[e] = cnt < G ? cnt : G;
 }
 
-// chunk bases per expert (in place) and the replica tables of the plan; one
-// wavefront per expert column, columns dealt over the whole grid
+// per-chunk histogram of the dispatch keys (workgroups below ws.nb) and the replica tables of the
+// plan (the workgroups above, one wavefront per expert)
+__global__ __launch_bounds__(kPermThreads) void perm_count_kernel(const int32_t* __restrict__ keys, int mode, int T,
+                                                                   int k, int E, int G, int S,
+                                                                   const int32_t* __restrict__ hist_true,
+                                                                   const int32_t* __restrict__ hist_pred,
+                                                                   const int32_t* __restrict__ slot_expert,
+                                                                   const int32_t* __restrict__ slot_quota, PermWs ws) {
+    __shared__ int bins[MOE_MAX_EXPERTS];
+    if ((int)blockIdx.x >= ws.nb) {
+        const int e = ((int)blockIdx.x - ws.nb) * kPermWaves + (int)threadIdx.x / kWave;
+        if (e < E) replica_table(e, mode, G, G * S, hist_true, hist_pred, slot_expert, slot_quota, ws);
+        return;
+    }
+    const int tpc = tokens_per_chunk(k, ws.rounds);
+    const int64_t lo = (int64_t)blockIdx.x * tpc * k;
+    const int64_t A = (int64_t)T * k;
+    const int64_t hi = lo + (int64_t)tpc * k < A ? lo + (int64_t)tpc * k : A;
+    for (int e = threadIdx.x; e < E; e += blockDim.x) bins[e] = 0;
+    __syncthreads();
+    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) atomicAdd(&bins[clamp_key(keys[i], E)], 1);
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += blockDim.x) ws.bh1[(size_t)blockIdx.x * E + e] = bins[e];
+}
+
+// chunk bases per expert (in place), one wavefront per expert column, columns dealt over the whole grid
 constexpr int kScan1Threads = 256;
-__global__ __launch_bounds__(kScan1Threads) void perm_scan1_kernel(int mode, int nb, int E, int G, int S,
-                                                           const int32_t* __restrict__ hist_true,
-                                                           const int32_t* __restrict__ hist_pred,
-                                                           const int32_t* __restrict__ slot_expert,
-                                                           const int32_t* __restrict__ slot_quota, PermWs ws) {
-    const int nseg = G * S;
+__global__ __launch_bounds__(kScan1Threads) void perm_scan1_kernel(int E, PermWs ws) {
     const int wave = threadIdx.x / kWave, nwaves = blockDim.x / kWave;
     for (int e = blockIdx.x * nwaves + wave; e < E; e += gridDim.x * nwaves) {
         int unused[1];
-        wave_columns_scan<1>(ws.bh1, nb, E, e, unused);
-        replica_table(e, mode, G, nseg, hist_true, hist_pred, slot_expert, slot_quota, ws);
+        wave_columns_scan<1>(ws.bh1, ws.nb, E, e, unused);
     }
+}
+
+// Sums down the columns of a [nb, ncols] table of counts by the whole workgroup: base[c] over the
+// rows below `upto`, and, where total is given, total[c] over all rows (both in LDS, ncols ints).
+// Threads lie side by side along a row; several groups of them share the rows.
+__device__ __forceinline__ void block_column_sums(const int32_t* __restrict__ table, int nb, int ncols, int upto,
+                                                  int* base, int* total) {
+    const int tid = threadIdx.x;
+    for (int c = tid; c < ncols; c += kPermThreads) {
+        base[c] = 0;
+        if (total) total[c] = 0;
+    }
+    __syncthreads();
+    int width = kWave;
+    while (width < ncols && width < kPermThreads) width <<= 1;
+    const int groups = kPermThreads / width, grp = tid / width;
+    const int rows = total ? nb : upto;
+    constexpr int U = 8;  // loads in flight per thread
+    for (int c = tid % width; c < ncols; c += width) {
+        int below = 0, all = 0;
+        for (int b0 = grp; b0 < rows; b0 += groups * U) {
+            int v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int b = b0 + u * groups;
+                v[u] = b < rows ? table[(size_t)b * ncols + c] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                all += v[u];
+                below += b0 + u * groups < upto ? v[u] : 0;
+            }
+        }
+        if (below) atomicAdd(&base[c], below);
+        if (total && all) atomicAdd(&total[c], all);
+    }
+    __syncthreads();
 }
 
 // Segment of an assignment to expert e that stands at place i of the plan's order for e
@@ -252,7 +328,8 @@ __device__ __forceinline__ int segment_of(int e, int i, int H, int S, int G, con
     return sg;
 }
 
-// segment id per assignment + per-chunk segment histogram
+// segment id per assignment + per-chunk segment histogram.  SCANNED: ws.bh1 holds chunk bases, else counts.
+template <bool SCANNED>
 __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, int T, int k, int E, int G, int S,
                                                                      const int32_t* __restrict__ topk_idx,
                                                                      const int32_t* __restrict__ pred_idx,
@@ -260,12 +337,14 @@ __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, in
     __shared__ int wcnt[kPermWaves * MOE_MAX_EXPERTS];
     __shared__ int prank[kChunk];
     __shared__ int seg_bins[MOE_MAX_SEGMENTS];
+    __shared__ int ebase[MOE_MAX_EXPERTS];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int w = tid / kWave;
     const int nseg = G * S;
     const int H = (E + G - 1) / G;
-    const int tpc = tokens_per_chunk(k);
+    const int tpc = tokens_per_chunk(k, ws.rounds);
+    const int rounds = ws.rounds;
     const int64_t A = (int64_t)T * k;
     const int64_t base = (int64_t)blockIdx.x * tpc * k;
     const int n_b = (int)((base + (int64_t)tpc * k < A ? base + (int64_t)tpc * k : A) - base);
@@ -277,24 +356,25 @@ __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, in
     const int32_t* rank_keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int p = w * (kRounds * kWave) + r * kWave + lane;
-        valid[r] = p < n_b;
+        const int p = (w * rounds + r) * kWave + lane;
+        valid[r] = r < rounds && p < n_b;
         key[r] = valid[r] ? clamp_key(rank_keys[base + p], E) : 0;
         rank[r] = 0;
     }
     if (mode != MOE_MODE_NONE) {
-        chunk_stable_rank<kPermWaves>(key, valid, E, wcnt, rank, nullptr);
+        if (!SCANNED) block_column_sums(ws.bh1, ws.nb, E, blockIdx.x, ebase, nullptr);
+        chunk_stable_rank<kPermWaves, kRounds>(key, valid, E, wcnt, rank, nullptr, rounds);
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const int p = w * (kRounds * kWave) + r * kWave + lane;
-            if (valid[r]) prank[p] = ws.bh1[(size_t)blockIdx.x * E + key[r]] + rank[r];
+            const int p = (w * rounds + r) * kWave + lane;
+            if (valid[r]) prank[p] = (SCANNED ? ws.bh1[(size_t)blockIdx.x * E + key[r]] : ebase[key[r]]) + rank[r];
         }
     }
     __syncthreads();
 
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int p = w * (kRounds * kWave) + r * kWave + lane;
+        const int p = (w * rounds + r) * kWave + lane;
         if (!valid[r]) continue;
         const int e = clamp_key(topk_idx[base + p], E);
         int i = -1;  // place of this assignment in the plan's order for expert e
@@ -310,7 +390,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, in
             }
         }
         const int sg = segment_of(e, i, H, S, G, ws);
-        ws.seg[base + p] = sg;
+        ws.seg[base + p] = (uint16_t)sg;
         atomicAdd(&seg_bins[sg], 1);
     }
     __syncthreads();
@@ -318,8 +398,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, in
 }
 
 // chunk bases per segment (in place), seg_offsets, rank_load
-__global__ __launch_bounds__(1024) void perm_scan2_kernel(int nb, int G, int S, PermWs ws,
-                                                           int32_t* __restrict__ seg_offsets,
+__global__ __launch_bounds__(1024) void perm_scan2_kernel(int G, int S, PermWs ws, int32_t* __restrict__ seg_offsets,
                                                            int32_t* __restrict__ rank_load) {
     __shared__ int tot[MOE_MAX_SEGMENTS + 1];
     __shared__ int wave_sum[16];
@@ -329,7 +408,7 @@ __global__ __launch_bounds__(1024) void perm_scan2_kernel(int nb, int G, int S, 
     constexpr int NC = 4;  // neighbouring segment columns one wavefront scans together
     for (int s0 = wave * NC; s0 < nseg; s0 += nwaves * NC) {
         int total[NC];
-        wave_columns_scan<NC>(ws.bh2, nb, nseg, s0, total);
+        wave_columns_scan<NC>(ws.bh2, ws.nb, nseg, s0, total);
         if ((tid & (kWave - 1)) == 0) {
 #pragma unroll
             for (int i = 0; i < NC; ++i)
@@ -342,17 +421,24 @@ __global__ __launch_bounds__(1024) void perm_scan2_kernel(int nb, int G, int S, 
     for (int g = tid; g < G; g += blockDim.x) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
 }
 
-// final position of every assignment
+// final position of every assignment.  SCANNED: ws.bh2 holds chunk bases and seg_offsets / rank_load
+// are written; else ws.bh2 holds counts, every workgroup works the offsets out and the first writes them.
+template <bool SCANNED>
 __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, int G, int S, PermWs ws,
-                                                                   const int32_t* __restrict__ seg_offsets,
+                                                                   int32_t* __restrict__ seg_offsets,
+                                                                   int32_t* __restrict__ rank_load,
                                                                    int32_t* __restrict__ row_of_assign,
                                                                    int32_t* __restrict__ assign_of_row) {
     __shared__ int wcnt[kPermWaves * kMaxKeys];
+    __shared__ int first[MOE_MAX_SEGMENTS];    // first row of this chunk in the segment
+    __shared__ int tot[MOE_MAX_SEGMENTS + 1];  // rows per segment -> seg_offsets
+    __shared__ int wave_sum[kPermWaves];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int w = tid / kWave;
     const int nseg = G * S;
-    const int tpc = tokens_per_chunk(k);
+    const int tpc = tokens_per_chunk(k, ws.rounds);
+    const int rounds = ws.rounds;
     const int64_t A = (int64_t)T * k;
     const int64_t base = (int64_t)blockIdx.x * tpc * k;
     const int n_b = (int)((base + (int64_t)tpc * k < A ? base + (int64_t)tpc * k : A) - base);
@@ -360,16 +446,42 @@ __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, 
     bool valid[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int p = w * (kRounds * kWave) + r * kWave + lane;
-        valid[r] = p < n_b;
+        const int p = (w * rounds + r) * kWave + lane;
+        valid[r] = r < rounds && p < n_b;
         key[r] = valid[r] ? ws.seg[base + p] : 0;
     }
-    chunk_stable_rank<kPermWaves>(key, valid, nseg, wcnt, rank, nullptr);
+    if (!SCANNED) {
+        block_column_sums(ws.bh2, ws.nb, nseg, blockIdx.x, first, tot);
+        // exclusive scan of tot: every thread takes `per` neighbouring segments
+        const int per = ceil_div(nseg, kPermThreads);
+        const int s0 = tid * per < nseg ? tid * per : nseg, s1 = s0 + per < nseg ? s0 + per : nseg;
+        int mine = 0;
+        for (int s = s0; s < s1; ++s) mine += tot[s];
+        const int incl = wave_incl_scan_i32(mine);
+        if (lane == kWave - 1) wave_sum[w] = incl;
+        __syncthreads();
+        int run = incl - mine;
+        for (int ww = 0; ww < w; ++ww) run += wave_sum[ww];
+        for (int s = s0; s < s1; ++s) {
+            const int c = tot[s];
+            tot[s] = run;
+            first[s] += run;
+            run += c;
+        }
+        if (s1 == nseg && s0 < s1) tot[nseg] = run;
+        __syncthreads();
+        if (blockIdx.x == 0) {
+            for (int s = tid; s <= nseg; s += kPermThreads) seg_offsets[s] = tot[s];
+            for (int g = tid; g < G; g += kPermThreads) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
+        }
+    }
+    chunk_stable_rank<kPermWaves, kRounds>(key, valid, nseg, wcnt, rank, nullptr, rounds);
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int p = w * (kRounds * kWave) + r * kWave + lane;
+        const int p = (w * rounds + r) * kWave + lane;
         if (!valid[r]) continue;
-        const int row = seg_offsets[key[r]] + ws.bh2[(size_t)blockIdx.x * nseg + key[r]] + rank[r];
+        const int row =
+            (SCANNED ? seg_offsets[key[r]] + ws.bh2[(size_t)blockIdx.x * nseg + key[r]] : first[key[r]]) + rank[r];
         row_of_assign[base + p] = row;
         assign_of_row[row] = (int)(base + p);
     }
@@ -384,7 +496,8 @@ __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, 
 // slot id), plus every expert's first slot.  Same ranks, same results as the kernels above.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kSmallA = kSmallThreads * kRounds;  // 8192
+constexpr int kSmallRounds = 2;
+constexpr int kSmallA = kSmallThreads * kSmallRounds;  // 2048
 constexpr int kSmallKeys = 512;
 
 // The per-slot tables, by one wavefront, 64 slots at a time in ascending order: the lanes
@@ -475,11 +588,11 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     // p = (w * rounds + r) * 64 + lane
     const int rounds = (n_b + kSmallThreads - 1) / kSmallThreads;
 
-    int key[kRounds], rank[kRounds], expert[kRounds];
-    bool valid[kRounds];
+    int key[kSmallRounds], rank[kSmallRounds], expert[kSmallRounds];
+    bool valid[kSmallRounds];
     const int32_t* rank_keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
+    for (int r = 0; r < kSmallRounds; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         valid[r] = r < rounds && p < n_b;
         key[r] = valid[r] ? clamp_key(rank_keys[p], E) : 0;
@@ -488,7 +601,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     }
     if (mode == MOE_MODE_TOKEN) {
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
+        for (int r = 0; r < kSmallRounds; ++r) {
             const int p = (w * rounds + r) * kWave + lane;
             if (valid[r]) expert[r] = clamp_key(topk_idx[p], E);
         }
@@ -511,10 +624,10 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
             const SmallTables t{s_e, s_q, s_cum, s_next, e_first, e_cnt, e_last, e_cum};
             small_slot_tables(E, nseg, t);
         }
-        chunk_stable_rank<kSmallWaves>(key, valid, E, buf, rank, nullptr, rounds);
+        chunk_stable_rank<kSmallWaves, kSmallRounds>(key, valid, E, buf, rank, nullptr, rounds);
         __syncthreads();  // the counters are dead, the buffer becomes rank and key by position
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
+        for (int r = 0; r < kSmallRounds; ++r) {
             const int p = (w * rounds + r) * kWave + lane;
             if (valid[r]) buf[p] = rank[r] | (key[r] << 16);
         }
@@ -535,10 +648,10 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     // segment of every assignment: its place i in the plan's order for its expert (-1: none),
     // then a walk over the expert's slots, at most G of them, to the one whose range holds i;
     // the rounds walk in step so that their LDS reads overlap
-    int sg[kRounds], place[kRounds];
-    bool walking[kRounds];
+    int sg[kSmallRounds], place[kSmallRounds];
+    bool walking[kSmallRounds];
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
+    for (int r = 0; r < kSmallRounds; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         sg[r] = 0;
         place[r] = -1;
@@ -568,7 +681,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     for (int seen = 1; mode != MOE_MODE_NONE && seen < G; ++seen) {
         bool more = false;
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) {  // no branches: sg[r] is a slot in any case, the reads overlap
+        for (int r = 0; r < kSmallRounds; ++r) {  // no branches: sg[r] is a slot in any case, the reads overlap
             if (r >= rounds) continue;       // (uniform)
             const int nx = s_next[sg[r]];
             const int hi = s_hi[sg[r]];
@@ -580,12 +693,12 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     }
     __syncthreads();  // every look-up of a rank is done before the buffer holds counters again
 
-    chunk_stable_rank<kSmallWaves>(sg, valid, nseg, buf, rank, tot, rounds);
+    chunk_stable_rank<kSmallWaves, kSmallRounds>(sg, valid, nseg, buf, rank, tot, rounds);
     block_exclusive_scan_2048(tot, nseg, wave_sum);
     for (int s = tid; s <= nseg; s += kSmallThreads) seg_offsets[s] = tot[s];
     for (int g = tid; g < G; g += kSmallThreads) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
+    for (int r = 0; r < kSmallRounds; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         if (!valid[r]) continue;
         const int row = tot[sg[r]] + rank[r];
@@ -636,7 +749,7 @@ extern "C" size_t moe_permute_workspace_bytes(int T, int E, int k, int G, int S)
     if (E > MOE_MAX_EXPERTS || k > MOE_MAX_TOPK || G > MOE_MAX_RANKS || S > MOE_MAX_SLOTS || G * S > MOE_MAX_SEGMENTS ||
         (int64_t)T * k >= (1ll << 31))
         return 0;
-    return perm_ws_layout(T, E, k, G, S, nullptr, nullptr);
+    return perm_ws_bytes(T, E, k, G, S);
 }
 
 namespace moegps {
@@ -659,12 +772,11 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
     if (mode == MOE_MODE_TOKEN && T > 0 && !pred_idx) return MOE_ERR_INVALID_ARG;
     if (mode == MOE_MODE_DISTRIBUTION && (!hist_true || !hist_pred)) return MOE_ERR_INVALID_ARG;
     if (x_perm && T > 0 && !x) return MOE_ERR_INVALID_ARG;
-    PermWs ws;
-    const size_t need = perm_ws_layout(T, E, k, G, S, (char*)workspace, &ws);
-    if (workspace_bytes < need) return MOE_ERR_WORKSPACE_TOO_SMALL;
+    if (workspace_bytes < perm_ws_bytes(T, E, k, G, S)) return MOE_ERR_WORKSPACE_TOO_SMALL;
+    const PermWs ws = perm_ws_layout(T, E, k, G, S, (char*)workspace);
 
     hipStream_t st = (hipStream_t)stream;
-    const int nb = T > 0 ? ceil_div(T, tokens_per_chunk(k)) : 0;
+    const int nb = ws.nb;
     int rc;
     const bool small = (int64_t)T * k <= kSmallA && E <= kSmallKeys && G * S <= kSmallKeys;
     if (small) {
@@ -673,26 +785,31 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
                            assign_of_row, rank_load);
         if ((rc = check_launch()) != MOE_OK) return rc;
     } else {
-        if (nb > 0 && mode != MOE_MODE_NONE) {
-            const int32_t* keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
-            hipLaunchKernelGGL(perm_count_kernel, dim3(nb), dim3(kPermThreads), 0, st, keys, T, k, E, ws.bh1);
-            if ((rc = check_launch()) != MOE_OK) return rc;
-        }
+        const bool scanned = nb == 0 || nb > kSelfScanChunks;
         if (mode != MOE_MODE_NONE) {
-            hipLaunchKernelGGL(perm_scan1_kernel, dim3(ceil_div(E, kScan1Threads / kWave)), dim3(kScan1Threads), 0, st,
-                               mode, nb, E, G, S, hist_true, hist_pred, slot_expert, slot_quota, ws);
+            const int32_t* keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
+            hipLaunchKernelGGL(perm_count_kernel, dim3(nb + ceil_div(E, kPermWaves)), dim3(kPermThreads), 0, st, keys,
+                               mode, T, k, E, G, S, hist_true, hist_pred, slot_expert, slot_quota, ws);
+            if ((rc = check_launch()) != MOE_OK) return rc;
+            if (scanned && nb > 0) {
+                hipLaunchKernelGGL(perm_scan1_kernel, dim3(ceil_div(E, kScan1Threads / kWave)), dim3(kScan1Threads), 0,
+                                   st, E, ws);
+                if ((rc = check_launch()) != MOE_OK) return rc;
+            }
+        }
+        if (nb > 0) {
+            hipLaunchKernelGGL(scanned ? perm_segment_kernel<true> : perm_segment_kernel<false>, dim3(nb),
+                               dim3(kPermThreads), 0, st, mode, T, k, E, G, S, topk_idx, pred_idx, ws);
+            if ((rc = check_launch()) != MOE_OK) return rc;
+        }
+        if (scanned) {
+            hipLaunchKernelGGL(perm_scan2_kernel, dim3(1), dim3(1024), 0, st, G, S, ws, seg_offsets, rank_load);
             if ((rc = check_launch()) != MOE_OK) return rc;
         }
         if (nb > 0) {
-            hipLaunchKernelGGL(perm_segment_kernel, dim3(nb), dim3(kPermThreads), 0, st, mode, T, k, E, G, S, topk_idx,
-                               pred_idx, ws);
-            if ((rc = check_launch()) != MOE_OK) return rc;
-        }
-        hipLaunchKernelGGL(perm_scan2_kernel, dim3(1), dim3(1024), 0, st, nb, G, S, ws, seg_offsets, rank_load);
-        if ((rc = check_launch()) != MOE_OK) return rc;
-        if (nb > 0) {
-            hipLaunchKernelGGL(perm_place_kernel, dim3(nb), dim3(kPermThreads), 0, st, T, k, G, S, ws, seg_offsets,
-                               row_of_assign, assign_of_row);
+            hipLaunchKernelGGL(scanned ? perm_place_kernel<true> : perm_place_kernel<false>, dim3(nb),
+                               dim3(kPermThreads), 0, st, T, k, G, S, ws, seg_offsets, rank_load, row_of_assign,
+                               assign_of_row);
             if ((rc = check_launch()) != MOE_OK) return rc;
         }
     }
@@ -770,7 +887,7 @@ extern "C" int moe_permute_static(int mode, const void* x, int dtype, int T, int
     using namespace moegps;
     if (T < 0 || E < 1 || k < 1 || G < 1 || S < 1) return MOE_ERR_INVALID_ARG;
     // sizes whose counters do not fit the fixed array are refused before anything is enqueued
-    if (perm_ws_layout(T, E, k, G, S, nullptr, nullptr) > (size_t)MOE_PERMUTE_STATIC_SCRATCH_BYTES)
+    if (perm_ws_bytes(T, E, k, G, S) > (size_t)MOE_PERMUTE_STATIC_SCRATCH_BYTES)
         return MOE_ERR_WORKSPACE_TOO_SMALL;
     void* ptr = nullptr;
     const int rc = static_scratch(&ptr);

@@ -183,6 +183,25 @@ def test_permute_small(mode, T, E, k, G, S):
     assert np.array_equal(out["x_perm"].cpu().numpy(), ref_rows)        # byte-exact row copy
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("T,E,k,G,S", [(128, 128, 16, 32, 5),   # the most one workgroup takes: 2048
+                                       (129, 128, 16, 32, 5),   # and one token more
+                                       (4097, 64, 6, 16, 5),    # chunks of 252 elements, last one ragged
+                                       (8193, 16, 4, 8, 3),     # just over 128 chunks of one round: two rounds
+                                       (3000, 1024, 8, 128, 16),   # chunk size limited by the scratch of 2048 slots
+                                       (66000, 16, 8, 8, 3)])   # more chunks than one workgroup adds up: the scans
+def test_permute_chunk_sizes(mode, T, E, k, G, S):
+    """The index outputs at the lines where the launches change: one workgroup or several, rounds
+    per chunk, counts added up by every workgroup or scanned first."""
+    cfg = wl.MoEConfig("p", T=T, d=16, ffn=8, E=E, k=k, G=G, S=S, dtype="f32", mode=mode, alpha=0.5,
+                       sigma_pred=0.3, acc=0.8, seed=T + k)
+    case = Case(cfg, with_x=False)
+    out = B.moe_permute(mode, None, dev_i32(case.idx), case.dev_pred_idx(), dev_i32(case.hist), case.dev_hist_plan(),
+                        dev_i32(case.plan.slot_expert), dev_i32(case.plan.slot_quota), E, G, S, copy_rows=False)
+    for name in ("seg_offsets", "row_of_assign", "assign_of_row", "rank_load"):
+        assert np.array_equal(out[name].cpu().numpy(), case.perm[name]), name
+
+
 def test_permute_empty_input():
     E, G, S, k = 4, 2, 2, 2
     plan = plan_duplicates(0, [0] * E, E, G, S, G)
