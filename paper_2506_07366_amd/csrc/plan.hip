@@ -178,30 +178,63 @@ __global__ __launch_bounds__(kWave) void plan_kernel(int mode, const int32_t* __
 // ---------------------------------------------------------------------------
 // Register-resident version for G <= 64: lane g owns rank g (its load and its S
 // slots live in registers; the copy count of an expert is a ballot over the lanes).  One iteration
-// is a few DPP reductions, ballots and lane reads; there is no barrier.  The
+// is a few DPP reductions, ballots and lane reads; there is no barrier.  The loop is one wavefront
+// running instructions one after the other (5-8 cycles each), so what counts is how many there
+// are.  An iteration first looks at the pair the serial scan of Algorithm 1 starts with, the
+// hottest expert of the hottest rank and the coldest rank: O(S) instructions.  Only if that
+// move is infeasible every rank looks at every slot of the hot rank, O(S^2): the
 // candidate a lane proposes is its first feasible slot of the hot rank in (rows
 // descending, slot ascending) order; the coldest proposing lane wins, which is the
-// candidate the serial scan of Algorithm 1 (with the fall-through order of the
-// header) reaches first.
+// candidate the serial scan (with the fall-through order of the header) reaches first.
+// A copy goes into the lowest empty slot and home slots are the lowest, so the occupied slots of
+// a rank are always a prefix and one counter stands for them.
+// Per call against looking at every slot for every rank each time (and reductions whose lane
+// permutes did not fold into the max): 8 ranks of 2 slots, 15 moves 10.5 -> 8.4 us; 32 of 5, 40 moves
+// 38.3 -> 31.0, 70 moves 69 -> 58; 16 of 5, 33 moves 34.4 -> 27.7; 8 of 10, 28 moves 47.4 -> 33.2.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int dpp_max_step(int v, int o) { return o > v ? o : v; }
 __device__ __forceinline__ int dpp_min_step(int v, int o) { return o < v ? o : v; }
 
-// reduction over the 64 lanes: quads and rows of 16 by DPP lane permutes, the four
-// rows by lane reads.  Every lane must be active.
+// Reductions over the first ROWS rows of 16 lanes (the lanes that hold ranks; those without one hold
+// neutral values): inside a row by DPP lane permutes, which fold into the max or min that takes
+// them, the rows by lane reads.  Every lane must be active.
 template <bool IS_MAX>
-__device__ __forceinline__ int wave_reduce_i32(int v) {
-    auto op = [](int a, int b) { return IS_MAX ? dpp_max_step(a, b) : dpp_min_step(a, b); };
-    v = op(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
-    v = op(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
-    v = op(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false));  // row_half_mirror
-    v = op(v, __builtin_amdgcn_update_dpp(v, v, 0x140, 0xf, 0xf, false));  // row_mirror
-    const int r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
-    const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-    return op(op(r0, r1), op(r2, r3));
+__device__ __forceinline__ int row_reduce_step(int v, int level) {
+    const int o = level == 0   ? __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true)    // quad_perm [1,0,3,2]
+                  : level == 1 ? __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true)    // quad_perm [2,3,0,1]
+                  : level == 2 ? __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true)   // row_half_mirror
+                               : __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);  // row_mirror
+    return IS_MAX ? dpp_max_step(v, o) : dpp_min_step(v, o);
+}
+template <bool IS_MAX, int ROWS>
+__device__ __forceinline__ int rows_reduce(int v) {
+    int r = __builtin_amdgcn_readlane(v, 0);
+#pragma unroll
+    for (int i = 1; i < ROWS; ++i) {
+        const int o = __builtin_amdgcn_readlane(v, 16 * i);
+        r = IS_MAX ? dpp_max_step(r, o) : dpp_min_step(r, o);
+    }
+    return __builtin_amdgcn_readfirstlane(r);
+}
+template <int ROWS>
+__device__ __forceinline__ int wave_min_i32(int v) {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) v = row_reduce_step<false>(v, l);
+    return rows_reduce<false, ROWS>(v);
+}
+// maximum of a and minimum of b, step by step side by side
+template <int ROWS>
+__device__ __forceinline__ void wave_max_min_i32(int a, int b, int& mx, int& mn) {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        a = row_reduce_step<true>(a, l);
+        b = row_reduce_step<false>(b, l);
+    }
+    mx = rows_reduce<true, ROWS>(a);
+    mn = rows_reduce<false, ROWS>(b);
 }
 
-template <int SMAX>
+template <int SMAX, int ROWS>
 __global__ __launch_bounds__(kWave) void plan_kernel_regs(int mode, const int32_t* __restrict__ hist_pred, int E,
                                                           int G, int S, int c_max,
                                                           int32_t* __restrict__ slot_expert,
@@ -214,13 +247,23 @@ __global__ __launch_bounds__(kWave) void plan_kernel_regs(int mode, const int32_
     constexpr int NONE = -2;  // slot index >= S: neither empty nor an expert
     const int IMAX = 0x7fffffff;
 
+    // slot of rank g that hosts expert e (one byte each), kNoHost: none
+    constexpr int kNoHost = 255;
+    __shared__ __align__(16) unsigned char host_of[MOE_MAX_EXPERTS * kWave];
+    if (mode != MOE_MODE_NONE) {
+        for (int i = lane * 16; i < E * kWave; i += kWave * 16)
+            *(uint4*)&host_of[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+        __syncthreads();
+    }
     int se[SMAX], q[SMAX];
-    int L = 0;
+    int L = 0, occupied = 0;
 #pragma unroll
     for (int s = 0; s < SMAX; ++s) {
         const int e = lane * H + s;
         const bool home = valid && s < H && e < E;
         se[s] = home ? e : (s < S ? -1 : NONE);
+        occupied += home ? 1 : 0;
+        if (home && mode != MOE_MODE_NONE) host_of[e * kWave + lane] = (unsigned char)s;
         int n = home ? hist_pred[e] : 0;
         q[s] = n > 0 ? n : 0;
         L += q[s];
@@ -229,68 +272,94 @@ __global__ __launch_bounds__(kWave) void plan_kernel_regs(int mode, const int32_
     int n_iters = 0;
     if (mode != MOE_MODE_NONE) {
         const int i_max = 16 * G * S;
+        const unsigned long long ranks = G < kWave ? (1ull << G) - 1ull : ~0ull;  // lanes that hold a rank
         while (n_iters < i_max) {
-            const int L_h = wave_reduce_i32<true>(valid ? L : -1);
-            const int L_min = wave_reduce_i32<false>(valid ? L : IMAX);
+            int L_h, L_min;
+            wave_max_min_i32<ROWS>(valid ? L : -1, valid ? L : IMAX, L_h, L_min);
             if (L_h - L_min <= 1) break;  // loop guard of Algorithm 1
-            const int g_h = __ffsll((unsigned long long)__ballot(valid && L == L_h)) - 1;  // ties -> lowest g
+            // hottest and coldest rank, ties -> lowest g
+            const int g_h = __builtin_ctzll(__ballot(L == L_h) & ranks);
+            int g_c = __builtin_ctzll(__ballot(L == L_min) & ranks);
+            int L_c = L_min;
 
-            // lowest empty slot of this lane's rank
-            int empty = -1;
+            // hottest expert of every rank (equal rows keep the lower slot); the hot rank's is wanted
+            int top_q = q[0];
 #pragma unroll
-            for (int t = SMAX - 1; t >= 0; --t)
-                if (se[t] == -1) empty = t;
-
-            const bool cand = valid && lane != g_h && (L_h - L > 1);
-            int best_q = 0, best_s = 0, best_sp = 0, best_new = 0, best_e = 0;
+            for (int t = 1; t < SMAX; ++t) top_q = q[t] > top_q ? q[t] : top_q;
+            int top_s = 0, top_e = se[0];
 #pragma unroll
-            for (int s = 0; s < SMAX; ++s) {
-                const int hq = __builtin_amdgcn_readlane(q[s], g_h);  // rows of the hot rank's slot s
-                const int he = __builtin_amdgcn_readlane(se[s], g_h);
-                if (hq > 0) {  // uniform
-                    int host = -1;
+            for (int t = SMAX - 1; t >= 0; --t) {
+                top_s = q[t] == top_q ? t : top_s;
+                top_e = q[t] == top_q ? se[t] : top_e;
+            }
+            int q_sel = __builtin_amdgcn_readlane(top_q, g_h);
+            int s_sel = __builtin_amdgcn_readlane(top_s, g_h);
+            int e_sel = __builtin_amdgcn_readlane(top_e, g_h);
+            int host = -1;
 #pragma unroll
-                    for (int t = SMAX - 1; t >= 0; --t)
-                        if (se[t] == he) host = t;
-                    // every rank hosts an expert at most once: copies = number of hosting lanes
-                    const int n_copies = __popcll((unsigned long long)__ballot(valid && host >= 0));
-                    const bool can_copy = n_copies < c_max && empty >= 0;
-                    const bool feasible = host >= 0 || can_copy;
-                    if (feasible && hq > best_q) {  // strict: equal rows keep the lower slot
-                        best_q = hq;
-                        best_s = s;
-                        best_sp = host >= 0 ? host : empty;
-                        best_new = host < 0;
-                        best_e = he;
+            for (int t = SMAX - 1; t >= 0; --t) host = se[t] == e_sel ? t : host;
+            // every rank hosts an expert at most once: copies = number of hosting lanes
+            const int copies = __popcll((unsigned long long)__ballot(host >= 0));
+            int sp_sel = __builtin_amdgcn_readlane(host, g_c);
+            bool feasible = sp_sel >= 0;
+            if (!feasible) {
+                sp_sel = __builtin_amdgcn_readlane(occupied, g_c);
+                feasible = copies < c_max && sp_sel < S;
+            }
+            if (!feasible) {
+                // per slot of the hot rank: which ranks host its expert (one byte per rank and expert in
+                // LDS, all slots' reads under way together) or have room for a copy
+                int hq[SMAX], he[SMAX], hv[SMAX];
+#pragma unroll
+                for (int s = 0; s < SMAX; ++s) {
+                    hq[s] = __builtin_amdgcn_readlane(q[s], g_h);
+                    he[s] = __builtin_amdgcn_readlane(se[s], g_h);
+                    hv[s] = host_of[(he[s] > 0 ? he[s] : 0) * kWave + lane];
+                }
+                const unsigned long long room = __ballot(occupied < S);
+                const unsigned long long colder = __ballot(L_h - L > 1) & ranks;
+                unsigned long long any = 0ull;
+                bool spare[SMAX];  // the expert may have another copy
+#pragma unroll
+                for (int s = 0; s < SMAX; ++s) {
+                    const unsigned long long hosts = __ballot(hv[s] != kNoHost);
+                    spare[s] = __popcll(hosts) < c_max;
+                    any |= hq[s] > 0 ? hosts | (spare[s] ? room : 0ull) : 0ull;
+                }
+                any &= colder;
+                if (any == 0ull) break;  // nothing feasible
+                const bool has = __builtin_amdgcn_inverse_ballot_w64(any);
+                L_c = wave_min_i32<ROWS>(has ? L : IMAX);
+                g_c = __builtin_ctzll(__ballot(L == L_c) & any);  // ties -> lowest g
+                // that rank's first feasible slot of the hot rank, equal rows keep the lower slot
+                const int free_slot = __builtin_amdgcn_readlane(occupied, g_c);
+                q_sel = 0;
+#pragma unroll
+                for (int s = 0; s < SMAX; ++s) {
+                    const int at = __builtin_amdgcn_readlane(hv[s], g_c);
+                    const bool ok = at != kNoHost || (spare[s] && free_slot < S);
+                    if (ok && hq[s] > q_sel) {
+                        q_sel = hq[s];
+                        s_sel = s;
+                        e_sel = he[s];
+                        sp_sel = at != kNoHost ? at : free_slot;
                     }
                 }
             }
-            const bool has = cand && best_q > 0;
-            const int L_c = wave_reduce_i32<false>(has ? L : IMAX);
-            if (L_c == IMAX) break;  // nothing feasible
-            const int g_c = __ffsll((unsigned long long)__ballot(has && L == L_c)) - 1;  // ties -> lowest g
-            const int s_sel = __builtin_amdgcn_readlane(best_s, g_c);
-            const int sp_sel = __builtin_amdgcn_readlane(best_sp, g_c);
-            const int new_sel = __builtin_amdgcn_readlane(best_new, g_c);
-            const int e_sel = __builtin_amdgcn_readlane(best_e, g_c);
-            const int q_sel = __builtin_amdgcn_readlane(best_q, g_c);
             const int delta = (L_h - L_c + 1) / 2;  // ceil((L_h - L_c) / 2)
             const int m = delta < q_sel ? delta : q_sel;
-            if (lane == g_h) {
+            // both ranks at once: the slot that changes hosts (or, with a copy, now hosts) e_sel
+            const bool cold = lane == g_c;
+            const int change = lane == g_h ? -m : (cold ? m : 0);
+            const int slot = lane == g_h ? s_sel : (cold ? sp_sel : -1);
 #pragma unroll
-                for (int t = 0; t < SMAX; ++t)
-                    if (t == s_sel) q[t] -= m;
-                L -= m;
+            for (int t = 0; t < SMAX; ++t) {
+                q[t] += t == slot ? change : 0;
+                se[t] = t == slot ? e_sel : se[t];
             }
-            if (lane == g_c) {
-#pragma unroll
-                for (int t = 0; t < SMAX; ++t)
-                    if (t == sp_sel) {
-                        q[t] += m;
-                        if (new_sel) se[t] = e_sel;  // copy weights of e* on g_c
-                    }
-                L += m;
-            }
+            L += change;
+            if (cold) host_of[e_sel * kWave + lane] = (unsigned char)sp_sel;
+            occupied += cold && sp_sel == occupied ? 1 : 0;
             ++n_iters;
         }
     }
@@ -327,22 +396,22 @@ extern "C" int moe_plan_duplicates(int mode, const int32_t* hist_pred, int E, in
         };
         // one instantiation per slot count: every loop over a rank's slots is unrolled to exactly S
         switch (S) {
-            case 1: launch(plan_kernel_regs<1>); break;
-            case 2: launch(plan_kernel_regs<2>); break;
-            case 3: launch(plan_kernel_regs<3>); break;
-            case 4: launch(plan_kernel_regs<4>); break;
-            case 5: launch(plan_kernel_regs<5>); break;
-            case 6: launch(plan_kernel_regs<6>); break;
-            case 7: launch(plan_kernel_regs<7>); break;
-            case 8: launch(plan_kernel_regs<8>); break;
-            case 9: launch(plan_kernel_regs<9>); break;
-            case 10: launch(plan_kernel_regs<10>); break;
-            case 11: launch(plan_kernel_regs<11>); break;
-            case 12: launch(plan_kernel_regs<12>); break;
-            case 13: launch(plan_kernel_regs<13>); break;
-            case 14: launch(plan_kernel_regs<14>); break;
-            case 15: launch(plan_kernel_regs<15>); break;
-            default: launch(plan_kernel_regs<16>); break;
+            case 1: launch(G <= 32 ? plan_kernel_regs<1, 2> : plan_kernel_regs<1, 4>); break;
+            case 2: launch(G <= 32 ? plan_kernel_regs<2, 2> : plan_kernel_regs<2, 4>); break;
+            case 3: launch(G <= 32 ? plan_kernel_regs<3, 2> : plan_kernel_regs<3, 4>); break;
+            case 4: launch(G <= 32 ? plan_kernel_regs<4, 2> : plan_kernel_regs<4, 4>); break;
+            case 5: launch(G <= 32 ? plan_kernel_regs<5, 2> : plan_kernel_regs<5, 4>); break;
+            case 6: launch(G <= 32 ? plan_kernel_regs<6, 2> : plan_kernel_regs<6, 4>); break;
+            case 7: launch(G <= 32 ? plan_kernel_regs<7, 2> : plan_kernel_regs<7, 4>); break;
+            case 8: launch(G <= 32 ? plan_kernel_regs<8, 2> : plan_kernel_regs<8, 4>); break;
+            case 9: launch(G <= 32 ? plan_kernel_regs<9, 2> : plan_kernel_regs<9, 4>); break;
+            case 10: launch(G <= 32 ? plan_kernel_regs<10, 2> : plan_kernel_regs<10, 4>); break;
+            case 11: launch(G <= 32 ? plan_kernel_regs<11, 2> : plan_kernel_regs<11, 4>); break;
+            case 12: launch(G <= 32 ? plan_kernel_regs<12, 2> : plan_kernel_regs<12, 4>); break;
+            case 13: launch(G <= 32 ? plan_kernel_regs<13, 2> : plan_kernel_regs<13, 4>); break;
+            case 14: launch(G <= 32 ? plan_kernel_regs<14, 2> : plan_kernel_regs<14, 4>); break;
+            case 15: launch(G <= 32 ? plan_kernel_regs<15, 2> : plan_kernel_regs<15, 4>); break;
+            default: launch(G <= 32 ? plan_kernel_regs<16, 2> : plan_kernel_regs<16, 4>); break;
         }
         return check_launch();
     }

@@ -140,6 +140,24 @@ def test_plan_random_small_cases():
             assert int(it.item()) == ref.n_iters
 
 
+@pytest.mark.parametrize("G", [1, 2, 16, 17, 32, 33, 63, 64])
+def test_plan_rank_rows_and_caps(G):
+    """Plans at the rank counts where rows of 16 lanes fill up, from one slot per rank to sixteen, with
+    caps that stop the first candidate (so that colder or less hot ones are taken) and with ties."""
+    rng = np.random.default_rng(G)
+    for S in (1, 2, 5, 10, 16):
+        for H in {1, S // 2, S} - {0}:
+            E = max(1, G * H - (G > 1 and H > 1))
+            for c_max in (1, 2, G):
+                for hist in (rng.zipf(1.3, E).clip(0, 10**6), rng.integers(0, 4, E), np.full(E, 7)):
+                    ref = plan_duplicates(1, hist.tolist(), E, G, S, c_max)
+                    se, q, load, it = B.moe_plan_duplicates(1, dev_i32(hist), G, S, c_max)
+                    key = (S, H, c_max)
+                    assert np.array_equal(se.cpu().numpy(), ref.slot_expert), key
+                    assert np.array_equal(q.cpu().numpy(), ref.slot_quota), key
+                    assert int(it) == ref.n_iters, key
+
+
 def test_plan_many_ranks():
     # more ranks than one wavefront has lanes
     rng = np.random.default_rng(3)
