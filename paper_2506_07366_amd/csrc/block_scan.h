@@ -1,4 +1,4 @@
-// Exclusive prefix sum of up to 2048 ints held in LDS, by a 1024-thread workgroup.
+// Prefix sums: of up to 2048 ints held in LDS, by a 1024-thread workgroup; over a wavefront.
 #pragma once
 #include "common.h"
 
@@ -37,63 +37,31 @@ __device__ inline void block_exclusive_scan_2048(int* data, int n, int* wave_sum
     __syncthreads();
 }
 
-// The same for two arrays at once (one pass, one pair of barriers): wave_sum has room for 32 ints.
-__device__ inline void block_exclusive_scan2_2048(int* da, int* db, int n, int* wave_sum) {
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int i0 = 2 * tid, i1 = 2 * tid + 1;
-    const int a0 = i0 < n ? da[i0] : 0, a1 = i1 < n ? da[i1] : 0;
-    const int b0 = i0 < n ? db[i0] : 0, b1 = i1 < n ? db[i1] : 0;
-    int ia = a0 + a1, ib = b0 + b1;
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
-        const int oa = __shfl_up(ia, m, kWave);
-        const int ob = __shfl_up(ib, m, kWave);
-        if (lane >= m) {
-            ia += oa;
-            ib += ob;
-        }
-    }
-    if (lane == kWave - 1) {
-        wave_sum[tid / kWave] = ia;
-        wave_sum[16 + tid / kWave] = ib;
-    }
-    __syncthreads();
-    int sa[16], sb[16];
-#pragma unroll
-    for (int ww = 0; ww < 16; ++ww) {
-        sa[ww] = wave_sum[ww];
-        sb[ww] = wave_sum[16 + ww];
-    }
-    int wa = 0, wb = 0, ta = 0, tb = 0;
-#pragma unroll
-    for (int ww = 0; ww < 16; ++ww) {
-        wa += ww < tid / kWave ? sa[ww] : 0;
-        wb += ww < tid / kWave ? sb[ww] : 0;
-        ta += sa[ww];
-        tb += sb[ww];
-    }
-    const int ea = wa + ia - (a0 + a1), eb = wb + ib - (b0 + b1);
-    if (i0 < n) {
-        da[i0] = ea;
-        db[i0] = eb;
-    }
-    if (i1 < n) {
-        da[i1] = ea + a0;
-        db[i1] = eb + b0;
-    }
-    if (tid == 0) {
-        da[n] = ta;
-        db[n] = tb;
-    }
-    __syncthreads();
-}
-
 // sum of v over the 64 lanes of a wavefront (every lane active), in every lane
 __device__ __forceinline__ int wave_sum_i32(int v) {
 #pragma unroll
     for (int m = kWave / 2; m > 0; m >>= 1) v += __shfl_xor(v, m, kWave);
     return v;
+}
+
+// inclusive prefix sums over the 64 lanes of a wavefront (every lane active), by DPP: inside rows of 16
+// lanes by shifts, then the last lane of a row added to the rows above
+__device__ __forceinline__ int wave_prefix_i32(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Between LDS writes and reads of one wavefront's lanes of each other's words: a wavefront's LDS
+// accesses are served in order, so this only keeps the compiler from moving them.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 }  // namespace moegps

@@ -172,234 +172,234 @@ struct TableSpec {
 // rounds run as whole tiles, and the remainder -- what would otherwise be a last round with
 // most workgroups idle -- is what gets split, smallest tiles first, unless it is most of a
 // round anyway (more than 5/8: splitting would add traffic and save little).
-// Every workgroup rebuilds the small per-segment and per-expert tables in LDS and then
-// fills its stripe of the row list; workgroup 0 writes the first table and clears the claim
-// counters, workgroup 1 (0 if it is alone) the second.
+// The work is small and what it costs is waiting: for barriers of 16 wavefronts and for chains of LDS
+// round trips.  So one wavefront does the parts that need an order (64 segments or experts at a
+// time, equal keys found by ballots, counts carried in LDS, prefix sums by DPP), without a
+// barrier between its steps, and the workgroup meets three times: segments loaded, list order
+// known, table prepared; the row list and the table entries are written by everybody.
+// Every workgroup works out the list order and fills its stripe of the row list; workgroup 0
+// writes the first table and clears the claim counters, workgroup 1 (0 if it is alone) the second.
+// The ragged tiles are ranked by counting their heights instead of comparing all pairs.
+// Against pairs of segments and of experts dealt over the workgroup, some 30 barriers, and stripes of
+// 4096 positions: 8 experts in 12 slots 10.3 -> 6.5 us (in 16 slots 9.4 -> 5.5); 128 experts in 160
+// slots, one token 15.8 -> 8.5, 128 tokens 17.5 -> 9.4, 777 tokens and two tables 19.6 -> 10.5; 64 experts
+// in 80 slots, 98304 rows 16.7 -> 11.
+
+// exclusive prefix sums of data[0 .. n) in LDS, in place, by one wavefront; data[n] = total, returned
+__device__ __forceinline__ int wave_scan_lds(int* data, int n) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int per = ceil_div(n, kWave);
+    const int i0 = lane * per < n ? lane * per : n, i1 = i0 + per < n ? i0 + per : n;
+    int mine = 0;
+    for (int i = i0; i < i1; ++i) mine += data[i];
+    const int incl = wave_prefix_i32(mine);
+    int run = incl - mine;
+    for (int i = i0; i < i1; ++i) {
+        const int c = data[i];
+        data[i] = run;
+        run += c;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    if (lane == 0) data[n] = total;
+    wave_lds_order();
+    return total;
+}
+
+// lanes that hold the same key (below 1 << nbits) among the lanes with `live`
+__device__ __forceinline__ unsigned long long same_key_lanes(int key, bool live, int nbits) {
+    unsigned long long same = __ballot(live);
+    for (int b = 0; b < nbits; ++b) {
+        const bool one = (key >> b) & 1;
+        const unsigned long long m = __ballot(live && one);
+        same &= one ? m : ~m;
+    }
+    return live ? same : 0ull;
+}
+
+constexpr int kTallest = 256;  // tile heights are powers of two up to this
+static_assert(MOE_MAX_EXPERTS <= 1 << 12 && MOE_MAX_SEGMENTS <= 1 << 19, "expert and place share one int");
+
 __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __restrict__ seg_offsets,
                                                              const int32_t* __restrict__ slot_expert, int seg_begin,
                                                              int seg_end, int E, TableSpec t1, TableSpec t2,
                                                              int32_t* __restrict__ rowlist,
                                                              int32_t* __restrict__ queues, int n_queues) {
-    __shared__ __align__(16) int s_rows[MOE_MAX_SEGMENTS];  // rows of the segment (0: not live)
-    __shared__ __align__(16) int s_ex[MOE_MAX_SEGMENTS];    // its expert
+    __shared__ int s_rows[MOE_MAX_SEGMENTS];       // rows of the segment
+    __shared__ int s_ex[MOE_MAX_SEGMENTS];         // its expert and, from bit 12, its place there; -1: not live
     __shared__ int s_first[MOE_MAX_SEGMENTS];      // first row of x_perm
     __shared__ int srt_base[MOE_MAX_SEGMENTS + 1]; // list position of the j-th segment in list order
     __shared__ int srt_first[MOE_MAX_SEGMENTS];    // its first row of x_perm
-    __shared__ int e_rows[MOE_MAX_EXPERTS + 1];    // rows per expert -> list base per expert
-    __shared__ int e_segs[MOE_MAX_EXPERTS + 1];    // live segments per expert -> base in list order; later: whole
-                                                   //   ragged tiles of the experts below
+    __shared__ int e_segs[MOE_MAX_EXPERTS + 1];    // live segments per expert -> base in list order
     __shared__ int e_full[MOE_MAX_EXPERTS + 1];    // full-height tiles per expert -> base
-    __shared__ __align__(16) int e_tail[MOE_MAX_EXPERTS];  // rows of the expert's ragged tile
+    __shared__ int e_whole[MOE_MAX_EXPERTS + 1];   // whole ragged tiles of the experts below
+    __shared__ int e_tail[MOE_MAX_EXPERTS];        // rows of the expert's ragged tile
     __shared__ int e_rank[MOE_MAX_EXPERTS];        // its place among the ragged tiles, tallest first
-    __shared__ int wave_sum[32];
-    __shared__ int total_tail, tail_rows;
+    __shared__ int h_count[kTallest + 1];          // ragged tiles of a height -> taller or as tall ones excluded
+    __shared__ int h_rows[kTallest + 1];           // rows of lower ragged tiles
+    __shared__ int h_same[kTallest];               // ragged tiles of the height
+    __shared__ int s_plan[4];                      // n_full, n_tail, n_fsplit, n_rsplit
     const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const bool leader = tid < kWave;
+    const unsigned long long lt = (1ull << lane) - 1ull;
     const int ns = seg_end - seg_begin;
     if (blockIdx.x == 0)
         for (int i = tid; i < n_queues; i += blockDim.x) queues[i] = 0;
-    for (int e = tid; e < E; e += blockDim.x) e_rows[e] = e_segs[e] = 0;
-    __syncthreads();
+    for (int e = tid; e < E; e += blockDim.x) e_segs[e] = 0;
     for (int i = tid; i < ns; i += blockDim.x) {
         const int s = seg_begin + i;
         const int lo = seg_offsets[s];
         const int rows = seg_offsets[s + 1] - lo;
         const int e = slot_expert[s];
-        const bool live = rows > 0 && e >= 0 && e < E;
-        s_rows[i] = live ? rows : 0;
-        s_ex[i] = e;
+        s_rows[i] = rows;
+        s_ex[i] = rows > 0 && e >= 0 && e < E ? e : -1;
         s_first[i] = lo;
-        if (live) {
-            atomicAdd(&e_rows[e], rows);
-            atomicAdd(&e_segs[e], 1);
-        }
     }
     __syncthreads();
-    // e_rows[e] = list base, e_rows[E] = rows in the range; e_segs[e] = base in list order
-    block_exclusive_scan2_2048(e_rows, e_segs, E, wave_sum);
-    const int n_list = e_rows[E], n_live = e_segs[E];
-    // place of every live segment in list order: behind the segments of lower experts and the
-    // lower segments of its own expert.  A thread's time goes by the instructions it runs one
-    // after the other, so the pairs (segment, lower segment) are dealt over the whole workgroup:
-    // `share` threads split the lower segments of one segment between them and add their
-    // counts up in LDS (srt_base / srt_first hold them by segment until the places are known).
-    for (int i = tid; i < ns; i += blockDim.x) srt_base[i] = srt_first[i] = 0;
-    __syncthreads();
-    {
-        int width = kWave;  // threads side by side on different segments
-        while (width < ns && width < (int)blockDim.x) width <<= 1;
-        const int share = blockDim.x / width, part = tid / width;
-        const int per = ceil_div(ceil_div(ns, 4), share);  // groups of four lower segments per thread
-        for (int i = tid % width; i < ns; i += width) {
-            if (s_rows[i] == 0) continue;
-            const int e = s_ex[i];
-            int before = 0, rows_before = 0;
-            const int g_end = (part + 1) * per < ceil_div(i, 4) ? (part + 1) * per : ceil_div(i, 4);
-            for (int g = part * per; g < g_end; ++g) {  // four segments per LDS read, no branches
-                const int j0 = 4 * g;
-                const int4 r4 = *reinterpret_cast<const int4*>(&s_rows[j0]);
-                const int4 x4 = *reinterpret_cast<const int4*>(&s_ex[j0]);
-                const int rs[4] = {r4.x, r4.y, r4.z, r4.w};
-                const int xs[4] = {x4.x, x4.y, x4.z, x4.w};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const bool same = j0 + u < i && rs[u] > 0 && xs[u] == e;
-                    before += same ? 1 : 0;
-                    rows_before += same ? rs[u] : 0;
-                }
+    if (leader) {
+        const int nbits = E > 1 ? 32 - __builtin_clz(E - 1) : 0;
+        for (int i0 = 0; i0 < ns; i0 += kWave) {
+            const int i = i0 + lane;
+            const int e = i < ns ? s_ex[i] : -1;
+            const unsigned long long same = same_key_lanes(e, e >= 0, nbits);
+            if (e >= 0) {
+                const int before = e_segs[e];
+                s_ex[i] = e | (before + __popcll(same & lt)) << 12;
+                if ((same & ~lt) == (1ull << lane)) e_segs[e] = before + __popcll(same);  // the last of them
             }
-            if (before) {
-                atomicAdd(&srt_base[i], before);
-                atomicAdd(&srt_first[i], rows_before);
-            }
+            wave_lds_order();
         }
+        wave_scan_lds(e_segs, E);
+        for (int i = lane; i < ns; i += kWave) {
+            const int v = s_ex[i];
+            if (v < 0) continue;
+            const int j = e_segs[v & 0xfff] + (v >> 12);
+            srt_base[j] = s_rows[i];
+            srt_first[j] = s_first[i];
+        }
+        wave_lds_order();
+        wave_scan_lds(srt_base, e_segs[E]);
     }
     __syncthreads();
-    {
-        constexpr int kPer = MOE_MAX_SEGMENTS / 1024;  // segments per thread
-        int before[kPer], rows_before[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int i = tid + q * (int)blockDim.x;
-            before[q] = i < ns ? srt_base[i] : 0;
-            rows_before[q] = i < ns ? srt_first[i] : 0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int i = tid + q * (int)blockDim.x;
-            if (i >= ns || s_rows[i] == 0) continue;
-            const int e = s_ex[i];
-            srt_base[e_segs[e] + before[q]] = e_rows[e] + rows_before[q];
-            srt_first[e_segs[e] + before[q]] = s_first[i];
-        }
-    }
-    if (tid == 0) srt_base[n_live] = n_list;
-    __syncthreads();
+    const int n_live = e_segs[E], n_list = srt_base[n_live];
     // row list: binary search of the position among the segments in list order
-    for (int p = blockIdx.x * blockDim.x + tid; p < n_list; p += gridDim.x * blockDim.x) {
-        int lo = 0, hi = n_live - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (srt_base[mid] <= p) lo = mid;
-            else hi = mid - 1;
+    auto fill_rows = [&] {
+        for (int p = blockIdx.x * blockDim.x + tid; p < n_list; p += gridDim.x * blockDim.x) {
+            int lo = 0, hi = n_live - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (srt_base[mid] <= p) lo = mid;
+                else hi = mid - 1;
+            }
+            rowlist[p] = srt_first[lo] + (p - srt_base[lo]);
         }
-        rowlist[p] = srt_first[lo] + (p - srt_base[lo]);
-    }
+    };
     // tables
+    auto list_base = [&](int e) { return srt_base[e_segs[e]]; };  // first list position of expert e
     const bool second = (gridDim.x > 1) ? blockIdx.x == 1 : true;
     const bool first = blockIdx.x == 0;
-    if (!first && !second) return;
+    const bool busy = leader && (first || second);  // prepares a table while the others fill in the row list
+    if (!busy) fill_rows();
     for (int which = 0; which < 2; ++which) {  // uniform per workgroup
         if (which == 0 ? !first : !second) continue;
         const TableSpec& ts = which == 0 ? t1 : t2;
         if (!ts.tiles) continue;
         const int BM = ts.bm;
-        __syncthreads();
-        if (tid == 0) total_tail = tail_rows = 0;
-        __syncthreads();
-        {   // (E <= blockDim.x: one expert per thread; one LDS atomic per wavefront)
-            const int e = tid;
-            const int rows = e < E ? e_rows[e + 1] - e_rows[e] : 0;
-            const int tl = rows % BM;
-            if (e < E) {
-                e_full[e] = rows / BM;
-                e_tail[e] = tl;
-            }
-            const int n_t = wave_sum_i32(tl > 0 ? 1 : 0), r_t = wave_sum_i32(tl);
-            if ((tid & (kWave - 1)) == 0 && n_t) {
-                atomicAdd(&total_tail, n_t);
-                atomicAdd(&tail_rows, r_t);
-            }
-        }
-        __syncthreads();
-        block_exclusive_scan_2048(e_full, E, wave_sum);
-        const int n_full = e_full[E], n_tail = total_tail;
-        // tiles split at the end of the order: the smallest ragged ones first, then full-height ones
-        int n_fsplit = 0, n_rsplit = 0, n_split = 0;
-        long long want = 0;  // half-rows of M-tiles to split
         const int P = ts.parts > kMaxParts ? kMaxParts : ts.parts;
-        if (P > 1) {
-            const long long units = (long long)n_full * 2 * BM + (long long)n_tail * BM + tail_rows;  // half-rows
-            const long long round_units = (long long)ts.grid * 2 * BM;  // one tile per workgroup, times n_ntiles
-            const long long rem = (units * ts.n_ntiles) % round_units;
-            if (ts.split_all) want = units;
-            else if (rem > 0 && rem * 8 <= round_units * 5) want = (rem + ts.n_ntiles - 1) / ts.n_ntiles;
-        }
-        // ragged tile of expert e: rank in the order (tallest first) and the half-rows of the ragged
-        // tiles behind it; it is split if those do not reach `want` yet
-        __syncthreads();
-        if (tid == 0) total_tail = 0;  // reused: number of split ragged tiles, their half-rows in tail_rows
-        __syncthreads();
-        if (tid == 0) tail_rows = 0;
-        __syncthreads();
-        // (pairs of experts dealt over the workgroup like the pairs of segments above; the
-        // half-rows behind a ragged tile are counted in srt_first, free since the row list is
-        // written: at most E * 2 * BM, an int)
-        int* e_behind = srt_first;
-        for (int e = tid; e < E; e += blockDim.x) e_rank[e] = e_behind[e] = 0;
-        __syncthreads();
-        {
-            int width = kWave;
-            while (width < E && width < (int)blockDim.x) width <<= 1;
-            const int share = blockDim.x / width, part = tid / width;
-            const int per = ceil_div(ceil_div(E, 4), share);
-            const int e = tid % width;
-            const int tl = e < E ? e_tail[e] : 0;
-            if (tl > 0) {
-                int rank = 0, behind = 0;
-                const int g_end = (part + 1) * per < ceil_div(E, 4) ? (part + 1) * per : ceil_div(E, 4);
-                for (int g = part * per; g < g_end; ++g) {
-                    const int j0 = 4 * g;
-                    const int4 t4 = *reinterpret_cast<const int4*>(&e_tail[j0]);
-                    const int ts4[4] = {t4.x, t4.y, t4.z, t4.w};
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int j = j0 + u, tj = ts4[u];
-                        const bool live = j < E && tj > 0;
-                        const bool ahead = tj > tl || (tj == tl && j < e);
-                        rank += (live && ahead) ? 1 : 0;
-                        behind += (live && !ahead && j != e) ? BM + tj : 0;
-                    }
+        if (which == 1 && first) __syncthreads();  // (alone: the first table's entries are written)
+        if (leader) {
+            const int shift = __builtin_ctz(BM);
+            for (int v = lane; v < BM; v += kWave) h_count[v] = 0;
+            wave_lds_order();
+            int n_tail_l = 0, tail_rows_l = 0;
+            for (int e0 = 0; e0 < E; e0 += kWave) {
+                const int e = e0 + lane;
+                const int rows = e < E ? list_base(e + 1) - list_base(e) : 0;
+                const int tl = rows & (BM - 1);
+                const unsigned long long same = same_key_lanes(tl, tl > 0, shift);
+                if (e < E) {
+                    e_full[e] = rows >> shift;
+                    e_tail[e] = tl;
                 }
-                if (rank) atomicAdd(&e_rank[e], rank);
-                if (behind) atomicAdd(&e_behind[e], behind);
+                if (tl > 0) {  // place among the ragged tiles of its height, lower experts first
+                    const int before = h_count[tl];
+                    e_rank[e] = before + __popcll(same & lt);
+                    if ((same & ~lt) == (1ull << lane)) h_count[tl] = before + __popcll(same);
+                    n_tail_l += 1;
+                    tail_rows_l += tl;
+                }
+                wave_lds_order();
+            }
+            const int n_full = wave_scan_lds(e_full, E);
+            const int n_tail = wave_sum_i32(n_tail_l), tail_rows = wave_sum_i32(tail_rows_l);
+            for (int v = lane; v < BM; v += kWave) {
+                const int c = h_count[v];
+                h_same[v] = c;
+                h_rows[v] = c * v;
+            }
+            wave_lds_order();
+            wave_scan_lds(h_count, BM);  // ragged tiles lower than v
+            wave_scan_lds(h_rows, BM);   // and their rows
+            // tiles split at the end of the order: the smallest ragged ones first, then full-height ones
+            long long want = 0;  // half-rows of M-tiles to split
+            if (P > 1) {
+                const long long units = (long long)n_full * 2 * BM + (long long)n_tail * BM + tail_rows;  // half-rows
+                const int round_units = ts.grid * 2 * BM;  // one tile per workgroup, times n_ntiles
+                const long long all = units * ts.n_ntiles;
+                const int rem = (int)((round_units & (round_units - 1)) == 0 ? (all & (round_units - 1)) : all % round_units);
+                if (ts.split_all) want = units;
+                else if (rem > 0 && (long long)rem * 8 <= (long long)round_units * 5) want = (rem + ts.n_ntiles - 1) / ts.n_ntiles;
+            }
+            // ragged tile of expert e: rank in the order (tallest first), and the half-rows of the ragged
+            // tiles behind it; it is split if those do not reach `want` yet
+            int n_cut_l = 0, cut_units_l = 0;
+            for (int e = lane; e < E; e += kWave) {
+                const int tl = e_tail[e];
+                if (tl == 0) continue;
+                const int tie = e_rank[e];
+                const int lower = h_count[tl], same = h_same[tl];
+                const int rank = n_tail - lower - same + tie;
+                e_rank[e] = rank;
+                const long long behind =
+                    (long long)(n_tail - 1 - rank) * BM + h_rows[tl] + (long long)tl * (same - 1 - tie);
+                if (behind < want) {
+                    n_cut_l += 1;
+                    cut_units_l += BM + tl;
+                }
+            }
+            int n_rsplit = wave_sum_i32(n_cut_l), n_fsplit = 0;
+            {
+                const long long have = wave_sum_i32(cut_units_l);
+                const long long f = want > have ? (want - have + 2 * BM - 1) >> (shift + 1) : 0;
+                n_fsplit = f < n_full ? (int)f : n_full;
+            }
+            if (n_fsplit + n_rsplit > ts.split_capacity) n_fsplit = n_rsplit = 0;  // stay in bounds (the host sizes for the rule)
+            // whole ragged tiles of the experts below e (each sits right behind its expert's full tiles)
+            wave_lds_order();
+            for (int e = lane; e < E; e += kWave)
+                e_whole[e] = (e_tail[e] > 0 && e_rank[e] < n_tail - n_rsplit) ? 1 : 0;
+            wave_lds_order();
+            wave_scan_lds(e_whole, E);
+            if (lane == 0) {
+                s_plan[0] = n_full;
+                s_plan[1] = n_tail;
+                s_plan[2] = n_fsplit;
+                s_plan[3] = n_rsplit;
             }
         }
         __syncthreads();
-        {
-            const int e = tid;
-            const int tl = e < E ? e_tail[e] : 0;
-            const bool cut = tl > 0 && (long long)e_behind[e] < want;
-            const int n_c = wave_sum_i32(cut ? 1 : 0), r_c = wave_sum_i32(cut ? BM + tl : 0);
-            if ((tid & (kWave - 1)) == 0 && n_c) {
-                atomicAdd(&total_tail, n_c);
-                atomicAdd(&tail_rows, r_c);
-            }
-        }
-        __syncthreads();
-        n_rsplit = total_tail;
-        {
-            const long long have = tail_rows;
-            const long long f = want > have ? (want - have + 2 * BM - 1) / (2 * BM) : 0;
-            n_fsplit = f < n_full ? (int)f : n_full;
-        }
-        n_split = n_fsplit + n_rsplit;
-        if (n_split > ts.split_capacity) n_fsplit = n_rsplit = n_split = 0;  // stay in bounds (the host sizes for the rule)
-        const bool split = n_split > 0;
+        const int n_full = s_plan[0], n_tail = s_plan[1], n_fsplit = s_plan[2], n_rsplit = s_plan[3];
+        const int n_split = n_fsplit + n_rsplit;
         const int n_whole_full = n_full - n_fsplit;
         const int n_whole_tail = n_tail - n_rsplit;
         const int n_whole = n_whole_full + n_whole_tail;
         const int n_entries = n_whole + n_split * P;
         const bool fits = n_entries <= ts.capacity;
         auto part_range = [&](int part, int& k0, int& k1) {
-            k0 = (int)((long long)ts.kt * part / P);
-            k1 = (int)((long long)ts.kt * (part + 1) / P);
+            const unsigned a = (unsigned)(ts.kt * part), b = (unsigned)(ts.kt * (part + 1));  // (at most 2^16 k-tiles)
+            k0 = (int)(P == kMaxParts ? a / kMaxParts : a / (unsigned)P);
+            k1 = (int)(P == kMaxParts ? b / kMaxParts : b / (unsigned)P);
         };
-        // whole ragged tiles of the experts below e (each sits right behind its expert's full tiles)
-        for (int e = tid; e < E; e += blockDim.x) e_segs[e] = (e_tail[e] > 0 && e_rank[e] < n_whole_tail) ? 1 : 0;
-        __syncthreads();
-        block_exclusive_scan_2048(e_segs, E, wave_sum);
-        auto whole_tails_below = [&](int e) { return e_segs[e]; };
         auto emit = [&](int list0, int rows, int expert, int whole_index, int split_index) {
             MTile mt;
             mt.list0 = list0;
@@ -410,8 +410,8 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             // (full tiles from n_whole_full on are split; entries of the experts below: their whole tiles)
             const int f0 = e_full[expert] < n_whole_full ? e_full[expert] : n_whole_full;
             const int f1 = e_full[expert + 1] < n_whole_full ? e_full[expert + 1] : n_whole_full;
-            mt.first = f0 + whole_tails_below(expert);
-            mt.n_same = f1 + whole_tails_below(expert + 1) - mt.first;
+            mt.first = f0 + e_whole[expert];
+            mt.n_same = f1 + e_whole[expert + 1] - mt.first;
             if (split_index < 0) {
                 ts.tiles[whole_index] = mt;
                 return;
@@ -433,8 +433,8 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
                     if (e_full[mid] <= t) lo = mid;
                     else hi = mid - 1;
                 }
-                const int list0 = e_rows[lo] + (t - e_full[lo]) * BM;
-                if (t < n_whole_full) emit(list0, BM, lo, t + whole_tails_below(lo), -1);
+                const int list0 = list_base(lo) + (t - e_full[lo]) * BM;
+                if (t < n_whole_full) emit(list0, BM, lo, t + e_whole[lo], -1);
                 else emit(list0, BM, lo, 0, t - n_whole_full);
             }
             // ragged tiles, tallest first (ties: lower expert first); the last n_rsplit of them are split
@@ -442,9 +442,9 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
                 const int tl = e_tail[e];
                 if (tl == 0) continue;
                 const int rank = e_rank[e];
-                const int list0 = e_rows[e] + (e_full[e + 1] - e_full[e]) * BM;
+                const int list0 = list_base(e) + (e_full[e + 1] - e_full[e]) * BM;
                 if (rank >= n_whole_tail) emit(list0, tl, e, 0, n_fsplit + rank - n_whole_tail);
-                else emit(list0, tl, e, (e_full[e + 1] < n_whole_full ? e_full[e + 1] : n_whole_full) + whole_tails_below(e), -1);
+                else emit(list0, tl, e, (e_full[e + 1] < n_whole_full ? e_full[e + 1] : n_whole_full) + e_whole[e], -1);
             }
         }
         if (tid == 0) {
@@ -454,6 +454,7 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             ts.counts[kCntSplit] = fits ? n_split : 0;
         }
     }
+    if (busy) fill_rows();
 }
 
 // ---------------------------------------------------------------------------
@@ -1536,7 +1537,8 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     hipStream_t st = (hipStream_t)stream;
     const size_t per = (size_t)E * d * ffn;
     const int nrange = seg_end - seg_begin;
-    const int build_grid = (int)(A / 4096 < 2 ? 2 : (A / 4096 > 64 ? 64 : A / 4096));
+    // one position of the row list per thread up to 256 workgroups
+    const int build_grid = (int)(A <= 1024 ? 2 : (A > 255 * 1024 ? 256 : ceil_div64(A, 1024) + 1));
     int rc;
     RowMap rm1{ws.rowlist, gather_rows, gather_div, nullptr, nullptr, nullptr};
     RowMap rm2{nullptr, nullptr, 1, ws.rowlist, scale_idx, scale};

@@ -387,6 +387,23 @@ def test_ffn_many_experts_full_and_ragged_tiles(split, ffn_options):
     assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * scale)
 
 
+@pytest.mark.parametrize("dtype,split", [("f32", -1), ("bf16", -1), ("bf16", 1)])
+@pytest.mark.parametrize("E,nseg,rows", [(1, 1, 5), (63, 64, 3000), (65, 130, 3000), (1023, 2047, 5000), (1024, 2048, 5000)])
+def test_ffn_tables_of_many_slots(E, nseg, rows, dtype, split, ffn_options):
+    """Row list and tile tables where segments, experts and rows cross wavefronts and workgroups:
+    replicas in any order, empty and unused slots, many ragged tiles of equal height."""
+    ffn_options(split=split)
+    rng = np.random.default_rng(E + nseg)
+    cfg = wl.MoEConfig("f", T=1, d=64, ffn=128, E=E, k=1, G=1, S=E, dtype=dtype, mode=0, seed=9)
+    slot_expert = rng.integers(-1, E, nseg).astype(np.int32)
+    slot_expert[: min(E, nseg)] = rng.permutation(E)[: min(E, nseg)]
+    rng.shuffle(slot_expert)
+    p = np.where(slot_expert >= 0, rng.random(nseg) ** 4, 0)
+    sizes = rng.multinomial(rows, p / p.sum()).tolist()
+    got, ref, _ = run_ffn_case(cfg, sizes, slot_expert, seed=2)
+    assert rel_err(got, ref) <= TOL[dtype]
+
+
 def test_ffn_one_huge_segment_and_empty_rest():
     """All rows in the last of 12 segments: 20 full-height tiles of one expert, nothing else."""
     cfg = wl.MoEConfig("huge", T=1, d=128, ffn=256, E=5, k=1, G=4, S=3, dtype="bf16", mode=0, seed=21)
