@@ -117,6 +117,20 @@ def test_histogram_sizes(n, E):
     assert np.array_equal(h2.cpu().numpy(), histogram(idx, E))
 
 
+@pytest.mark.parametrize("shift", [0, 1, 3])
+@pytest.mark.parametrize("n,E", [(3, 2), (2047, 8), (2048, 8), (2049, 8), (4099, 33), (65536, 1), (65541, 700)])
+def test_histogram_copies_and_alignment(n, E, shift):
+    """Around the size where bins are kept several times over, starting at addresses that are and are
+    not 16-byte aligned, with ids outside [0, E) that count for nobody."""
+    rng = np.random.default_rng(n)
+    idx = np.concatenate([rng.integers(0, E, size=shift + n // 2), np.zeros(n - n // 2, np.int64)]).astype(np.int32)
+    idx[::17] = -1
+    idx[5::23] = E
+    dev = torch.from_numpy(idx).cuda()[shift:]
+    ref = np.bincount(idx[shift:][(idx[shift:] >= 0) & (idx[shift:] < E)], minlength=E)
+    assert np.array_equal(B.moe_histogram(dev, E).cpu().numpy(), ref)
+
+
 # ---------------------------------------------------------------- plan
 def test_plan_random_small_cases():
     rng = np.random.default_rng(17)
