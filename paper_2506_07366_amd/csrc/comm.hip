@@ -13,7 +13,14 @@
 namespace moegps {
 
 constexpr int kCommThreads = 256;
-constexpr int kCommItems = 4096;       // assignments per workgroup
+// Assignments per workgroup: as many as make about one workgroup per CU, since a thread's time is its
+// chain of LDS reads (the binary search) per assignment; not more than 4096, not fewer than one
+// per thread.  12288 assignments, 16 ranks of 5 slots (both launches): 3 workgroups of 4096 16.2 us, 48 of
+// 256 5.7 us; 262144 assignments 18.2 -> 10.4; the divisions by k and T take 32 bits where they fit.
+static int comm_items(int64_t A) {
+    const int64_t n = align_up((size_t)ceil_div64(A, 256), (size_t)kCommThreads);
+    return n < 4096 ? (int)n : 4096;
+}
 constexpr int kCommLdsRanks = 64;      // G up to which both tables are privatised in LDS
 
 __global__ void comm_zero_kernel(int32_t* __restrict__ a, int32_t* __restrict__ b, int n) {
@@ -25,7 +32,7 @@ __global__ void comm_zero_kernel(int32_t* __restrict__ a, int32_t* __restrict__ 
 }
 
 template <bool LDS_BINS>
-__global__ __launch_bounds__(kCommThreads) void comm_count_kernel(int mode, int T, int k, int G, int S,
+__global__ __launch_bounds__(kCommThreads) void comm_count_kernel(int mode, int items, int T, int k, int G, int S,
                                                                    const int32_t* __restrict__ topk_idx,
                                                                    const int32_t* __restrict__ pred_idx,
                                                                    const int32_t* __restrict__ row_of_assign,
@@ -41,10 +48,11 @@ __global__ __launch_bounds__(kCommThreads) void comm_count_kernel(int mode, int 
         for (int i = threadIdx.x; i < 2 * GG; i += blockDim.x) bins[i] = 0;
     __syncthreads();
     const int64_t A = (int64_t)T * k;
-    const int64_t lo = (int64_t)blockIdx.x * kCommItems;
-    const int64_t hi = lo + kCommItems < A ? lo + kCommItems : A;
+    const int64_t lo = (int64_t)blockIdx.x * items;
+    const int64_t hi = lo + items < A ? lo + items : A;
+    const bool narrow = (int64_t)T * G < (1ll << 32);
     for (int64_t a = lo + threadIdx.x; a < hi; a += blockDim.x) {
-        const int t = (int)(a / k);
+        const int t = (int)((unsigned)a / (unsigned)k);  // (A < 2^31)
         const int row = row_of_assign[a];
         // segment sigma with so[sigma] <= row < so[sigma + 1] (empty segments have equal bounds)
         int l = 0, r = nseg;  // invariant: so[l] <= row < so[r]
@@ -54,7 +62,7 @@ __global__ __launch_bounds__(kCommThreads) void comm_count_kernel(int mode, int 
             else r = m;
         }
         const int dst = l / S;
-        const int own = (int)(((int64_t)t * G) / T);
+        const int own = narrow ? (int)((unsigned)t * (unsigned)G / (unsigned)T) : (int)(((int64_t)t * G) / T);
         int src = own;
         if (mode == MOE_MODE_TOKEN) {
             const int e = topk_idx[a];
@@ -96,12 +104,13 @@ extern "C" int moe_comm_matrix(int mode, int T, int k, int G, int S, const int32
     hipLaunchKernelGGL(comm_zero_kernel, dim3(ceil_div(GG, 256)), dim3(256), 0, st, dispatch, combine, GG);
     int rc = check_launch();
     if (rc != MOE_OK || T == 0) return rc;
-    const int grid = (int)ceil_div64((int64_t)T * k, kCommItems);
+    const int items = comm_items((int64_t)T * k);
+    const int grid = (int)ceil_div64((int64_t)T * k, items);
     if (G <= kCommLdsRanks)
-        hipLaunchKernelGGL((comm_count_kernel<true>), dim3(grid), dim3(kCommThreads), 0, st, mode, T, k, G, S,
-                           topk_idx, pred_idx, row_of_assign, seg_offsets, dispatch, combine);
+        hipLaunchKernelGGL((comm_count_kernel<true>), dim3(grid), dim3(kCommThreads), 0, st, mode, items, T, k, G,
+                           S, topk_idx, pred_idx, row_of_assign, seg_offsets, dispatch, combine);
     else
-        hipLaunchKernelGGL((comm_count_kernel<false>), dim3(grid), dim3(kCommThreads), 0, st, mode, T, k, G, S,
-                           topk_idx, pred_idx, row_of_assign, seg_offsets, dispatch, combine);
+        hipLaunchKernelGGL((comm_count_kernel<false>), dim3(grid), dim3(kCommThreads), 0, st, mode, items, T, k, G,
+                           S, topk_idx, pred_idx, row_of_assign, seg_offsets, dispatch, combine);
     return check_launch();
 }
