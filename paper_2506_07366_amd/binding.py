@@ -117,11 +117,15 @@ def _check(rc: int, what: str) -> None:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # (the declared argument types turn an int or None into a pointer)
+    return None if t is None else t.data_ptr()
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """Handle of the current stream of the current device.  torch.cuda.current_stream() builds a
+    Stream object on every call, a fifth of a small step's host time (with the pointers as plain
+    integers: 256 tokens of the tiny layer, 59 -> 46 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _need(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
@@ -230,9 +234,8 @@ def moe_permute(mode: int, x: Optional[torch.Tensor], topk_idx: torch.Tensor, pr
                                       _ptr(out["assign_of_row"]), _ptr(out["x_perm"]), _ptr(out["rank_load"]),
                                       _stream()), "moe_permute_static")
         return out
-    need = moe_permute_workspace_bytes(T, E, k, G, S)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        workspace = torch.empty(moe_permute_workspace_bytes(T, E, k, G, S), dtype=torch.uint8, device=dev)
     _check(lib.moe_permute(mode, _ptr(x), dt, T, d, E, k, G, S, _ptr(topk_idx), _ptr(pred_idx), _ptr(hist_true),
                            _ptr(hist_pred), _ptr(slot_expert), _ptr(slot_quota), _ptr(out["seg_offsets"]),
                            _ptr(out["row_of_assign"]), _ptr(out["assign_of_row"]), _ptr(out["x_perm"]),
@@ -292,8 +295,8 @@ def moe_grouped_ffn(x_perm: torch.Tensor, seg_offsets: torch.Tensor, slot_expert
     if seg_end is None:
         seg_end = nseg
     y = out if out is not None else torch.zeros_like(x_perm)
-    need = moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, dt)
     if workspace is None:
+        need = moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, dt)
         workspace = torch.empty(need, dtype=torch.uint8, device=x_perm.device)
     fn = lib.moe_grouped_ffn_relu if relu else lib.moe_grouped_ffn
     _check(fn(_ptr(x_perm), dt, A, d, ffn, E, _ptr(seg_offsets), _ptr(slot_expert), nseg, seg_begin, seg_end,
@@ -321,8 +324,8 @@ def moe_grouped_ffn_gather(x: torch.Tensor, assign_of_row: torch.Tensor, k: int,
     if seg_end is None:
         seg_end = nseg
     y = out if out is not None else torch.zeros((A, d), dtype=x.dtype, device=x.device)
-    need = moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, dt)
     if workspace is None:
+        need = moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, dt)
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
     if topk_w is not None:
         _need(topk_w, torch.float32, "topk_w")
