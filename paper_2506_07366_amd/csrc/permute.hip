@@ -27,10 +27,8 @@
 //   262144              128         160         57.0 / 64.7 -> 40.0 / 47.4
 //   65536               128         160         38.2 / 45.7 -> 27.1 / 28.6
 //
-// A batch of at most kSmallA assignments (decode, short prompts) takes the index steps in
-// one workgroup and one launch: the same ranks and scans, the chunk being the whole batch.  The
-// line lies where the two meet: 2056 assignments to 128 experts 15.2 us in one workgroup, 15.9 in
-// three launches; 3200 17.3 against 16.3; 8192 29.3 against 17.1 (mode 2: 39.7 against 18.9).
+// A batch of a few thousand assignments (decode, short prompts) takes the index steps in one
+// workgroup and one launch: the same ranks and scans, the chunk being the whole batch (one_workgroup_limit).
 #include "common.h"
 #include "block_scan.h"
 #include <initializer_list>
@@ -487,7 +485,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, 
     }
 }
 
-// All five index steps for a batch of at most kSmallA assignments, E and G*S at most
+// All five index steps for a batch of at most SR * 1024 assignments, E and G*S at most
 // kSmallKeys, in one workgroup of 1024 threads: the chunk is the whole batch, so the chunk
 // bases are zero and both scans run in LDS.  A thread's time here goes by the number of
 // instructions it runs one after the other, so the batch is dealt over all 16 wavefronts in
@@ -496,9 +494,24 @@ __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, 
 // slot id), plus every expert's first slot.  Same ranks, same results as the kernels above.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kSmallRounds = 2;
-constexpr int kSmallA = kSmallThreads * kSmallRounds;  // 2048
 constexpr int kSmallKeys = 512;
+constexpr int kSmallMaxRounds = 6;
+
+// Assignments up to which one workgroup is used (-1: never).  It pays a round for every 1024 of them,
+// the three launches pay their starts and, with many experts or slots, the chunks' tables of counts:
+// us for the index steps, one workgroup against three launches (two in mode 0), modes 0 / 1 / 2 (one
+// workgroup past the limits: with up to eight rounds compiled in, some 0.7 us slower for that):
+//   3000 assignments,   8 experts in  16 slots    6.0 / 11.2 / 13.4    7.1 / 11.7 / 11.8
+//                     128             160         7.4 / 15.7 / 20.4    8.6 / 16.8 / 18.1
+//                     512             512         8.2 / 19.3 / 21.4   11.9 / 23.2 / 25.6
+//   3600                8              16         7.4 / 13.2 / 15.2    7.0 / 11.7 / 11.8
+//   4096              512             512         9.6 / 21.7 / 24.7   12.1 / 23.4 / 25.4
+//   5000              512             512        11.2 / 24.3 / 28.1   12.1 / 23.5 / 26.0
+static int one_workgroup_limit(int mode, int E, int nseg) {
+    if (E > kSmallKeys || nseg > kSmallKeys) return -1;
+    if (E > 256 || nseg > 256) return mode == MOE_MODE_NONE ? 6 * kSmallThreads : 4 * kSmallThreads;
+    return mode == MOE_MODE_TOKEN ? 2 * kSmallThreads : 3 * kSmallThreads;
+}
 
 // The per-slot tables, by one wavefront, 64 slots at a time in ascending order: the lanes
 // holding one expert find each other by ballots; what earlier chunks hold for the expert
@@ -561,6 +574,7 @@ __device__ __forceinline__ void small_slot_tables(int E, int nseg, const SmallTa
     }
 }
 
+template <int SR>  // rounds of 64 elements per wavefront, at most
 __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     int mode, int T, int k, int E, int G, int S, const int32_t* __restrict__ topk_idx,
     const int32_t* __restrict__ pred_idx, const int32_t* __restrict__ hist_true, const int32_t* __restrict__ hist_pred,
@@ -570,8 +584,9 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     // one buffer, three lives: wavefront counters of the first rank; rank and key by position
     // (token-to-expert mode looks up those of the token's predicted ids); counters of the second
     __shared__ int buf[kSmallWaves * kSmallKeys];
-    static_assert(kSmallWaves * kSmallKeys >= kSmallA, "ranks by position share the counters' buffer");
-    static_assert(kSmallA <= (1 << 16) && kSmallKeys <= (1 << 15), "rank and key share one int");
+    constexpr int kMaxA = kSmallThreads * SR;
+    static_assert(SR <= kSmallMaxRounds && kSmallWaves * kSmallKeys >= kMaxA, "ranks by position share the counters' buffer");
+    static_assert(kMaxA <= (1 << 16) && kSmallKeys <= (1 << 15), "rank and key share one int");
     __shared__ int s_e[kSmallKeys], s_q[kSmallKeys], s_hi[kSmallKeys], s_next[kSmallKeys];
     __shared__ int e_first[kSmallKeys], e_cnt[kSmallKeys], e_last[kSmallKeys], e_true[kSmallKeys], e_hat[kSmallKeys];
     __shared__ int e_home[kSmallKeys];  // home slot of the expert
@@ -588,11 +603,11 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     // p = (w * rounds + r) * 64 + lane
     const int rounds = (n_b + kSmallThreads - 1) / kSmallThreads;
 
-    int key[kSmallRounds], rank[kSmallRounds], expert[kSmallRounds];
-    bool valid[kSmallRounds];
+    int key[SR], rank[SR], expert[SR];
+    bool valid[SR];
     const int32_t* rank_keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
 #pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
+    for (int r = 0; r < SR; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         valid[r] = r < rounds && p < n_b;
         key[r] = valid[r] ? clamp_key(rank_keys[p], E) : 0;
@@ -601,7 +616,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     }
     if (mode == MOE_MODE_TOKEN) {
 #pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
+        for (int r = 0; r < SR; ++r) {
             const int p = (w * rounds + r) * kWave + lane;
             if (valid[r]) expert[r] = clamp_key(topk_idx[p], E);
         }
@@ -624,10 +639,10 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
             const SmallTables t{s_e, s_q, s_cum, s_next, e_first, e_cnt, e_last, e_cum};
             small_slot_tables(E, nseg, t);
         }
-        chunk_stable_rank<kSmallWaves, kSmallRounds>(key, valid, E, buf, rank, nullptr, rounds);
+        chunk_stable_rank<kSmallWaves, SR>(key, valid, E, buf, rank, nullptr, rounds);
         __syncthreads();  // the counters are dead, the buffer becomes rank and key by position
 #pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
+        for (int r = 0; r < SR; ++r) {
             const int p = (w * rounds + r) * kWave + lane;
             if (valid[r]) buf[p] = rank[r] | (key[r] << 16);
         }
@@ -648,10 +663,10 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     // segment of every assignment: its place i in the plan's order for its expert (-1: none),
     // then a walk over the expert's slots, at most G of them, to the one whose range holds i;
     // the rounds walk in step so that their LDS reads overlap
-    int sg[kSmallRounds], place[kSmallRounds];
-    bool walking[kSmallRounds];
+    int sg[SR], place[SR];
+    bool walking[SR];
 #pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
+    for (int r = 0; r < SR; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         sg[r] = 0;
         place[r] = -1;
@@ -681,7 +696,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     for (int seen = 1; mode != MOE_MODE_NONE && seen < G; ++seen) {
         bool more = false;
 #pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {  // no branches: sg[r] is a slot in any case, the reads overlap
+        for (int r = 0; r < SR; ++r) {  // no branches: sg[r] is a slot in any case, the reads overlap
             if (r >= rounds) continue;       // (uniform)
             const int nx = s_next[sg[r]];
             const int hi = s_hi[sg[r]];
@@ -693,12 +708,12 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     }
     __syncthreads();  // every look-up of a rank is done before the buffer holds counters again
 
-    chunk_stable_rank<kSmallWaves, kSmallRounds>(sg, valid, nseg, buf, rank, tot, rounds);
+    chunk_stable_rank<kSmallWaves, SR>(sg, valid, nseg, buf, rank, tot, rounds);
     block_exclusive_scan_2048(tot, nseg, wave_sum);
     for (int s = tid; s <= nseg; s += kSmallThreads) seg_offsets[s] = tot[s];
     for (int g = tid; g < G; g += kSmallThreads) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
 #pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
+    for (int r = 0; r < SR; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         if (!valid[r]) continue;
         const int row = tot[sg[r]] + rank[r];
@@ -778,11 +793,13 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
     hipStream_t st = (hipStream_t)stream;
     const int nb = ws.nb;
     int rc;
-    const bool small = (int64_t)T * k <= kSmallA && E <= kSmallKeys && G * S <= kSmallKeys;
-    if (small) {
-        hipLaunchKernelGGL(perm_small_kernel, dim3(1), dim3(kSmallThreads), 0, st, mode, T, k, E, G, S, topk_idx,
-                           pred_idx, hist_true, hist_pred, slot_expert, slot_quota, seg_offsets, row_of_assign,
-                           assign_of_row, rank_load);
+    const int64_t A = (int64_t)T * k;
+    if (A <= one_workgroup_limit(mode, E, G * S)) {
+        hipLaunchKernelGGL(A <= 2 * kSmallThreads ? perm_small_kernel<2>
+                           : A <= 3 * kSmallThreads ? perm_small_kernel<3>
+                           : A <= 4 * kSmallThreads ? perm_small_kernel<4> : perm_small_kernel<kSmallMaxRounds>,
+                           dim3(1), dim3(kSmallThreads), 0, st, mode, T, k, E, G, S, topk_idx, pred_idx, hist_true,
+                           hist_pred, slot_expert, slot_quota, seg_offsets, row_of_assign, assign_of_row, rank_load);
         if ((rc = check_launch()) != MOE_OK) return rc;
     } else {
         const bool scanned = nb == 0 || nb > kSelfScanChunks;

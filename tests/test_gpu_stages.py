@@ -1,5 +1,7 @@
 """GPU parity, stage by stage: the HIP path through the C ABI against the CPU oracle
 on the same seeded inputs.  Integer results must match bit for bit."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -193,8 +195,8 @@ def test_plan_many_ranks():
                                        # whole numbers of 2048-assignment chunks and one over; 256 / 257 experts
                                        (4096, 8, 2, 8, 2), (8192, 8, 1, 8, 2), (8193, 8, 1, 8, 2),
                                        (512, 256, 16, 64, 4), (512, 257, 16, 64, 5), (2731, 64, 3, 16, 5),
-                                       # both sides of the one-workgroup path's limits: 8192 assignments,
-                                       # 512 experts, 512 segments
+                                       # both sides of the one-workgroup path's limits of 512 experts and
+                                       # 512 segments
                                        (400, 512, 8, 64, 8), (400, 513, 8, 64, 9), (1024, 300, 8, 32, 16),
                                        (1024, 300, 8, 33, 16), (1, 1, 1, 1, 1), (8192, 512, 1, 128, 4),
                                        # hundreds of chunks; many chunks at the largest expert and segment counts
@@ -216,7 +218,7 @@ def test_permute_small(mode, T, E, k, G, S):
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
-@pytest.mark.parametrize("T,E,k,G,S", [(128, 128, 16, 32, 5),   # the most one workgroup takes: 2048
+@pytest.mark.parametrize("T,E,k,G,S", [(128, 128, 16, 32, 5),   # the most one workgroup takes in mode 2: 2048
                                        (129, 128, 16, 32, 5),   # and one token more
                                        (4097, 64, 6, 16, 5),    # chunks of 252 elements, last one ragged
                                        (8193, 16, 4, 8, 3),     # just over 128 chunks of one round: two rounds
@@ -232,6 +234,56 @@ def test_permute_chunk_sizes(mode, T, E, k, G, S):
                         dev_i32(case.plan.slot_expert), dev_i32(case.plan.slot_quota), E, G, S, copy_rows=False)
     for name in ("seg_offsets", "row_of_assign", "assign_of_row", "rank_load"):
         assert np.array_equal(out[name].cpu().numpy(), case.perm[name]), name
+
+
+def _launches(fn):
+    """Kernels that one call enqueues, counted in a graph it is captured into."""
+    fn()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fn()
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("T,E,k,G,S,modes", [(1536, 8, 2, 8, 2, (0, 1)),      # 3072: the most with up to 256 experts
+                                             (1032, 8, 2, 8, 2, (0, 1)),      # just over two rounds
+                                             (1025, 256, 2, 32, 8, (0, 1)),
+                                             (2050, 257, 1, 64, 6, (0, 1, 2)),   # over 256 experts and slots
+                                             (256, 512, 16, 64, 8, (0, 1, 2)),   # 4096 of them
+                                             (1366, 512, 3, 64, 8, (0,)),        # just over four rounds
+                                             (6144, 512, 1, 64, 8, (0,))])       # the most without a prediction
+def test_permute_one_workgroup(T, E, k, G, S, modes):
+    """Batches that one workgroup finishes sooner than three launches take one, with the oracle's
+    integers; one token more than the limits and all of it in no more than four."""
+    for mode in modes:
+        for tokens, limit in ((T, 1), (T + 1 if T * k in (3072, 4096, 6144) else T, 4)):
+            cfg = wl.MoEConfig("p", T=tokens, d=16, ffn=8, E=E, k=k, G=G, S=S, dtype="f32", mode=mode, alpha=0.5,
+                               sigma_pred=0.3, acc=0.8, seed=tokens + k)
+            case = Case(cfg, with_x=False)
+            args = (mode, None, dev_i32(case.idx), case.dev_pred_idx(), dev_i32(case.hist), case.dev_hist_plan(),
+                    dev_i32(case.plan.slot_expert), dev_i32(case.plan.slot_quota), E, G, S)
+            out = B.moe_permute(*args, copy_rows=False)
+            for name in ("seg_offsets", "row_of_assign", "assign_of_row", "rank_load"):
+                assert np.array_equal(out[name].cpu().numpy(), case.perm[name]), (mode, tokens, name)
+            ws = torch.empty(B.moe_permute_workspace_bytes(tokens, E, k, G, S), dtype=torch.uint8, device="cuda")
+            assert _launches(lambda: B.moe_permute(*args, copy_rows=False, out=out, workspace=ws)) <= limit
+
+
+@pytest.mark.parametrize("E", [4, 513])
+def test_permute_no_tokens(E):
+    """No token: offsets and loads are zero, below and above what one workgroup holds."""
+    G = max(2, -(-E // 16))
+    S = -(-E // G)
+    z = dev_i32(np.zeros(E))
+    se, sq, _, _ = B.moe_plan_duplicates(0, z, G, S, G)
+    out = B.moe_permute(1, None, torch.zeros((0, 2), dtype=torch.int32, device="cuda"), None, z, z, se, sq, E, G, S,
+                        copy_rows=False)
+    assert not out["seg_offsets"].any() and not out["rank_load"].any()
 
 
 def test_permute_empty_input():
