@@ -341,8 +341,10 @@ __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, in
     const int w = tid / kWave;
     const int nseg = G * S;
     const int H = (E + G - 1) / G;
-    const int tpc = tokens_per_chunk(k, ws.rounds);
-    const int rounds = ws.rounds;
+    // (more than kSelfScanChunks chunks are always chunks of kRounds: fixed loops, 5 % of the index steps
+    // of 600000 assignments to 8 experts)
+    const int rounds = SCANNED ? kRounds : ws.rounds;
+    const int tpc = tokens_per_chunk(k, rounds);
     const int64_t A = (int64_t)T * k;
     const int64_t base = (int64_t)blockIdx.x * tpc * k;
     const int n_b = (int)((base + (int64_t)tpc * k < A ? base + (int64_t)tpc * k : A) - base);
@@ -435,8 +437,10 @@ __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, 
     const int lane = tid & (kWave - 1);
     const int w = tid / kWave;
     const int nseg = G * S;
-    const int tpc = tokens_per_chunk(k, ws.rounds);
-    const int rounds = ws.rounds;
+    // (more than kSelfScanChunks chunks are always chunks of kRounds: fixed loops, 5 % of the index steps
+    // of 600000 assignments to 8 experts)
+    const int rounds = SCANNED ? kRounds : ws.rounds;
+    const int tpc = tokens_per_chunk(k, rounds);
     const int64_t A = (int64_t)T * k;
     const int64_t base = (int64_t)blockIdx.x * tpc * k;
     const int n_b = (int)((base + (int64_t)tpc * k < A ? base + (int64_t)tpc * k : A) - base);
@@ -802,7 +806,7 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
                            hist_pred, slot_expert, slot_quota, seg_offsets, row_of_assign, assign_of_row, rank_load);
         if ((rc = check_launch()) != MOE_OK) return rc;
     } else {
-        const bool scanned = nb == 0 || nb > kSelfScanChunks;
+        const bool scanned = nb == 0 || (nb > kSelfScanChunks && ws.rounds == kRounds);
         if (mode != MOE_MODE_NONE) {
             const int32_t* keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
             hipLaunchKernelGGL(perm_count_kernel, dim3(nb + ceil_div(E, kPermWaves)), dim3(kPermThreads), 0, st, keys,
