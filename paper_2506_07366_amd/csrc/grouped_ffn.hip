@@ -1352,25 +1352,38 @@ static int launch_gemm_bf16(const GemmVariant& v, const bf16_t* A, int lda, cons
 
 // Whether a product streams its weights through registers (ffn_stream.h): 0 no, else the form.
 // The rule goes by the whole batch (A rows, E experts), not by the launched slot range, so that
-// a row gets the same bits from a launch over some slots as from one over all.
-// Up to 24 rows per expert on average (routing is skewed: up to three times as many per expert that
-// holds any) the streaming forms lead the LDS-staged tiles at every skew measured (both products,
-// 128 experts of 4096 x 1536: 256 tokens 580 -> 506 us, with popularity 0.1 297 -> 273; 64 experts
-// of 2048 x 1408, 250 tokens: 191 -> 162); at 32 the most skewed batches fall behind (512 tokens at
-// popularity 0.1: 329 against 361 us).  A product whose 128 x 256 tiles would not go once
-// round the chip is better off with the finer units up to 64 (16 experts of 4096 x 688, 200
-// tokens, first product: 68 -> 43 us; the second, 352 tiles: 25 against 27).
+// a row gets the same bits from a launch over some slots as from one over all.  How the rows lie is
+// only known on the device, so a line has to do for all rows on one expert as well as for an equal share
+// on each.  Spread out, the streaming forms lead far beyond these lines; batches that lie on a
+// few experts fall behind once the LDS-staged tiles of so many rows fill the chip.  Both
+// products, us, tiles -> streaming:
+//   up to 16 rows per expert on average: 128 experts of 4096 x 1536, 2048 rows on all of them 807 -> 736, on
+//     16 140 -> 165, on one 102 -> 108 (1536 rows on all 128 823 -> 730, on 16 136 -> 155); 8 experts of
+//     4096 x 14336, 128 rows on 8 / 1 519 -> 421 / 162 -> 135;
+//   up to 24 where the tiles of A rows on one expert are fewer than 18 k-tiles per CU (64 experts of 2048 x 1408,
+//     132 tiles of 32 and 96 of 22, 1536 rows on 64 / 16 / 1 214 -> 186 / 85 -> 75 / 71 -> 60) or K is short (128
+//     experts of 768 x 3072, ReLU, first product, 12 k-tiles: 3072 rows on 128 / 16 / 1 120 -> 110 / 36 -> 33 /
+//     36 -> 34); with more than that too much is lost (128 experts of 4096 x 1536, 240 tiles of 64 and 320 of 24, 2560
+//     rows on 128 / 32 / 16 820 -> 772 / 261 -> 282 / 187 -> 209; 64 experts of 4096 x 4096, second product, 160
+//     tiles of 64, 1280 rows on 16 / 8 / 4 102 -> 122 / 73 -> 90 / 68 -> 84);
+//   up to 64 where even every expert's own ragged 128 x 256 tiles would not go once round the chip (16
+//     experts of 4096 x 688, 1024 rows on 16 / 1, first product: 67 -> 43 / 61 -> 33).
+// Above 16 rows per expert a long K is left to the tiles in any case, their closing ones are computed as
+// parts of K (8 experts, K = 14336, second product, 192 rows on 1 / 2 experts: 77 / 91 against 110 / 111).
 // Of the two, form 1 (finer units) leads up to 4 rows per expert, and up to 16 where the 128-column
 // units of form 2 would not go round the 512 workgroups the chip holds (8 experts, 64 tokens,
 // second product: 112 against 130 us; 128 tokens: 178 against 140 the other way); above, form 2
 // reads the activations half as often.
-static int stream_form(int forced_tile, int64_t A, int E, int n_cols) {
+static int stream_form(int forced_tile, int64_t A, int E, int n_cols, int k_tiles) {
     const int opt = g_opt_stream.load();
     if (forced_tile >= 0 || opt == 0 || A > 65536) return 0;
     if (opt > 0) return opt;
-    if (A > (int64_t)24 * E &&
-        (A > (int64_t)64 * E || (ceil_div64(A, 128) + E) * ceil_div(n_cols, 256) > kGemmGrid))
-        return 0;
+    if (A > (int64_t)16 * E) {
+        const int64_t m_tiles = ceil_div64(A, 128), n_tiles = ceil_div(n_cols, 256);
+        const bool idle = m_tiles * n_tiles * k_tiles <= 18 * kGemmGrid || k_tiles <= 16;
+        const bool once = (m_tiles + E) * n_tiles <= kGemmGrid;
+        if (k_tiles > 64 || !((A <= (int64_t)24 * E && idle) || (A <= (int64_t)64 * E && once))) return 0;
+    }
     if (A <= (int64_t)4 * E) return 1;
     return A > (int64_t)16 * E || (int64_t)E * (n_cols / 128) >= 2 * kGemmGrid ? 2 : 1;
 }
@@ -1599,8 +1612,8 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     const int n1 = relu ? 1 : 2;            // matrices in the first product
     const int v1 = pick(g_opt_tile1.load(), n1 * fp);
     const int v2 = pick(g_opt_tile2.load(), d);
-    const int s1 = stream_form(g_opt_tile1.load(), A, E, n1 * fp);
-    const int s2 = g_opt_split.load() == 1 ? 0 : stream_form(g_opt_tile2.load(), A, E, d);
+    const int s1 = stream_form(g_opt_tile1.load(), A, E, n1 * fp, d / kPackK);
+    const int s2 = g_opt_split.load() == 1 ? 0 : stream_form(g_opt_tile2.load(), A, E, d, fp / kPackK);
     // N-tiles walked side by side under one run of M-tiles.  A run of 32 tiles is 32/g M-tiles
     // under g weight panels; every group streams the activation rows again.  Up to 12 N-tiles
     // are walked together, so the rows are read once.  Wider outputs are walked in groups: of 4

@@ -479,6 +479,52 @@ def test_ffn_streaming_forms(form, d, ffn, relu):
         B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, -1)
 
 
+def _order_sensitive(E, d, ffn, A, nseg, rows_on, seed):
+    """A bf16 batch whose sums show the order they were taken in: every term of a product has its
+    negative somewhere in the other half of K, so that what is left is rounding of the partial sums."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    r = lambda *shape: torch.randn(shape, device="cuda", generator=g).bfloat16()
+    p = torch.randperm(d // 2, device="cuda", generator=g)
+    q = torch.randperm(ffn // 2, device="cuda", generator=g)
+    u, gate, up, down = r(A, d // 2), r(E, d // 2, ffn // 2), r(E, d, ffn // 2), r(E, ffn // 2, d)
+    x = torch.cat([u, u[:, p]], 1)
+    W1 = torch.cat([gate, -gate[:, p]], 1)
+    W1, W3 = (torch.cat([w, w[:, :, q]], 2).contiguous() for w in (W1, up))   # hidden columns come in equal pairs
+    packed = B.moe_pack_weights(W1, W3, torch.cat([down, -down[:, q]], 1))
+    sizes = np.zeros(nseg, dtype=np.int64)
+    sizes[:rows_on] = A // rows_on
+    sizes[0] += A - sizes.sum()
+    return x, dev_i32(np.concatenate([[0], np.cumsum(sizes)])), dev_i32(np.arange(nseg) % E), packed, E, ffn
+
+
+@pytest.mark.parametrize("E,d,ffn,A,form1,form2", [
+    (4, 512, 512, 16, 1, 1), (4, 512, 512, 64, 1, 1), (4, 512, 512, 65, 2, 2),   # up to 16 rows per expert; above
+    (4, 512, 512, 256, 2, 2), (4, 512, 512, 257, 0, 0),         # up to 64 while tiles do not go once round
+    (128, 512, 512, 512, 1, 1), (128, 512, 512, 513, 2, 2),     # 4 rows per expert: the second form
+    (128, 512, 512, 3072, 2, 2), (128, 512, 512, 3073, 0, 0),   # 24 rows per expert
+    (4, 512, 4224, 64, 1, 1), (4, 512, 4224, 65, 2, 0),         # 66 k-tiles in the second product
+    (32, 1088, 6912, 545, 2, 0), (32, 1088, 7040, 545, 0, 0),   # 270 and 275 tiles of 17 k-tiles in the first product
+])
+def test_ffn_streaming_rule(E, d, ffn, A, form1, form2, ffn_options):
+    """Which batches stream their weights: the automatic choice gives the bits of the form it is meant to
+    be, on inputs where each form of either product gives its own."""
+    args = _order_sensitive(E, d, ffn, A, E, min(E, 3), seed=A)
+
+    def run(stream, tile1=-1, tile2=-1):
+        ffn_options(tile1=tile1, tile2=tile2)
+        B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, stream)
+        return B.moe_grouped_ffn(*args)
+
+    try:
+        forms = {(0, 0): run(0), (1, 1): run(1), (2, 2): run(2), (2, 0): run(2, tile2=1), (1, 0): run(1, tile2=1)}
+        auto = run(-1)
+    finally:
+        B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, -1)
+    assert not any(torch.equal(forms[f], forms[h]) for f in forms for h in forms if f < h)
+    assert torch.equal(auto, forms[form1, form2])
+
+
 @pytest.mark.parametrize("relu", [False, True])
 def test_ffn_split_k_matches_whole_tiles(relu, ffn_options):
     """Closing tiles computed as parts of K: same result as whole tiles up to the fp32
