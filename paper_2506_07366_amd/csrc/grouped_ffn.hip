@@ -183,17 +183,23 @@ struct TableSpec {
 // Against pairs of segments and of experts dealt over the workgroup, some 30 barriers, and stripes of
 // 4096 positions: 8 experts in 12 slots 10.3 -> 6.5 us (in 16 slots 9.4 -> 5.5); 128 experts in 160
 // slots, one token 15.8 -> 8.5, 128 tokens 17.5 -> 9.4, 777 tokens and two tables 19.6 -> 10.5; 64 experts
-// in 80 slots, 98304 rows 16.7 -> 11.
+// in 80 slots, 98304 rows 16.7 -> 11.  Pairs cost nothing for slots without rows; with hundreds of
+// experts, groups of 64 slots or experts without rows are therefore skipped and the scans keep four reads
+// under way (1024 experts in as many slots, 1024 rows on 16 of them, whole FFN of 64 x 64 weights: pairs 26.1,
+// without the skip 38.7, now 25.2 us; on all 1024 216, 48.4, 48.2).
 
 // exclusive prefix sums of data[0 .. n) in LDS, in place, by one wavefront; data[n] = total, returned
+template <int UNROLL = 1>  // reads under way together: more than one pays with eight words per lane and up
 __device__ __forceinline__ int wave_scan_lds(int* data, int n) {
     const int lane = threadIdx.x & (kWave - 1);
     const int per = ceil_div(n, kWave);
     const int i0 = lane * per < n ? lane * per : n, i1 = i0 + per < n ? i0 + per : n;
     int mine = 0;
+#pragma unroll UNROLL
     for (int i = i0; i < i1; ++i) mine += data[i];
     const int incl = wave_prefix_i32(mine);
     int run = incl - mine;
+#pragma unroll UNROLL
     for (int i = i0; i < i1; ++i) {
         const int c = data[i];
         data[i] = run;
@@ -203,6 +209,11 @@ __device__ __forceinline__ int wave_scan_lds(int* data, int n) {
     if (lane == 0) data[n] = total;
     wave_lds_order();
     return total;
+}
+
+// the same over the experts
+__device__ __forceinline__ int wave_scan_experts(int* data, int E) {
+    return E >= 8 * kWave ? wave_scan_lds<4>(data, E) : wave_scan_lds(data, E);
 }
 
 // lanes that hold the same key (below 1 << nbits) among the lanes with `live`
@@ -243,6 +254,7 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
     const bool leader = tid < kWave;
     const unsigned long long lt = (1ull << lane) - 1ull;
     const int ns = seg_end - seg_begin;
+    const bool many = E > 4 * kWave;  // experts enough that looking for groups of 64 without rows pays
     if (blockIdx.x == 0)
         for (int i = tid; i < n_queues; i += blockDim.x) queues[i] = 0;
     for (int e = tid; e < E; e += blockDim.x) e_segs[e] = 0;
@@ -261,6 +273,7 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
         for (int i0 = 0; i0 < ns; i0 += kWave) {
             const int i = i0 + lane;
             const int e = i < ns ? s_ex[i] : -1;
+            if (many && __ballot(e >= 0) == 0ull) continue;
             const unsigned long long same = same_key_lanes(e, e >= 0, nbits);
             if (e >= 0) {
                 const int before = e_segs[e];
@@ -269,7 +282,7 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             }
             wave_lds_order();
         }
-        wave_scan_lds(e_segs, E);
+        wave_scan_experts(e_segs, E);
         for (int i = lane; i < ns; i += kWave) {
             const int v = s_ex[i];
             if (v < 0) continue;
@@ -314,6 +327,10 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             int n_tail_l = 0, tail_rows_l = 0;
             for (int e0 = 0; e0 < E; e0 += kWave) {
                 const int e = e0 + lane;
+                if (many && e_segs[e0] == e_segs[e0 + kWave < E ? e0 + kWave : E]) {  // no segment holds any of them
+                    if (e < E) e_full[e] = e_tail[e] = 0;
+                    continue;
+                }
                 const int rows = e < E ? list_base(e + 1) - list_base(e) : 0;
                 const int tl = rows & (BM - 1);
                 const unsigned long long same = same_key_lanes(tl, tl > 0, shift);
@@ -330,7 +347,8 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
                 }
                 wave_lds_order();
             }
-            const int n_full = wave_scan_lds(e_full, E);
+            wave_lds_order();
+            const int n_full = wave_scan_experts(e_full, E);
             const int n_tail = wave_sum_i32(n_tail_l), tail_rows = wave_sum_i32(tail_rows_l);
             for (int v = lane; v < BM; v += kWave) {
                 const int c = h_count[v];
@@ -379,7 +397,7 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             for (int e = lane; e < E; e += kWave)
                 e_whole[e] = (e_tail[e] > 0 && e_rank[e] < n_tail - n_rsplit) ? 1 : 0;
             wave_lds_order();
-            wave_scan_lds(e_whole, E);
+            wave_scan_experts(e_whole, E);
             if (lane == 0) {
                 s_plan[0] = n_full;
                 s_plan[1] = n_tail;

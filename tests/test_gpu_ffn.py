@@ -404,6 +404,22 @@ def test_ffn_tables_of_many_slots(E, nseg, rows, dtype, split, ffn_options):
     assert rel_err(got, ref) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("split", [-1, 1])
+@pytest.mark.parametrize("E,nseg,live", [(257, 300, [256]), (512, 512, [0, 511]), (1024, 1024, [63, 64, 320, 1023]),
+                                         (1000, 2048, [127, 128, 129, 999])])
+def test_ffn_tables_few_experts_of_many(E, nseg, live, split, ffn_options):
+    """Rows on a handful of experts at the ends of groups of 64: the groups without rows are skipped."""
+    ffn_options(split=split)
+    rng = np.random.default_rng(E)
+    cfg = wl.MoEConfig("f", T=1, d=64, ffn=128, E=E, k=1, G=1, S=E, dtype="bf16", mode=0, seed=9)
+    slot_expert = np.concatenate([np.arange(E), rng.integers(0, E, nseg - E)]).astype(np.int32)
+    rng.shuffle(slot_expert)
+    sizes = np.where(np.isin(slot_expert, live), rng.integers(0, 300, nseg), 0).tolist()
+    sizes[int(np.flatnonzero(slot_expert == live[-1])[0])] = 65   # (one at least holds rows)
+    got, ref, _ = run_ffn_case(cfg, sizes, slot_expert, seed=2)
+    assert rel_err(got, ref) <= TOL["bf16"]
+
+
 def test_ffn_one_huge_segment_and_empty_rest():
     """All rows in the last of 12 segments: 20 full-height tiles of one expert, nothing else."""
     cfg = wl.MoEConfig("huge", T=1, d=128, ffn=256, E=5, k=1, G=4, S=3, dtype="bf16", mode=0, seed=21)
