@@ -1377,33 +1377,38 @@ static int launch_gemm_bf16(const GemmVariant& v, const bf16_t* A, int lda, cons
 // products, us, tiles -> streaming:
 //   up to 16 rows per expert on average: 128 experts of 4096 x 1536, 2048 rows on all of them 807 -> 736, on
 //     16 140 -> 165, on one 102 -> 108 (1536 rows on all 128 823 -> 730, on 16 136 -> 155); 8 experts of
-//     4096 x 14336, 128 rows on 8 / 1 519 -> 421 / 162 -> 135;
-//   up to 24 where the tiles of A rows on one expert are fewer than 18 k-tiles per CU (64 experts of 2048 x 1408,
-//     132 tiles of 32 and 96 of 22, 1536 rows on 64 / 16 / 1 214 -> 186 / 85 -> 75 / 71 -> 60) or K is short (128
-//     experts of 768 x 3072, ReLU, first product, 12 k-tiles: 3072 rows on 128 / 16 / 1 120 -> 110 / 36 -> 33 /
-//     36 -> 34); with more than that too much is lost (128 experts of 4096 x 1536, 240 tiles of 64 and 320 of 24, 2560
-//     rows on 128 / 32 / 16 820 -> 772 / 261 -> 282 / 187 -> 209; 64 experts of 4096 x 4096, second product, 160
-//     tiles of 64, 1280 rows on 16 / 8 / 4 102 -> 122 / 73 -> 90 / 68 -> 84);
+//     4096 x 14336, 128 rows on 8 / 1 519 -> 421 / 162 -> 135; but not with so many experts that the tiles of A
+//     rows on one of them are more than 128 k-tiles per CU (512 experts of 4096 x 1536, first product, 6144 rows on
+//     512 / 64: 2062 -> 1917 / 288 -> 373);
+//   up to 24 where those are no more than 18 per CU and K is not short (64 experts of 2048 x 1408, 132 tiles of 32 and 96 of 22,
+//     1536 rows on 64 / 16 / 1 214 -> 186 / 85 -> 75 / 71 -> 60); with more than that too much is lost (128 experts
+//     of 4096 x 1536, 240 tiles of 64 and 320 of 24, 2560 rows on 128 / 32 / 16 820 -> 772 / 261 -> 282 / 187 ->
+//     209; 64 experts of 4096 x 4096, second product, 160 tiles of 64, 1280 rows on 16 / 8 / 4 102 -> 122 / 73 ->
+//     90 / 68 -> 84; 1024 experts of 1024 x 512, second product, 8 k-tiles, 18432 rows on 16 / 1 39 -> 46 / 40 -> 47);
 //   up to 64 where even every expert's own ragged 128 x 256 tiles would not go once round the chip (16
 //     experts of 4096 x 688, 1024 rows on 16 / 1, first product: 67 -> 43 / 61 -> 33).
 // Above 16 rows per expert a long K is left to the tiles in any case, their closing ones are computed as
 // parts of K (8 experts, K = 14336, second product, 192 rows on 1 / 2 experts: 77 / 91 against 110 / 111).
-// Of the two, form 1 (finer units) leads up to 4 rows per expert, and up to 16 where the 128-column
-// units of form 2 would not go round the 512 workgroups the chip holds (8 experts, 64 tokens,
-// second product: 112 against 130 us; 128 tokens: 178 against 140 the other way); above, form 2
-// reads the activations half as often.
+// Of the two, form 1 (finer units) takes what the 128-column units of form 2 would not bring round the 512
+// workgroups the chip holds, up to 16 rows per expert (8 experts, K = 14336, second product, 32 rows on 8 / 4
+// 139 against 148 / 74 against 94), and small batches of up to 4 (64 experts of 2048 x 1408, first
+// product, 256 rows on 64 118 against 128).  The rest is form 2's, which reads the activations half as
+// often: 128 experts of 4096 x 1536, first product, 512 rows on 128 / 1 580 against 486 / 57 against 33; 512
+// experts, 2048 rows on 512 / 8 2235 against 1893 / 176 against 88.
 static int stream_form(int forced_tile, int64_t A, int E, int n_cols, int k_tiles) {
     const int opt = g_opt_stream.load();
     if (forced_tile >= 0 || opt == 0 || A > 65536) return 0;
     if (opt > 0) return opt;
+    const int64_t m_tiles = ceil_div64(A, 128), n_tiles = ceil_div(n_cols, 256);
+    const int64_t work = m_tiles * n_tiles * k_tiles;  // k-tiles of A rows on one expert
+    if (work > 128 * kGemmGrid) return 0;
     if (A > (int64_t)16 * E) {
-        const int64_t m_tiles = ceil_div64(A, 128), n_tiles = ceil_div(n_cols, 256);
-        const bool idle = m_tiles * n_tiles * k_tiles <= 18 * kGemmGrid || k_tiles <= 16;
+        const bool idle = work <= 18 * kGemmGrid && k_tiles > 16;
         const bool once = (m_tiles + E) * n_tiles <= kGemmGrid;
-        if (k_tiles > 64 || !((A <= (int64_t)24 * E && idle) || (A <= (int64_t)64 * E && once))) return 0;
+        return k_tiles <= 64 && ((A <= (int64_t)24 * E && idle) || (A <= (int64_t)64 * E && once)) ? 2 : 0;
     }
-    if (A <= (int64_t)4 * E) return 1;
-    return A > (int64_t)16 * E || (int64_t)E * (n_cols / 128) >= 2 * kGemmGrid ? 2 : 1;
+    if (A <= (int64_t)4 * E && A <= 256) return 1;
+    return (A < E ? A : E) * (n_cols / 128) >= 2 * kGemmGrid ? 2 : 1;
 }
 
 template <int EPI>

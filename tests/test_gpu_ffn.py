@@ -517,10 +517,12 @@ def _order_sensitive(E, d, ffn, A, nseg, rows_on, seed):
 @pytest.mark.parametrize("E,d,ffn,A,form1,form2", [
     (4, 512, 512, 16, 1, 1), (4, 512, 512, 64, 1, 1), (4, 512, 512, 65, 2, 2),   # up to 16 rows per expert; above
     (4, 512, 512, 256, 2, 2), (4, 512, 512, 257, 0, 0),         # up to 64 while tiles do not go once round
-    (128, 512, 512, 512, 1, 1), (128, 512, 512, 513, 2, 2),     # 4 rows per expert: the second form
-    (128, 512, 512, 3072, 2, 2), (128, 512, 512, 3073, 0, 0),   # 24 rows per expert
+    (128, 512, 512, 256, 1, 1), (128, 512, 512, 257, 2, 2),     # small batches of up to 4 rows per expert
+    (128, 512, 512, 2048, 2, 2), (128, 512, 512, 2049, 0, 0),   # short K: up to 16
+    (32, 1088, 1088, 768, 2, 2), (32, 1088, 1088, 769, 0, 2),   # 24 rows per expert; the second product's tiles go once round
     (4, 512, 4224, 64, 1, 1), (4, 512, 4224, 65, 2, 0),         # 66 k-tiles in the second product
     (32, 1088, 6912, 545, 2, 0), (32, 1088, 7040, 545, 0, 0),   # 270 and 275 tiles of 17 k-tiles in the first product
+    (1024, 2048, 1088, 14336, 2, 2), (1024, 2048, 1088, 14592, 0, 2),   # 126 and 128.25 k-tiles per CU in the first
 ])
 def test_ffn_streaming_rule(E, d, ffn, A, form1, form2, ffn_options):
     """Which batches stream their weights: the automatic choice gives the bits of the form it is meant to
@@ -533,7 +535,7 @@ def test_ffn_streaming_rule(E, d, ffn, A, form1, form2, ffn_options):
         return B.moe_grouped_ffn(*args)
 
     try:
-        forms = {(0, 0): run(0), (1, 1): run(1), (2, 2): run(2), (2, 0): run(2, tile2=1), (1, 0): run(1, tile2=1)}
+        forms = {(0, 0): run(0), (1, 1): run(1), (2, 2): run(2), (2, 0): run(2, tile2=1), (0, 2): run(2, tile1=1)}
         auto = run(-1)
     finally:
         B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, -1)
