@@ -40,6 +40,7 @@ namespace moegps {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;  // four floats at any float's address, still one access
 typedef unsigned short bf16_t;  // storage
 
 // One entry of an M-tile table: up to BM consecutive positions of the row list, all of one
@@ -102,7 +103,7 @@ __host__ __device__ inline int swz(int row) { return (row >> 1) & 7; }
 // out[packed_index(n, k)] = in[k][n] for one expert per blockIdx.z, zero where k >= K or
 // n >= N (the output is K_out x N_out, padded); optional interleave of the output row
 // index: rows of W1 go to (n/32)*64 + n%32, rows of W3 32 further.  A workgroup turns 32 k x
-// 64 n through LDS: 16-byte reads along n (VEC: the row length N is a multiple of 8), whole
+// 64 n through LDS: 16-byte reads along n (VEC: row length N a multiple of 8, matrix 16-byte aligned), whole
 // fragments of 1 KiB written by a wavefront each.
 template <bool VEC>
 __global__ __launch_bounds__(256) void pack_transpose_kernel(const bf16_t* __restrict__ in, bf16_t* __restrict__ out,
@@ -1134,7 +1135,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(const float* __re
                 const int kc = in ? k : 0;
 #pragma unroll
                 for (int i = 0; i < MT; ++i) {
-                    const f32x4 v = *(const f32x4*)(arow[i] + kc);
+                    const f32x4 v = *(const f32x4_any*)(arow[i] + kc);
                     o.a[s][i] = in ? v : f32x4{0.f, 0.f, 0.f, 0.f};
                 }
 #pragma unroll
@@ -1183,7 +1184,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(const float* __re
                 else if (relu) v[j] = fmaxf(v[j], 0.f);
                 v[j] *= sc;
             }
-            *(f32x4*)(C + (size_t)crow * ldc + c0) = v;
+            *(f32x4_any*)(C + (size_t)crow * ldc + c0) = v;
         }
     }
 }
@@ -1502,7 +1503,7 @@ static int pack_weights_impl(const void* W1, const void* W3, const void* W2, int
     auto pack = [&](const void* W, bf16_t* out, int K, int N, int K_out, int N_out, size_t out_stride, int interleave,
                     int sel) {
         const dim3 grid(ceil_div(N_out, 64), K_out / 32, E);
-        if (N % 8 == 0)
+        if (N % 8 == 0 && (uintptr_t)W % 16 == 0)
             hipLaunchKernelGGL(pack_transpose_kernel<true>, grid, dim3(256), 0, st, (const bf16_t*)W, out, K, N, K_out,
                                N_out, es, out_stride, interleave, sel);
         else

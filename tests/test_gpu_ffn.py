@@ -117,6 +117,32 @@ def test_ffn_f32_tile_edges(d, ffn, scale, relu):
     assert rel_err(y, ref) <= TOL["f32"]
 
 
+def test_ffn_pack_and_f32_rows_at_any_address():
+    """Weights packed from, and fp32 rows read and written at, addresses that only suit their element
+    type: the same bytes as from aligned tensors."""
+    def shifted(t, by):
+        room = torch.zeros(t.numel() + by, dtype=t.dtype, device="cuda")
+        room[by:] = t.flatten()
+        return room[by:].view(t.shape)
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    E, d, ffn, A = 3, 64, 72, 50
+    so, se = dev_i32([0, 20, 30, A]), dev_i32([0, 2, 1])
+    for dtype in (torch.bfloat16, torch.float32):
+        W = [torch.randn(sh, device="cuda", generator=g).to(dtype) for sh in ((E, d, ffn), (E, d, ffn), (E, ffn, d))]
+        packed = B.moe_pack_weights(*W)
+        if dtype == torch.bfloat16:
+            for by in (1, 3, 4):
+                assert torch.equal(packed, B.moe_pack_weights(*[shifted(w, by) for w in W]))
+            continue
+        x = torch.randn((A, d), device="cuda", generator=g)
+        y = B.moe_grouped_ffn(x, so, se, packed, E, ffn)
+        for by in (1, 2, 3):
+            out = shifted(torch.zeros_like(x), by)
+            assert torch.equal(y, B.moe_grouped_ffn(shifted(x, by), so, se, packed, E, ffn, out=out))
+
+
 def test_ffn_slot_range_only_touches_its_rows():
     cfg = wl.MoEConfig("f", T=1, d=128, ffn=256, E=5, k=1, G=4, S=3, dtype="bf16", mode=0, seed=21)
     rng = np.random.default_rng(5)
