@@ -121,11 +121,17 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (not public: may be absent)
+
+
 def _stream() -> int:
     """Handle of the current stream of the current device.  torch.cuda.current_stream() builds a
     Stream object on every call, a fifth of a small step's host time (with the pointers as plain
     integers: 256 tokens of the tiny layer, 59 -> 46 us)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    device = torch.cuda.current_device()
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device)
 
 
 def _need(t: torch.Tensor, dtype, name: str) -> torch.Tensor:

@@ -95,3 +95,16 @@ def test_ffn_workspace_size_rule():
         assert opt(SPLIT, 2) == -1 and opt(99, 0) == -1 and opt(binding.FFN_OPT_TILE1, 3) == -1
     finally:
         opt(SPLIT, -1)
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_stream_handle_with_and_without_the_private_call(private, monkeypatch):
+    """The current stream's handle comes from torch's private shortcut where there is one, else from
+    the public call."""
+    import types
+    import torch
+    from paper_2506_07366_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev: types.SimpleNamespace(cuda_stream=100 + dev))
+    monkeypatch.setattr(binding, "_raw_stream", (lambda dev: 200 + dev) if private else None)
+    assert binding._stream() == (203 if private else 103)
