@@ -63,10 +63,9 @@ constexpr int kGemmGrid = 256;  // persistent workgroups of a GEMM launch: 8 XCD
 constexpr int kPartRows = 256;  // rows of one slab of partial sums (the tallest tile shape)
 constexpr int kMaxParts = 4;    // parts of K of a split tile
 
-// counts[] of a table: number of entries, end of the first pass (whole full-height tiles),
-// end of the second pass (whole ragged tiles; the third pass holds the parts of split
-// tiles), number of split M-tiles
-constexpr int kCntEntries = 0, kCntPass0 = 1, kCntPass1 = 2, kCntSplit = 3, kCntStride = 4;
+// counts[] of a table: number of entries, how many of them are whole tiles (they come first; behind
+// them the parts of split tiles), number of split M-tiles
+constexpr int kCntEntries = 0, kCntWhole = 1, kCntSplit = 2, kCntStride = 4;
 
 // ---------------------------------------------------------------------------
 // weight packing (one-off, weights are static across inputs)
@@ -162,12 +161,13 @@ struct TableSpec {
 };
 
 // Row list: position p holds a row of x_perm; the rows of an expert's segments (ascending
-// slot id, rows ascending) are consecutive, experts ascending.  M-tile tables: first every
-// full-height tile by expert, so that neighbours read the same expert's weights; then the
-// ragged last tile of every expert, tallest first, so that the cheap tiles come last and
-// fill the gaps at the end of the launch.  With parts > 1 the closing M-tiles of that order are
-// listed once per part of K instead, part by part, each entry writing fp32 partial sums to a
-// slab of its own (slab = split tile * parts + part).  How many: the work of the product,
+// slot id, rows ascending) are consecutive, experts ascending.  M-tile tables: the whole tiles by
+// expert, an expert's ragged last tile right behind its full-height ones, so that neighbours
+// share weight panels (MTile::first and n_same, by which the streaming kernels walk the tiles of one
+// expert, rely on it).  With parts > 1 the closing M-tiles -- the order for this is full-height
+// tiles by expert, then ragged ones, tallest first -- are listed once per part of K instead, behind the
+// whole ones and part by part, each entry writing fp32 partial sums to a slab of its own (slab =
+// split tile * parts + part).  How many: the work of the product,
 // counted in tiles (a ragged tile of r rows as (BM + r) / 2BM of a tile: its weight panel
 // streams in full), is so many whole rounds of one tile per workgroup plus a remainder; the
 // rounds run as whole tiles, and the remainder -- what would otherwise be a last round with
@@ -179,7 +179,7 @@ struct TableSpec {
 // barrier between its steps, and the workgroup meets three times: segments loaded, list order
 // known, table prepared; the row list and the table entries are written by everybody.
 // Every workgroup works out the list order and fills its stripe of the row list; workgroup 0
-// writes the first table and clears the claim counters, workgroup 1 (0 if it is alone) the second.
+// writes the first table and clears the claim counters, workgroup 1 the second (the launch has two at least).
 // The ragged tiles are ranked by counting their heights instead of comparing all pairs.
 // Against pairs of segments and of experts dealt over the workgroup, some 30 barriers, and stripes of
 // 4096 positions: 8 experts in 12 slots 10.3 -> 6.5 us (in 16 slots 9.4 -> 5.5); 128 experts in 160
@@ -310,17 +310,13 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
     };
     // tables
     auto list_base = [&](int e) { return srt_base[e_segs[e]]; };  // first list position of expert e
-    const bool second = (gridDim.x > 1) ? blockIdx.x == 1 : true;
-    const bool first = blockIdx.x == 0;
-    const bool busy = leader && (first || second);  // prepares a table while the others fill in the row list
+    const TableSpec& ts = blockIdx.x == 0 ? t1 : t2;
+    const bool table = blockIdx.x < 2 && ts.tiles;
+    const bool busy = leader && table;  // prepares the table while the others fill in the row list
     if (!busy) fill_rows();
-    for (int which = 0; which < 2; ++which) {  // uniform per workgroup
-        if (which == 0 ? !first : !second) continue;
-        const TableSpec& ts = which == 0 ? t1 : t2;
-        if (!ts.tiles) continue;
+    if (table) {  // (uniform)
         const int BM = ts.bm;
         const int P = ts.parts > kMaxParts ? kMaxParts : ts.parts;
-        if (which == 1 && first) __syncthreads();  // (alone: the first table's entries are written)
         if (leader) {
             const int shift = __builtin_ctz(BM);
             for (int v = lane; v < BM; v += kWave) h_count[v] = 0;
@@ -468,8 +464,7 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
         }
         if (tid == 0) {
             ts.counts[kCntEntries] = fits ? n_entries : 0;
-            ts.counts[kCntPass0] = fits ? n_whole : 0;
-            ts.counts[kCntPass1] = fits ? n_whole : 0;
+            ts.counts[kCntWhole] = fits ? n_whole : 0;
             ts.counts[kCntSplit] = fits ? n_split : 0;
         }
     }
@@ -619,14 +614,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
     const int wm = wave / WGN, wn = wave % WGN;
 
     const int n_entries = counts[kCntEntries];
-    const int pass0_end = counts[kCntPass0];  // whole full-height tiles
-    const int pass1_end = counts[kCntPass1];  // whole ragged tiles; behind them the parts of split tiles
+    const int n_whole = counts[kCntWhole];  // behind the whole tiles come the parts of split ones
     const int n_ntiles = (N + BN - 1) / BN;
 
-    // Tile order.  The (entry, N-tile) space is walked in three passes: the full-height
-    // M-tiles, the ragged ones (tallest first), the parts of split tiles (part by part).
+    // Tile order.  The (entry, N-tile) space is walked in two passes: the whole M-tiles, then
+    // the parts of split ones (part by part).
     // Inside a pass tiles are numbered in groups of group_n neighbouring N-tiles; inside a
-    // group the N-tile index runs fastest, then the entry (full M-tiles are sorted by expert),
+    // group the N-tile index runs fastest, then the entry (whole M-tiles are sorted by expert),
     // so a run of 32 consecutive tiles is a patch of about 32/group_n x group_n tiles that
     // share their activation and weight panels.  Workgroups are dealt to the 8 XCDs
     // round-robin (workgroup b runs on XCD b % 8) and every XCD has its own L2, so run c of
@@ -639,7 +633,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
     const int xcd = blockIdx.x & 7;
     constexpr int run = kGemmGrid / 8;  // the launch is always kGemmGrid workgroups
     const int total = n_entries * n_ntiles;
-    const int total0 = pass0_end * n_ntiles, total1 = pass1_end * n_ntiles;
+    const int total_whole = n_whole * n_ntiles;
     __shared__ volatile int next_tile;
     // The claims are the business of wavefront 0, and every value involved is the same in
     // all its lanes, so the state lives in scalar registers (lane 0 performs the atomic, its
@@ -703,10 +697,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
             ahead_q = next_counter();
             if (ahead_q >= 0) ahead_pending = claim_from(ahead_q);
         }
-        const int pass = t_all < total0 ? 0 : (t_all < total1 ? 1 : 2);
-        const int t = pass == 0 ? t_all : (pass == 1 ? t_all - total0 : t_all - total1);
-        const int m_base = pass == 0 ? 0 : (pass == 1 ? pass0_end : pass1_end);
-        const int m_count = pass == 0 ? pass0_end : (pass == 1 ? pass1_end - pass0_end : n_entries - pass1_end);
+        const bool whole = t_all < total_whole;
+        const int t = whole ? t_all : t_all - total_whole;
+        const int m_base = whole ? 0 : n_whole;
+        const int m_count = whole ? n_whole : n_entries - n_whole;
         const int per_group = m_count * group_n;
         const int grp = t / per_group;
         const int rem = t - grp * per_group;
