@@ -474,7 +474,7 @@ def test_ffn_every_tile_variant(tile1, tile2, split, ffn_options):
 
 
 @pytest.mark.parametrize("form", [1, 2])
-@pytest.mark.parametrize("d,ffn,relu", [(64, 64, False),      # one k-tile: one half / seven parts of K are empty
+@pytest.mark.parametrize("d,ffn,relu", [(64, 64, False),      # one k-tile: one half / three parts of K are empty
                                         (192, 320, False),    # odd numbers of k-tiles, half a unit at the edge of N
                                         (576, 1088, True),    # nine and seventeen k-tiles, ReLU
                                         (2176, 192, False)])  # K above and below 32 k-tiles
@@ -483,11 +483,29 @@ def test_ffn_streaming_forms(form, d, ffn, relu):
     each other, empty slots and more experts than rows, in place and through the row gather with
     gate weights: against the oracle (bf16 tolerance of this file), the same bits twice and from a
     launch over a part of the slots."""
-    E = 6
+    _check_streaming(form, 6, d, ffn, relu)
+
+
+@pytest.mark.parametrize("E,d,ffn,relu", [
+    # up to 8 rows per expert on average and few columns: units of 32 columns, eight parts of K
+    (46, 64, 64, False),      # one k-tile: seven parts of K are empty
+    (46, 2176, 320, False),   # 34 k-tiles under gate and up columns
+    (46, 576, 2176, False),   # and in the second product, nine in the first
+    (46, 2176, 704, True),    # and under ReLU
+    # more rows per expert: units of 64 columns, eight parts of a K above 32 k-tiles
+    (6, 192, 2176, False),    # in the second product
+    (6, 2176, 192, True)])    # and under ReLU
+def test_ffn_streaming_first_form_units(E, d, ffn, relu):
+    """The kernels of the first streaming form that the smallest batches take, with all eight wavefronts
+    holding part of K."""
+    _check_streaming(1, E, d, ffn, relu)
+
+
+def _check_streaming(form, E, d, ffn, relu):
     cfg = wl.MoEConfig("s", T=1, d=d, ffn=ffn, E=E, k=1, G=4, S=3, dtype="bf16", mode=0, seed=41,
                        act="relu" if relu else "swiglu")
     seg_sizes = [1, 0, 16, 17, 0, 33, 64, 65, 130, 0, 5, 31]
-    slot_expert = [0, 1, 2, 3, -1, 4, 0, 1, 2, -1, 4, 3]     # expert 5 has no slot
+    slot_expert = [0, 1, 2, 3, -1, 4, 0, 1, 2, -1, 4, 3]     # the last experts have no slot
     A = sum(seg_sizes)
     rng = np.random.default_rng(43)
     x = wl.quantize(rng.standard_normal((A, d)).astype(np.float32), "bf16")
