@@ -176,7 +176,8 @@ int moe_permute_static(int mode, const void* x, int dtype, int T, int d, int E, 
  * stored transposed, in tiles of 256 output columns by 64 of the contracted dimension,
  * each tile 32 KiB in one piece in the order the kernels hold it on chip; the hidden width
  * is padded to a multiple of 64 and the output columns to whole tiles with zeros (the
- * size query includes the padding).  The packed form is opaque: only these calls read it.
+ * size query includes the padding).  The packed form is opaque: only these calls read it, and it may
+ * differ between versions of the library (pack again rather than keep it in a file).
  */
 size_t moe_packed_weights_bytes(int E, int d, int ffn, int dtype);
 int moe_pack_weights(const void* W1, const void* W3, const void* W2, int dtype,
@@ -243,7 +244,8 @@ int moe_grouped_ffn_gather(const void* x, int dtype, int T, int k, const int32_t
  * Overrides of the automatic choices inside the grouped FFN, for tests and experiments
  * (process-wide; set them before sizing a workspace, the split option changes its size):
  *   MOE_FFN_OPT_TILE1 / TILE2  tile shape of the first / second product: -1 automatic,
- *                              0 = 256x256x64, 1 = 128x256x64, 2 = 32x256x64
+ *                              0 = 256x256x64, 1 = 128x256x64, 2 = 32x256x64 (never
+ *                              chosen automatically)
  *   MOE_FFN_OPT_SPLIT_K        closing tiles of the second product as parts of K:
  *                              -1 automatic, 0 never, 1 whenever the shapes allow
  *   MOE_FFN_OPT_GROUP_N        N-tiles walked side by side under one run of M-tiles, 0 automatic

@@ -3,11 +3,12 @@
 // Included by grouped_ffn.hip inside namespace moegps (uses its types).
 //
 // Both forms load weight fragments from memory straight into registers (a fragment of the packed
-// form is one contiguous kilobyte, so nothing is gained by a detour through LDS) and rely on
-// occupancy for the bytes in flight: a wavefront asks for one k-tile of its columns at a time,
-// and two or three workgroups of eight wavefronts share a CU, so a unit's prologue, exchange
-// and stores run under the loads of the others.  Asking two or three k-tiles ahead per
-// wavefront was no faster (the registers it takes cost a workgroup per CU).  The grid walks
+// form is one contiguous kilobyte, so nothing is gained by a detour through LDS).  A wavefront asks for
+// one k-tile of its columns at a time and eight to sixteen of them share a CU: two workgroups of
+// eight with form 2 and with form 1's units of 32 columns, two of four or one of eight with its
+// units of 64 (the registers of the 64-row body decide), so that except for the last a unit's
+// prologue, exchange and stores run under the loads of another workgroup.  Asking two or three k-tiles
+// ahead per wavefront was no faster.  The grid walks
 // units (M-tile of up to 64 rows) x (64 .. 128 columns) with a fixed stride: units are short
 // (0.2 - 0.5 MB of weights) and a workgroup that is left alone at the end gets the bandwidth of
 // the ones that have finished.

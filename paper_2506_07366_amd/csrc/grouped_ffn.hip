@@ -1228,9 +1228,10 @@ static inline size_t packed_elems2(int d, int fp) { return packed_rows((size_t)d
 
 // Whether (and how) the closing tiles of the second product are computed as parts of K.  It
 // pays when the product has only a few rounds of tiles per workgroup, so that the uneven end
-// of the launch matters, and the segments are not slivers (decode streams weights; splitting K
-// would only add traffic).  Decided from the sizes the workspace is laid out for, so that the
-// layout and the call agree.  split_capacity bounds the M-tiles the table builder may split:
+// of the launch matters, and the segments are not slivers (splitting K would only add
+// traffic).  Decided from the sizes the workspace is laid out for, so that the layout and the call
+// agree; the number of experts is not among them, so a batch that streams its weights (stream_form) has
+// room for slabs that it leaves unused.  split_capacity bounds the M-tiles the table builder may split:
 // at most 5/8 of a round of tiles, each M-tile at least half a tile's worth per N-tile.
 static void split_plan(int64_t A, int d, int ffn, int nseg, int dtype, int* split_capacity, int* parts,
                        int* split_all) {
@@ -1249,11 +1250,10 @@ static void split_plan(int64_t A, int d, int ffn, int nseg, int dtype, int* spli
         return;
     }
     if (kt < 4 * kMaxParts) return;
-    // slivers of rows stream weights: splitting a tile of a few k-tiles only adds traffic, but a
-    // long one (64 k-tiles and more) is worth splitting where the tiles do not fill the chip
-    // (8 experts of hidden width 14336 at a few tokens: 96 tiles of 224 k-tiles for 256 workgroups)
-    // (eight parts instead of four: 5 % faster at 16 and 32 tokens, 5-20 % slower from 64 on, where
-    // adding up the slabs costs more than the extra round saves)
+    // fewer than 64 rows per slot: splitting a tile of a few k-tiles only adds traffic, but a
+    // long one (64 k-tiles and more) is worth splitting where the tiles do not fill the chip (8 experts
+    // of hidden width 14336, 128 to 512 tokens: 96 tiles of 224 k-tiles for 256 workgroups; eight parts
+    // instead of four were 5-20 % slower there, adding up the slabs cost more than the extra round saved)
     if (A < (int64_t)64 * nseg && kt < 64) return;
     const int64_t est_tiles = (A / 256 + (nseg + 1) / 2) * n_ntiles;
     if (est_tiles > 8 * kGemmGrid) return;
@@ -1414,7 +1414,9 @@ static int launch_stream(int form, int64_t A, int E, const bf16_t* X, int lda, c
         hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, X, lda, Bp, b_stride, C, ldc, tiles, counts, N, K, rm);
         return check_launch();
     };
-    // as many workgroups as the registers let a CU hold
+    // The registers let a CU hold two workgroups of form 2; of form 1 one (<4, 8>) or two, its kernels
+    // having been compiled for M-tiles of up to 64 rows.  Form 1 is launched with more than that, so
+    // that a CU goes on to the next one as soon as one has run out of units.
     if (form == 2) return go(grouped_gemm_stream_shared_kernel<EPI>, 2 * kGemmGrid, 512);
     // Units of 32 columns where those of 64 would make fewer than three per CU (one token, 8 experts
     // of 3072 columns: 37 -> 35 us; 16 tokens, 4096 columns over K = 14336: 107 -> 98 us) and the
@@ -1609,7 +1611,9 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     // per product: 256x256 unless the product has too few such tiles to keep 256 workgroups
     // busy for two rounds, or the segments are slivers, then 128x256 with three stages.  The tile
     // count is only known on the device; the host estimates it from the row count.  (32x256 is
-    // left to the option: the batches it was ahead on are streamed now.)
+    // left to the option: ahead of 128x256 only where streaming is further ahead, and with many replicas or
+    // a few experts that hold everything far behind: 64 experts of 2048 x 1408 in 160 slots, 2500 rows on 64 / 16 of
+    // them, whole FFN 258 / 165 us with it against 233 / 110.)
     auto pick = [&](int forced, int n_cols) {
         if (forced >= 0) return forced;
         if (A < (int64_t)64 * nrange) return 1;
