@@ -35,8 +35,8 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 KERNEL_SOURCE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2506_07366_amd", "csrc",
                              "grouped_ffn.hip")
 TRAFFIC = {
-    "cfg2_mixtral_dist": {"source_sha256": "9c6f1f8e1a2058a98947e29b6091b227298f31f4f07085077b45739037d168dd",
-                          "fetch_bytes": 5569264970, "write_bytes": 235027924,
+    "cfg2_mixtral_dist": {"source_sha256": "b145f100b2c17601aa170ea9e97129a1dc282f2deb473dc7bbe86dba282b4a97",
+                          "fetch_bytes": 5546718416, "write_bytes": 235025126,
                           "profile": "profiles/gemm1_cfg2_mixtral_traffic_counters.md"},
 }
 
@@ -297,7 +297,7 @@ def main():
             bytes_ffn = (n_mat * cfg.d * cfg.ffn * 2 * len(touched) + 2 * cfg.A * cfg.d * 2
                          + 2 * cfg.A * cfg.ffn * 2)
             ach = bytes_ffn / ((g1_ms + g2_ms) * 1e-3) / 1e9
-            roofline = {"bound": "hbm", "kernel": "grouped_gemm_bf16_kernel, both products (weight streaming)",
+            roofline = {"bound": "hbm", "kernel": "grouped FFN, both products (weight streaming)",
                         "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": ach / PEAK_HBM_GBS,
                         "traffic": None, "traffic_source": None, "avg_ms": g1_ms + g2_ms,
                         "experts_touched": len(touched), "algorithmic_bytes": bytes_ffn,
