@@ -9,23 +9,24 @@
 // units of 64 (the registers of the 64-row body decide), so that except for the last a unit's
 // prologue, exchange and stores run under the loads of another workgroup.  Asking two or three k-tiles
 // ahead per wavefront was no faster.  The grid walks
-// units (M-tile of up to 64 rows) x (64 .. 128 columns) with a fixed stride: units are short
-// (0.2 - 0.5 MB of weights) and a workgroup that is left alone at the end gets the bandwidth of
+// units (M-tile of up to 64 rows) x (32 .. 128 columns) with a fixed stride: units are short
+// (0.1 - 1 MB of weights) and a workgroup that is left alone at the end gets the bandwidth of
 // the ones that have finished.
 //
 // Against the LDS-staged 128- and 32-row tiles (whose waves all wait at one barrier per k-tile
-// and whose 2 MiB tiles leave most CUs idle in the last round), both products, 4096 x 1536
-// experts: 1 token (8 experts) 99 -> 54 us (5.6 TB/s of weights), 16 tokens 352 -> 292 us
-// (6.5 TB/s), 128 tokens 541 -> 472 us (6.4 TB/s), 256 tokens 609 -> 570 us; 4096 x 14336
-// experts: 16 tokens 373 -> 273 us, 64 tokens 393 -> 297 us.
+// and whose 2 MiB tiles leave most CUs idle in the last round), both products of bench.py's batches:
+// 4096 x 1536 experts, top-8 of 128 (cfg5_decode_m1, --tokens): 1 token (8 experts) 99 -> 55 us (5.5 TB/s of
+// weights), 16 tokens (54) 382 -> 325 us (6.3 TB/s), 128 tokens (85) 569 -> 503 us (6.4 TB/s), 256 tokens (91)
+// 638 -> 587 us (5.9 TB/s); 4096 x 14336 experts, top-2 of 8 (cfg2_mixtral_dist): 16 tokens 369 -> 280 us, 64
+// tokens 421 -> 340 us (6.3 TB/s both).
 #pragma once
 
 // Form 1: the wavefronts of a workgroup share the unit's columns and split K between them; each
 // reads its own activation fragments (16 rows x 64 bytes per load, from the L2) and nothing
 // synchronises until the fp32 sums are added up through LDS, wavefront 0 first, so the result does
-// not depend on timing.  The finest units, so it is the form for few experts and for the
-// lowest row counts; from about 16 rows per expert on its activation loads, repeated for
-// every 64 columns, cost more than form 2's barrier.
+// not depend on timing.  The finest units, so it is the form for few experts and small
+// batches; in others its activation loads, repeated for every 64 columns, cost more than form 2's
+// barrier (stream_form).
 //   NT  16-column groups per unit: 4, or 2 where the product has too few units
 //   NW  wavefronts per workgroup = parts of K: 8, or 4 for short K
 template <int NT, int NW, int EPI>
