@@ -7,10 +7,9 @@
 //   GEMM-1: H[A, ffn]  = swiglu( X[A, d] * [W1|W3]_e )    (gate/up columns interleaved
 //           by 32 in the packed weights, so the SwiGLU happens on the accumulators)
 //   GEMM-2: Y[A, d]    = H[A, ffn] * W2_e
-// Packed weights are stored transposed and by MFMA fragment (see packed_index), activations
-// by row; both stream as K-contiguous 16-byte pieces straight from global memory into LDS
-// (global_load_lds_dwordx4) and feed v_mfma_f32_16x16x32_bf16 fragments with one ds_read_b128
-// each.  With a few rows per expert the weights go past LDS into registers (ffn_stream.h).
+// Packed weights are stored transposed and by MFMA fragment (see packed_index), activations by row.
+// Weights go from memory into registers fragment by fragment, activations through LDS, both to
+// v_mfma_f32_16x16x32_bf16 (ffn_tiles.h; with a few rows per expert ffn_stream.h).
 //
 // Rows are tiled by EXPERT, not by segment: replicas of an expert hold the same
 // weights, so the rows of all its segments in the launched slot range are listed
@@ -78,11 +77,8 @@ constexpr int kCntEntries = 0, kCntWhole = 1, kCntSplit = 2, kCntStride = 4;
 // fragments of a 16-row group along K side by side.  So
 //   - a k-tile of a weight panel is one contiguous read instead of 256 pieces of 128 bytes a row
 //     apart, which the memory system serves a quarter slower at some row lengths (8 KiB among
-//     them), and goes to LDS as it comes;
-//   - a fragment in LDS is read at base + 16 * lane: free of bank conflicts, and every
-//     fragment of a stage is the same lane address plus a constant;
-//   - a kernel that streams weights without LDS loads a fragment into registers as one
-//     contiguous kilobyte.
+//     them);
+//   - a fragment is loaded into registers as one contiguous kilobyte, without a detour through LDS.
 constexpr int kPackN = 256, kPackK = 64;
 constexpr int kFragElems = 16 * 32;  // one MFMA operand fragment
 __host__ __device__ inline size_t packed_index(int n, int k, int K_out) {
@@ -257,7 +253,7 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
     const int ns = seg_end - seg_begin;
     const bool many = E > 4 * kWave;  // experts enough that looking for groups of 64 without rows pays
     if (blockIdx.x == 0)
-        for (int i = tid; i < n_queues; i += blockDim.x) queues[i] = 0;
+        for (int i = tid; i < n_queues; i += blockDim.x) queues[i] = kGemmGrid / 8;  // every workgroup's first tile is its own
     for (int e = tid; e < E; e += blockDim.x) e_segs[e] = 0;
     for (int i = tid; i < ns; i += blockDim.x) {
         const int s = seg_begin + i;
@@ -528,18 +524,6 @@ __device__ __forceinline__ void lane_swap_pairs(unsigned& p, unsigned& q) {
     q = t[1];
 }
 
-// 16 bytes per lane from global memory straight into LDS: lane l's piece comes from
-// base + voff (uniform 64-bit base in scalar registers, 32-bit byte offset per lane: an
-// addressing mode of the instruction, so a load costs no vector ALU work and one address
-// register) and lands at LDS byte address lds_addr + 16 * l (uniform, handed over in M0).
-// Counts on vmcnt like any load.
-__device__ __forceinline__ void global_to_lds_b128(const void* base, unsigned voff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(base)
-                 : "memory");
-}
-
 // two floats rounded to bf16 (nearest even) and packed, low half first: one conversion instruction
 __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
     typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
@@ -572,454 +556,7 @@ struct RowMap {
     const float* scale;
 };
 
-template <int BM, int BN, int BK, int WGM, int WGN, int NSTAGE, int EPI>
-__global__ __launch_bounds__(WGM* WGN * 64) void grouped_gemm_bf16_kernel(
-    const bf16_t* __restrict__ A, int lda,           // activations [rows, K]
-    const bf16_t* __restrict__ Bp, size_t b_stride,  // packed weights [E][N-tile][k-tile][kPackN x kPackK]
-    bf16_t* __restrict__ C, int ldc,                 // output [rows, SWIGLU ? N/2 : N]
-    const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int32_t* __restrict__ queues,
-    int N, int K, int group_n, RowMap rm,
-    float* __restrict__ partials) {  // [slab][kPartRows][N] fp32 sums of entries that cover part of K (plain product only)
-    constexpr bool SWIGLU = EPI == kEpiSwiglu;
-    constexpr int NW = WGM * WGN;
-    constexpr int WTM = BM / WGM, WTN = BN / WGN;
-    constexpr int CPR = BK / 8;                 // 16-byte pieces per tile row
-    constexpr int IA = BM * CPR / 64;           // wave-wide load instructions per A tile
-    constexpr int IB = BN * CPR / 64;
-    // per wavefront.  A tile of few rows has fewer activation loads than the workgroup has
-    // wavefronts; the upper wavefronts then repeat the lower ones' loads (same pieces to the
-    // same place), so that every wavefront counts the same number of loads per k-tile.
-    constexpr bool A_SHARED = IA < NW;
-    constexpr int IAW = A_SHARED ? 1 : IA / NW, IBW = IB / NW;
-    constexpr int LPT = IAW + IBW;              // loads per thread per k-tile
-    constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
-    constexpr int TM16 = WTM / 16, TN16 = WTN / 16;
-    static_assert((A_SHARED ? NW % IA == 0 : IA % NW == 0) && IB % NW == 0, "tile loads must divide over the wavefronts");
-    static_assert(WTM % 16 == 0 && WTN % 16 == 0, "wave tile is a grid of 16x16 MFMA tiles");
-    static_assert(!SWIGLU || (WTN % 64 == 0), "gate/up pairs must sit in one wavefront");
-    static_assert(LPT * NSTAGE < 64, "vmcnt range");
-    static_assert(CPR == 8 && BK == 64 && TM16 + TN16 <= 12, "the K loop is written for 64-deep k-tiles");
-    static_assert(BN == kPackN && BK == kPackK, "a weight tile is one tile of the packed form");
-    // With two stages every wait drains all loads, so loads of rows past the end of a
-    // ragged M-tile can simply be left out; with deeper prefetch the wait counts a fixed
-    // number of loads per k-tile and such rows are clamped to the last valid row instead.
-    constexpr bool SKIP_TAIL_LOADS = (NSTAGE == 2);
-    constexpr int ROWS_PER_LOAD = 64 / CPR;
-
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WGN, wn = wave % WGN;
-
-    const int n_entries = counts[kCntEntries];
-    const int n_whole = counts[kCntWhole];  // behind the whole tiles come the parts of split ones
-    const int n_ntiles = (N + BN - 1) / BN;
-
-    // Tile order.  The (entry, N-tile) space is walked in two passes: the whole M-tiles, then
-    // the parts of split ones (part by part).
-    // Inside a pass tiles are numbered in groups of group_n neighbouring N-tiles; inside a
-    // group the N-tile index runs fastest, then the entry (whole M-tiles are sorted by expert),
-    // so a run of 32 consecutive tiles is a patch of about 32/group_n x group_n tiles that
-    // share their activation and weight panels.  Workgroups are dealt to the 8 XCDs
-    // round-robin (workgroup b runs on XCD b % 8) and every XCD has its own L2, so run c of
-    // the numbering belongs to XCD c % 8: its workgroups claim the tiles of its runs one by
-    // one from a counter (tiles differ in cost, a fixed deal would leave workgroups idle at
-    // the end) and so work side by side on one patch, sharing its panels through that L2; the
-    // 8 XCDs are on 8 consecutive runs (further along M under the same weight panels, shared
-    // through the memory-side cache).  A workgroup whose own XCD has no tile left claims from
-    // the other XCDs' counters.
-    const int xcd = blockIdx.x & 7;
-    constexpr int run = kGemmGrid / 8;  // the launch is always kGemmGrid workgroups
-    const int total = n_entries * n_ntiles;
-    const int total_whole = n_whole * n_ntiles;
-    __shared__ volatile int next_tile;
-    // The claims are the business of wavefront 0, and every value involved is the same in
-    // all its lanes, so the state lives in scalar registers (lane 0 performs the atomic, its
-    // result is broadcast): nothing of it occupies a vector register across the K loop
-    // except the pending result of the claim made ahead.
-    int dry = 0;  // bit q set = counter q has run out
-    // tile number for claim i of XCD q's counter, -1 if that counter has run out
-    auto tile_of_claim = [&](int q, int i) {
-        const int t = (q + 8 * (i / run)) * run + i % run;
-        return t < total ? t : -1;  // claims only grow: past the end once, past the end for good
-    };
-    // number of claims counter q can serve: its runs are q, q + 8, ... of which the first
-    // total / run are whole and run number total / run holds the remainder
-    auto claims_of = [&](int q, int total) {  // (total handed in opaque: worked out only when needed)
-        const int whole = total / run, part = total - whole * run;
-        return (whole > q ? (whole - q + 7) / 8 * run : 0) + ((whole >= q && ((whole - q) & 7) == 0) ? part : 0);
-    };
-    // the counter to claim from next, own XCD first; -1 when all have run out
-    auto next_counter = [&]() {
-        for (int j = 0; j < 8; ++j) {
-            const int q = (xcd + j) & 7;
-            if (!((dry >> q) & 1)) return q;
-        }
-        return -1;
-    };
-    auto claim_from = [&](int q) {  // one claim, result not yet waited for (lane 0 holds it)
-        int r = 0;
-        if (lane == 0) r = atomicAdd(&queues[q], 1);
-        return r;
-    };
-    // Turns a claim made ahead of time (or none: q < 0) into a tile, making further claims as
-    // needed; -1 when every counter has run out.  Once a claim has come back empty all eight
-    // counters are read in one go (one round trip, not one per counter), and those that stand
-    // at their limit are struck off.
-    auto settle_claim = [&](int q, int i) {
-        for (;;) {
-            if (q >= 0) {
-                const int t = tile_of_claim(q, i);
-                if (t >= 0) return t;
-                dry |= 1 << q;
-                const int seen = __hip_atomic_load(&queues[opaque(lane) & 7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int total_now = opaque_uniform(total);
-#pragma unroll
-                for (int c = 0; c < 8; ++c)
-                    if (__builtin_amdgcn_readlane(seen, c) >= claims_of(c, total_now)) dry |= 1 << c;
-            }
-            q = next_counter();
-            if (q < 0) return -1;
-            i = __builtin_amdgcn_readfirstlane(claim_from(q));
-        }
-    };
-    if (wave == 0) next_tile = settle_claim(-1, 0);
-    for (;;) {
-        lds_wait<0>();                 // thread 0's store of next_tile
-        __builtin_amdgcn_s_barrier();  // also: every wavefront is done reading the previous tile's stages
-        const int t_all = __builtin_amdgcn_readfirstlane(next_tile);
-        if (t_all < 0) break;
-        // the claim for the tile after this one is made now and looked at after the K loop
-        int ahead_q = -1, ahead_pending = 0;
-        if (wave == 0) {
-            ahead_q = next_counter();
-            if (ahead_q >= 0) ahead_pending = claim_from(ahead_q);
-        }
-        const bool whole = t_all < total_whole;
-        const int t = whole ? t_all : t_all - total_whole;
-        const int m_base = whole ? 0 : n_whole;
-        const int m_count = whole ? n_whole : n_entries - n_whole;
-        const int per_group = m_count * group_n;
-        const int grp = t / per_group;
-        const int rem = t - grp * per_group;
-        const int gw = (n_ntiles - grp * group_n) < group_n ? (n_ntiles - grp * group_n) : group_n;
-        const int mt_i = m_base + rem / gw;
-        const int nt_i = grp * group_n + rem % gw;
-        const MTile mt = mtiles[mt_i];
-        const int n0 = nt_i * BN;
-        // k-tiles of this entry: all of K, or the part of it a split tile covers
-        const int KT = mt.kt1 > 0 ? mt.kt1 - mt.kt0 : K / BK;
-        // rows that go through a list are addressed from the start of A (32-bit byte offsets:
-        // the host checks that A fits), rows in place from the tile's first row
-        const bf16_t* Ab = (rm.a_rows ? A : A + (size_t)mt.list0 * lda) + mt.kt0 * BK;
-        const bf16_t* Bb = Bp + (size_t)mt.expert * b_stride + ((size_t)nt_i * (K / BK) + mt.kt0) * (BN * BK);
-        const int n_valid = (N - n0) < BN ? (N - n0) : BN;
-
-        // per-lane byte offsets of the pieces this lane fetches (activation rows beyond the
-        // segment are clamped to the last valid row, weight rows beyond the matrix edge are
-        // zero rows of the packed form; their products are computed and dropped in the
-        // epilogue).  (uniform base) + (32-bit lane offset) is an addressing mode of the load
-        // instruction, so the loads spend no vector ALU work on addresses.  A weight tile is
-        // stored as it sits in LDS: load i of the wavefront takes its 1 KiB of it as it comes, so
-        // one lane offset serves all of them and the rest of the address is uniform.  Whether
-        // that offset is kept in a register or worked out at each load (one instruction) decides,
-        // at the 256 registers of the tallest shape, which of the three epilogues the compiler
-        // fits without scratch memory: the form below keeps all of them at none.
-        constexpr bool KEEP_OFFB = SWIGLU;
-        unsigned offA_b[IAW];
-        unsigned offB_kept[KEEP_OFFB ? IBW : 1];
-        const int lane_p = opaque(lane);
-        const int wave_a = A_SHARED ? wave % IA : wave;
-#pragma unroll
-        for (int i = 0; i < IAW; ++i) {
-            const int p = (wave_a + i * NW) * 64 + lane_p;
-            const int row = p / CPR, slot = p % CPR;
-            int r = row < mt.rows ? row : mt.rows - 1;
-            if (rm.a_rows) {
-                r = rm.a_rows[mt.list0 + r];
-                if (rm.a_rows2) r = rm.a_rows2[r] / opaque_uniform(rm.a_div);
-            }
-            offA_b[i] = ((unsigned)r * (unsigned)lda + (unsigned)((slot ^ swz(row)) * 8)) * 2u;
-        }
-        if constexpr (KEEP_OFFB) {
-#pragma unroll
-            for (int i = 0; i < IBW; ++i) offB_kept[i] = (unsigned)(((wave + i * NW) * 64 + lane_p) * 16);
-        }
-
-
-        // load l of this wavefront's LPT loads of k-tile kt (activations first), one instruction
-        const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
-        const unsigned lds_wave = lds_base + (unsigned)wave * 1024u;
-        const unsigned lds_wave_a = lds_base + (unsigned)wave_a * 1024u;
-        auto issue_load_n = [&](auto L, int kt, int stage) {
-            constexpr int l = decltype(L)::value;
-            const unsigned sA = lds_wave + (unsigned)(stage * STAGE_BYTES);
-            if constexpr (l < IAW) {
-                const unsigned char* base = (const unsigned char*)Ab + (size_t)(kt * (BK * 2));
-                if (!SKIP_TAIL_LOADS || (wave + l * NW) * ROWS_PER_LOAD < mt.rows)
-                    global_to_lds_b128(base, offA_b[l], lds_wave_a + (unsigned)(stage * STAGE_BYTES + l * NW * 1024));
-            } else {
-                if constexpr (KEEP_OFFB) {
-                    const unsigned char* base = (const unsigned char*)Bb + (size_t)kt * B_BYTES;
-                    global_to_lds_b128(base, offB_kept[l - IAW], sA + (unsigned)(A_BYTES + (l - IAW) * NW * 1024));
-                } else {
-                    const unsigned char* base =
-                        (const unsigned char*)Bb + ((size_t)kt * B_BYTES + (l - IAW) * NW * 1024);
-                    global_to_lds_b128(base, (unsigned)((wave * 64 + opaque(lane)) * 16),
-                                       sA + (unsigned)(A_BYTES + (l - IAW) * NW * 1024));
-                }
-            }
-        };
-        auto issue_loads = [&](int kt, int stage) {
-            static_for<LPT>([&](auto L) { issue_load_n(L, kt, stage); });
-        };
-
-        // the first k-tiles are requested before the accumulators are cleared: the clearing
-        // then runs while the loads are under way
-#pragma unroll
-        for (int s = 0; s < NSTAGE; ++s)
-            if (s < KT) issue_loads(s, s);
-        __builtin_amdgcn_sched_barrier(0);
-
-        // Accumulators hold the transposed product: the weight fragment is the MFMA's row
-        // operand and the activation fragment its column operand, so element r of lane
-        // (l16, g16) in tile (i, j) is output row i*16 + l16 and output column j*16 + g16*4 + r:
-        // four consecutive columns per lane.
-        f32x4 acc16[TM16][TN16];
-#pragma unroll
-        for (int i = 0; i < TM16; ++i)
-#pragma unroll
-            for (int j = 0; j < TN16; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc16[i][j][r] = 0.f;
-        const int lane_k = opaque(lane);
-        const int l16 = lane_k & 15, g16 = lane_k >> 4;
-
-        // K loop.  A step is 32 deep: TM16 activation fragments (16 rows each) and TN16 weight
-        // fragments, TM16 * TN16 MFMAs, taken row of tiles by row of tiles.  The weight
-        // fragments are double-buffered; an activation fragment is free once its row of tiles
-        // has been issued, so its register is refilled for the next step right behind that
-        // row.  LDS reads complete in issue order (weights of a step first, then its activation
-        // fragments 0, 1, ...), which fixes how many may still be in flight before each row.
-        // The hand-over to the next k-tile (own loads landed, barrier, refill of the stage just
-        // left) opens a k-tile's last step, when every fragment of that k-tile is in a
-        // register; the loads of the refill go out one or two per row of tiles.  The loop
-        // exists twice: FULL (every 16-row sub-tile of this wavefront is valid, no conditions
-        // inside) and ragged (sub-tiles past the end of the M-tile are not multiplied); both run
-        // the same sequence of barriers, so wavefronts of one workgroup may take different ones.
-        auto k_loop16 = [&](auto full_tag) {
-            constexpr bool FULL = decltype(full_tag)::value;
-            constexpr int ROW_BYTES = CPR * 16;
-            const int rows_w16 = mt.rows - wm * WTM;
-            const int tmv16 = rows_w16 <= 0 ? 0 : (rows_w16 >= WTM ? TM16 : (rows_w16 + 15) / 16);
-            const int sw16 = swz(l16);  // rows differ by multiples of 16 -> same swizzle
-            const unsigned a_base = lds_base + (unsigned)((wm * WTM + l16) * ROW_BYTES);
-            // weight fragment (16-row group j of this wavefront, step ks) sits at b_base + stage +
-            // (j * 2 + ks) KiB
-            const unsigned b_base = lds_base + (unsigned)(A_BYTES + wn * WTN * ROW_BYTES + lane_k * 16);
-            bf16x8 af[TM16], bfr[2][TN16];
-            auto piece_of = [&](int kt, int ks) {
-                return (unsigned)((kt % NSTAGE) * STAGE_BYTES + (((ks * 4 + g16) ^ sw16) * 16));
-            };
-            auto read_a = [&](auto I, unsigned piece) {
-                constexpr int i = decltype(I)::value;
-                // read even where the rows lie past the end of a ragged tile (whatever the stage
-                // holds there: those tiles are not multiplied), so the count of reads in flight
-                // is the same for every wavefront
-                lds_read_b128<i * 16 * ROW_BYTES>(af[i], a_base + piece);
-            };
-            auto read_b_all = [&](auto KS, int buf, int kt) {
-                const unsigned base = b_base + (unsigned)((kt % NSTAGE) * STAGE_BYTES);
-                static_for<TN16>([&](auto J) {
-                    constexpr int j = decltype(J)::value;
-                    lds_read_b128<(j * 2 + decltype(KS)::value) * 1024>(bfr[buf][j], base);
-                });
-            };
-            auto row_mfmas = [&](auto I, int buf) {
-                constexpr int i = decltype(I)::value;
-                lds_landed(af[i]);
-                __builtin_amdgcn_sched_barrier(0);
-                if (FULL || i < tmv16) {
-#pragma unroll
-                    for (int j = 0; j < TN16; ++j)
-                        acc16[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[buf][j], af[i], acc16[i][j], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            // One step.  On entry the reads of its own fragments are in flight or done, in the
-            // order weights, activation 0, 1, ...  NEXT: a step follows and its fragments are read
-            // here.  HANDOVER: this is the last step of k-tile kt and k-tile kt + 1 exists.
-            auto step = [&](int kt, auto ks_tag, auto next_tag, auto hand_tag) {
-                constexpr int ks = decltype(ks_tag)::value;
-                constexpr bool NEXT = decltype(next_tag)::value, HANDOVER = decltype(hand_tag)::value;
-                constexpr int cur = ks & 1, nxt = cur ^ 1;
-                const unsigned np = HANDOVER ? piece_of(kt + 1, 0) : piece_of(kt, ks + 1);
-                if constexpr (NEXT && !HANDOVER)
-                    lds_wait<TM16 - 1>();  // the weights and activation fragment 0 have landed
-                else
-                    lds_wait<0>();
-#pragma unroll
-                for (int j = 0; j < TN16; ++j) lds_landed(bfr[cur][j]);
-                if constexpr (NEXT && !HANDOVER) read_b_all(std::integral_constant<int, ks + 1>{}, nxt, kt);
-                static_for<TM16>([&](auto I) {
-                    constexpr int i = decltype(I)::value;
-                    if constexpr (HANDOVER && i == 0) {
-                        // every fragment of k-tile kt is in a register (waited for on entry); this
-                        // wavefront's pieces of k-tile kt + 1 have landed; the barrier extends both
-                        // to every wavefront, so the stage of k-tile kt can be refilled
-                        if (KT - 2 - kt >= NSTAGE - 2)
-                            wait_vmcnt<LPT*(NSTAGE - 2)>();
-                        else
-                            wait_vmcnt<0>();
-                        __builtin_amdgcn_s_barrier();
-                        read_b_all(std::integral_constant<int, 0>{}, nxt, kt + 1);
-                    }
-                    if constexpr (i > 0 && NEXT && !HANDOVER)
-                        lds_wait<TM16 - 1 + TN16>();  // activation fragment i has landed
-                    row_mfmas(I, cur);
-                    if constexpr (NEXT) read_a(I, np);
-                    if constexpr (HANDOVER) {
-                        // the refill of the stage k-tile kt has left: this wavefront's loads of
-                        // k-tile kt + NSTAGE, dealt over the rows of tiles behind the hand-over so
-                        // that a load waiting for the CU's one address unit holds up a few MFMAs of
-                        // this wavefront, not the SIMD (its other wavefront keeps issuing)
-                        constexpr int l0 = i * LPT / TM16, l1 = (i + 1) * LPT / TM16;
-                        if (kt + NSTAGE < KT)
-                            static_for<l1 - l0>([&](auto D) {
-                                issue_load_n(std::integral_constant<int, l0 + decltype(D)::value>{}, kt + NSTAGE,
-                                             kt % NSTAGE);
-                            });
-                    }
-                });
-            };
-            if ((!SKIP_TAIL_LOADS || mt.rows == BM) && KT >= NSTAGE)
-                wait_vmcnt<LPT*(NSTAGE - 1)>();  // k-tile 0 landed, the others may be in flight
-            else
-                wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();
-            read_b_all(std::integral_constant<int, 0>{}, 0, 0);
-            static_for<TM16>([&](auto I) { read_a(I, piece_of(0, 0)); });
-            int kt = 0;
-            for (; kt + 1 < KT; ++kt) {
-                step(kt, std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{});
-                step(kt, std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{});
-            }
-            step(kt, std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{});
-            step(kt, std::integral_constant<int, 1>{}, std::false_type{}, std::false_type{});
-        };
-        if (mt.rows - wm * WTM >= WTM)
-            k_loop16(std::true_type{});
-        else
-            k_loop16(std::false_type{});
-        // every wavefront has read next_tile (the K loop holds a barrier)
-        if (wave == 0) next_tile = settle_claim(ahead_q, __builtin_amdgcn_readfirstlane(ahead_pending));
-
-        // epilogue: 4 consecutive columns per lane and tile -> 8-byte stores (16 bytes of fp32 partial sums)
-        const int lane_e = opaque(lane);
-        const int l16e = lane_e & 15, g16e = lane_e >> 4;
-        const int n_out = SWIGLU ? N / 2 : N;
-        const int col0 = (SWIGLU ? (n0 + wn * WTN) / 2 : (n0 + wn * WTN));
-        constexpr int TNO16 = SWIGLU ? TN16 / 2 : TN16;  // 16-column tiles of output per wavefront
-        static_assert(!SWIGLU || TN16 % 4 == 0, "gate and up tiles pair up inside 64 packed columns");
-        float* slab = nullptr;
-        if constexpr (EPI == kEpiNone)
-            if (mt.part >= 0) slab = partials + (size_t)mt.part * kPartRows * N;
-        // output row and scale of this lane's TM16 rows, fetched as one batch (row by row each
-        // would wait out a memory round trip, and with it the stores of the row before)
-        int crow_of[TM16];
-        float sc_of[TM16];
-#pragma unroll
-        for (int i = 0; i < TM16; ++i) {
-            const int row = wm * WTM + i * 16 + l16e;
-            crow_of[i] = mt.list0 + (row < mt.rows ? row : mt.rows - 1);
-            sc_of[i] = 1.0f;
-        }
-        if constexpr (EPI == kEpiNone) {
-            if (!slab) {
-                if (rm.c_rows) {
-#pragma unroll
-                    for (int i = 0; i < TM16; ++i) crow_of[i] = rm.c_rows[crow_of[i]];
-                }
-                if (rm.scale) {
-                    int si[TM16];
-#pragma unroll
-                    for (int i = 0; i < TM16; ++i) si[i] = rm.scale_idx[crow_of[i]];
-#pragma unroll
-                    for (int i = 0; i < TM16; ++i) sc_of[i] = rm.scale[si[i]];
-                }
-            }
-        }
-        // values of output tile jo (16 columns) of row block i for this lane: 4 consecutive columns
-        auto tile_values = [&](int i, int jo, float sc, float (&v)[4]) {
-            // output tile jo: packed tiles (jo/2)*4 + jo%2 (gate) and + 2 (up) with SwiGLU
-            const int jg = SWIGLU ? (jo / 2) * 4 + (jo % 2) : jo;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (SWIGLU)
-                    v[c] = silu_f(acc16[i][jg][c]) * acc16[i][jg + 2][c];
-                else if (EPI == kEpiRelu)
-                    v[c] = fmaxf(acc16[i][jg][c], 0.f);
-                else
-                    v[c] = acc16[i][jg][c] * sc;
-            }
-        };
-        if (slab) {
-#pragma unroll
-            for (int i = 0; i < TM16; ++i) {
-                const int row = wm * WTM + i * 16 + l16e;
-                if (row < mt.rows) {
-#pragma unroll
-                    for (int jo = 0; jo < TNO16; ++jo)
-                        if (col0 + jo * 16 < n_out) {
-                            float v[4];
-                            tile_values(i, jo, 1.0f, v);
-                            float4 o;
-                            o.x = v[0];
-                            o.y = v[1];
-                            o.z = v[2];
-                            o.w = v[3];
-                            *(float4*)(slab + (size_t)row * N + col0 + jo * 16 + g16e * 4) = o;
-                        }
-                }
-            }
-        } else {
-            // Rounded to bf16 a lane holds 8 bytes of a row per output tile.  Two tiles side by
-            // side are regrouped with the two lane-swap instructions (quarter q of the wavefront
-            // = lanes 16q .. 16q+15, all of one row set): swapping the upper half of the first
-            // tile's register with the lower half of the second's, then the odd quarters of the
-            // first with the even quarters of the second, leaves quarter q with columns 8q .. 8q+3
-            // of the 32 in the first register and 8q+4 .. 8q+7 in the second: 16 bytes in a row
-            // per lane, half as many store instructions, each writing 64-byte pieces.
-            static_assert(TNO16 % 2 == 0, "output tiles are stored in pairs");
-#pragma unroll
-            for (int i = 0; i < TM16; ++i) {
-                const int row = wm * WTM + i * 16 + l16e;
-                bf16_t* crow = C + (size_t)crow_of[i] * ldc + col0 + g16e * 8;
-#pragma unroll
-                for (int jo = 0; jo < TNO16; jo += 2) {
-                    float v0[4], v1[4];
-                    tile_values(i, jo, sc_of[i], v0);
-                    tile_values(i, jo + 1, sc_of[i], v1);
-                    unsigned px = pack_bf16x2(v0[0], v0[1]), py = pack_bf16x2(v0[2], v0[3]);
-                    unsigned qx = pack_bf16x2(v1[0], v1[1]), qy = pack_bf16x2(v1[2], v1[3]);
-                    lane_swap_pairs(px, qx);
-                    lane_swap_pairs(py, qy);
-                    if (row < mt.rows && col0 + jo * 16 < n_out) {
-                        uint4 o;
-                        o.x = px;
-                        o.y = py;
-                        o.z = qx;
-                        o.w = qy;
-                        *(uint4*)(crow + jo * 16) = o;
-                    }
-                }
-            }
-        }
-    }
-}
-
+#include "ffn_tiles.h"
 #include "ffn_stream.h"
 
 // Adds up the fp32 slabs of every split M-tile in the order of the parts and writes the rows
@@ -1289,42 +826,9 @@ static size_t ffn_ws_layout(int64_t A, int d, int ffn, int nseg, int dtype, char
     return off;
 }
 
-struct GemmVariant {
-    int bm, bn, bk;
-    size_t lds;
-    int threads;
-    void (*kern)(const bf16_t*, int, const bf16_t*, size_t, bf16_t*, int, const MTile*, const int32_t*, int32_t*, int,
-                 int, int, RowMap, float*);
-    std::atomic<unsigned long long>* attr_set;  // bit per device: the dynamic-LDS attribute has been raised
-};
-
-template <int BM, int BN, int BK, int WGM, int WGN, int NSTAGE, int EPI>
-static GemmVariant make_variant() {
-    static std::atomic<unsigned long long> attr_set{0};
-    GemmVariant v;
-    v.bm = BM;
-    v.bn = BN;
-    v.bk = BK;
-    v.lds = (size_t)NSTAGE * (BM + BN) * BK * 2;
-    v.threads = WGM * WGN * 64;
-    v.kern = grouped_gemm_bf16_kernel<BM, BN, BK, WGM, WGN, NSTAGE, EPI>;
-    v.attr_set = &attr_set;
-    return v;
-}
-
-// Tile shapes built into the library: 0 = 256x256x64 with two LDS stages, 1 = 128x256x64 with
-// three (for products with too few 256-row tiles to fill the chip twice), 2 = 32x256x64 with
-// four (by option only; slivers of a few rows per expert are streamed, ffn_stream.h).
-constexpr int kNumVariants = 3;
-static const GemmVariant kGemmSwiglu[kNumVariants] = {make_variant<256, 256, 64, 2, 4, 2, kEpiSwiglu>(),
-                                                      make_variant<128, 256, 64, 2, 4, 3, kEpiSwiglu>(),
-                                                      make_variant<32, 256, 64, 2, 4, 4, kEpiSwiglu>()};
-static const GemmVariant kGemmRelu[kNumVariants] = {make_variant<256, 256, 64, 2, 4, 2, kEpiRelu>(),
-                                                    make_variant<128, 256, 64, 2, 4, 3, kEpiRelu>(),
-                                                    make_variant<32, 256, 64, 2, 4, 4, kEpiRelu>()};
-static const GemmVariant kGemmPlain[kNumVariants] = {make_variant<256, 256, 64, 2, 4, 2, kEpiNone>(),
-                                                     make_variant<128, 256, 64, 2, 4, 3, kEpiNone>(),
-                                                     make_variant<32, 256, 64, 2, 4, 4, kEpiNone>()};
+// Tile heights of the options: tables of up to 256, 128 or 32 rows per tile.
+constexpr int kNumShapes = 3;
+constexpr int kShapeRows[kNumShapes] = {256, 128, 32};
 
 // timing hook: events recorded around the two products of the next call on this thread
 static thread_local hipEvent_t g_time_events[4];
@@ -1342,24 +846,27 @@ static int num_cus() {
     return cus;
 }
 
-static int launch_gemm_bf16(const GemmVariant& v, const bf16_t* A, int lda, const bf16_t* Bp, size_t b_stride,
-                            bf16_t* C, int ldc, const MTile* tiles, const int32_t* counts, int32_t* queues, int N,
-                            int K, int group_n, const RowMap& rm, float* partials, hipStream_t st) {
-    // the kernels use more LDS than the default limit: raised once per kernel and device
+template <int EPI>
+static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_stride, bf16_t* C, int ldc,
+                        const MTile* tiles, const int32_t* counts, int32_t* queues, int N, int K, int group_n,
+                        const RowMap& rm, float* partials, hipStream_t st) {
+    // the kernel uses more LDS than the default limit: raised once per kernel and device
+    static std::atomic<unsigned long long> attr_set{0};  // bit per device
+    const auto kern = grouped_gemm_tile_kernel<EPI>;
     int dev = 0;
     (void)hipGetDevice(&dev);
     const unsigned long long bit = 1ull << (dev & 63);
-    if (!(v.attr_set->load() & bit)) {
-        hipError_t e = hipFuncSetAttribute((const void*)v.kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)v.lds);
+    if (!(attr_set.load() & bit)) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds);
         if (e != hipSuccess) {
             set_last_hip_error(e);
             return MOE_ERR_HIP;
         }
-        v.attr_set->fetch_or(bit);
+        attr_set.fetch_or(bit);
     }
     // 32 workgroups for each of the 8 XCDs; they claim tiles from `queues` (cleared by the table builder)
-    hipLaunchKernelGGL(v.kern, dim3(kGemmGrid), dim3(v.threads), v.lds, st, A, lda, Bp, b_stride, C, ldc, tiles,
-                       counts, queues, N, K, group_n, rm, partials);
+    hipLaunchKernelGGL(kern, dim3(kGemmGrid), dim3(512), kTileLds, st, A, lda, Bp, b_stride, C, ldc, tiles, counts,
+                       queues, N, K, group_n, rm, partials);
     return check_launch();
 }
 
@@ -1437,7 +944,7 @@ extern "C" int moe_grouped_ffn_set_option(int option, int value) {
     switch (option) {
         case MOE_FFN_OPT_TILE1:
         case MOE_FFN_OPT_TILE2:
-            if (value < -1 || value >= kNumVariants) return MOE_ERR_INVALID_ARG;
+            if (value < -1 || value >= kNumShapes) return MOE_ERR_INVALID_ARG;
             (option == MOE_FFN_OPT_TILE1 ? g_opt_tile1 : g_opt_tile2).store(value);
             return MOE_OK;
         case MOE_FFN_OPT_SPLIT_K:
@@ -1646,23 +1153,21 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     // 1.5 % slower; down products of 16 N-tiles, 6 is 2-8 % faster than 16 below 1 GiB of rows,
     // 8 is 2 % faster than 6 at 1.9 GiB.
     const int group_opt = g_opt_group_n.load();
-    auto group_for = [&](int n_cols, int bn, int64_t a_bytes) {
+    auto group_for = [&](int n_cols, int64_t a_bytes) {
         if (group_opt > 0) return group_opt;
-        const int n_ntiles = ceil_div(n_cols, bn);
+        const int n_ntiles = ceil_div(n_cols, kPackN);
         if (n_ntiles <= 12) return n_ntiles;
         if (n_ntiles <= 16) return a_bytes <= ((int64_t)1 << 30) ? 6 : 8;
         return a_bytes <= ((int64_t)96 << 20) ? 4 : 6;
     };
-    const GemmVariant& g1 = relu ? kGemmRelu[v1] : kGemmSwiglu[v1];
-    const GemmVariant& g2 = kGemmPlain[v2];
     // one launch builds the row list and both tables; the second product shares the first one's
     // table when it has the same tile height and splits nothing
-    const int bm1 = s1 ? kStreamBM : g1.bm, bm2 = s2 ? kStreamBM : g2.bm;
+    const int bm1 = s1 ? kStreamBM : kShapeRows[v1], bm2 = s2 ? kStreamBM : kShapeRows[v2];
     const bool split = ws.split_capacity > 0 && !s2;
     const bool own2 = bm2 != bm1 || split;
-    TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / g1.bk, 0, 1, kGemmGrid, 0, 0};
-    TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / g2.bk,
-                 split ? ws.parts : 0, ceil_div(d, g2.bn), kGemmGrid, ws.split_all, ws.split_capacity};
+    TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / kPackK, 0, 1, kGemmGrid, 0, 0};
+    TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / kPackK,
+                 split ? ws.parts : 0, ceil_div(d, kPackN), kGemmGrid, ws.split_all, ws.split_capacity};
     hipLaunchKernelGGL(build_tables_kernel, dim3(build_grid), dim3(1024), 0, st, seg_offsets, slot_expert, seg_begin,
                        seg_end, E, t1, t2, ws.rowlist, ws.queues, 16);
     if ((rc = check_launch()) != MOE_OK) return rc;
@@ -1677,9 +1182,9 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
                   : launch_stream<kEpiSwiglu>(s1, A, E, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp),
                                               (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, st);
     } else {
-        rc = launch_gemm_bf16(g1, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h, fp, ws.tiles1,
-                              ws.counts, ws.queues, n1 * fp, d, group_for(n1 * fp, g1.bn, A * (int64_t)d * 2), rm1,
-                              nullptr, st);
+        const auto go = relu ? launch_tiles<kEpiRelu> : launch_tiles<kEpiSwiglu>;
+        rc = go((const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, ws.queues,
+                n1 * fp, d, group_for(n1 * fp, A * (int64_t)d * 2), rm1, nullptr, st);
     }
     if (timed) (void)hipEventRecord(g_time_events[1], st);
     if (rc != MOE_OK) return rc;
@@ -1688,8 +1193,8 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
         rc = launch_stream<kEpiNone>(s2, A, E, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d,
                                      tiles2, count2, d, fp, rm2, st);
     else
-        rc = launch_gemm_bf16(g2, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d, tiles2, count2,
-                              ws.queues + 8, d, fp, group_for(d, g2.bn, A * (int64_t)fp * 2), rm2, ws.partials, st);
+        rc = launch_tiles<kEpiNone>((const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d, tiles2, count2,
+                                    ws.queues + 8, d, fp, group_for(d, A * (int64_t)fp * 2), rm2, ws.partials, st);
     if (rc == MOE_OK && split) {
         hipLaunchKernelGGL(add_partials_kernel, dim3(ws.split_capacity < 64 ? ws.split_capacity : 64, 32), dim3(256),
                            0, st, ws.partials, ws.splits, count2, ws.parts, (bf16_t*)y_perm, d, d, rm2);

@@ -473,6 +473,29 @@ def test_ffn_every_tile_variant(tile1, tile2, split, ffn_options):
     assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * scale)
 
 
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("d,ffn", [(64, 128), (192, 256), (320, 384), (448, 576), (704, 832)])
+def test_ffn_tile_heights_and_depths(d, ffn, relu, ffn_options):
+    """Tiles of every height the kernel has a K loop for, at its edges, with every remainder of the
+    number of k-tiles (1 to 13) by the three or four that are under way at a time."""
+    ffn_options(tile1=0, tile2=0, split=0)
+    sizes = [1, 31, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 256, 256 + 40]
+    E = len(sizes)
+    cfg = wl.MoEConfig("h", T=1, d=d, ffn=ffn, E=E, k=1, G=E, S=1, dtype="bf16", mode=0, seed=47,
+                       act="relu" if relu else "swiglu")
+    A = sum(sizes)
+    x = wl.quantize(np.random.default_rng(48).standard_normal((A, d)).astype(np.float32), "bf16")
+    so = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    W1s, W3s, W2s = host_weights(cfg)
+    Wf = [wl.from_storage(w, "bf16") for w in (W1s, W3s, W2s)]
+    packed = B.moe_pack_weights_relu(to_device(W1s, "bf16"), to_device(W2s, "bf16")) if relu \
+        else B.moe_pack_weights(*dev_weights(cfg, (W1s, W3s, W2s)))
+    got = to_host_f32(B.moe_grouped_ffn(to_device(wl.to_storage(x, "bf16"), "bf16"), dev_i32(so), dev_i32(range(E)),
+                                        packed, E, ffn, relu=relu))
+    ref = grouped_ffn(x, so, list(range(E)), Wf[0], None if relu else Wf[1], Wf[2])
+    assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * np.max(np.abs(ref)))
+
+
 @pytest.mark.parametrize("form", [1, 2])
 @pytest.mark.parametrize("d,ffn,relu", [(64, 64, False),      # one k-tile: one half / three parts of K are empty
                                         (192, 320, False),    # odd numbers of k-tiles, half a unit at the edge of N
