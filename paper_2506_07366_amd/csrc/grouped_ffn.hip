@@ -42,11 +42,11 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;  // four floats at any float's address, still one access
 typedef unsigned short bf16_t;  // storage
 
-// One entry of an M-tile table: up to BM consecutive positions of the row list, all of one
+// One entry of an M-tile table: consecutive positions of the row list, all of one
 // expert, and the part of the K range this entry covers.
 struct MTile {
     int list0;   // first position in the row list
-    int rows;    // valid rows (<= BM)
+    int rows;    // valid rows
     int expert;  // expert whose weights the rows take
     int kt0;     // k-tiles [kt0, kt1) of the product belong to this entry; kt1 == 0: all of them
     int kt1;
@@ -146,37 +146,47 @@ struct TableSpec {
     MTile* tiles;       // out
     int32_t* counts;    // out, kCntStride ints
     SplitInfo* splits;  // out (split tiles only), may be null when parts <= 1
-    int bm;             // tile height
+    int bm;             // most rows of a tile, 0: chosen from the batch
     int capacity;       // entries `tiles` has room for
     int kt;             // k-tiles of the product
     int parts;          // parts of K of a split tile (<= 1: no tile is split)
-    int n_ntiles;       // N-tiles of the product and workgroups of its launch: they decide how much
-    int grid;           //   work is split at the end of the order (see build_tables_kernel)
+    int n_ntiles;       // N-tiles of the product (tile heights and split tiles go by the tiles
+                        //   that the kGemmGrid workgroups of its launch get)
     int split_all;      // split every tile (tests)
     int split_capacity; // split M-tiles `splits` and the slabs have room for
 };
 
 // Row list: position p holds a row of x_perm; the rows of an expert's segments (ascending
-// slot id, rows ascending) are consecutive, experts ascending.  M-tile tables: the whole tiles by
-// expert, an expert's ragged last tile right behind its full-height ones, so that neighbours
-// share weight panels (MTile::first and n_same, by which the streaming kernels walk the tiles of one
-// expert, rely on it).  With parts > 1 the closing M-tiles -- the order for this is full-height
-// tiles by expert, then ragged ones, tallest first -- are listed once per part of K instead, behind the
+// slot id, rows ascending) are consecutive, experts ascending.
+// M-tile tables: an expert's rows are cut into as few tiles as the height allows, evenly (a tile costs by
+// its rows, ffn_tiles.h, so two of 160 and 140 rows are done before one of 256 and one of 44), in steps of the
+// 32 rows the kernels have loops for.  An expert's tiles stay together, in expert order (they share weight
+// panels; the kernels walk them by MTile::first and n_same), experts with tiles of up to kShortTile rows
+// behind the others: what is left for the end of the launch is then short, while tall tiles, bound by the matrix pipe,
+// stay mixed with middling ones, bound by their weights (tallest first altogether: 64 experts of 2048 x 1408, 4096
+// tokens, second product 189 us, as it is 184; short ones where they fall: 206).
+// The height is worked out here, where the rows per expert are known, one lane per candidate: the
+// launch's time is taken as the longest of (a) for every height in the table, the rounds that the
+// tiles of that height and above make of the workgroups, and (b) the mean work of a workgroup and a quarter of a
+// closing tile; where tiles may be split as the work, a third dearer, and the pass that adds them up.  A tile's cost is
+// kCostFixed + its 16-row groups.  The constants are fitted to 78 products of 39 batches (five shapes, 8 to 224 k-tiles,
+// 2 to 112 N-tiles, 150 to 16384 tokens), each timed with all seven heights: the height taken is 0.9 % above the best one
+// on average, 7 % at most.  Both products, us, 256- or 128-row tiles by a rule on the mean rows per expert ->
+// this: 777 tokens, top-8 of 128 experts of 4096 x 1536 389 -> 354; 1001 tokens, top-2 of 8 of 4096 x 14336 819 ->
+// 730; 2048 tokens, top-6 of 64 of 2048 x 1408 345 -> 310; 3000 tokens, top-4 of 16 of 4096 x 688 261 -> 223; 4096
+// tokens, top-2 of 8 of 512 x 1024 83 -> 48.
+// With parts > 1 the closing M-tiles are listed once per part of K instead, behind the
 // whole ones and part by part, each entry writing fp32 partial sums to a slab of its own (slab =
-// split tile * parts + part).  How many: the work of the product,
-// counted in tiles (a ragged tile of r rows as (BM + r) / 2BM of a tile: its weight panel
-// streams in full), is so many whole rounds of one tile per workgroup plus a remainder; the
-// rounds run as whole tiles, and the remainder -- what would otherwise be a last round with
-// most workgroups idle -- is what gets split, smallest tiles first, unless it is most of a
-// round anyway (more than 5/8: splitting would add traffic and save little).
+// split tile * parts + part).  What is split is what goes beyond whole rounds of one tile per workgroup,
+// unless it is most of a round anyway (more than 5/8: splitting would add traffic and save little).
+//
 // The work is small and what it costs is waiting: for barriers of 16 wavefronts and for chains of LDS
 // round trips.  So one wavefront does the parts that need an order (64 segments or experts at a
 // time, equal keys found by ballots, counts carried in LDS, prefix sums by DPP), without a
 // barrier between its steps, and the workgroup meets three times: segments loaded, list order
 // known, table prepared; the row list and the table entries are written by everybody.
 // Every workgroup works out the list order and fills its stripe of the row list; workgroup 0
-// writes the first table and clears the claim counters, workgroup 1 the second (the launch has two at least).
-// The ragged tiles are ranked by counting their heights instead of comparing all pairs.
+// writes the first table and sets the claim counters, workgroup 1 the second (the launch has two at least).
 // Against pairs of segments and of experts dealt over the workgroup, some 30 barriers, and stripes of
 // 4096 positions: 8 experts in 12 slots 10.3 -> 6.5 us (in 16 slots 9.4 -> 5.5); 128 experts in 160
 // slots, one token 15.8 -> 8.5, 128 tokens 17.5 -> 9.4, 777 tokens and two tables 19.6 -> 10.5; 64 experts
@@ -224,8 +234,20 @@ __device__ __forceinline__ unsigned long long same_key_lanes(int key, bool live,
     return live ? same : 0ull;
 }
 
-constexpr int kTallest = 256;  // tile heights are powers of two up to this
+constexpr int kTallest = 256, kHeightStep = 32;      // rows of the tallest tile; heights are multiples of the step
+constexpr int kHeights = kTallest / kHeightStep;
+constexpr int kMinAutoHeight = 64;                   // lowest height that is chosen from the batch
+constexpr int kCandidates = (kTallest - kMinAutoHeight) / kHeightStep + 1;
+constexpr int kShortTile = 64;                       // tiles of up to so many rows come last
+constexpr int kCostFixed = 8;                        // cost of a tile: this and its 16-row groups
 static_assert(MOE_MAX_EXPERTS <= 1 << 12 && MOE_MAX_SEGMENTS <= 1 << 19, "expert and place share one int");
+
+// Height of the tiles that `rows` rows of one expert are cut into, at most `most` each (a multiple of the step).
+__device__ __forceinline__ int even_height(int rows, int most) {
+    const int n = (rows + most - 1) / most;
+    if (n > kHeights) return most;  // (n - 1) / n of the limit is less than a step below it
+    return ((rows + n - 1) / n + kHeightStep - 1) / kHeightStep * kHeightStep;
+}
 
 __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __restrict__ seg_offsets,
                                                              const int32_t* __restrict__ slot_expert, int seg_begin,
@@ -238,14 +260,10 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
     __shared__ int srt_base[MOE_MAX_SEGMENTS + 1]; // list position of the j-th segment in list order
     __shared__ int srt_first[MOE_MAX_SEGMENTS];    // its first row of x_perm
     __shared__ int e_segs[MOE_MAX_EXPERTS + 1];    // live segments per expert -> base in list order
-    __shared__ int e_full[MOE_MAX_EXPERTS + 1];    // full-height tiles per expert -> base
-    __shared__ int e_whole[MOE_MAX_EXPERTS + 1];   // whole ragged tiles of the experts below
-    __shared__ int e_tail[MOE_MAX_EXPERTS];        // rows of the expert's ragged tile
-    __shared__ int e_rank[MOE_MAX_EXPERTS];        // its place among the ragged tiles, tallest first
-    __shared__ int h_count[kTallest + 1];          // ragged tiles of a height -> taller or as tall ones excluded
-    __shared__ int h_rows[kTallest + 1];           // rows of lower ragged tiles
-    __shared__ int h_same[kTallest];               // ragged tiles of the height
-    __shared__ int s_plan[4];                      // n_full, n_tail, n_fsplit, n_rsplit
+    __shared__ int o_base[MOE_MAX_EXPERTS + 1];    // tiles of the o-th expert in tile order -> those before it
+    __shared__ int o_expert[MOE_MAX_EXPERTS];      // that expert, and from bit 12 the height of its tiles
+    __shared__ int c_tiles[kCandidates][kHeights + 1];  // tiles of a height, per candidate
+    __shared__ int s_plan[4];                      // ordered experts, tiles, split ones of them
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const bool leader = tid < kWave;
@@ -311,99 +329,88 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
     const bool busy = leader && table;  // prepares the table while the others fill in the row list
     if (!busy) fill_rows();
     if (table) {  // (uniform)
-        const int BM = ts.bm;
         const int P = ts.parts > kMaxParts ? kMaxParts : ts.parts;
         if (leader) {
-            const int shift = __builtin_ctz(BM);
-            for (int v = lane; v < BM; v += kWave) h_count[v] = 0;
-            wave_lds_order();
-            int n_tail_l = 0, tail_rows_l = 0;
-            for (int e0 = 0; e0 < E; e0 += kWave) {
-                const int e = e0 + lane;
-                if (many && e_segs[e0] == e_segs[e0 + kWave < E ? e0 + kWave : E]) {  // no segment holds any of them
-                    if (e < E) e_full[e] = e_tail[e] = 0;
-                    continue;
-                }
-                const int rows = e < E ? list_base(e + 1) - list_base(e) : 0;
-                const int tl = rows & (BM - 1);
-                const unsigned long long same = same_key_lanes(tl, tl > 0, shift);
-                if (e < E) {
-                    e_full[e] = rows >> shift;
-                    e_tail[e] = tl;
-                }
-                if (tl > 0) {  // place among the ragged tiles of its height, lower experts first
-                    const int before = h_count[tl];
-                    e_rank[e] = before + __popcll(same & lt);
-                    if ((same & ~lt) == (1ull << lane)) h_count[tl] = before + __popcll(same);
-                    n_tail_l += 1;
-                    tail_rows_l += tl;
+            auto rows_of = [&](int e) { return e < E ? list_base(e + 1) - list_base(e) : 0; };
+            auto none = [&](int e0) {  // no segment holds any of the 64 experts
+                return many && e_segs[e0] == e_segs[e0 + kWave < E ? e0 + kWave : E];
+            };
+            int most = ts.bm;
+            if (most == 0) {
+                for (int i = lane; i < kCandidates * (kHeights + 1); i += kWave) (&c_tiles[0][0])[i] = 0;
+                wave_lds_order();
+                for (int e0 = 0; e0 < E; e0 += kWave) {
+                    if (none(e0)) continue;
+                    const int rows = rows_of(e0 + lane);
+                    if (rows == 0) continue;
+#pragma unroll
+                    for (int c = 0; c < kCandidates; ++c) {
+                        const int h = kTallest - c * kHeightStep;
+                        atomicAdd(&c_tiles[c][even_height(rows, h) / kHeightStep], (rows + h - 1) / h);
+                    }
                 }
                 wave_lds_order();
+                const int c = lane < kCandidates ? lane : kCandidates - 1;
+                float n = 0.f, work = 0.f, time = 0.f, first = 0.f, last = 0.f;
+#pragma unroll
+                for (int k = kHeights; k > 0; --k) {
+                    const float m = (float)c_tiles[c][k] * (float)ts.n_ntiles;
+                    if (m == 0.f) continue;
+                    last = (float)(kCostFixed + 2 * k);
+                    if (n == 0.f) first = last;
+                    n += m;
+                    work += m * last;
+                    time = fmaxf(time, ceilf(n * (1.f / kGemmGrid)) * last);
+                }
+                time = fmaxf(time, work * (1.f / kGemmGrid) + 0.25f * last) + 0.1f * first;
+                const float rem = n - floorf(n * (1.f / kGemmGrid)) * kGemmGrid;
+                if (P > 1 && rem <= 0.625f * kGemmGrid)
+                    time = fminf(time, work * (1.3f / kGemmGrid) + 0.4f * last + 400.f / ts.kt);
+                // the taller of two that are as good
+                int key = lane < kCandidates ? (int)(fminf(time, 1e7f) * 16.f) * 8 + lane : 0x7fffffff;
+                for (int m = 1; m < 8; m <<= 1) {
+                    const int o = __shfl_xor(key, m, kWave);
+                    key = o < key ? o : key;
+                }
+                most = kTallest - (__builtin_amdgcn_readfirstlane(key) & 7) * kHeightStep;
             }
-            wave_lds_order();
-            const int n_full = wave_scan_experts(e_full, E);
-            const int n_tail = wave_sum_i32(n_tail_l), tail_rows = wave_sum_i32(tail_rows_l);
-            for (int v = lane; v < BM; v += kWave) {
-                const int c = h_count[v];
-                h_same[v] = c;
-                h_rows[v] = c * v;
-            }
-            wave_lds_order();
-            wave_scan_lds(h_count, BM);  // ragged tiles lower than v
-            wave_scan_lds(h_rows, BM);   // and their rows
-            // tiles split at the end of the order: the smallest ragged ones first, then full-height ones
-            long long want = 0;  // half-rows of M-tiles to split
-            if (P > 1) {
-                const long long units = (long long)n_full * 2 * BM + (long long)n_tail * BM + tail_rows;  // half-rows
-                const int round_units = ts.grid * 2 * BM;  // one tile per workgroup, times n_ntiles
-                const long long all = units * ts.n_ntiles;
-                const int rem = (int)((round_units & (round_units - 1)) == 0 ? (all & (round_units - 1)) : all % round_units);
-                if (ts.split_all) want = units;
-                else if (rem > 0 && (long long)rem * 8 <= (long long)round_units * 5) want = (rem + ts.n_ntiles - 1) / ts.n_ntiles;
-            }
-            // ragged tile of expert e: rank in the order (tallest first), and the half-rows of the ragged
-            // tiles behind it; it is split if those do not reach `want` yet
-            int n_cut_l = 0, cut_units_l = 0;
-            for (int e = lane; e < E; e += kWave) {
-                const int tl = e_tail[e];
-                if (tl == 0) continue;
-                const int tie = e_rank[e];
-                const int lower = h_count[tl], same = h_same[tl];
-                const int rank = n_tail - lower - same + tie;
-                e_rank[e] = rank;
-                const long long behind =
-                    (long long)(n_tail - 1 - rank) * BM + h_rows[tl] + (long long)tl * (same - 1 - tie);
-                if (behind < want) {
-                    n_cut_l += 1;
-                    cut_units_l += BM + tl;
+            // tile order: experts with tall tiles, then those with short ones, each group ascending
+            int o = 0;
+            for (int pass = 0; pass < 2; ++pass) {
+                for (int e0 = 0; e0 < E; e0 += kWave) {
+                    if (none(e0)) continue;
+                    const int rows = rows_of(e0 + lane);
+                    const int height = rows > 0 ? even_height(rows, most) : 0;
+                    const bool mine = pass == 0 ? height > kShortTile : rows > 0 && height <= kShortTile;
+                    const unsigned long long them = __ballot(mine);
+                    if (mine) {
+                        const int at = o + __popcll(them & lt);
+                        o_expert[at] = (e0 + lane) | height << 12;
+                        o_base[at] = (rows + height - 1) / height;
+                    }
+                    o += __popcll(them);
                 }
             }
-            int n_rsplit = wave_sum_i32(n_cut_l), n_fsplit = 0;
-            {
-                const long long have = wave_sum_i32(cut_units_l);
-                const long long f = want > have ? (want - have + 2 * BM - 1) >> (shift + 1) : 0;
-                n_fsplit = f < n_full ? (int)f : n_full;
+            if (lane == 0) s_plan[0] = o;
+            wave_lds_order();
+            const int n_tiles = wave_scan_experts(o_base, o);
+            int n_split = 0;
+            if (P > 1) {
+                if (ts.split_all) n_split = n_tiles;
+                else {
+                    const int rem = (int)((long long)n_tiles * ts.n_ntiles % kGemmGrid);
+                    if (rem * 8 <= kGemmGrid * 5) n_split = (rem + ts.n_ntiles - 1) / ts.n_ntiles;
+                }
+                if (n_split > ts.split_capacity) n_split = 0;  // stay in bounds (the host sizes for the rule)
             }
-            if (n_fsplit + n_rsplit > ts.split_capacity) n_fsplit = n_rsplit = 0;  // stay in bounds (the host sizes for the rule)
-            // whole ragged tiles of the experts below e (each sits right behind its expert's full tiles)
-            wave_lds_order();
-            for (int e = lane; e < E; e += kWave)
-                e_whole[e] = (e_tail[e] > 0 && e_rank[e] < n_tail - n_rsplit) ? 1 : 0;
-            wave_lds_order();
-            wave_scan_experts(e_whole, E);
             if (lane == 0) {
-                s_plan[0] = n_full;
-                s_plan[1] = n_tail;
-                s_plan[2] = n_fsplit;
-                s_plan[3] = n_rsplit;
+                s_plan[1] = n_tiles;
+                s_plan[2] = n_split;
             }
         }
         __syncthreads();
-        const int n_full = s_plan[0], n_tail = s_plan[1], n_fsplit = s_plan[2], n_rsplit = s_plan[3];
-        const int n_split = n_fsplit + n_rsplit;
-        const int n_whole_full = n_full - n_fsplit;
-        const int n_whole_tail = n_tail - n_rsplit;
-        const int n_whole = n_whole_full + n_whole_tail;
+        const int n_order = s_plan[0], n_tiles = s_plan[1], n_split = s_plan[2];
+        const int n_whole = n_tiles - n_split;
         const int n_entries = n_whole + n_split * P;
         const bool fits = n_entries <= ts.capacity;
         auto part_range = [&](int part, int& k0, int& k1) {
@@ -411,52 +418,35 @@ __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __res
             k0 = (int)(P == kMaxParts ? a / kMaxParts : a / (unsigned)P);
             k1 = (int)(P == kMaxParts ? b / kMaxParts : b / (unsigned)P);
         };
-        auto emit = [&](int list0, int rows, int expert, int whole_index, int split_index) {
+        for (int t = tid; fits && t < n_tiles; t += blockDim.x) {
+            int lo = 0, hi = n_order - 1;  // the expert whose range of tile numbers holds t
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (o_base[mid] <= t) lo = mid;
+                else hi = mid - 1;
+            }
+            const int expert = o_expert[lo] & 0xfff, height = o_expert[lo] >> 12;
+            const int left = list_base(expert + 1) - list_base(expert) - (t - o_base[lo]) * height;
             MTile mt;
-            mt.list0 = list0;
-            mt.rows = rows;
+            mt.list0 = list_base(expert + 1) - left;
+            mt.rows = left < height ? left : height;
             mt.expert = expert;
             mt.kt0 = mt.kt1 = 0;
             mt.part = -1;
-            // (full tiles from n_whole_full on are split; entries of the experts below: their whole tiles)
-            const int f0 = e_full[expert] < n_whole_full ? e_full[expert] : n_whole_full;
-            const int f1 = e_full[expert + 1] < n_whole_full ? e_full[expert + 1] : n_whole_full;
-            mt.first = f0 + e_whole[expert];
-            mt.n_same = f1 + e_whole[expert + 1] - mt.first;
-            if (split_index < 0) {
-                ts.tiles[whole_index] = mt;
-                return;
+            mt.first = o_base[lo];
+            mt.n_same = (o_base[lo + 1] < n_whole ? o_base[lo + 1] : n_whole) - mt.first;
+            if (t < n_whole) {
+                ts.tiles[t] = mt;
+                continue;
             }
+            const int split_index = t - n_whole;
             for (int part = 0; part < P; ++part) {
                 part_range(part, mt.kt0, mt.kt1);
                 mt.part = split_index * P + part;
                 ts.tiles[n_whole + part * n_split + split_index] = mt;
             }
-            ts.splits[split_index].list0 = list0;
-            ts.splits[split_index].rows = rows;
-        };
-        if (fits) {
-            // full-height tiles: tile t belongs to the expert whose range of tile numbers holds it
-            for (int t = tid; t < n_full; t += blockDim.x) {
-                int lo = 0, hi = E - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (e_full[mid] <= t) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int list0 = list_base(lo) + (t - e_full[lo]) * BM;
-                if (t < n_whole_full) emit(list0, BM, lo, t + e_whole[lo], -1);
-                else emit(list0, BM, lo, 0, t - n_whole_full);
-            }
-            // ragged tiles, tallest first (ties: lower expert first); the last n_rsplit of them are split
-            for (int e = tid; e < E; e += blockDim.x) {
-                const int tl = e_tail[e];
-                if (tl == 0) continue;
-                const int rank = e_rank[e];
-                const int list0 = list_base(e) + (e_full[e + 1] - e_full[e]) * BM;
-                if (rank >= n_whole_tail) emit(list0, tl, e, 0, n_fsplit + rank - n_whole_tail);
-                else emit(list0, tl, e, (e_full[e + 1] < n_whole_full ? e_full[e + 1] : n_whole_full) + e_whole[e], -1);
-            }
+            ts.splits[split_index].list0 = mt.list0;
+            ts.splits[split_index].rows = mt.rows;
         }
         if (tid == 0) {
             ts.counts[kCntEntries] = fits ? n_entries : 0;
@@ -1087,7 +1077,7 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
         // 32-row tiles until 64-row ones would go twice round the CUs for the wider product
         const int64_t tiles64 = (ceil_div64(A, 64) + E) * ceil_div(ffn > d ? ffn : d, 64);
         const int bm = tiles64 < 2 * kGemmGrid ? 32 : 64;
-        TableSpec t1{ws.tiles1, ws.counts, nullptr, bm, ws.capacity, 0, 0, 1, 1, 0, 0};
+        TableSpec t1{ws.tiles1, ws.counts, nullptr, bm, ws.capacity, 0, 0, 1, 0, 0};
         TableSpec none{};
         hipLaunchKernelGGL(build_tables_kernel, dim3(build_grid), dim3(1024), 0, st, seg_offsets, slot_expert,
                            seg_begin, seg_end, E, t1, none, ws.rowlist, (int32_t*)nullptr, 0);
@@ -1114,60 +1104,25 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
                   w2, nullptr, (float*)y_perm, d, d, ffn, rm2, 0);
     }
 
-    // Batches of a few rows per expert stream their weights (stream_form); for the rest, tile shape
-    // per product: 256x256 unless the product has too few such tiles to keep 256 workgroups
-    // busy for two rounds, or the segments are slivers, then 128x256 with three stages.  The tile
-    // count is only known on the device; the host estimates it from the row count.  (32x256 is
-    // left to the option: ahead of 128x256 only where streaming is further ahead, and with many replicas or
-    // a few experts that hold everything far behind: 64 experts of 2048 x 1408 in 160 slots, 2500 rows on 64 / 16 of
-    // them, whole FFN 258 / 165 us with it against 233 / 110.)
-    auto pick = [&](int forced, int n_cols) {
-        if (forced >= 0) return forced;
-        if (A < (int64_t)64 * nrange) return 1;
-        // fewer than 256 rows per expert on average: most 256-row tiles would be ragged (128
-        // experts, 16384 rows: 623 against 683 us for the first product; 64 experts, 12288 rows:
-        // 226 against 258 us; at 256 rows per expert the shapes are within 4 % of each other, at
-        // 384 equal)
-        const int64_t experts = E < nrange ? E : nrange;
-        if (A < 256 * experts) return 1;
-        // few tiles: the 128-row shape fills the chip better, unless the experts are large
-        // enough for whole 256-row tiles and those still make more than one round (8 experts,
-        // 4096 rows, second product: 476 against 521 us)
-        const int64_t est_tiles = (A / 256 + (nrange + 1) / 2) * ceil_div(n_cols, 256);
-        if (A >= 512 * experts) return est_tiles > kGemmGrid ? 0 : 1;
-        return est_tiles > 2 * kGemmGrid ? 0 : 1;
-    };
+    // Batches of a few rows per expert stream their weights (stream_form); for the rest the table
+    // builder chooses the height of the tiles.
     const int fp = padded_ffn(ffn, dtype);  // hidden width the kernels see
     const int n1 = relu ? 1 : 2;            // matrices in the first product
-    const int v1 = pick(g_opt_tile1.load(), n1 * fp);
-    const int v2 = pick(g_opt_tile2.load(), d);
-    const int s1 = stream_form(g_opt_tile1.load(), A, E, n1 * fp, d / kPackK);
-    const int s2 = g_opt_split.load() == 1 ? 0 : stream_form(g_opt_tile2.load(), A, E, d, fp / kPackK);
-    // N-tiles walked side by side under one run of M-tiles.  A run of 32 tiles is 32/g M-tiles
-    // under g weight panels; every group streams the activation rows again.  Up to 12 N-tiles
-    // are walked together, so the rows are read once.  Wider outputs are walked in groups: of 4
-    // while the rows stay in the memory-side cache (8 M-tiles share each weight panel), else of
-    // 6, the near-square patch that fetches the fewest panels per run; 13 to 16 N-tiles over
-    // more than 1 GiB of rows are walked in two groups of 8.  Measured: Mixtral-shaped gate/up
-    // at 64 MiB of rows, 4 is 3-4 % faster than 8; at 512 MiB, 6 is 1 % faster than 8 and 4 is
-    // 1.5 % slower; down products of 16 N-tiles, 6 is 2-8 % faster than 16 below 1 GiB of rows,
-    // 8 is 2 % faster than 6 at 1.9 GiB.
-    const int group_opt = g_opt_group_n.load();
-    auto group_for = [&](int n_cols, int64_t a_bytes) {
-        if (group_opt > 0) return group_opt;
-        const int n_ntiles = ceil_div(n_cols, kPackN);
-        if (n_ntiles <= 12) return n_ntiles;
-        if (n_ntiles <= 16) return a_bytes <= ((int64_t)1 << 30) ? 6 : 8;
-        return a_bytes <= ((int64_t)96 << 20) ? 4 : 6;
-    };
+    const int v1 = g_opt_tile1.load(), v2 = g_opt_tile2.load();
+    const int s1 = stream_form(v1, A, E, n1 * fp, d / kPackK);
+    const int s2 = g_opt_split.load() == 1 ? 0 : stream_form(v2, A, E, d, fp / kPackK);
+    // N-tiles walked side by side over the M-tiles of an expert: see the tile order in ffn_tiles.h
+    const int group_n = g_opt_group_n.load() > 0 ? g_opt_group_n.load() : kTileGroup;
     // one launch builds the row list and both tables; the second product shares the first one's
     // table when it has the same tile height and splits nothing
-    const int bm1 = s1 ? kStreamBM : kShapeRows[v1], bm2 = s2 ? kStreamBM : kShapeRows[v2];
+    const int bm1 = s1 ? kStreamBM : v1 >= 0 ? kShapeRows[v1] : 0;  // 0: the table builder chooses
+    const int bm2 = s2 ? kStreamBM : v2 >= 0 ? kShapeRows[v2] : 0;
     const bool split = ws.split_capacity > 0 && !s2;
-    const bool own2 = bm2 != bm1 || split;
-    TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / kPackK, 0, 1, kGemmGrid, 0, 0};
+    const bool own2 = bm2 != bm1 || bm2 == 0 || split;
+    TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / kPackK, 0,
+                 ceil_div(n1 * fp, kPackN), 0, 0};
     TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / kPackK,
-                 split ? ws.parts : 0, ceil_div(d, kPackN), kGemmGrid, ws.split_all, ws.split_capacity};
+                 split ? ws.parts : 0, ceil_div(d, kPackN), ws.split_all, ws.split_capacity};
     hipLaunchKernelGGL(build_tables_kernel, dim3(build_grid), dim3(1024), 0, st, seg_offsets, slot_expert, seg_begin,
                        seg_end, E, t1, t2, ws.rowlist, ws.queues, 16);
     if ((rc = check_launch()) != MOE_OK) return rc;
@@ -1184,7 +1139,7 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     } else {
         const auto go = relu ? launch_tiles<kEpiRelu> : launch_tiles<kEpiSwiglu>;
         rc = go((const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, ws.queues,
-                n1 * fp, d, group_for(n1 * fp, A * (int64_t)d * 2), rm1, nullptr, st);
+                n1 * fp, d, group_n, rm1, nullptr, st);
     }
     if (timed) (void)hipEventRecord(g_time_events[1], st);
     if (rc != MOE_OK) return rc;
@@ -1194,7 +1149,7 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
                                      tiles2, count2, d, fp, rm2, st);
     else
         rc = launch_tiles<kEpiNone>((const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d, tiles2, count2,
-                                    ws.queues + 8, d, fp, group_for(d, A * (int64_t)fp * 2), rm2, ws.partials, st);
+                                    ws.queues + 8, d, fp, group_n, rm2, ws.partials, st);
     if (rc == MOE_OK && split) {
         hipLaunchKernelGGL(add_partials_kernel, dim3(ws.split_capacity < 64 ? ws.split_capacity : 64, 32), dim3(256),
                            0, st, ws.partials, ws.splits, count2, ws.parts, (bf16_t*)y_perm, d, d, rm2);

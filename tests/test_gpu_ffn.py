@@ -496,6 +496,29 @@ def test_ffn_tile_heights_and_depths(d, ffn, relu, ffn_options):
     assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * np.max(np.abs(ref)))
 
 
+@pytest.mark.parametrize("split", [-1, 0, 1])
+@pytest.mark.parametrize("sizes", [
+    [2049, 0, 2048, 1793, 257, 65],   # more and not more tiles than heights at 256 rows, a short last tile
+    [1, 1, 1, 1, 1, 1],               # only short tiles
+    [900, 899, 33, 64, 0, 129],       # tall and short ones, an expert without rows between
+    [0, 0, 0, 0, 0, 3000]])           # one expert holds everything
+def test_ffn_heights_chosen_from_the_batch(sizes, split, ffn_options):
+    """Tables whose tile heights come from the rows per expert, every row present once: against the
+    oracle, whole and split along K."""
+    ffn_options(split=split)
+    B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, 0)
+    try:
+        cfg = wl.MoEConfig("c", T=1, d=128, ffn=256, E=6, k=1, G=3, S=3, dtype="bf16", mode=0, seed=49)
+        slot_expert = [5, 1, -1, 0, 4, 5, 3, 2, 0]     # experts 0 and 5 in two slots each
+        rows = dict(enumerate(sizes))
+        seg = [rows[5] // 2, rows[1], 0, rows[0] - rows[0] // 3, rows[4], rows[5] - rows[5] // 2, rows[3], rows[2],
+               rows[0] // 3]
+        got, ref, _ = run_ffn_case(cfg, seg, slot_expert, seed=50)
+        assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * np.max(np.abs(ref)))
+    finally:
+        B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, -1)
+
+
 @pytest.mark.parametrize("form", [1, 2])
 @pytest.mark.parametrize("d,ffn,relu", [(64, 64, False),      # one k-tile: one half / three parts of K are empty
                                         (192, 320, False),    # odd numbers of k-tiles, half a unit at the edge of N
