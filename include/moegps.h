@@ -241,6 +241,37 @@ int moe_grouped_ffn_gather(const void* x, int dtype, int T, int k, const int32_t
                            void* y_perm, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * One step of the layer: moe_route_topk, moe_histogram, moe_plan_duplicates, moe_permute, the grouped
+ * FFN and moe_combine of one batch, whose small launches are shared where the shape allows (the results are
+ * those of the single calls).  Meaning, sizes and requirements of the fields are those of the
+ * arguments of these calls.
+ *   x_perm NULL: the FFN gathers the token rows (moe_grouped_ffn_gather), and with gate_in_ffn
+ *   it applies the gate weights (moe_grouped_ffn_fused); SwiGLU only.
+ *   hist_pred is read in mode 1; pred_idx is read and hist_plan (its histogram) written in mode 2.
+ * T = 0 is a no-op.  Arguments are checked before the first launch, apart from those limits that only
+ * the FFN has: on one of its errors, and on MOE_ERR_HIP, earlier steps have been enqueued.
+ */
+typedef struct moe_layer_step_args {
+    int32_t mode, dtype, T, d, ffn, E, k, G, S, c_max, relu, gate_in_ffn;
+    const float* logits;
+    const void* x;
+    const int32_t *hist_pred, *pred_idx;
+    const void* packed;
+    int32_t* topk_idx;
+    float* topk_w;
+    int32_t *hist, *hist_plan, *slot_expert, *slot_quota, *rank_load_pred, *n_iters;
+    int32_t *seg_offsets, *row_of_assign, *assign_of_row;
+    void* x_perm;
+    int32_t* rank_load;
+    void *y_perm, *out;
+    void* workspace_perm;
+    size_t workspace_perm_bytes;
+    void* workspace_ffn;
+    size_t workspace_ffn_bytes;
+} moe_layer_step_args;
+int moe_layer_step(const moe_layer_step_args* args, void* stream);
+
+/*
  * Overrides of the automatic choices inside the grouped FFN, for tests and experiments
  * (process-wide; set them before sizing a workspace, the split option changes its size):
  *   MOE_FFN_OPT_TILE1 / TILE2  height of the tiles of the first / second product: -1 automatic,

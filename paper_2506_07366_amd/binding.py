@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional
 
 import torch
@@ -28,7 +29,7 @@ EXPORTS = [
     "moe_pack_weights", "moe_grouped_ffn_workspace_bytes", "moe_grouped_ffn", "moe_grouped_ffn_gather",
     "moe_grouped_ffn_fused", "moe_grouped_ffn_set_option", "moe_grouped_ffn_time_next_call",
     "moe_combine", "moe_comm_matrix", "moe_predictor_update", "moe_predictor_predict",
-    "moe_packed_weights_relu_bytes", "moe_pack_weights_relu", "moe_grouped_ffn_relu",
+    "moe_packed_weights_relu_bytes", "moe_pack_weights_relu", "moe_grouped_ffn_relu", "moe_layer_step",
 ]
 
 
@@ -103,6 +104,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.moe_predictor_predict.argtypes = [vp, c_int, c_i64, vp, vp]
     lib.moe_comm_matrix.restype = c_int
     lib.moe_comm_matrix.argtypes = [c_int, c_int, c_int, c_int, c_int, vp, vp, vp, vp, vp, vp, vp]
+    lib.moe_layer_step.restype = c_int
+    lib.moe_layer_step.argtypes = [ctypes.c_char_p, vp]
     if path is None:
         _lib = lib
     return lib
@@ -247,6 +250,38 @@ def moe_permute(mode: int, x: Optional[torch.Tensor], topk_idx: torch.Tensor, pr
                            _ptr(out["row_of_assign"]), _ptr(out["assign_of_row"]), _ptr(out["x_perm"]),
                            _ptr(out["rank_load"]), _ptr(workspace), workspace.numel(), _stream()), "moe_permute")
     return out
+
+
+# moe_layer_step_args: twelve int32, then pointers and sizes of eight bytes
+_STEP_ARGS = struct.Struct("@12i24Q")
+
+
+def moe_layer_step(mode, dtype, T, d, ffn, E, k, G, S, c_max, relu, gate_in_ffn, *, logits, x, hist_pred, pred_idx,
+                   packed, topk_idx, topk_w, hist, hist_plan, slot_expert, slot_quota, rank_load_pred, n_iters,
+                   seg_offsets, row_of_assign, assign_of_row, x_perm, rank_load, y_perm, out, workspace_perm,
+                   workspace_ffn) -> None:
+    """One step of the layer in one call; tensors as the single calls take them (``x_perm`` None: the FFN
+    gathers the token rows)."""
+    for t in (hist_pred, pred_idx):
+        if t is not None:
+            _need(t, torch.int32, "hist_pred / pred_idx")
+    for t in (topk_idx, hist, hist_plan, slot_expert, slot_quota, rank_load_pred, n_iters, seg_offsets, row_of_assign,
+              assign_of_row, rank_load):
+        _need(t, torch.int32, "an index tensor")
+    _need(logits, torch.float32, "logits")
+    _need(topk_w, torch.float32, "topk_w")
+    for t in (x, y_perm, out):
+        _need(t, x.dtype, "x, y_perm and out")
+    if dtype_code(x) != dtype:
+        raise MoeGpsError(f"x must have the layer's data type, got {x.dtype}")
+    p = _ptr
+    args = _STEP_ARGS.pack(
+        mode, dtype, T, d, ffn, E, k, G, S, c_max, relu, gate_in_ffn, p(logits), p(x), p(hist_pred) or 0,
+        p(pred_idx) or 0, p(packed), p(topk_idx), p(topk_w), p(hist), p(hist_plan), p(slot_expert), p(slot_quota),
+        p(rank_load_pred), p(n_iters), p(seg_offsets), p(row_of_assign), p(assign_of_row), p(x_perm) or 0,
+        p(rank_load), p(y_perm), p(out), p(workspace_perm), workspace_perm.numel(), p(workspace_ffn),
+        workspace_ffn.numel())
+    _check(load_library().moe_layer_step(args, _stream()), "moe_layer_step")
 
 
 def moe_packed_weights_bytes(E: int, d: int, ffn: int, dtype: int) -> int:

@@ -1,0 +1,177 @@
+// A whole step of the layer in one call: route, histogram, duplication plan, permutation, grouped FFN and
+// combine of one batch, with launches shared between the small ones.
+//
+// The index steps of a decode or prompt batch are a chain of launches of 2 to 20 us of work, 4.7 us apart at
+// least, and each is a call from the host.  Two things shorten it where the shape allows:
+//   - under a prediction the plan does not need the routing: one workgroup makes it (under Token-to-Expert
+//     after counting the predicted ids) while the others of the same launch route the tokens;
+//   - where the permutation is one workgroup's work it also writes the histogram, and without a prediction
+//     the plan, which then is the home placement.
+// Anything else goes through the calls of the single steps; the results are the same integers either way.
+// Whole steps, us, six calls (seven with predicted ids) -> one: 256 tokens of the small fp32 layer 45.0 -> 41.0 (no
+// longer bound by the host), one token on 128 experts 80.2 -> 76.7, 16 tokens of the Mixtral shape as a graph
+// 285 -> 279, 777 tokens with Token-to-Expert 438 -> 427.
+#include "permute.h"
+#include "plan_regs.h"
+#include "route_tokens.h"
+
+namespace moegps {
+
+constexpr int kPlanMaxExperts = 256;   // the planner's table of hosts takes 64 bytes of LDS per expert, and
+                                       // every workgroup of the launch has it
+constexpr int kPlanMaxSlots = 10;      // slots per rank the launch is compiled for, up to 32 ranks
+constexpr int kPlanCountMax = 16384;   // predicted ids one workgroup counts ahead of its plan
+
+struct PlanJob {
+    int mode, E, G, S, c_max;
+    const int32_t* hist_pred;  // null: counted from pred_idx
+    const int32_t* pred_idx;
+    int n_pred;
+    int32_t *hist_plan, *slot_expert, *slot_quota, *rank_load_pred, *n_iters;
+};
+
+// Workgroup 0 plans, the others route.  The plan is the longer of the two up to some 30000 tokens: us of
+// the launch against those of its parts, 128 experts, 128 tokens 17.1 (17.8 and 4.9), 777 tokens with
+// Token-to-Expert 29.2 (26.6, 5.1 and 4.9 for the count); 64 experts, 2048 tokens 23.6 (22.7 and 5.2).
+template <int S>
+__global__ __launch_bounds__(kRouteThreads) void route_plan_kernel(PlanJob p, const float* __restrict__ logits, int T,
+                                                                    int k, int32_t* __restrict__ topk_idx,
+                                                                    float* __restrict__ topk_w) {
+    extern __shared__ __align__(16) unsigned char host_of[];
+    __shared__ int bins[kPlanMaxExperts];
+    const int E = p.E;
+    if (blockIdx.x > 0) {
+        const int block = blockIdx.x - 1;
+        if (E <= 2) route_tokens<2, 1>(block, logits, T, E, k, topk_idx, topk_w);
+        else if (E <= 4) route_tokens<4, 1>(block, logits, T, E, k, topk_idx, topk_w);
+        else if (E <= 8) route_tokens<8, 1>(block, logits, T, E, k, topk_idx, topk_w);
+        else if (E <= 16) route_tokens<16, 1>(block, logits, T, E, k, topk_idx, topk_w);
+        else if (E <= 32) route_tokens<16, 2>(block, logits, T, E, k, topk_idx, topk_w);
+        else if (E <= 64) route_tokens<16, 4>(block, logits, T, E, k, topk_idx, topk_w);
+        else if (E <= 128) route_tokens<16, 8>(block, logits, T, E, k, topk_idx, topk_w);
+        else route_tokens<16, 16>(block, logits, T, E, k, topk_idx, topk_w);
+        return;
+    }
+    const int32_t* hist = p.hist_pred;
+    if (!hist) {
+        static_assert(kPlanMaxExperts <= kRouteThreads, "a thread per expert");
+        const int tid = threadIdx.x;
+        bins[tid] = 0;
+        __syncthreads();
+        constexpr int U = 8;  // ids under way per thread
+        for (int i0 = tid; i0 < p.n_pred; i0 += kRouteThreads * U) {
+            int e[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kRouteThreads;
+                e[u] = i < p.n_pred ? p.pred_idx[i] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (e[u] >= 0 && e[u] < E) atomicAdd(&bins[e[u]], 1);
+        }
+        __syncthreads();
+        if (tid < E) p.hist_plan[tid] = bins[tid];
+        hist = bins;
+    }
+    if (threadIdx.x < kWave)
+        plan_regs<S, 2>(p.mode, hist, E, p.G, S, p.c_max, host_of, p.slot_expert, p.slot_quota, p.rank_load_pred, p.n_iters);
+}
+
+static int route_and_plan(const PlanJob& p, const float* logits, int T, int k, int32_t* topk_idx, float* topk_w,
+                          hipStream_t st) {
+    const int lanes = p.E <= 2 ? 2 : p.E <= 4 ? 4 : p.E <= 8 ? 8 : 16;  // per token, as moe_route_topk has them
+    const int grid = 1 + ceil_div(T, kRouteThreads / lanes);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kRouteThreads), (size_t)p.E * kWave, st, p, logits, T, k, topk_idx, topk_w);
+        return check_launch();
+    };
+    switch (p.S) {
+        case 1: return go(route_plan_kernel<1>);
+        case 2: return go(route_plan_kernel<2>);
+        case 3: return go(route_plan_kernel<3>);
+        case 4: return go(route_plan_kernel<4>);
+        case 5: return go(route_plan_kernel<5>);
+        case 6: return go(route_plan_kernel<6>);
+        case 7: return go(route_plan_kernel<7>);
+        case 8: return go(route_plan_kernel<8>);
+        case 9: return go(route_plan_kernel<9>);
+        default: return go(route_plan_kernel<kPlanMaxSlots>);
+    }
+}
+
+}  // namespace moegps
+
+extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
+    using namespace moegps;
+    if (!a) return MOE_ERR_INVALID_ARG;
+    const int mode = a->mode, T = a->T, E = a->E, k = a->k, G = a->G, S = a->S;
+    // what the calls of the single steps would refuse, before the first launch
+    if (mode < MOE_MODE_NONE || mode > MOE_MODE_TOKEN) return MOE_ERR_INVALID_ARG;
+    if (a->dtype != MOE_DTYPE_F32 && a->dtype != MOE_DTYPE_BF16) return MOE_ERR_INVALID_ARG;
+    if (T < 0 || a->d < 1 || a->ffn < 1 || E < 1 || k < 1 || k > E || G < 1 || S < 1 || a->c_max < 1)
+        return MOE_ERR_INVALID_ARG;
+    if (E > MOE_MAX_EXPERTS || k > MOE_MAX_TOPK || G > MOE_MAX_RANKS || S > MOE_MAX_SLOTS || G * S > MOE_MAX_SEGMENTS)
+        return MOE_ERR_UNSUPPORTED;
+    if (ceil_div(E, G) > S) return MOE_ERR_INVALID_ARG;
+    if ((int64_t)T * k >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;
+    if (((size_t)a->d * dtype_size(a->dtype)) % 16 != 0) return MOE_ERR_UNSUPPORTED;
+    if (a->relu && !a->x_perm) return MOE_ERR_UNSUPPORTED;  // the row gather is built for the SwiGLU form only
+    if (T == 0) return MOE_OK;
+    if (!a->logits || !a->x || !a->packed || !a->topk_idx || !a->topk_w || !a->hist || !a->slot_expert ||
+        !a->slot_quota || !a->rank_load_pred || !a->n_iters || !a->seg_offsets || !a->row_of_assign ||
+        !a->assign_of_row || !a->rank_load || !a->y_perm || !a->out || !a->workspace_perm || !a->workspace_ffn)
+        return MOE_ERR_INVALID_ARG;
+    if (mode == MOE_MODE_DISTRIBUTION && !a->hist_pred) return MOE_ERR_INVALID_ARG;
+    if (mode == MOE_MODE_TOKEN && (!a->pred_idx || !a->hist_plan)) return MOE_ERR_INVALID_ARG;
+    const int64_t A = (int64_t)T * k;
+    if (a->workspace_perm_bytes < moe_permute_workspace_bytes(T, E, k, G, S)) return MOE_ERR_WORKSPACE_TOO_SMALL;
+    if (a->workspace_ffn_bytes < moe_grouped_ffn_workspace_bytes(A, a->d, a->ffn, G * S, a->dtype))
+        return MOE_ERR_WORKSPACE_TOO_SMALL;
+    hipStream_t st = (hipStream_t)stream;
+    int rc;
+    const int32_t* hp = mode == MOE_MODE_TOKEN ? a->hist_plan : mode == MOE_MODE_DISTRIBUTION ? a->hist_pred : a->hist;
+    const bool small = permute_in_one_workgroup(mode, A, E, G * S);
+    const bool together = mode != MOE_MODE_NONE && E <= kPlanMaxExperts && S <= kPlanMaxSlots && G <= 32;
+    auto plan = [&] {
+        return moe_plan_duplicates(mode, hp, E, G, S, a->c_max, a->slot_expert, a->slot_quota, a->rank_load_pred,
+                                   a->n_iters, stream);
+    };
+    if (together) {
+        const bool count = mode == MOE_MODE_TOKEN && A <= kPlanCountMax;
+        if (mode == MOE_MODE_TOKEN && !count && (rc = moe_histogram(a->pred_idx, A, E, a->hist_plan, stream)) != MOE_OK)
+            return rc;
+        const PlanJob p{mode, E, G, S, a->c_max, count ? nullptr : hp, a->pred_idx, (int)A, a->hist_plan,
+                        a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters};
+        if ((rc = route_and_plan(p, a->logits, T, k, a->topk_idx, a->topk_w, st)) != MOE_OK) return rc;
+    } else {
+        if ((rc = moe_route_topk(a->logits, T, E, k, a->topk_idx, a->topk_w, stream)) != MOE_OK) return rc;
+        if (mode == MOE_MODE_TOKEN && (rc = moe_histogram(a->pred_idx, A, E, a->hist_plan, stream)) != MOE_OK) return rc;
+        if (mode != MOE_MODE_NONE && (rc = plan()) != MOE_OK) return rc;
+    }
+    if (small) {
+        const HomePlan home{a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters};
+        rc = permute_and_count(mode, T, k, E, G, S, a->topk_idx, a->pred_idx, hp, a->slot_expert, a->slot_quota,
+                               a->seg_offsets, a->row_of_assign, a->assign_of_row, a->rank_load, a->hist, home, st);
+        if (rc == MOE_OK && a->x_perm) rc = scatter_rows(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm, st);
+    } else {
+        if ((rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
+        if (mode == MOE_MODE_NONE && (rc = plan()) != MOE_OK) return rc;
+        rc = moe_permute(mode, a->x_perm ? a->x : nullptr, a->dtype, T, a->d, E, k, G, S, a->topk_idx,
+                         mode == MOE_MODE_TOKEN ? a->pred_idx : nullptr, a->hist, hp, a->slot_expert, a->slot_quota,
+                         a->seg_offsets, a->row_of_assign, a->assign_of_row, a->x_perm, a->rank_load, a->workspace_perm,
+                         a->workspace_perm_bytes, stream);
+    }
+    if (rc != MOE_OK) return rc;
+    const float* gate = a->x_perm ? nullptr : a->gate_in_ffn ? a->topk_w : nullptr;
+    if (a->x_perm)
+        rc = (a->relu ? moe_grouped_ffn_relu : moe_grouped_ffn)(
+            a->x_perm, a->dtype, A, a->d, a->ffn, E, a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed,
+            a->y_perm, a->workspace_ffn, a->workspace_ffn_bytes, stream);
+    else
+        rc = moe_grouped_ffn_fused(a->x, a->dtype, T, k, a->assign_of_row, gate, a->d, a->ffn, E, a->seg_offsets,
+                                   a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm, a->workspace_ffn,
+                                   a->workspace_ffn_bytes, stream);
+    if (rc != MOE_OK) return rc;
+    return moe_combine(a->y_perm, a->dtype, T, a->d, k, a->row_of_assign, gate ? nullptr : a->topk_w, a->out, stream);
+}

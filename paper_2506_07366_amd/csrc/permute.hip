@@ -29,7 +29,7 @@
 //
 // A batch of a few thousand assignments (decode, short prompts) takes the index steps in one
 // workgroup and one launch: the same ranks and scans, the chunk being the whole batch (one_workgroup_limit).
-#include "common.h"
+#include "permute.h"
 #include "block_scan.h"
 #include <initializer_list>
 #include <mutex>
@@ -578,13 +578,16 @@ __device__ __forceinline__ void small_slot_tables(int E, int nseg, const SmallTa
     }
 }
 
-template <int SR>  // rounds of 64 elements per wavefront, at most
+// SR: rounds of 64 elements per wavefront, at most.  COUNTS: the histogram of topk_idx is an output (hist_out)
+// and not an input, and in mode 0 the home plan is too (`home`); both cost next to nothing here, where the
+// ids pass by anyway, and a launch of their own (4.7 us, 9.4 in mode 0) as calls.
+template <int SR, bool COUNTS>
 __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     int mode, int T, int k, int E, int G, int S, const int32_t* __restrict__ topk_idx,
     const int32_t* __restrict__ pred_idx, const int32_t* __restrict__ hist_true, const int32_t* __restrict__ hist_pred,
     const int32_t* __restrict__ slot_expert, const int32_t* __restrict__ slot_quota,
     int32_t* __restrict__ seg_offsets, int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row,
-    int32_t* __restrict__ rank_load) {
+    int32_t* __restrict__ rank_load, int32_t* __restrict__ hist_out, HomePlan home) {
     // one buffer, three lives: wavefront counters of the first rank; rank and key by position
     // (token-to-expert mode looks up those of the token's predicted ids); counters of the second
     __shared__ int buf[kSmallWaves * kSmallKeys];
@@ -626,6 +629,9 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
         }
     }
     for (int e = tid; e < E; e += kSmallThreads) e_home[e] = home_slot_of(e, H, S);
+    const bool count = COUNTS && mode != MOE_MODE_DISTRIBUTION;  // (there the ranks' counters are the histogram)
+    if (count)
+        for (int e = tid; e < E; e += kSmallThreads) e_true[e] = 0;
     if (mode != MOE_MODE_NONE) {
         for (int i = tid; i < kSmallKeys; i += kSmallThreads) {
             s_e[i] = i < nseg ? slot_expert[i] : -1;
@@ -634,7 +640,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
             e_cnt[i] = 0;
             e_cum[i] = 0ll;
             if (mode == MOE_MODE_DISTRIBUTION && i < E) {
-                e_true[i] = hist_true[i];
+                if (!COUNTS) e_true[i] = hist_true[i];
                 e_hat[i] = hist_pred[i];
             }
         }
@@ -643,7 +649,8 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
             const SmallTables t{s_e, s_q, s_cum, s_next, e_first, e_cnt, e_last, e_cum};
             small_slot_tables(E, nseg, t);
         }
-        chunk_stable_rank<kSmallWaves, SR>(key, valid, E, buf, rank, nullptr, rounds);
+        chunk_stable_rank<kSmallWaves, SR>(key, valid, E, buf, rank,
+                                           COUNTS && mode == MOE_MODE_DISTRIBUTION ? e_true : nullptr, rounds);
         __syncthreads();  // the counters are dead, the buffer becomes rank and key by position
 #pragma unroll
         for (int r = 0; r < SR; ++r) {
@@ -663,6 +670,10 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
         if (mode == MOE_MODE_DISTRIBUTION && tid < E && e_hat[tid] <= 0) e_first[tid] = -1;
     }
     __syncthreads();
+    if (count)
+#pragma unroll
+        for (int r = 0; r < SR; ++r)
+            if (valid[r]) atomicAdd(&e_true[expert[r]], 1);
 
     // segment of every assignment: its place i in the plan's order for its expert (-1: none),
     // then a walk over the expert's slots, at most G of them, to the one whose range holds i;
@@ -716,6 +727,19 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     block_exclusive_scan_2048(tot, nseg, wave_sum);
     for (int s = tid; s <= nseg; s += kSmallThreads) seg_offsets[s] = tot[s];
     for (int g = tid; g < G; g += kSmallThreads) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
+    if (COUNTS) {  // (barriers lie between the counting and here)
+        for (int e = tid; e < E; e += kSmallThreads) hist_out[e] = e_true[e];
+        if (mode == MOE_MODE_NONE) {
+            for (int s = tid; s < nseg; s += kSmallThreads) {
+                const int j = s % S, e = s / S * H + j;
+                const bool held = j < H && e < E;
+                home.slot_expert[s] = held ? e : -1;
+                home.slot_quota[s] = held ? e_true[e] : 0;
+            }
+            for (int g = tid; g < G; g += kSmallThreads) home.rank_load_pred[g] = tot[(g + 1) * S] - tot[g * S];
+            if (tid == 0) home.n_iters[0] = 0;
+        }
+    }
 #pragma unroll
     for (int r = 0; r < SR; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
@@ -772,6 +796,47 @@ extern "C" size_t moe_permute_workspace_bytes(int T, int E, int k, int G, int S)
 }
 
 namespace moegps {
+template <bool COUNTS>
+static void launch_small(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
+                         const int32_t* hist_true, const int32_t* hist_pred, const int32_t* slot_expert,
+                         const int32_t* slot_quota, int32_t* seg_offsets, int32_t* row_of_assign,
+                         int32_t* assign_of_row, int32_t* rank_load, int32_t* hist_out, const HomePlan& home,
+                         hipStream_t st) {
+    const int64_t A = (int64_t)T * k;
+    hipLaunchKernelGGL((A <= 2 * kSmallThreads ? perm_small_kernel<2, COUNTS>
+                        : A <= 3 * kSmallThreads ? perm_small_kernel<3, COUNTS>
+                        : A <= 4 * kSmallThreads ? perm_small_kernel<4, COUNTS> : perm_small_kernel<kSmallMaxRounds, COUNTS>),
+                       dim3(1), dim3(kSmallThreads), 0, st, mode, T, k, E, G, S, topk_idx, pred_idx, hist_true, hist_pred,
+                       slot_expert, slot_quota, seg_offsets, row_of_assign, assign_of_row, rank_load, hist_out, home);
+}
+
+bool permute_in_one_workgroup(int mode, int64_t A, int E, int nseg) { return A <= one_workgroup_limit(mode, E, nseg); }
+
+int permute_and_count(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
+                      const int32_t* hist_pred, const int32_t* slot_expert, const int32_t* slot_quota,
+                      int32_t* seg_offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* rank_load,
+                      int32_t* hist_out, const HomePlan& home, hipStream_t st) {
+    launch_small<true>(mode, T, k, E, G, S, topk_idx, pred_idx, nullptr, hist_pred, slot_expert, slot_quota, seg_offsets,
+                       row_of_assign, assign_of_row, rank_load, hist_out, home, st);
+    return check_launch();
+}
+
+int scatter_rows(const void* x, int dtype, int T, int d, int k, const int32_t* row_of_assign, void* x_perm,
+                 hipStream_t st) {
+    const int chunks = (int)((size_t)d * dtype_size(dtype) / 16);
+    const int unroll = chunks >= 4 * kWave ? 4 : 1;
+    // a small batch: split every row over several wavefronts until there are a few thousand
+    int slices = 1;
+    while (slices < 16 && (int64_t)T * slices < 4096 && chunks >= 2 * slices * kWave * unroll) slices *= 2;
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64((int64_t)T * slices, 4)), dim3(256), 0, st, (const uint4*)x,
+                           (uint4*)x_perm, row_of_assign, T, k, chunks, slices);
+    };
+    if (unroll == 4) launch(perm_scatter_rows_kernel<4>);
+    else launch(perm_scatter_rows_kernel<1>);
+    return check_launch();
+}
+
 static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E, int k, int G, int S,
                         const int32_t* topk_idx, const int32_t* pred_idx, const int32_t* hist_true,
                         const int32_t* hist_pred, const int32_t* slot_expert, const int32_t* slot_quota,
@@ -799,11 +864,8 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
     int rc;
     const int64_t A = (int64_t)T * k;
     if (A <= one_workgroup_limit(mode, E, G * S)) {
-        hipLaunchKernelGGL(A <= 2 * kSmallThreads ? perm_small_kernel<2>
-                           : A <= 3 * kSmallThreads ? perm_small_kernel<3>
-                           : A <= 4 * kSmallThreads ? perm_small_kernel<4> : perm_small_kernel<kSmallMaxRounds>,
-                           dim3(1), dim3(kSmallThreads), 0, st, mode, T, k, E, G, S, topk_idx, pred_idx, hist_true,
-                           hist_pred, slot_expert, slot_quota, seg_offsets, row_of_assign, assign_of_row, rank_load);
+        launch_small<false>(mode, T, k, E, G, S, topk_idx, pred_idx, hist_true, hist_pred, slot_expert, slot_quota,
+                            seg_offsets, row_of_assign, assign_of_row, rank_load, nullptr, HomePlan{}, st);
         if ((rc = check_launch()) != MOE_OK) return rc;
     } else {
         const bool scanned = nb == 0 || (nb > kSelfScanChunks && ws.rounds == kRounds);
@@ -835,20 +897,7 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
         }
     }
     if (nb > 0) {
-        if (x_perm) {
-            const int chunks = (int)((size_t)d * dtype_size(dtype) / 16);
-            const int unroll = chunks >= 4 * kWave ? 4 : 1;
-            // a small batch: split every row over several wavefronts until there are a few thousand
-            int slices = 1;
-            while (slices < 16 && (int64_t)T * slices < 4096 && chunks >= 2 * slices * kWave * unroll) slices *= 2;
-            auto launch = [&](auto kern) {
-                hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64((int64_t)T * slices, 4)), dim3(256), 0, st,
-                                   (const uint4*)x, (uint4*)x_perm, row_of_assign, T, k, chunks, slices);
-            };
-            if (unroll == 4) launch(perm_scatter_rows_kernel<4>);
-            else launch(perm_scatter_rows_kernel<1>);
-            if ((rc = check_launch()) != MOE_OK) return rc;
-        }
+        if (x_perm && (rc = scatter_rows(x, dtype, T, d, k, row_of_assign, x_perm, st)) != MOE_OK) return rc;
     }
     return MOE_OK;
 }

@@ -120,10 +120,40 @@ class MoELayer:
         B.moe_combine(self.y_perm, self.perm["row_of_assign"], None if self.fused_weights else self.topk_w, c.T, c.k,
                       out=self.out)
 
+    def _one_call(self, logits, x, hist_pred, pred_idx, mode) -> bool:
+        """The whole step as one C-ABI call, for inputs of the layer's own sizes; anything else is left to
+        the calls of the single steps (and to what they say about it)."""
+        c = self.cfg
+        if type(self) is not MoELayer or self.packed is None or mode not in (MODE_NONE, MODE_DISTRIBUTION, MODE_TOKEN):
+            return False
+        if c.T < 1 or logits.shape != (c.T, c.E) or x.shape != (c.T, c.d) or x.dtype != self.out.dtype:
+            return False
+        if mode == MODE_DISTRIBUTION and (hist_pred is None or hist_pred.numel() != c.E):
+            return False
+        if mode == MODE_TOKEN and (pred_idx is None or pred_idx.numel() != c.A):
+            return False
+        hist_pred = hist_pred if mode == MODE_DISTRIBUTION else None
+        pred_idx = pred_idx if mode == MODE_TOKEN else None
+        p = self.perm
+        dtype = B.MOE_DTYPE_F32 if c.dtype == "f32" else B.MOE_DTYPE_BF16
+        B.moe_layer_step(mode, dtype, c.T, c.d, c.ffn, c.E, c.k, c.G, c.S, c.cmax, c.act == "relu", self.fused_weights,
+                         logits=logits, x=x, hist_pred=hist_pred, pred_idx=pred_idx, packed=self.packed,
+                         topk_idx=self.topk_idx, topk_w=self.topk_w, hist=self.hist, hist_plan=self.hist_plan,
+                         slot_expert=self.slot_expert, slot_quota=self.slot_quota,
+                         rank_load_pred=self.rank_load_pred, n_iters=self.n_iters, seg_offsets=p["seg_offsets"],
+                         row_of_assign=p["row_of_assign"], assign_of_row=p["assign_of_row"], x_perm=p["x_perm"],
+                         rank_load=p["rank_load"], y_perm=self.y_perm, out=self.out, workspace_perm=self.ws_perm,
+                         workspace_ffn=self.ws_ffn)
+        self._x = x
+        self._hp = {MODE_NONE: self.hist, MODE_DISTRIBUTION: hist_pred, MODE_TOKEN: self.hist_plan}[mode]
+        return True
+
     # the whole path -----------------------------------------------------------
     def step(self, logits: torch.Tensor, x: torch.Tensor, hist_pred: Optional[torch.Tensor] = None,
              pred_idx: Optional[torch.Tensor] = None, mode: Optional[int] = None) -> torch.Tensor:
         mode = self.cfg.mode if mode is None else mode
+        if self._one_call(logits, x, hist_pred, pred_idx, mode):
+            return self.out
         self.route(logits)
         self.histogram()
         self.plan(mode, hist_pred, pred_idx)

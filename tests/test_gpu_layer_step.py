@@ -1,0 +1,90 @@
+"""The whole step as one call against the calls of the single steps: the same outputs, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_07366_amd import workloads as wl
+from paper_2506_07366_amd.layer import MoELayer, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def outputs(layer):
+    p = layer.perm
+    names = ("topk_idx", "topk_w", "hist", "slot_expert", "slot_quota", "rank_load_pred", "n_iters", "out")
+    res = {n: getattr(layer, n).clone() for n in names}
+    res.update({n: p[n].clone() for n in ("seg_offsets", "row_of_assign", "assign_of_row", "rank_load")})
+    return res
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("T,E,k,G,S,dtype", [
+    (1, 8, 2, 8, 2, "bf16"),          # one token
+    (7, 2, 1, 2, 1, "f32"),           # two lanes per token, no spare slot
+    (33, 3, 2, 2, 3, "bf16"),         # four lanes, an uneven home placement
+    (256, 8, 2, 8, 3, "f32"),
+    (1024, 16, 2, 4, 5, "bf16"),      # 2048 assignments: the last in one workgroup with predicted ids
+    (1025, 16, 2, 4, 5, "bf16"),
+    (512, 24, 6, 12, 3, "bf16"),      # 3072: the last in one workgroup without
+    (513, 24, 6, 12, 3, "bf16"),
+    (2048, 64, 8, 16, 5, "bf16"),     # 16384: the last whose predicted ids one workgroup counts
+    (2049, 64, 8, 16, 5, "bf16"),
+    (100, 256, 4, 32, 10, "bf16"),    # the planner's launch is shared up to here
+    (100, 257, 4, 32, 10, "bf16"),
+    (100, 32, 4, 33, 2, "bf16"),
+    (100, 22, 4, 2, 11, "bf16"),
+    (300, 600, 8, 64, 16, "bf16"),    # tables too large for one workgroup
+])
+def test_step_equals_single_calls(T, E, k, G, S, dtype, mode):
+    d, ffn = 64, 64
+    cfg = wl.MoEConfig("st", T=T, d=d, ffn=ffn, E=E, k=k, G=G, S=S, dtype=dtype, mode=mode, seed=61)
+    rng = np.random.default_rng([62, T, E, mode])
+    logits = torch.from_numpy(rng.standard_normal((T, E)).astype(np.float32) - np.log1p(np.arange(E))[None]
+                              .astype(np.float32)).cuda()
+    x = to_device(wl.to_storage(rng.standard_normal((T, d)).astype(np.float32), dtype), dtype)
+    ws = [to_device(wl.to_storage((rng.standard_normal(s) * 0.02).astype(np.float32), dtype), dtype)
+          for s in ((E, d, ffn), (E, d, ffn), (E, ffn, d))]
+    pred_idx = torch.topk(logits + 0.5 * torch.randn_like(logits), k, dim=1).indices.to(torch.int32).contiguous()
+    hist_pred = torch.bincount(pred_idx.reshape(-1).long(), minlength=E).to(torch.int32)
+    for gather, weights in ((False, False), (True, False), (True, True)):
+        layer = MoELayer(cfg, fused_gather=gather, fused_weights=weights)
+        layer.set_weights(*ws)
+        layer.route(logits)
+        layer.histogram()
+        layer.plan(mode, hist_pred, pred_idx)
+        layer.permute(mode, x, pred_idx)
+        layer.ffn()
+        layer.combine()
+        want = outputs(layer)
+        plan_hist = layer.hist_plan.clone()
+        for t in (layer.hist, layer.hist_plan, layer.slot_expert, layer.slot_quota, layer.n_iters, layer.topk_idx,
+                  *(v for v in layer.perm.values() if v is not None), layer.out, layer.y_perm):
+            t.fill_(-7)
+        assert layer._one_call(logits, x, hist_pred, pred_idx, mode)
+        got = outputs(layer)
+        for n, v in want.items():
+            assert torch.equal(got[n], v), n
+        if mode == 2:
+            assert torch.equal(layer.hist_plan, plan_hist)
+
+
+def test_step_leaves_other_inputs_to_the_single_calls():
+    """Inputs that are not the layer's own sizes keep the behaviour (and the errors) of the single calls."""
+    cfg = wl.CONFIGS["mid_bf16"]
+    layer = MoELayer(cfg)
+    x = torch.zeros((cfg.T, cfg.d), dtype=torch.bfloat16, device="cuda")
+    logits = torch.zeros((cfg.T, cfg.E), device="cuda")
+    hist = torch.ones(cfg.E, dtype=torch.int32, device="cuda")
+    assert not layer._one_call(logits, x, hist, None, 1)              # no weights yet
+    with pytest.raises(Exception):
+        layer.step(logits, x, hist_pred=hist)
+    layer.packed = torch.empty(256, dtype=torch.uint8, device="cuda")  # (never read below)
+    assert not layer._one_call(logits, x, None, None, 1)
+    assert not layer._one_call(logits, x, hist, None, 2)
+    assert not layer._one_call(logits[:-1], x, hist, None, 1)
+    assert not layer._one_call(logits, x.float(), hist, None, 1)
+    assert not layer._one_call(logits, x, hist, None, 3)
+    with pytest.raises(Exception):
+        layer.step(logits.double(), x, hist_pred=hist)
+    with pytest.raises(Exception):
+        layer.step(logits, x, hist_pred=hist.long())
