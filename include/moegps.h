@@ -248,8 +248,8 @@ int moe_grouped_ffn_gather(const void* x, int dtype, int T, int k, const int32_t
  *   x_perm NULL: the FFN gathers the token rows (moe_grouped_ffn_gather), and with gate_in_ffn
  *   it applies the gate weights (moe_grouped_ffn_fused); SwiGLU only.
  *   hist_pred is read in mode 1; pred_idx is read and hist_plan (its histogram) written in mode 2.
- * T = 0 is a no-op.  Arguments are checked before the first launch, apart from those limits that only
- * the FFN has: on one of its errors, and on MOE_ERR_HIP, earlier steps have been enqueued.
+ * T = 0 is a no-op.  Arguments are checked before the first launch; on MOE_ERR_HIP earlier steps may
+ * have been enqueued.
  */
 typedef struct moe_layer_step_args {
     int32_t mode, dtype, T, d, ffn, E, k, G, S, c_max, relu, gate_in_ffn;

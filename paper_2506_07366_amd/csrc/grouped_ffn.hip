@@ -29,8 +29,7 @@
 // the same two products with another epilogue on the first.
 //
 // fp32 path (small reference-precision configs): the fp32 matrix instruction, operands from memory.
-#include "common.h"
-#include "block_scan.h"
+#include "ffn_tables.h"
 #include <atomic>
 #include <type_traits>
 #include <utility>
@@ -41,30 +40,6 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;  // four floats at any float's address, still one access
 typedef unsigned short bf16_t;  // storage
-
-// One entry of an M-tile table: consecutive positions of the row list, all of one
-// expert, and the part of the K range this entry covers.
-struct MTile {
-    int list0;   // first position in the row list
-    int rows;    // valid rows
-    int expert;  // expert whose weights the rows take
-    int kt0;     // k-tiles [kt0, kt1) of the product belong to this entry; kt1 == 0: all of them
-    int kt1;
-    int part;    // < 0: results go to the output; else fp32 partial sums go to slab `part`
-    int first;   // whole tiles: the expert's whole tiles are the entries [first, first + n_same)
-    int n_same;
-};
-// An M-tile whose K range is split, for the pass that adds up the partial sums
-struct SplitInfo {
-    int list0, rows;
-};
-constexpr int kGemmGrid = 256;  // persistent workgroups of a GEMM launch: 8 XCDs x 32
-constexpr int kPartRows = 256;  // rows of one slab of partial sums (the tallest tile shape)
-constexpr int kMaxParts = 4;    // parts of K of a split tile
-
-// counts[] of a table: number of entries, how many of them are whole tiles (they come first; behind
-// them the parts of split tiles), number of split M-tiles
-constexpr int kCntEntries = 0, kCntWhole = 1, kCntSplit = 2, kCntStride = 4;
 
 // ---------------------------------------------------------------------------
 // weight packing (one-off, weights are static across inputs)
@@ -138,323 +113,11 @@ __global__ void copy_u4_kernel(const uint4* __restrict__ in, uint4* __restrict__
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) out[i] = in[i];
 }
 
-// ---------------------------------------------------------------------------
-// row list and M-tile tables from the ragged segments
-// ---------------------------------------------------------------------------
-// What one product's table is built for.
-struct TableSpec {
-    MTile* tiles;       // out
-    int32_t* counts;    // out, kCntStride ints
-    SplitInfo* splits;  // out (split tiles only), may be null when parts <= 1
-    int bm;             // most rows of a tile, 0: chosen from the batch
-    int capacity;       // entries `tiles` has room for
-    int kt;             // k-tiles of the product
-    int parts;          // parts of K of a split tile (<= 1: no tile is split)
-    int n_ntiles;       // N-tiles of the product (tile heights and split tiles go by the tiles
-                        //   that the kGemmGrid workgroups of its launch get)
-    int split_all;      // split every tile (tests)
-    int split_capacity; // split M-tiles `splits` and the slabs have room for
-};
-
-// Row list: position p holds a row of x_perm; the rows of an expert's segments (ascending
-// slot id, rows ascending) are consecutive, experts ascending.
-// M-tile tables: an expert's rows are cut into as few tiles as the height allows, evenly (a tile costs by
-// its rows, ffn_tiles.h, so two of 160 and 140 rows are done before one of 256 and one of 44), in steps of the
-// 32 rows the kernels have loops for.  An expert's tiles stay together, in expert order (they share weight
-// panels; the kernels walk them by MTile::first and n_same), experts with tiles of up to kShortTile rows
-// behind the others: what is left for the end of the launch is then short, while tall tiles, bound by the matrix pipe,
-// stay mixed with middling ones, bound by their weights (tallest first altogether: 64 experts of 2048 x 1408, 4096
-// tokens, second product 189 us, as it is 184; short ones where they fall: 206).
-// The height is worked out here, where the rows per expert are known, one lane per candidate: the
-// launch's time is taken as the longest of (a) for every height in the table, the rounds that the
-// tiles of that height and above make of the workgroups, and (b) the mean work of a workgroup and a quarter of a
-// closing tile; where tiles may be split as the work, a third dearer, and the pass that adds them up.  A tile's cost is
-// kCostFixed + its 16-row groups.  The constants are fitted to 78 products of 39 batches (five shapes, 8 to 224 k-tiles,
-// 2 to 112 N-tiles, 150 to 16384 tokens), each timed with all seven heights: the height taken is 0.9 % above the best one
-// on average, 7 % at most.  Both products, us, 256- or 128-row tiles by a rule on the mean rows per expert ->
-// this: 777 tokens, top-8 of 128 experts of 4096 x 1536 389 -> 354; 1001 tokens, top-2 of 8 of 4096 x 14336 819 ->
-// 730; 2048 tokens, top-6 of 64 of 2048 x 1408 345 -> 310; 3000 tokens, top-4 of 16 of 4096 x 688 261 -> 223; 4096
-// tokens, top-2 of 8 of 512 x 1024 83 -> 48.
-// With parts > 1 the closing M-tiles are listed once per part of K instead, behind the
-// whole ones and part by part, each entry writing fp32 partial sums to a slab of its own (slab =
-// split tile * parts + part).  What is split is what goes beyond whole rounds of one tile per workgroup,
-// unless it is most of a round anyway (more than 5/8: splitting would add traffic and save little).
-//
-// The work is small and what it costs is waiting: for barriers of 16 wavefronts and for chains of LDS
-// round trips.  So one wavefront does the parts that need an order (64 segments or experts at a
-// time, equal keys found by ballots, counts carried in LDS, prefix sums by DPP), without a
-// barrier between its steps, and the workgroup meets three times: segments loaded, list order
-// known, table prepared; the row list and the table entries are written by everybody.
-// Every workgroup works out the list order and fills its stripe of the row list; workgroup 0
-// writes the first table and sets the claim counters, workgroup 1 the second (the launch has two at least).
-// Against pairs of segments and of experts dealt over the workgroup, some 30 barriers, and stripes of
-// 4096 positions: 8 experts in 12 slots 10.3 -> 6.5 us (in 16 slots 9.4 -> 5.5); 128 experts in 160
-// slots, one token 15.8 -> 8.5, 128 tokens 17.5 -> 9.4, 777 tokens and two tables 19.6 -> 10.5; 64 experts
-// in 80 slots, 98304 rows 16.7 -> 11.  Pairs cost nothing for slots without rows; with hundreds of
-// experts, groups of 64 slots or experts without rows are therefore skipped and the scans keep four reads
-// under way (1024 experts in as many slots, 1024 rows on 16 of them, whole FFN of 64 x 64 weights: pairs 26.1,
-// without the skip 38.7, now 25.2 us; on all 1024 216, 48.4, 48.2).
-
-// exclusive prefix sums of data[0 .. n) in LDS, in place, by one wavefront; data[n] = total, returned
-template <int UNROLL = 1>  // reads under way together: more than one pays with eight words per lane and up
-__device__ __forceinline__ int wave_scan_lds(int* data, int n) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int per = ceil_div(n, kWave);
-    const int i0 = lane * per < n ? lane * per : n, i1 = i0 + per < n ? i0 + per : n;
-    int mine = 0;
-#pragma unroll UNROLL
-    for (int i = i0; i < i1; ++i) mine += data[i];
-    const int incl = wave_prefix_i32(mine);
-    int run = incl - mine;
-#pragma unroll UNROLL
-    for (int i = i0; i < i1; ++i) {
-        const int c = data[i];
-        data[i] = run;
-        run += c;
-    }
-    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
-    if (lane == 0) data[n] = total;
-    wave_lds_order();
-    return total;
-}
-
-// the same over the experts
-__device__ __forceinline__ int wave_scan_experts(int* data, int E) {
-    return E >= 8 * kWave ? wave_scan_lds<4>(data, E) : wave_scan_lds(data, E);
-}
-
-// lanes that hold the same key (below 1 << nbits) among the lanes with `live`
-__device__ __forceinline__ unsigned long long same_key_lanes(int key, bool live, int nbits) {
-    unsigned long long same = __ballot(live);
-    for (int b = 0; b < nbits; ++b) {
-        const bool one = (key >> b) & 1;
-        const unsigned long long m = __ballot(live && one);
-        same &= one ? m : ~m;
-    }
-    return live ? same : 0ull;
-}
-
-constexpr int kTallest = 256, kHeightStep = 32;      // rows of the tallest tile; heights are multiples of the step
-constexpr int kHeights = kTallest / kHeightStep;
-constexpr int kMinAutoHeight = 64;                   // lowest height that is chosen from the batch
-constexpr int kCandidates = (kTallest - kMinAutoHeight) / kHeightStep + 1;
-constexpr int kShortTile = 64;                       // tiles of up to so many rows come last
-constexpr int kCostFixed = 8;                        // cost of a tile: this and its 16-row groups
-static_assert(MOE_MAX_EXPERTS <= 1 << 12 && MOE_MAX_SEGMENTS <= 1 << 19, "expert and place share one int");
-
-// Height of the tiles that `rows` rows of one expert are cut into, at most `most` each (a multiple of the step).
-__device__ __forceinline__ int even_height(int rows, int most) {
-    const int n = (rows + most - 1) / most;
-    if (n > kHeights) return most;  // (n - 1) / n of the limit is less than a step below it
-    return ((rows + n - 1) / n + kHeightStep - 1) / kHeightStep * kHeightStep;
-}
-
+// Workgroup 0 makes the first table, workgroup 1 the second (ffn_tables.h).
 __global__ __launch_bounds__(1024) void build_tables_kernel(const int32_t* __restrict__ seg_offsets,
-                                                             const int32_t* __restrict__ slot_expert, int seg_begin,
-                                                             int seg_end, int E, TableSpec t1, TableSpec t2,
-                                                             int32_t* __restrict__ rowlist,
-                                                             int32_t* __restrict__ queues, int n_queues) {
-    __shared__ int s_rows[MOE_MAX_SEGMENTS];       // rows of the segment
-    __shared__ int s_ex[MOE_MAX_SEGMENTS];         // its expert and, from bit 12, its place there; -1: not live
-    __shared__ int s_first[MOE_MAX_SEGMENTS];      // first row of x_perm
-    __shared__ int srt_base[MOE_MAX_SEGMENTS + 1]; // list position of the j-th segment in list order
-    __shared__ int srt_first[MOE_MAX_SEGMENTS];    // its first row of x_perm
-    __shared__ int e_segs[MOE_MAX_EXPERTS + 1];    // live segments per expert -> base in list order
-    __shared__ int o_base[MOE_MAX_EXPERTS + 1];    // tiles of the o-th expert in tile order -> those before it
-    __shared__ int o_expert[MOE_MAX_EXPERTS];      // that expert, and from bit 12 the height of its tiles
-    __shared__ int c_tiles[kCandidates][kHeights + 1];  // tiles of a height, per candidate
-    __shared__ int s_plan[4];                      // ordered experts, tiles, split ones of them
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const bool leader = tid < kWave;
-    const unsigned long long lt = (1ull << lane) - 1ull;
-    const int ns = seg_end - seg_begin;
-    const bool many = E > 4 * kWave;  // experts enough that looking for groups of 64 without rows pays
-    if (blockIdx.x == 0)
-        for (int i = tid; i < n_queues; i += blockDim.x) queues[i] = kGemmGrid / 8;  // every workgroup's first tile is its own
-    for (int e = tid; e < E; e += blockDim.x) e_segs[e] = 0;
-    for (int i = tid; i < ns; i += blockDim.x) {
-        const int s = seg_begin + i;
-        const int lo = seg_offsets[s];
-        const int rows = seg_offsets[s + 1] - lo;
-        const int e = slot_expert[s];
-        s_rows[i] = rows;
-        s_ex[i] = rows > 0 && e >= 0 && e < E ? e : -1;
-        s_first[i] = lo;
-    }
-    __syncthreads();
-    if (leader) {
-        const int nbits = E > 1 ? 32 - __builtin_clz(E - 1) : 0;
-        for (int i0 = 0; i0 < ns; i0 += kWave) {
-            const int i = i0 + lane;
-            const int e = i < ns ? s_ex[i] : -1;
-            if (many && __ballot(e >= 0) == 0ull) continue;
-            const unsigned long long same = same_key_lanes(e, e >= 0, nbits);
-            if (e >= 0) {
-                const int before = e_segs[e];
-                s_ex[i] = e | (before + __popcll(same & lt)) << 12;
-                if ((same & ~lt) == (1ull << lane)) e_segs[e] = before + __popcll(same);  // the last of them
-            }
-            wave_lds_order();
-        }
-        wave_scan_experts(e_segs, E);
-        for (int i = lane; i < ns; i += kWave) {
-            const int v = s_ex[i];
-            if (v < 0) continue;
-            const int j = e_segs[v & 0xfff] + (v >> 12);
-            srt_base[j] = s_rows[i];
-            srt_first[j] = s_first[i];
-        }
-        wave_lds_order();
-        wave_scan_lds(srt_base, e_segs[E]);
-    }
-    __syncthreads();
-    const int n_live = e_segs[E], n_list = srt_base[n_live];
-    // row list: binary search of the position among the segments in list order
-    auto fill_rows = [&] {
-        for (int p = blockIdx.x * blockDim.x + tid; p < n_list; p += gridDim.x * blockDim.x) {
-            int lo = 0, hi = n_live - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (srt_base[mid] <= p) lo = mid;
-                else hi = mid - 1;
-            }
-            rowlist[p] = srt_first[lo] + (p - srt_base[lo]);
-        }
-    };
-    // tables
-    auto list_base = [&](int e) { return srt_base[e_segs[e]]; };  // first list position of expert e
-    const TableSpec& ts = blockIdx.x == 0 ? t1 : t2;
-    const bool table = blockIdx.x < 2 && ts.tiles;
-    const bool busy = leader && table;  // prepares the table while the others fill in the row list
-    if (!busy) fill_rows();
-    if (table) {  // (uniform)
-        const int P = ts.parts > kMaxParts ? kMaxParts : ts.parts;
-        if (leader) {
-            auto rows_of = [&](int e) { return e < E ? list_base(e + 1) - list_base(e) : 0; };
-            auto none = [&](int e0) {  // no segment holds any of the 64 experts
-                return many && e_segs[e0] == e_segs[e0 + kWave < E ? e0 + kWave : E];
-            };
-            int most = ts.bm;
-            if (most == 0) {
-                for (int i = lane; i < kCandidates * (kHeights + 1); i += kWave) (&c_tiles[0][0])[i] = 0;
-                wave_lds_order();
-                for (int e0 = 0; e0 < E; e0 += kWave) {
-                    if (none(e0)) continue;
-                    const int rows = rows_of(e0 + lane);
-                    if (rows == 0) continue;
-#pragma unroll
-                    for (int c = 0; c < kCandidates; ++c) {
-                        const int h = kTallest - c * kHeightStep;
-                        atomicAdd(&c_tiles[c][even_height(rows, h) / kHeightStep], (rows + h - 1) / h);
-                    }
-                }
-                wave_lds_order();
-                const int c = lane < kCandidates ? lane : kCandidates - 1;
-                float n = 0.f, work = 0.f, time = 0.f, first = 0.f, last = 0.f;
-#pragma unroll
-                for (int k = kHeights; k > 0; --k) {
-                    const float m = (float)c_tiles[c][k] * (float)ts.n_ntiles;
-                    if (m == 0.f) continue;
-                    last = (float)(kCostFixed + 2 * k);
-                    if (n == 0.f) first = last;
-                    n += m;
-                    work += m * last;
-                    time = fmaxf(time, ceilf(n * (1.f / kGemmGrid)) * last);
-                }
-                time = fmaxf(time, work * (1.f / kGemmGrid) + 0.25f * last) + 0.1f * first;
-                const float rem = n - floorf(n * (1.f / kGemmGrid)) * kGemmGrid;
-                if (P > 1 && rem <= 0.625f * kGemmGrid)
-                    time = fminf(time, work * (1.3f / kGemmGrid) + 0.4f * last + 400.f / ts.kt);
-                // the taller of two that are as good
-                int key = lane < kCandidates ? (int)(fminf(time, 1e7f) * 16.f) * 8 + lane : 0x7fffffff;
-                for (int m = 1; m < 8; m <<= 1) {
-                    const int o = __shfl_xor(key, m, kWave);
-                    key = o < key ? o : key;
-                }
-                most = kTallest - (__builtin_amdgcn_readfirstlane(key) & 7) * kHeightStep;
-            }
-            // tile order: experts with tall tiles, then those with short ones, each group ascending
-            int o = 0;
-            for (int pass = 0; pass < 2; ++pass) {
-                for (int e0 = 0; e0 < E; e0 += kWave) {
-                    if (none(e0)) continue;
-                    const int rows = rows_of(e0 + lane);
-                    const int height = rows > 0 ? even_height(rows, most) : 0;
-                    const bool mine = pass == 0 ? height > kShortTile : rows > 0 && height <= kShortTile;
-                    const unsigned long long them = __ballot(mine);
-                    if (mine) {
-                        const int at = o + __popcll(them & lt);
-                        o_expert[at] = (e0 + lane) | height << 12;
-                        o_base[at] = (rows + height - 1) / height;
-                    }
-                    o += __popcll(them);
-                }
-            }
-            if (lane == 0) s_plan[0] = o;
-            wave_lds_order();
-            const int n_tiles = wave_scan_experts(o_base, o);
-            int n_split = 0;
-            if (P > 1) {
-                if (ts.split_all) n_split = n_tiles;
-                else {
-                    const int rem = (int)((long long)n_tiles * ts.n_ntiles % kGemmGrid);
-                    if (rem * 8 <= kGemmGrid * 5) n_split = (rem + ts.n_ntiles - 1) / ts.n_ntiles;
-                }
-                if (n_split > ts.split_capacity) n_split = 0;  // stay in bounds (the host sizes for the rule)
-            }
-            if (lane == 0) {
-                s_plan[1] = n_tiles;
-                s_plan[2] = n_split;
-            }
-        }
-        __syncthreads();
-        const int n_order = s_plan[0], n_tiles = s_plan[1], n_split = s_plan[2];
-        const int n_whole = n_tiles - n_split;
-        const int n_entries = n_whole + n_split * P;
-        const bool fits = n_entries <= ts.capacity;
-        auto part_range = [&](int part, int& k0, int& k1) {
-            const unsigned a = (unsigned)(ts.kt * part), b = (unsigned)(ts.kt * (part + 1));  // (at most 2^16 k-tiles)
-            k0 = (int)(P == kMaxParts ? a / kMaxParts : a / (unsigned)P);
-            k1 = (int)(P == kMaxParts ? b / kMaxParts : b / (unsigned)P);
-        };
-        for (int t = tid; fits && t < n_tiles; t += blockDim.x) {
-            int lo = 0, hi = n_order - 1;  // the expert whose range of tile numbers holds t
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (o_base[mid] <= t) lo = mid;
-                else hi = mid - 1;
-            }
-            const int expert = o_expert[lo] & 0xfff, height = o_expert[lo] >> 12;
-            const int left = list_base(expert + 1) - list_base(expert) - (t - o_base[lo]) * height;
-            MTile mt;
-            mt.list0 = list_base(expert + 1) - left;
-            mt.rows = left < height ? left : height;
-            mt.expert = expert;
-            mt.kt0 = mt.kt1 = 0;
-            mt.part = -1;
-            mt.first = o_base[lo];
-            mt.n_same = (o_base[lo + 1] < n_whole ? o_base[lo + 1] : n_whole) - mt.first;
-            if (t < n_whole) {
-                ts.tiles[t] = mt;
-                continue;
-            }
-            const int split_index = t - n_whole;
-            for (int part = 0; part < P; ++part) {
-                part_range(part, mt.kt0, mt.kt1);
-                mt.part = split_index * P + part;
-                ts.tiles[n_whole + part * n_split + split_index] = mt;
-            }
-            ts.splits[split_index].list0 = mt.list0;
-            ts.splits[split_index].rows = mt.rows;
-        }
-        if (tid == 0) {
-            ts.counts[kCntEntries] = fits ? n_entries : 0;
-            ts.counts[kCntWhole] = fits ? n_whole : 0;
-            ts.counts[kCntSplit] = fits ? n_split : 0;
-        }
-    }
-    if (busy) fill_rows();
+                                                             const int32_t* __restrict__ slot_expert, TableJob job) {
+    __shared__ TableScratch<MOE_MAX_SEGMENTS, MOE_MAX_EXPERTS, 1> sh;
+    build_tables(sh, blockIdx.x, gridDim.x, blockIdx.x, seg_offsets, slot_expert, job);
 }
 
 // ---------------------------------------------------------------------------
@@ -1041,13 +704,13 @@ namespace moegps {
 // Rows of the first product: x_perm rows in place (gather_rows == nullptr; `rows_in` = A), or
 // row r is x[gather_rows[r] / gather_div] (`rows_in` = rows of x).  With `scale`, row r of
 // the output is multiplied by scale[scale_idx[r]] before it is rounded.
-static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const int32_t* gather_rows, int gather_div,
-                            const int32_t* scale_idx, const float* scale, int dtype, int64_t A, int d, int ffn,
-                            int E, const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin,
-                            int seg_end, const void* packed, void* y_perm, void* workspace, size_t workspace_bytes,
-                            void* stream) {
-    const bool timed = g_time_armed;
-    g_time_armed = false;  // the hook belongs to this call, whatever becomes of it
+int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t* gather_rows, int gather_div,
+                     const int32_t* scale_idx, const float* scale, int dtype, int64_t A, int d, int ffn, int E,
+                     const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin, int seg_end,
+                     const void* packed, void* y_perm, void* workspace, size_t workspace_bytes, void* stream,
+                     FfnStage stage, TableJob* job_out) {
+    const bool timed = g_time_armed && stage != kFfnJobOnly;
+    if (stage != kFfnJobOnly) g_time_armed = false;  // the hook belongs to this call, whatever becomes of it
     if (dtype != MOE_DTYPE_F32 && dtype != MOE_DTYPE_BF16) return MOE_ERR_INVALID_ARG;
     if (A < 0 || d < 1 || ffn < 1 || E < 1 || nseg < 1) return MOE_ERR_INVALID_ARG;
     if (seg_begin < 0 || seg_end > nseg || seg_begin > seg_end) return MOE_ERR_INVALID_ARG;
@@ -1063,13 +726,28 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
     FfnWs ws;
     const size_t need = ffn_ws_layout(A, d, ffn, nseg, dtype, (char*)workspace, &ws);
     if (workspace_bytes < need) return MOE_ERR_WORKSPACE_TOO_SMALL;
-    if (A == 0 || seg_begin == seg_end) return MOE_OK;
+    if (A == 0 || seg_begin == seg_end) {
+        if (job_out) *job_out = TableJob{};
+        return MOE_OK;
+    }
     hipStream_t st = (hipStream_t)stream;
     const size_t per = (size_t)E * d * ffn;
     const int nrange = seg_end - seg_begin;
     // one position of the row list per thread up to 256 workgroups
     const int build_grid = (int)(A <= 1024 ? 2 : (A > 255 * 1024 ? 256 : ceil_div64(A, 1024) + 1));
     int rc;
+    // the table builder's turn; false: the call ends here
+    auto tables = [&](const TableJob& job, int* rc_out) {
+        *rc_out = MOE_OK;
+        if (stage == kFfnJobOnly) {
+            *job_out = job;
+            return false;
+        }
+        if (stage == kFfnTablesBuilt) return true;
+        hipLaunchKernelGGL(build_tables_kernel, dim3(build_grid), dim3(1024), 0, st, seg_offsets, slot_expert, job);
+        *rc_out = check_launch();
+        return *rc_out == MOE_OK;
+    };
     RowMap rm1{ws.rowlist, gather_rows, gather_div, nullptr, nullptr, nullptr};
     RowMap rm2{nullptr, nullptr, 1, ws.rowlist, scale_idx, scale};
 
@@ -1079,9 +757,7 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
         const int bm = tiles64 < 2 * kGemmGrid ? 32 : 64;
         TableSpec t1{ws.tiles1, ws.counts, nullptr, bm, ws.capacity, 0, 0, 1, 0, 0};
         TableSpec none{};
-        hipLaunchKernelGGL(build_tables_kernel, dim3(build_grid), dim3(1024), 0, st, seg_offsets, slot_expert,
-                           seg_begin, seg_end, E, t1, none, ws.rowlist, (int32_t*)nullptr, 0);
-        if ((rc = check_launch()) != MOE_OK) return rc;
+        if (!tables(TableJob{E, seg_begin, seg_end, t1, none, ws.rowlist, nullptr, 0}, &rc)) return rc;
         const float* w1 = (const float*)packed;
         const float* w3 = w1 + per;
         const float* w2 = relu ? w3 : w3 + per;
@@ -1123,9 +799,7 @@ static int grouped_ffn_impl(int relu, const void* x_in, int64_t rows_in, const i
                  ceil_div(n1 * fp, kPackN), 0, 0};
     TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / kPackK,
                  split ? ws.parts : 0, ceil_div(d, kPackN), ws.split_all, ws.split_capacity};
-    hipLaunchKernelGGL(build_tables_kernel, dim3(build_grid), dim3(1024), 0, st, seg_offsets, slot_expert, seg_begin,
-                       seg_end, E, t1, t2, ws.rowlist, ws.queues, 16);
-    if ((rc = check_launch()) != MOE_OK) return rc;
+    if (!tables(TableJob{E, seg_begin, seg_end, t1, t2, ws.rowlist, ws.queues, 16}, &rc)) return rc;
     const MTile* tiles2 = own2 ? ws.tiles2 : ws.tiles1;
     const int32_t* count2 = own2 ? ws.counts + kCntStride : ws.counts;
     const bf16_t* p13 = (const bf16_t*)packed;
@@ -1164,7 +838,7 @@ extern "C" int moe_grouped_ffn(const void* x_perm, int dtype, int64_t A, int d, 
                                const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin,
                                int seg_end, const void* packed, void* y_perm, void* workspace,
                                size_t workspace_bytes, void* stream) {
-    return moegps::grouped_ffn_impl(0, x_perm, A, nullptr, 1, nullptr, nullptr, dtype, A, d, ffn, E, seg_offsets,
+    return moegps::grouped_ffn_call(0, x_perm, A, nullptr, 1, nullptr, nullptr, dtype, A, d, ffn, E, seg_offsets,
                                     slot_expert, nseg, seg_begin, seg_end, packed, y_perm, workspace, workspace_bytes,
                                     stream);
 }
@@ -1173,7 +847,7 @@ extern "C" int moe_grouped_ffn_relu(const void* x_perm, int dtype, int64_t A, in
                                     const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin,
                                     int seg_end, const void* packed, void* y_perm, void* workspace,
                                     size_t workspace_bytes, void* stream) {
-    return moegps::grouped_ffn_impl(1, x_perm, A, nullptr, 1, nullptr, nullptr, dtype, A, d, ffn, E, seg_offsets,
+    return moegps::grouped_ffn_call(1, x_perm, A, nullptr, 1, nullptr, nullptr, dtype, A, d, ffn, E, seg_offsets,
                                     slot_expert, nseg, seg_begin, seg_end, packed, y_perm, workspace, workspace_bytes,
                                     stream);
 }
@@ -1186,7 +860,7 @@ extern "C" int moe_grouped_ffn_fused(const void* x, int dtype, int T, int k, con
     if (T < 0 || k < 1 || d < 1) return MOE_ERR_INVALID_ARG;
     if ((int64_t)T * d >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;  // 32-bit element offsets into x
     if (T > 0 && !assign_of_row) return MOE_ERR_INVALID_ARG;
-    return moegps::grouped_ffn_impl(0, x, T, assign_of_row, k, topk_w ? assign_of_row : nullptr, topk_w, dtype,
+    return moegps::grouped_ffn_call(0, x, T, assign_of_row, k, topk_w ? assign_of_row : nullptr, topk_w, dtype,
                                     (int64_t)T * k, d, ffn, E, seg_offsets, slot_expert, nseg, seg_begin, seg_end,
                                     packed, y_perm, workspace, workspace_bytes, stream);
 }

@@ -5,12 +5,12 @@
 // least, and each is a call from the host.  Two things shorten it where the shape allows:
 //   - under a prediction the plan does not need the routing: one workgroup makes it (under Token-to-Expert
 //     after counting the predicted ids) while the others of the same launch route the tokens;
-//   - where the permutation is one workgroup's work it also writes the histogram, and without a prediction
-//     the plan, which then is the home placement.
+//   - where the permutation is one workgroup's work it also writes the histogram, without a prediction
+//     the plan, which then is the home placement, and goes on to the tables of the grouped FFN.
 // Anything else goes through the calls of the single steps; the results are the same integers either way.
-// Whole steps, us, six calls (seven with predicted ids) -> one: 256 tokens of the small fp32 layer 45.0 -> 41.0 (no
-// longer bound by the host), one token on 128 experts 80.2 -> 76.7, 16 tokens of the Mixtral shape as a graph
-// 285 -> 279, 777 tokens with Token-to-Expert 438 -> 427.
+// Whole steps, us, six calls (seven with predicted ids) -> one: 256 tokens of the small fp32 layer 45.0 -> 39.9 (no
+// longer bound by the host, which takes 22), one token on 128 experts 80.2 -> 74.9, 16 tokens of the Mixtral
+// shape as a graph 296 -> 289, 777 tokens with Token-to-Expert 438 -> 427.
 #include "permute.h"
 #include "plan_regs.h"
 #include "route_tokens.h"
@@ -124,6 +124,7 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
         return MOE_ERR_INVALID_ARG;
     if (mode == MOE_MODE_DISTRIBUTION && !a->hist_pred) return MOE_ERR_INVALID_ARG;
     if (mode == MOE_MODE_TOKEN && (!a->pred_idx || !a->hist_plan)) return MOE_ERR_INVALID_ARG;
+    if (!a->x_perm && (int64_t)T * a->d >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;  // 32-bit element offsets into x
     const int64_t A = (int64_t)T * k;
     if (a->workspace_perm_bytes < moe_permute_workspace_bytes(T, E, k, G, S)) return MOE_ERR_WORKSPACE_TOO_SMALL;
     if (a->workspace_ffn_bytes < moe_grouped_ffn_workspace_bytes(A, a->d, a->ffn, G * S, a->dtype))
@@ -137,6 +138,21 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
         return moe_plan_duplicates(mode, hp, E, G, S, a->c_max, a->slot_expert, a->slot_quota, a->rank_load_pred,
                                    a->n_iters, stream);
     };
+    const float* gate = a->x_perm ? nullptr : a->gate_in_ffn ? a->topk_w : nullptr;
+    auto ffn = [&](FfnStage stage, TableJob* job) {
+        const bool gather = !a->x_perm;
+        return grouped_ffn_call(a->relu, gather ? a->x : a->x_perm, gather ? T : A, gather ? a->assign_of_row : nullptr,
+                                gather ? k : 1, gate ? a->assign_of_row : nullptr, gate, a->dtype, A, a->d, a->ffn, E,
+                                a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm, a->workspace_ffn,
+                                a->workspace_ffn_bytes, stream, stage, job);
+    };
+    TableJob job{};
+    if ((rc = ffn(kFfnJobOnly, &job)) != MOE_OK) return rc;  // (checks its limits, launches nothing)
+    // The workgroup that permutes builds the tables too where their tile heights are given: one token on 128
+    // experts 15.0 us against 8.9 and 6.9, 128 tokens 17.9 against 10.9 and 7.9, and a launch less.  Where it would
+    // have to choose them first, a launch of its own is ahead (1001 tokens, 8 experts 28.7 against 13.9 and 9.7).
+    const bool tables_too = small && job.t1.bm != 0 && (!job.t2.tiles || job.t2.bm != 0);
+    if (!tables_too) job = TableJob{};
     if (together) {
         const bool count = mode == MOE_MODE_TOKEN && A <= kPlanCountMax;
         if (mode == MOE_MODE_TOKEN && !count && (rc = moe_histogram(a->pred_idx, A, E, a->hist_plan, stream)) != MOE_OK)
@@ -152,7 +168,7 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     if (small) {
         const HomePlan home{a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters};
         rc = permute_and_count(mode, T, k, E, G, S, a->topk_idx, a->pred_idx, hp, a->slot_expert, a->slot_quota,
-                               a->seg_offsets, a->row_of_assign, a->assign_of_row, a->rank_load, a->hist, home, st);
+                               a->seg_offsets, a->row_of_assign, a->assign_of_row, a->rank_load, a->hist, home, job, st);
         if (rc == MOE_OK && a->x_perm) rc = scatter_rows(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm, st);
     } else {
         if ((rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
@@ -163,15 +179,6 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
                          a->workspace_perm_bytes, stream);
     }
     if (rc != MOE_OK) return rc;
-    const float* gate = a->x_perm ? nullptr : a->gate_in_ffn ? a->topk_w : nullptr;
-    if (a->x_perm)
-        rc = (a->relu ? moe_grouped_ffn_relu : moe_grouped_ffn)(
-            a->x_perm, a->dtype, A, a->d, a->ffn, E, a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed,
-            a->y_perm, a->workspace_ffn, a->workspace_ffn_bytes, stream);
-    else
-        rc = moe_grouped_ffn_fused(a->x, a->dtype, T, k, a->assign_of_row, gate, a->d, a->ffn, E, a->seg_offsets,
-                                   a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm, a->workspace_ffn,
-                                   a->workspace_ffn_bytes, stream);
-    if (rc != MOE_OK) return rc;
+    if ((rc = ffn(tables_too ? kFfnTablesBuilt : kFfnAll, nullptr)) != MOE_OK) return rc;
     return moe_combine(a->y_perm, a->dtype, T, a->d, k, a->row_of_assign, gate ? nullptr : a->topk_w, a->out, stream);
 }

@@ -1,6 +1,6 @@
 // Parts of the permutation that the whole-layer call launches on its own (permute.hip).
 #pragma once
-#include "common.h"
+#include "ffn_tables.h"
 
 namespace moegps {
 
@@ -12,11 +12,12 @@ struct HomePlan {
 // Whether moe_permute does the index steps of A assignments in one workgroup.
 bool permute_in_one_workgroup(int mode, int64_t A, int E, int nseg);
 
-// These index steps, with the histogram of topk_idx as an output (and in mode 0 the plan, `home`).
+// These index steps, with the histogram of topk_idx as an output (and in mode 0 the plan, `home`), and
+// the tables of the grouped FFN behind them if `job` has a row list.
 int permute_and_count(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
                       const int32_t* hist_pred, const int32_t* slot_expert, const int32_t* slot_quota,
                       int32_t* seg_offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* rank_load,
-                      int32_t* hist_out, const HomePlan& home, hipStream_t st);
+                      int32_t* hist_out, const HomePlan& home, const TableJob& job, hipStream_t st);
 
 // x_perm[row_of_assign[t*k + j], :] = x[t, :] (row bytes a multiple of 16, T >= 1).
 int scatter_rows(const void* x, int dtype, int T, int d, int k, const int32_t* row_of_assign, void* x_perm,

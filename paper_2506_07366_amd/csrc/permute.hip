@@ -578,16 +578,17 @@ __device__ __forceinline__ void small_slot_tables(int E, int nseg, const SmallTa
     }
 }
 
-// SR: rounds of 64 elements per wavefront, at most.  COUNTS: the histogram of topk_idx is an output (hist_out)
-// and not an input, and in mode 0 the home plan is too (`home`); both cost next to nothing here, where the
-// ids pass by anyway, and a launch of their own (4.7 us, 9.4 in mode 0) as calls.
-template <int SR, bool COUNTS>
+// SR: rounds of 64 elements per wavefront, at most.  WHOLE_STEP: the histogram of topk_idx is an output (hist_out)
+// and not an input, in mode 0 the home plan is too (`home`), and the workgroup goes on to build the
+// tables of the grouped FFN (`job`, if it has a row list).  The counts cost next to nothing here, where the ids pass by
+// anyway (as calls 4.7 us, 9.4 in mode 0), the tables their own work without another launch.
+template <int SR, bool WHOLE_STEP>
 __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     int mode, int T, int k, int E, int G, int S, const int32_t* __restrict__ topk_idx,
     const int32_t* __restrict__ pred_idx, const int32_t* __restrict__ hist_true, const int32_t* __restrict__ hist_pred,
     const int32_t* __restrict__ slot_expert, const int32_t* __restrict__ slot_quota,
     int32_t* __restrict__ seg_offsets, int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row,
-    int32_t* __restrict__ rank_load, int32_t* __restrict__ hist_out, HomePlan home) {
+    int32_t* __restrict__ rank_load, int32_t* __restrict__ hist_out, HomePlan home, TableJob job) {
     // one buffer, three lives: wavefront counters of the first rank; rank and key by position
     // (token-to-expert mode looks up those of the token's predicted ids); counters of the second
     __shared__ int buf[kSmallWaves * kSmallKeys];
@@ -629,7 +630,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
         }
     }
     for (int e = tid; e < E; e += kSmallThreads) e_home[e] = home_slot_of(e, H, S);
-    const bool count = COUNTS && mode != MOE_MODE_DISTRIBUTION;  // (there the ranks' counters are the histogram)
+    const bool count = WHOLE_STEP && mode != MOE_MODE_DISTRIBUTION;  // (there the ranks' counters are the histogram)
     if (count)
         for (int e = tid; e < E; e += kSmallThreads) e_true[e] = 0;
     if (mode != MOE_MODE_NONE) {
@@ -640,7 +641,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
             e_cnt[i] = 0;
             e_cum[i] = 0ll;
             if (mode == MOE_MODE_DISTRIBUTION && i < E) {
-                if (!COUNTS) e_true[i] = hist_true[i];
+                if (!WHOLE_STEP) e_true[i] = hist_true[i];
                 e_hat[i] = hist_pred[i];
             }
         }
@@ -650,7 +651,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
             small_slot_tables(E, nseg, t);
         }
         chunk_stable_rank<kSmallWaves, SR>(key, valid, E, buf, rank,
-                                           COUNTS && mode == MOE_MODE_DISTRIBUTION ? e_true : nullptr, rounds);
+                                           WHOLE_STEP && mode == MOE_MODE_DISTRIBUTION ? e_true : nullptr, rounds);
         __syncthreads();  // the counters are dead, the buffer becomes rank and key by position
 #pragma unroll
         for (int r = 0; r < SR; ++r) {
@@ -727,13 +728,13 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     block_exclusive_scan_2048(tot, nseg, wave_sum);
     for (int s = tid; s <= nseg; s += kSmallThreads) seg_offsets[s] = tot[s];
     for (int g = tid; g < G; g += kSmallThreads) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
-    if (COUNTS) {  // (barriers lie between the counting and here)
+    if (WHOLE_STEP) {  // (barriers lie between the counting and here)
         for (int e = tid; e < E; e += kSmallThreads) hist_out[e] = e_true[e];
         if (mode == MOE_MODE_NONE) {
             for (int s = tid; s < nseg; s += kSmallThreads) {
                 const int j = s % S, e = s / S * H + j;
                 const bool held = j < H && e < E;
-                home.slot_expert[s] = held ? e : -1;
+                s_e[s] = home.slot_expert[s] = held ? e : -1;
                 home.slot_quota[s] = held ? e_true[e] : 0;
             }
             for (int g = tid; g < G; g += kSmallThreads) home.rank_load_pred[g] = tot[(g + 1) * S] - tot[g * S];
@@ -747,6 +748,12 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
         const int row = tot[sg[r]] + rank[r];
         row_of_assign[p] = row;
         assign_of_row[row] = p;
+    }
+    if (WHOLE_STEP && job.rowlist) {
+        __syncthreads();  // the counters are dead for good
+        using Scratch = TableScratch<kSmallKeys, kSmallKeys, 2>;
+        static_assert(sizeof(Scratch) <= sizeof(buf), "the tables' scratch takes the counters' place");
+        build_tables(*(Scratch*)buf, 0, 1, 0, tot, s_e, job);
     }
 }
 
@@ -796,18 +803,19 @@ extern "C" size_t moe_permute_workspace_bytes(int T, int E, int k, int G, int S)
 }
 
 namespace moegps {
-template <bool COUNTS>
+template <bool WHOLE_STEP>
 static void launch_small(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
                          const int32_t* hist_true, const int32_t* hist_pred, const int32_t* slot_expert,
                          const int32_t* slot_quota, int32_t* seg_offsets, int32_t* row_of_assign,
                          int32_t* assign_of_row, int32_t* rank_load, int32_t* hist_out, const HomePlan& home,
-                         hipStream_t st) {
+                         const TableJob& job, hipStream_t st) {
     const int64_t A = (int64_t)T * k;
-    hipLaunchKernelGGL((A <= 2 * kSmallThreads ? perm_small_kernel<2, COUNTS>
-                        : A <= 3 * kSmallThreads ? perm_small_kernel<3, COUNTS>
-                        : A <= 4 * kSmallThreads ? perm_small_kernel<4, COUNTS> : perm_small_kernel<kSmallMaxRounds, COUNTS>),
+    hipLaunchKernelGGL((A <= 2 * kSmallThreads ? perm_small_kernel<2, WHOLE_STEP>
+                        : A <= 3 * kSmallThreads ? perm_small_kernel<3, WHOLE_STEP>
+                        : A <= 4 * kSmallThreads ? perm_small_kernel<4, WHOLE_STEP>
+                                                 : perm_small_kernel<kSmallMaxRounds, WHOLE_STEP>),
                        dim3(1), dim3(kSmallThreads), 0, st, mode, T, k, E, G, S, topk_idx, pred_idx, hist_true, hist_pred,
-                       slot_expert, slot_quota, seg_offsets, row_of_assign, assign_of_row, rank_load, hist_out, home);
+                       slot_expert, slot_quota, seg_offsets, row_of_assign, assign_of_row, rank_load, hist_out, home, job);
 }
 
 bool permute_in_one_workgroup(int mode, int64_t A, int E, int nseg) { return A <= one_workgroup_limit(mode, E, nseg); }
@@ -815,9 +823,9 @@ bool permute_in_one_workgroup(int mode, int64_t A, int E, int nseg) { return A <
 int permute_and_count(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
                       const int32_t* hist_pred, const int32_t* slot_expert, const int32_t* slot_quota,
                       int32_t* seg_offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* rank_load,
-                      int32_t* hist_out, const HomePlan& home, hipStream_t st) {
+                      int32_t* hist_out, const HomePlan& home, const TableJob& job, hipStream_t st) {
     launch_small<true>(mode, T, k, E, G, S, topk_idx, pred_idx, nullptr, hist_pred, slot_expert, slot_quota, seg_offsets,
-                       row_of_assign, assign_of_row, rank_load, hist_out, home, st);
+                       row_of_assign, assign_of_row, rank_load, hist_out, home, job, st);
     return check_launch();
 }
 
@@ -865,7 +873,8 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
     const int64_t A = (int64_t)T * k;
     if (A <= one_workgroup_limit(mode, E, G * S)) {
         launch_small<false>(mode, T, k, E, G, S, topk_idx, pred_idx, hist_true, hist_pred, slot_expert, slot_quota,
-                            seg_offsets, row_of_assign, assign_of_row, rank_load, nullptr, HomePlan{}, st);
+                            seg_offsets, row_of_assign, assign_of_row, rank_load, nullptr, HomePlan{},
+                            TableJob{}, st);
         if ((rc = check_launch()) != MOE_OK) return rc;
     } else {
         const bool scanned = nb == 0 || (nb > kSelfScanChunks && ws.rounds == kRounds);
