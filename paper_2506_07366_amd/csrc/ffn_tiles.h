@@ -22,6 +22,7 @@
 
 constexpr int kTileMaxRows = 256;  // rows of the tallest tile
 constexpr int kTileGroup = 4;      // N-tiles walked side by side
+constexpr int kNonTemporal = 2;    // cache policy of a buffer load: nt
 constexpr size_t kTileLds = (size_t)3 * kTileMaxRows * kPackK * 2;  // dynamic LDS of a workgroup
 
 template <int EPI>
@@ -30,7 +31,7 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
     const bf16_t* __restrict__ Bp, size_t b_stride,  // packed weights [E][N-tile][k-tile][kPackN x kPackK]
     bf16_t* __restrict__ C, int ldc,                 // output [rows, SWIGLU ? N/2 : N]
     const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int32_t* __restrict__ queues,
-    int N, int K, int group_n, RowMap rm,
+    int N, int K, int group_n, bool past_caches, RowMap rm,
     float* __restrict__ partials) {  // [slab][kPartRows][N] fp32 sums of entries that cover part of K (plain product only)
     constexpr bool SWIGLU = EPI == kEpiSwiglu;
     constexpr int BN = kPackN, BK = kPackK, NW = 8;
@@ -182,8 +183,14 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
         // extends that to every wavefront's, and says that the stage of this k-tile is free.  The loads of
         // k-tile kt + D - 1 go into the buffers that k-tile kt - 1 has left, dealt over the fragments before the hand-over.
         // (k-tile kt uses buffers kt % D; the loop is unrolled by D so that these are registers by name.)
-        auto k_loop = [&](auto TM_tag) {
+        // once_tag: no other tile wants these weights (the expert's only M-tile, over all of K), they are read past
+        // the caches, which are left to the rows.  Products 1 and 2, us, without -> with it: 128 experts of 4096 x
+        // 1536, 400 tokens 170 + 103 -> 151 + 98, 1024 on all of them 568 + 316 -> 515 + 312; 64 of 2048 x 1408, 1024
+        // tokens 168 + 92 -> 152 + 88; 8 of 4096 x 14336, 256 tokens 289 + 197 -> 270 + 206, 512 tokens, most
+        // experts with two M-tiles, 330 + 211 -> 322 + 222.  26 batches: 2.1 % on average, 0.991 the worst.
+        auto k_loop = [&](auto TM_tag, auto once_tag) {
             constexpr int TM = decltype(TM_tag)::value;
+            constexpr int kAux = decltype(once_tag)::value ? kNonTemporal : 0;
             constexpr int D = TM <= 8 ? 4 : 3;                          // k-tiles under way
             constexpr int STAGE = (TM <= 8 ? 128 : 256) * ROW_BYTES;    // activation bytes of one of them
             static_assert((size_t)D * STAGE <= kTileLds, "LDS of the launch");
@@ -215,7 +222,7 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
                     constexpr int j = l >> 1, ks = l & 1;
                     const unsigned off = in ? lane_off + (unsigned)kt * B_BYTES : kWPast;
                     w[b][j][ks] = __builtin_bit_cast(
-                        bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off + ks * kFragElems * 2, j * JB, 0));
+                        bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off + ks * kFragElems * 2, j * JB, kAux));
                 } else {
                     constexpr int i = l - 4;
                     const unsigned off = in ? offA[i] + (unsigned)kt * ROW_BYTES : kAPast;
@@ -304,9 +311,14 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
             for (int r = 0; r < R; ++r) lds_landed(af[r]);
         };
         // one K loop per 32 rows of height; every one runs the same barriers
+        const bool once = past_caches && mt.part < 0 && mt.n_same == 1;
         static_for<TM_MAX / 2>([&](auto H2) {
             constexpr int tm = 2 * decltype(H2)::value + 2;
-            if (mt.rows > 16 * (tm - 2) && mt.rows <= 16 * tm) k_loop(std::integral_constant<int, tm>{});
+            const std::integral_constant<int, tm> TM{};
+            if (mt.rows > 16 * (tm - 2) && mt.rows <= 16 * tm) {
+                if (once) k_loop(TM, std::true_type{});
+                else k_loop(TM, std::false_type{});
+            }
         });
         // every wavefront has read next_tile (the K loop holds a barrier)
         if (wave == 0) next_tile = settle_claim(ahead_q, __builtin_amdgcn_readfirstlane(ahead_pending));

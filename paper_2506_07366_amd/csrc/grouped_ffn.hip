@@ -499,10 +499,17 @@ static int num_cus() {
     return cus;
 }
 
+// Weights of a product above this are read past the caches by tiles that share them with no other tile: the
+// next product or call would not find them there anyway.  128 MiB is half the memory-side cache, which the weights
+// of both products pass through.  Below it the caches are worth more: 16 experts of 1024 x 512 (16 + 8 MiB), 1500 tokens,
+// both products 33 us through the caches, 35 past them.  Above it: see the K loop of the tile kernel.
+constexpr size_t kCachedWeights = (size_t)128 << 20;
+
 template <int EPI>
-static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_stride, bf16_t* C, int ldc,
+static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_stride, int E, bf16_t* C, int ldc,
                         const MTile* tiles, const int32_t* counts, int32_t* queues, int N, int K, int group_n,
                         const RowMap& rm, float* partials, hipStream_t st) {
+    const bool past_caches = (size_t)E * b_stride * sizeof(bf16_t) > kCachedWeights;
     // the kernel uses more LDS than the default limit: raised once per kernel and device
     static std::atomic<unsigned long long> attr_set{0};  // bit per device
     const auto kern = grouped_gemm_tile_kernel<EPI>;
@@ -519,7 +526,7 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
     }
     // 32 workgroups for each of the 8 XCDs; they claim tiles from `queues` (cleared by the table builder)
     hipLaunchKernelGGL(kern, dim3(kGemmGrid), dim3(512), kTileLds, st, A, lda, Bp, b_stride, C, ldc, tiles, counts,
-                       queues, N, K, group_n, rm, partials);
+                       queues, N, K, group_n, past_caches, rm, partials);
     return check_launch();
 }
 
@@ -535,8 +542,8 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
 //     4096 x 14336, 128 rows on 8 / 1 519 -> 421 / 162 -> 135; but not with so many experts that the tiles of A
 //     rows on one of them are more than 128 k-tiles per CU (512 experts of 4096 x 1536, first product, 6144 rows on
 //     512 / 64: 2062 -> 1917 / 288 -> 373);
-//   up to 24 where those are no more than 18 per CU and K is not short (64 experts of 2048 x 1408, 132 tiles of 32 and 96 of 22,
-//     1536 rows on 64 / 16 / 1 214 -> 186 / 85 -> 75 / 71 -> 60); with more than that too much is lost (128 experts
+//   up to 24 where those are no more than 18 per CU and K is not short (64 experts of 2048 x 1408, 132 tiles of
+//     32 and 96 of 22, 1536 rows on 64 / 16 / 1 214 -> 186 / 85 -> 75 / 71 -> 60); with more than that too much is lost (128 experts
 //     of 4096 x 1536, 240 tiles of 64 and 320 of 24, 2560 rows on 128 / 32 / 16 820 -> 772 / 261 -> 282 / 187 ->
 //     209; 64 experts of 4096 x 4096, second product, 160 tiles of 64, 1280 rows on 16 / 8 / 4 102 -> 122 / 73 ->
 //     90 / 68 -> 84; 1024 experts of 1024 x 512, second product, 8 k-tiles, 18432 rows on 16 / 1 39 -> 46 / 40 -> 47);
@@ -812,7 +819,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
                                               (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, st);
     } else {
         const auto go = relu ? launch_tiles<kEpiRelu> : launch_tiles<kEpiSwiglu>;
-        rc = go((const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, ws.queues,
+        rc = go((const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), E, (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, ws.queues,
                 n1 * fp, d, group_n, rm1, nullptr, st);
     }
     if (timed) (void)hipEventRecord(g_time_events[1], st);
@@ -822,7 +829,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
         rc = launch_stream<kEpiNone>(s2, A, E, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d,
                                      tiles2, count2, d, fp, rm2, st);
     else
-        rc = launch_tiles<kEpiNone>((const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d, tiles2, count2,
+        rc = launch_tiles<kEpiNone>((const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), E, (bf16_t*)y_perm, d, tiles2, count2,
                                     ws.queues + 8, d, fp, group_n, rm2, ws.partials, st);
     if (rc == MOE_OK && split) {
         hipLaunchKernelGGL(add_partials_kernel, dim3(ws.split_capacity < 64 ? ws.split_capacity : 64, 32), dim3(256),

@@ -496,6 +496,28 @@ def test_ffn_tile_heights_and_depths(d, ffn, relu, ffn_options):
     assert np.all(np.max(np.abs(got - ref), axis=1) <= TOL["bf16"] * np.max(np.abs(ref)))
 
 
+@pytest.mark.parametrize("relu", [False, True])
+def test_ffn_weights_read_past_the_caches(relu, ffn_options):
+    """A layer whose weights are too large for the caches reads those of an expert's only M-tile past them,
+    whatever its height: the same bits as the same experts in a small layer."""
+    ffn_options(tile1=0, tile2=0, split=0)
+    d, ffn, many = 512, 832, 170                   # W2 of 170 experts: 138 MiB; 8 and 13 k-tiles
+    sizes = [1, 31, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 256, 256 + 40]
+    E, A = len(sizes), sum(sizes)
+    gen = torch.Generator().manual_seed(51)
+    w = [(torch.randn(E, *shape, generator=gen) * 0.05).to(torch.bfloat16).cuda()
+         for shape in ([(d, ffn)] if relu else [(d, ffn), (d, ffn)]) + [(ffn, d)]]
+    x = torch.randn(A, d, generator=gen).to(torch.bfloat16).cuda()
+    so = dev_i32(np.concatenate([[0], np.cumsum(sizes)]))
+    got = []
+    for n in (E, many):
+        # the small layer's experts are the large one's last
+        packed = (B.moe_pack_weights_relu if relu else B.moe_pack_weights)(
+            *[torch.cat([torch.zeros(n - E, *m.shape[1:], dtype=m.dtype, device=m.device), m]) for m in w])
+        got.append(B.moe_grouped_ffn(x, so, dev_i32(range(n - E, n)), packed, n, ffn, relu=relu))
+    assert torch.equal(got[0], got[1]) and torch.isfinite(got[0]).all() and got[0].any(dim=1).all()
+
+
 @pytest.mark.parametrize("split", [-1, 0, 1])
 @pytest.mark.parametrize("sizes", [
     [2049, 0, 2048, 1793, 257, 65],   # more and not more tiles than heights at 256 rows, a short last tile
