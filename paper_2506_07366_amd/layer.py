@@ -1,4 +1,4 @@
-"""One MoE FFN layer with dynamic expert duplication, as a sequence of C-ABI calls.
+"""One MoE FFN layer with dynamic expert duplication, as one C-ABI call or a sequence of them.
 
 ``MoELayer`` owns the device buffers (allocated once through torch) and runs the
 path route -> histogram -> duplication plan -> permute -> grouped FFN -> combine
