@@ -32,8 +32,8 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # reads for the library's plain copy kernel).  The figures come from the profile named in
 # `profile`, not from this run, and belong to one version of the kernel source: they are
 # reported only while its digest still matches and no tuning option is forced.
-KERNEL_SOURCE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2506_07366_amd", "csrc",
-                             "grouped_ffn.hip")
+KERNEL_SOURCES = [os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2506_07366_amd", "csrc", f)
+                  for f in ("grouped_ffn.hip", "ffn_tiles.h", "ffn_tables.h")]
 TRAFFIC = {
     "cfg2_mixtral_dist": {"source_sha256": "b145f100b2c17601aa170ea9e97129a1dc282f2deb473dc7bbe86dba282b4a97",
                           "fetch_bytes": 5546718416, "write_bytes": 235025126,
@@ -45,11 +45,14 @@ def measured_traffic(config_name):
     """(bytes per launch, profile it comes from) or (None, None)."""
     import hashlib
     rec = TRAFFIC.get(config_name)
-    if not rec or not rec["source_sha256"] or not os.path.exists(KERNEL_SOURCE):
+    if not rec or not rec["source_sha256"] or not all(os.path.exists(p) for p in KERNEL_SOURCES):
         return None, None
-    with open(KERNEL_SOURCE, "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != rec["source_sha256"]:
-            return None, None
+    sha = hashlib.sha256()
+    for p in KERNEL_SOURCES:
+        with open(p, "rb") as f:
+            sha.update(f.read())
+    if sha.hexdigest() != rec["source_sha256"]:
+        return None, None
     return rec["fetch_bytes"] + rec["write_bytes"], rec["profile"]
 
 
@@ -277,8 +280,8 @@ def main():
         g1_ms = float(np.mean([q[0].elapsed_time(q[1]) for q in evs]))
         g2_ms = float(np.mean([q[2].elapsed_time(q[3]) for q in evs]))
         achieved = flops1 / (g1_ms * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": ("grouped_gemm_bf16_kernel<relu> (first product)" if cfg.act == "relu"
-                                                else "grouped_gemm_bf16_kernel<swiglu> (gate/up product)"),
+        roofline = {"bound": "mfma", "kernel": ("grouped_gemm_tile_kernel<relu> (first product)" if cfg.act == "relu"
+                                                else "grouped_gemm_tile_kernel<swiglu> (gate/up product)"),
                     "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                     "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic, "traffic_source": traffic_source,
                     "avg_ms": g1_ms,
