@@ -35,8 +35,8 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 KERNEL_SOURCES = [os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2506_07366_amd", "csrc", f)
                   for f in ("grouped_ffn.hip", "ffn_tiles.h", "ffn_tables.h")]
 TRAFFIC = {
-    "cfg2_mixtral_dist": {"source_sha256": "b145f100b2c17601aa170ea9e97129a1dc282f2deb473dc7bbe86dba282b4a97",
-                          "fetch_bytes": 5546718416, "write_bytes": 235025126,
+    "cfg2_mixtral_dist": {"source_sha256": "0477f0c2a58294cad3dd01a4f666891e8c7fb544893c277cf55ebdb28ad3821e",
+                          "fetch_bytes": 5670507540, "write_bytes": 235089928,
                           "profile": "profiles/gemm1_cfg2_mixtral_traffic_counters.md"},
 }
 

@@ -535,8 +535,11 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
 // a row gets the same bits from a launch over some slots as from one over all.  How the rows lie is
 // only known on the device, so a line has to do for all rows on one expert as well as for an equal share
 // on each.  Spread out, the streaming forms lead far beyond these lines; batches that lie on a
-// few experts fall behind once the LDS-staged tiles of so many rows fill the chip.  Both
-// products, us, tiles -> streaming:
+// few experts fall behind once the tiles of so many rows fill the chip.  The figures are from tiles with both operands in
+// LDS and of one height; against the present ones, both products, us, tiles -> streaming: 128 experts of 4096 x 1536, 2048
+// rows on 128 / 16 / 1 750 -> 739 / 126 -> 166 / 89 -> 107; 64 of 2048 x 1408, 1536 rows on 64 / 16 / 1 190 -> 186 /
+// 80 -> 78 / 48 -> 58; 16 of 4096 x 688, 1024 rows on 16 / 1 84 -> 65 / 53 -> 48; 8 of 4096 x 14336, 128 rows on 8 / 1
+// 466 -> 425 / 126 -> 135.  As the lines were set, both products, us, tiles -> streaming:
 //   up to 16 rows per expert on average: 128 experts of 4096 x 1536, 2048 rows on all of them 807 -> 736, on
 //     16 140 -> 165, on one 102 -> 108 (1536 rows on all 128 823 -> 730, on 16 136 -> 155); 8 experts of
 //     4096 x 14336, 128 rows on 8 / 1 519 -> 421 / 162 -> 135; but not with so many experts that the tiles of A
