@@ -70,7 +70,8 @@ int moe_abi_version(void);
  *   topk_idx [T, k] int32  out  experts ordered by (logit descending, index
  *                               ascending): equal logits go to the lowest index
  *   topk_w   [T, k] float  out  softmax over the k selected logits
- * 1 <= k <= min(E, MOE_MAX_TOPK), E <= MOE_MAX_EXPERTS.  T = 0 is a no-op.
+ * 1 <= k <= min(E, MOE_MAX_TOPK), E <= MOE_MAX_EXPERTS.  T = 0 is a no-op.  T times the lanes of
+ * a token (2, 4 and 8 for up to so many experts, 16 up to 512, 32 above) stays below 2^32.
  */
 int moe_route_topk(const float* logits, int T, int E, int k,
                    int32_t* topk_idx, float* topk_w, void* stream);

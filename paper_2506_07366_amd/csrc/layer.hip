@@ -80,8 +80,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_plan_kernel(PlanJob p, co
 
 static int route_and_plan(const PlanJob& p, const float* logits, int T, int k, int32_t* topk_idx, float* topk_w,
                           hipStream_t st) {
-    const int lanes = p.E <= 2 ? 2 : p.E <= 4 ? 4 : p.E <= 8 ? 8 : 16;  // per token, as moe_route_topk has them
-    const int grid = 1 + ceil_div(T, kRouteThreads / lanes);
+    const int grid = 1 + route_blocks(T, p.E);
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(grid), dim3(kRouteThreads), (size_t)p.E * kWave, st, p, logits, T, k, topk_idx, topk_w);
         return check_launch();
@@ -114,7 +113,7 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     if (E > MOE_MAX_EXPERTS || k > MOE_MAX_TOPK || G > MOE_MAX_RANKS || S > MOE_MAX_SLOTS || G * S > MOE_MAX_SEGMENTS)
         return MOE_ERR_UNSUPPORTED;
     if (ceil_div(E, G) > S) return MOE_ERR_INVALID_ARG;
-    if ((int64_t)T * k >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;
+    if ((int64_t)T * k >= (1ll << 31) || route_blocks(T, E) >= kRouteMaxBlocks) return MOE_ERR_UNSUPPORTED;
     if (((size_t)a->d * dtype_size(a->dtype)) % 16 != 0) return MOE_ERR_UNSUPPORTED;
     if (a->relu && !a->x_perm) return MOE_ERR_UNSUPPORTED;  // the row gather is built for the SwiGLU form only
     if (T == 0) return MOE_OK;

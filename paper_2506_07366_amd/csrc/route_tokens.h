@@ -64,12 +64,27 @@ __device__ __forceinline__ int group_min(int e) {
 // exponential per lane, summed over the group's lanes.
 // Workgroup `block` of those that share the tokens, kRouteThreads threads each.
 constexpr int kRouteThreads = 256;
+constexpr int kRouteMaxBlocks = (int)((1ll << 32) / kRouteThreads) - 1;  // a launch counts its threads in 32 bits
+
+// Wavefront of a thread.  It does not go by the thread's number, which passes 2^31 at 2^27 tokens of 16 lanes.
+__host__ __device__ constexpr int route_wave(int block, int thread) {
+    return block * (kRouteThreads / kWave) + thread / kWave;
+}
+static_assert(route_wave(kRouteMaxBlocks - 1, kRouteThreads - 1) == ((long long)kRouteMaxBlocks * kRouteThreads - 1) / kWave &&
+              (route_wave(kRouteMaxBlocks - 1, kRouteThreads - 1) + 1ll) * (kWave / 2) < 1ll << 31,
+              "wavefronts of the largest launch, and tokens at the fewest lanes each, are ints");
+
+// Lanes that own a token: the power of two covering E up to one row of 16 lanes, which then holds ceil(E/16)
+// logits per lane, two rows above 512; k <= min(E, 16) <= lanes always holds.
+constexpr int route_lanes(int E) { return E <= 2 ? 2 : E <= 4 ? 4 : E <= 8 ? 8 : E <= 512 ? 16 : 32; }
+constexpr int route_blocks(int T, int E) { return ceil_div(T, kRouteThreads / route_lanes(E)); }
+
 template <int LPT, int VPL>
 __device__ __forceinline__ void route_tokens(int block, const float* __restrict__ logits, int T, int E, int k,
                                              int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
     constexpr int TPW = kWave / LPT;  // tokens per wavefront
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = (block * kRouteThreads + (int)threadIdx.x) / kWave;
+    const int wave = route_wave(block, threadIdx.x);
     const int sub = lane % LPT;
     const int token = wave * TPW + lane / LPT;
     const bool live = token < T;

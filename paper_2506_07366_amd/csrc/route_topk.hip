@@ -12,10 +12,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(const float* 
 
 template <int LPT, int VPL>
 static int launch_route(const float* logits, int T, int E, int k, int32_t* idx, float* w, hipStream_t st) {
-    constexpr int TPW = kWave / LPT;
-    const int tokens_per_block = 4 * TPW;
-    const int grid = ceil_div(T, tokens_per_block);
-    hipLaunchKernelGGL((route_topk_kernel<LPT, VPL>), dim3(grid), dim3(kRouteThreads), 0, st, logits, T, E, k, idx, w);
+    hipLaunchKernelGGL((route_topk_kernel<LPT, VPL>), dim3(ceil_div(T, kRouteThreads / LPT)), dim3(kRouteThreads), 0, st,
+                       logits, T, E, k, idx, w);
     return check_launch();
 }
 
@@ -26,11 +24,11 @@ extern "C" int moe_route_topk(const float* logits, int T, int E, int k, int32_t*
     using namespace moegps;
     if (T < 0 || E < 1 || k < 1 || k > E) return MOE_ERR_INVALID_ARG;
     if (E > MOE_MAX_EXPERTS || k > MOE_MAX_TOPK) return MOE_ERR_UNSUPPORTED;
+    if (route_blocks(T, E) > kRouteMaxBlocks) return MOE_ERR_UNSUPPORTED;
     if (T == 0) return MOE_OK;
     if (!logits || !topk_idx || !topk_w) return MOE_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
-    // lanes per token: the power of two covering E up to one row of 16 lanes, which then
-    // holds ceil(E/16) logits per lane; k <= min(E, 16) <= lanes always holds
+    // lanes per token as route_lanes has them
     if (E <= 2) return launch_route<2, 1>(logits, T, E, k, topk_idx, topk_w, st);
     if (E <= 4) return launch_route<4, 1>(logits, T, E, k, topk_idx, topk_w, st);
     if (E <= 8) return launch_route<8, 1>(logits, T, E, k, topk_idx, topk_w, st);

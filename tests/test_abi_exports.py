@@ -59,6 +59,13 @@ def test_host_side_argument_checks_need_no_gpu():
     assert lib.moe_grouped_ffn_workspace_bytes(8192, 4096, 14336, 16, 1) >= 8192 * 14336 * 2
 
 
+@pytest.mark.parametrize("E,lanes", [(2, 2), (4, 4), (8, 8), (9, 16), (512, 16), (513, 32)])
+def test_routing_refuses_more_threads_than_a_launch_holds(E, lanes):
+    """Tokens times lanes of a token from 2^32 on, which no launch can count, are refused on the host."""
+    from paper_2506_07366_amd import binding
+    assert binding.load_library().moe_route_topk(16, min(2**31 - 1, 2**32 // lanes), E, 1, 16, 16, None) == -2
+
+
 def test_missing_library_fails_loudly(tmp_path):
     from paper_2506_07366_amd import binding
     with pytest.raises(binding.MoeGpsError):
