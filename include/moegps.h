@@ -249,6 +249,9 @@ int moe_grouped_ffn_gather(const void* x, int dtype, int T, int k, const int32_t
  *   x_perm NULL: the FFN gathers the token rows (moe_grouped_ffn_gather), and with gate_in_ffn
  *   it applies the gate weights (moe_grouped_ffn_fused); SwiGLU only.
  *   hist_pred is read in mode 1; pred_idx is read and hist_plan (its histogram) written in mode 2.
+ *   Either may lie in topk_idx, topk_w or hist, and is then what this step writes there (topk_idx as
+ *   pred_idx: perfect prediction; hist as hist_pred: a plan on the true counts).  Outputs and
+ *   workspaces do not overlap one another.
  * T = 0 is a no-op.  Arguments are checked before the first launch; on MOE_ERR_HIP earlier steps may
  * have been enqueued.
  */

@@ -7,7 +7,8 @@
 //     after counting the predicted ids) while the others of the same launch route the tokens;
 //   - where the permutation is one workgroup's work it also writes the histogram, without a prediction
 //     the plan, which then is the home placement, and goes on to the tables of the grouped FFN.
-// Anything else goes through the calls of the single steps; the results are the same integers either way.
+// Anything else goes through the calls of the single steps, in their order; the results are the same integers
+// either way.
 // Whole steps, us, six calls (seven with predicted ids) -> one: 256 tokens of the small fp32 layer 45.0 -> 39.9 (no
 // longer bound by the host, which takes 22), one token on 128 experts 80.2 -> 74.9, 16 tokens of the Mixtral
 // shape as a graph 296 -> 289, 777 tokens with Token-to-Expert 438 -> 427.
@@ -99,6 +100,10 @@ static int route_and_plan(const PlanJob& p, const float* logits, int T, int k, i
     }
 }
 
+static bool share_bytes(const void* a, size_t na, const void* b, size_t nb) {
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 }  // namespace moegps
 
 extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
@@ -131,8 +136,16 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     int rc;
     const int32_t* hp = mode == MOE_MODE_TOKEN ? a->hist_plan : mode == MOE_MODE_DISTRIBUTION ? a->hist_pred : a->hist;
-    const bool small = permute_in_one_workgroup(mode, A, E, G * S);
-    const bool together = mode != MOE_MODE_NONE && E <= kPlanMaxExperts && S <= kPlanMaxSlots && G <= 32;
+    // The prediction may be one of the step's own outputs (topk_idx as predicted ids, hist as predicted counts): it
+    // then is what this step writes there, and nothing may run ahead of that or beside it.
+    const size_t ids = (size_t)A * sizeof(int32_t), counts = (size_t)E * sizeof(int32_t);
+    const void* pred = mode == MOE_MODE_TOKEN ? a->pred_idx : mode == MOE_MODE_DISTRIBUTION ? a->hist_pred : nullptr;
+    const size_t n_pred = mode == MOE_MODE_TOKEN ? ids : counts;
+    const bool own_pred = pred && (share_bytes(pred, n_pred, a->topk_idx, ids) || share_bytes(pred, n_pred, a->topk_w, ids) ||
+                                   share_bytes(pred, n_pred, a->hist, counts));
+    const bool small = !own_pred && permute_in_one_workgroup(mode, A, E, G * S);
+    const bool together =
+        !own_pred && mode != MOE_MODE_NONE && E <= kPlanMaxExperts && S <= kPlanMaxSlots && G <= 32;
     auto plan = [&] {
         return moe_plan_duplicates(mode, hp, E, G, S, a->c_max, a->slot_expert, a->slot_quota, a->rank_load_pred,
                                    a->n_iters, stream);
@@ -161,6 +174,7 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
         if ((rc = route_and_plan(p, a->logits, T, k, a->topk_idx, a->topk_w, st)) != MOE_OK) return rc;
     } else {
         if ((rc = moe_route_topk(a->logits, T, E, k, a->topk_idx, a->topk_w, stream)) != MOE_OK) return rc;
+        if (own_pred && (rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
         if (mode == MOE_MODE_TOKEN && (rc = moe_histogram(a->pred_idx, A, E, a->hist_plan, stream)) != MOE_OK) return rc;
         if (mode != MOE_MODE_NONE && (rc = plan()) != MOE_OK) return rc;
     }
@@ -170,7 +184,7 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
                                a->seg_offsets, a->row_of_assign, a->assign_of_row, a->rank_load, a->hist, home, job, st);
         if (rc == MOE_OK && a->x_perm) rc = scatter_rows(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm, st);
     } else {
-        if ((rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
+        if (!own_pred && (rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
         if (mode == MOE_MODE_NONE && (rc = plan()) != MOE_OK) return rc;
         rc = moe_permute(mode, a->x_perm ? a->x : nullptr, a->dtype, T, a->d, E, k, G, S, a->topk_idx,
                          mode == MOE_MODE_TOKEN ? a->pred_idx : nullptr, a->hist, hp, a->slot_expert, a->slot_quota,

@@ -68,6 +68,41 @@ def test_step_equals_single_calls(T, E, k, G, S, dtype, mode):
             assert torch.equal(layer.hist_plan, plan_hist)
 
 
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("T,E,k,G,S", [
+    (64, 16, 2, 4, 5),        # one workgroup permutes, routing and plan would share a launch
+    (3000, 16, 8, 4, 5),      # 24000 ids: three launches permute, a launch of its own counts the predicted ids
+    (100, 300, 4, 32, 10),    # routing and plan never share a launch
+])
+def test_step_on_its_own_outputs_as_prediction(T, E, k, G, S, mode):
+    """A perfect prediction is the step's own topk_idx (or hist): the step uses what it has just written there,
+    as the single calls do, and not what an earlier batch left."""
+    cfg = wl.MoEConfig("own", T=T, d=64, ffn=64, E=E, k=k, G=G, S=S, dtype="bf16", mode=mode, seed=63)
+    gen = torch.Generator(device="cuda").manual_seed(64)
+    ws = [torch.randn(s, device="cuda", generator=gen).mul_(0.02).to(torch.bfloat16)
+          for s in ((E, 64, 64), (E, 64, 64), (E, 64, 64))]
+    want_layer, layer = MoELayer(cfg), MoELayer(cfg)
+    want_layer.set_weights(*ws)
+    layer.set_weights(*ws)
+    skew = torch.log1p(torch.arange(E, device="cuda", dtype=torch.float32))
+    for batch in range(2):                             # (the second finds the first one's ids and counts in place)
+        logits = torch.randn((T, E), device="cuda", generator=gen) + (skew if batch else -skew)
+        x = torch.randn((T, 64), device="cuda", generator=gen).to(torch.bfloat16)
+        want_layer.route(logits)
+        want_layer.histogram()
+        want_layer.plan(mode, want_layer.hist, want_layer.topk_idx)
+        want_layer.permute(mode, x, want_layer.topk_idx)
+        want_layer.ffn()
+        want_layer.combine()
+        if batch == 0:
+            layer.hist.zero_()
+            layer.topk_idx.zero_()
+        assert layer._one_call(logits, x, layer.hist, layer.topk_idx, mode)
+        want, got = outputs(want_layer), outputs(layer)
+        for n, v in want.items():
+            assert torch.equal(got[n], v), n
+
+
 def test_step_leaves_other_inputs_to_the_single_calls():
     """Inputs that are not the layer's own sizes keep the behaviour (and the errors) of the single calls."""
     cfg = wl.CONFIGS["mid_bf16"]
