@@ -613,20 +613,26 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
 
     int key[SR], rank[SR], expert[SR];
     bool valid[SR];
+    unsigned no_expert = 0;  // bit r: the id of round r is outside [0, E) (NaN logits), which no histogram counts
     const int32_t* rank_keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
 #pragma unroll
     for (int r = 0; r < SR; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         valid[r] = r < rounds && p < n_b;
-        key[r] = valid[r] ? clamp_key(rank_keys[p], E) : 0;
+        const int id = valid[r] ? rank_keys[p] : 0;
+        key[r] = clamp_key(id, E);
         expert[r] = key[r];
+        if (WHOLE_STEP && key[r] != id) no_expert |= 1u << r;
         rank[r] = 0;
     }
     if (mode == MOE_MODE_TOKEN) {
+        no_expert = 0;
 #pragma unroll
         for (int r = 0; r < SR; ++r) {
             const int p = (w * rounds + r) * kWave + lane;
-            if (valid[r]) expert[r] = clamp_key(topk_idx[p], E);
+            const int id = valid[r] ? topk_idx[p] : 0;
+            expert[r] = clamp_key(id, E);
+            if (WHOLE_STEP && expert[r] != id) no_expert |= 1u << r;
         }
     }
     for (int e = tid; e < E; e += kSmallThreads) e_home[e] = home_slot_of(e, H, S);
@@ -652,6 +658,10 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
         }
         chunk_stable_rank<kSmallWaves, SR>(key, valid, E, buf, rank,
                                            WHOLE_STEP && mode == MOE_MODE_DISTRIBUTION ? e_true : nullptr, rounds);
+        if (WHOLE_STEP && mode == MOE_MODE_DISTRIBUTION && no_expert != 0)
+#pragma unroll
+            for (int r = 0; r < SR; ++r)
+                if ((no_expert >> r) & 1) atomicAdd(&e_true[key[r]], -1);
         __syncthreads();  // the counters are dead, the buffer becomes rank and key by position
 #pragma unroll
         for (int r = 0; r < SR; ++r) {
@@ -674,7 +684,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     if (count)
 #pragma unroll
         for (int r = 0; r < SR; ++r)
-            if (valid[r]) atomicAdd(&e_true[expert[r]], 1);
+            if (valid[r] && !((no_expert >> r) & 1)) atomicAdd(&e_true[expert[r]], 1);
 
     // segment of every assignment: its place i in the plan's order for its expert (-1: none),
     // then a walk over the expert's slots, at most G of them, to the one whose range holds i;
@@ -737,7 +747,11 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
                 s_e[s] = home.slot_expert[s] = held ? e : -1;
                 home.slot_quota[s] = held ? e_true[e] : 0;
             }
-            for (int g = tid; g < G; g += kSmallThreads) home.rank_load_pred[g] = tot[(g + 1) * S] - tot[g * S];
+            for (int g = tid; g < G; g += kSmallThreads) {
+                int load = 0;
+                for (int e = g * H; e < (g + 1) * H && e < E; ++e) load += e_true[e];
+                home.rank_load_pred[g] = load;
+            }
             if (tid == 0) home.n_iters[0] = 0;
         }
     }

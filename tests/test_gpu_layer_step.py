@@ -103,6 +103,40 @@ def test_step_on_its_own_outputs_as_prediction(T, E, k, G, S, mode):
             assert torch.equal(got[n], v), n
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("T,E,k,G,S", [(64, 16, 2, 4, 5),      # one workgroup permutes
+                                       (700, 12, 4, 5, 3),     # the same without predicted ids, an uneven home placement
+                                       (3000, 16, 8, 4, 5)])
+def test_step_with_ids_of_no_expert(T, E, k, G, S, mode):
+    """A row of NaN logits gets ids outside [0, E): no histogram counts them, whoever makes it, and what follows
+    from the counts is the same."""
+    cfg = wl.MoEConfig("nan", T=T, d=64, ffn=64, E=E, k=k, G=G, S=S, dtype="bf16", mode=mode, seed=65)
+    gen = torch.Generator(device="cuda").manual_seed(66)
+    layer = MoELayer(cfg)
+    layer.set_weights(*[torch.randn((E, 64, 64), device="cuda", generator=gen).mul_(0.02).to(torch.bfloat16)
+                        for _ in range(3)])
+    logits = torch.randn((T, E), device="cuda", generator=gen)
+    logits[[0, T // 2, T - 1]] = float("nan")
+    x = torch.randn((T, 64), device="cuda", generator=gen).to(torch.bfloat16)
+    pred_idx = torch.randint(0, E, (T, k), device="cuda", generator=gen, dtype=torch.int32)
+    pred_idx[1], pred_idx[2] = -1, E
+    hist_pred = torch.bincount(pred_idx[3:].reshape(-1).long(), minlength=E).to(torch.int32)
+    layer.route(logits)
+    layer.histogram()
+    layer.plan(mode, hist_pred, pred_idx)
+    layer.permute(mode, x, pred_idx)
+    layer.ffn()
+    layer.combine()
+    want = outputs(layer)
+    assert int(want["hist"].sum()) == (T - 3) * k
+    for n in want:
+        (layer.perm[n] if n in layer.perm else getattr(layer, n)).fill_(-7)
+    assert layer._one_call(logits, x, hist_pred, pred_idx, mode)
+    got = outputs(layer)
+    for n, v in want.items():
+        assert torch.equal(got[n].nan_to_num(3.5), v.nan_to_num(3.5)), n
+
+
 def test_step_leaves_other_inputs_to_the_single_calls():
     """Inputs that are not the layer's own sizes keep the behaviour (and the errors) of the single calls."""
     cfg = wl.CONFIGS["mid_bf16"]
