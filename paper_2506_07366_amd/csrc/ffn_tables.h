@@ -378,13 +378,20 @@ __device__ __forceinline__ void build_tables(TableScratch<MAXSEG, MAXE, NT>& sh,
     if (busy) fill_rows();
 }
 
+// Overrides of the automatic choices (moe_grouped_ffn_set_option).  A call reads them once: another thread may
+// set one at any time, and its kernels must be those that its tables were built for.
+struct FfnOptions {
+    int tile1, tile2, split, group_n, stream;
+};
+FfnOptions ffn_options();
+
 // How much of a grouped FFN call is done: all of it; nothing but its checks and the job of its table
-// builder; or everything behind the builder, which has run.
+// builder; or everything behind the builder, which has run (with the options that the job was made with).
 enum FfnStage { kFfnAll, kFfnJobOnly, kFfnTablesBuilt };
 int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t* gather_rows, int gather_div,
                      const int32_t* scale_idx, const float* scale, int dtype, int64_t A, int d, int ffn, int E,
                      const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin, int seg_end,
                      const void* packed, void* y_perm, void* workspace, size_t workspace_bytes, void* stream,
-                     FfnStage stage = kFfnAll, TableJob* job_out = nullptr);
+                     const FfnOptions& opt, FfnStage stage = kFfnAll, TableJob* job_out = nullptr);
 
 }  // namespace moegps

@@ -396,6 +396,10 @@ constexpr int kMinBM = 32;  // the lowest tile shape
 // Process-wide overrides of the automatic choices (moe_grouped_ffn_set_option); -1 / 0 = automatic.
 static std::atomic<int> g_opt_tile1{-1}, g_opt_tile2{-1}, g_opt_split{-1}, g_opt_group_n{0}, g_opt_stream{-1};
 
+FfnOptions ffn_options() {
+    return {g_opt_tile1.load(), g_opt_tile2.load(), g_opt_split.load(), g_opt_group_n.load(), g_opt_stream.load()};
+}
+
 // The bf16 kernels work on a hidden width padded to a multiple of 64: the packed weights
 // carry zero columns (W1, W3) and zero rows (W2) for the padding, so the padded hidden
 // activations are exact zeros and add nothing to the second product.
@@ -423,11 +427,11 @@ static inline size_t packed_elems2(int d, int fp) { return packed_rows((size_t)d
 // agree; the number of experts is not among them, so a batch that streams its weights (stream_form) has
 // room for slabs that it leaves unused.  split_capacity bounds the M-tiles the table builder may split:
 // at most 5/8 of a round of tiles, each M-tile at least half a tile's worth per N-tile.
-static void split_plan(int64_t A, int d, int ffn, int nseg, int dtype, int* split_capacity, int* parts,
+// mode: 0 never, 1 every tile whenever the kernels can (for tests), -1 the rule.
+static void split_plan(int64_t A, int d, int ffn, int nseg, int dtype, int mode, int* split_capacity, int* parts,
                        int* split_all) {
     *split_capacity = *parts = *split_all = 0;
     if (dtype != MOE_DTYPE_BF16 || A < 1) return;
-    const int mode = g_opt_split.load();  // 0: never, 1: every tile whenever the kernels can (for tests), -1: rule
     if (mode == 0) return;
     const int kt = padded_ffn(ffn, dtype) / 64;
     const int n_ntiles = ceil_div(d, 256);
@@ -452,7 +456,7 @@ static void split_plan(int64_t A, int d, int ffn, int nseg, int dtype, int* spli
     *split_capacity = (int)(by_rule < all_mtiles ? by_rule : all_mtiles);
 }
 
-static size_t ffn_ws_layout(int64_t A, int d, int ffn, int nseg, int dtype, char* base, FfnWs* ws) {
+static size_t ffn_ws_layout(int64_t A, int d, int ffn, int nseg, int dtype, int split, char* base, FfnWs* ws) {
     size_t off = 0;
     auto take = [&](size_t bytes) {
         void* p = base ? (void*)(base + off) : nullptr;
@@ -461,7 +465,7 @@ static size_t ffn_ws_layout(int64_t A, int d, int ffn, int nseg, int dtype, char
     };
     const int64_t A1 = A > 0 ? A : 1;
     FfnWs w;
-    split_plan(A, d, ffn, nseg, dtype, &w.split_capacity, &w.parts, &w.split_all);
+    split_plan(A, d, ffn, nseg, dtype, split, &w.split_capacity, &w.parts, &w.split_all);
     w.capacity = (int)(ceil_div64(A1, kMinBM) + nseg + (int64_t)w.split_capacity * kMaxParts);
     w.h = take((size_t)A1 * padded_ffn(ffn, dtype) * dtype_size(dtype));
     w.rowlist = (int32_t*)take((size_t)A1 * sizeof(int32_t));
@@ -560,8 +564,7 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
 // product, 256 rows on 64 118 against 128).  The rest is form 2's, which reads the activations half as
 // often: 128 experts of 4096 x 1536, first product, 512 rows on 128 / 1 580 against 486 / 57 against 33; 512
 // experts, 2048 rows on 512 / 8 2235 against 1893 / 176 against 88.
-static int stream_form(int forced_tile, int64_t A, int E, int n_cols, int k_tiles) {
-    const int opt = g_opt_stream.load();
+static int stream_form(int opt, int forced_tile, int64_t A, int E, int n_cols, int k_tiles) {
     if (forced_tile >= 0 || opt == 0 || A > 65536) return 0;
     if (opt > 0) return opt;
     const int64_t m_tiles = ceil_div64(A, 128), n_tiles = ceil_div(n_cols, 256);
@@ -707,7 +710,7 @@ extern "C" int moe_pack_weights_relu(const void* W1, const void* W2, int dtype, 
 extern "C" size_t moe_grouped_ffn_workspace_bytes(int64_t A, int d, int ffn, int nseg, int dtype) {
     using namespace moegps;
     if (!ffn_shape_in_range(A, d, ffn, nseg, dtype)) return 0;
-    return ffn_ws_layout(A, d, ffn, nseg, dtype, nullptr, nullptr);
+    return ffn_ws_layout(A, d, ffn, nseg, dtype, ffn_options().split, nullptr, nullptr);
 }
 
 namespace moegps {
@@ -718,7 +721,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
                      const int32_t* scale_idx, const float* scale, int dtype, int64_t A, int d, int ffn, int E,
                      const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin, int seg_end,
                      const void* packed, void* y_perm, void* workspace, size_t workspace_bytes, void* stream,
-                     FfnStage stage, TableJob* job_out) {
+                     const FfnOptions& opt, FfnStage stage, TableJob* job_out) {
     const bool timed = g_time_armed && stage != kFfnJobOnly;
     if (stage != kFfnJobOnly) g_time_armed = false;  // the hook belongs to this call, whatever becomes of it
     if (dtype != MOE_DTYPE_F32 && dtype != MOE_DTYPE_BF16) return MOE_ERR_INVALID_ARG;
@@ -734,7 +737,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     if (A > 0 && (!x_in || !y_perm)) return MOE_ERR_INVALID_ARG;
     if ((scale != nullptr) != (scale_idx != nullptr)) return MOE_ERR_INVALID_ARG;
     FfnWs ws;
-    const size_t need = ffn_ws_layout(A, d, ffn, nseg, dtype, (char*)workspace, &ws);
+    const size_t need = ffn_ws_layout(A, d, ffn, nseg, dtype, opt.split, (char*)workspace, &ws);
     if (workspace_bytes < need) return MOE_ERR_WORKSPACE_TOO_SMALL;
     if (A == 0 || seg_begin == seg_end) {
         if (job_out) *job_out = TableJob{};
@@ -794,11 +797,11 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     // builder chooses the height of the tiles.
     const int fp = padded_ffn(ffn, dtype);  // hidden width the kernels see
     const int n1 = relu ? 1 : 2;            // matrices in the first product
-    const int v1 = g_opt_tile1.load(), v2 = g_opt_tile2.load();
-    const int s1 = stream_form(v1, A, E, n1 * fp, d / kPackK);
-    const int s2 = g_opt_split.load() == 1 ? 0 : stream_form(v2, A, E, d, fp / kPackK);
+    const int v1 = opt.tile1, v2 = opt.tile2;
+    const int s1 = stream_form(opt.stream, v1, A, E, n1 * fp, d / kPackK);
+    const int s2 = opt.split == 1 ? 0 : stream_form(opt.stream, v2, A, E, d, fp / kPackK);
     // N-tiles walked side by side over the M-tiles of an expert: see the tile order in ffn_tiles.h
-    const int group_n = g_opt_group_n.load() > 0 ? g_opt_group_n.load() : kTileGroup;
+    const int group_n = opt.group_n > 0 ? opt.group_n : kTileGroup;
     // one launch builds the row list and both tables; the second product shares the first one's
     // table when it has the same tile height and splits nothing
     const int bm1 = s1 ? kStreamBM : v1 >= 0 ? kShapeRows[v1] : 0;  // 0: the table builder chooses
@@ -850,7 +853,7 @@ extern "C" int moe_grouped_ffn(const void* x_perm, int dtype, int64_t A, int d, 
                                size_t workspace_bytes, void* stream) {
     return moegps::grouped_ffn_call(0, x_perm, A, nullptr, 1, nullptr, nullptr, dtype, A, d, ffn, E, seg_offsets,
                                     slot_expert, nseg, seg_begin, seg_end, packed, y_perm, workspace, workspace_bytes,
-                                    stream);
+                                    stream, moegps::ffn_options());
 }
 
 extern "C" int moe_grouped_ffn_relu(const void* x_perm, int dtype, int64_t A, int d, int ffn, int E,
@@ -859,7 +862,7 @@ extern "C" int moe_grouped_ffn_relu(const void* x_perm, int dtype, int64_t A, in
                                     size_t workspace_bytes, void* stream) {
     return moegps::grouped_ffn_call(1, x_perm, A, nullptr, 1, nullptr, nullptr, dtype, A, d, ffn, E, seg_offsets,
                                     slot_expert, nseg, seg_begin, seg_end, packed, y_perm, workspace, workspace_bytes,
-                                    stream);
+                                    stream, moegps::ffn_options());
 }
 
 extern "C" int moe_grouped_ffn_fused(const void* x, int dtype, int T, int k, const int32_t* assign_of_row,
@@ -872,7 +875,7 @@ extern "C" int moe_grouped_ffn_fused(const void* x, int dtype, int T, int k, con
     if (T > 0 && !assign_of_row) return MOE_ERR_INVALID_ARG;
     return moegps::grouped_ffn_call(0, x, T, assign_of_row, k, topk_w ? assign_of_row : nullptr, topk_w, dtype,
                                     (int64_t)T * k, d, ffn, E, seg_offsets, slot_expert, nseg, seg_begin, seg_end,
-                                    packed, y_perm, workspace, workspace_bytes, stream);
+                                    packed, y_perm, workspace, workspace_bytes, stream, moegps::ffn_options());
 }
 
 extern "C" int moe_grouped_ffn_gather(const void* x, int dtype, int T, int k, const int32_t* assign_of_row, int d,

@@ -131,8 +131,6 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     if (!a->x_perm && (int64_t)T * a->d >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;  // 32-bit element offsets into x
     const int64_t A = (int64_t)T * k;
     if (a->workspace_perm_bytes < moe_permute_workspace_bytes(T, E, k, G, S)) return MOE_ERR_WORKSPACE_TOO_SMALL;
-    if (a->workspace_ffn_bytes < moe_grouped_ffn_workspace_bytes(A, a->d, a->ffn, G * S, a->dtype))
-        return MOE_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)stream;
     int rc;
     const int32_t* hp = mode == MOE_MODE_TOKEN ? a->hist_plan : mode == MOE_MODE_DISTRIBUTION ? a->hist_pred : a->hist;
@@ -151,15 +149,16 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
                                    a->n_iters, stream);
     };
     const float* gate = a->x_perm ? nullptr : a->gate_in_ffn ? a->topk_w : nullptr;
+    const FfnOptions opt = ffn_options();  // (once: the job and the products go by the same)
     auto ffn = [&](FfnStage stage, TableJob* job) {
         const bool gather = !a->x_perm;
         return grouped_ffn_call(a->relu, gather ? a->x : a->x_perm, gather ? T : A, gather ? a->assign_of_row : nullptr,
                                 gather ? k : 1, gate ? a->assign_of_row : nullptr, gate, a->dtype, A, a->d, a->ffn, E,
                                 a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm, a->workspace_ffn,
-                                a->workspace_ffn_bytes, stream, stage, job);
+                                a->workspace_ffn_bytes, stream, opt, stage, job);
     };
     TableJob job{};
-    if ((rc = ffn(kFfnJobOnly, &job)) != MOE_OK) return rc;  // (checks its limits, launches nothing)
+    if ((rc = ffn(kFfnJobOnly, &job)) != MOE_OK) return rc;  // (checks its arguments, launches nothing)
     // The workgroup that permutes builds the tables too where their tile heights are given: one token on 128
     // experts 15.0 us against 8.9 and 6.9, 128 tokens 17.9 against 10.9 and 7.9, and a launch less.  Where it would
     // have to choose them first, a launch of its own is ahead (1001 tokens, 8 experts 28.7 against 13.9 and 9.7).

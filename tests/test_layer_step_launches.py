@@ -1,0 +1,141 @@
+"""What moe_layer_step launches, recorded on the host by a stand-in for the HIP runtime (no GPU needed).
+
+A child process loads a few C functions in place of the runtime's (kernel registration and launch) ahead of
+the library, calls it with made-up device addresses, which only kernels would follow, and prints the names of
+the kernels in launch order.
+"""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+RUNTIME = textwrap.dedent('''
+    #include <stddef.h>
+    #include <stdint.h>
+    #include <stdio.h>
+    #include <string.h>
+    typedef struct { uint32_t x, y, z; } dim3;
+    static struct { const void* fn; const char* name; } kernels[1024];
+    static int n_kernels;
+    static struct { dim3 grid, block; size_t shared; void* stream; } config;
+    static void* module;
+    static char log_[1 << 16];
+    static void (*hook)(int);
+    static int n_launches;
+    void** __hipRegisterFatBinary(const void* data) { (void)data; return &module; }
+    void __hipUnregisterFatBinary(void** m) { (void)m; }
+    void __hipRegisterFunction(void** m, const void* fn, char* device, const char* name, unsigned limit, void* tid,
+                               void* bid, dim3* block, dim3* grid, int* size) {
+        (void)m; (void)device; (void)limit; (void)tid; (void)bid; (void)block; (void)grid; (void)size;
+        kernels[n_kernels].fn = fn;
+        kernels[n_kernels++].name = name;
+    }
+    void __hipRegisterVar(void** m, void* v, char* a, char* b, int c, size_t d, int e, int f) {
+        (void)m; (void)v; (void)a; (void)b; (void)c; (void)d; (void)e; (void)f;
+    }
+    int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, void* stream) {
+        config.grid = grid; config.block = block; config.shared = shared; config.stream = stream;
+        return 0;
+    }
+    int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, void** stream) {
+        *grid = config.grid; *block = config.block; *shared = config.shared; *stream = config.stream;
+        return 0;
+    }
+    int hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args, size_t shared, void* stream) {
+        (void)block; (void)args; (void)shared; (void)stream;
+        for (int i = 0; i < n_kernels; ++i)
+            if (kernels[i].fn == fn) {
+                const size_t at = strlen(log_);
+                snprintf(log_ + at, sizeof(log_) - at, "%s %u\\n", kernels[i].name, grid.x);
+            }
+        if (hook) hook(++n_launches);
+        return 0;
+    }
+    int hipGetLastError(void) { return 0; }
+    int hipGetDevice(int* d) { *d = 0; return 0; }
+    int hipFuncSetAttribute(const void* fn, int a, int v) { (void)fn; (void)a; (void)v; return 0; }
+    int hipGetDevicePropertiesR0600(void* p, int d) { (void)p; (void)d; return 1; }
+    const char* launches(void) { return log_; }
+    void start(void (*h)(int)) { log_[0] = 0; n_launches = 0; hook = h; }
+''')
+
+CHILD = textwrap.dedent('''
+    import ctypes, struct, sys
+    rt = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+    lib = ctypes.CDLL(sys.argv[2])
+    c_int, c_i64, c_sz = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
+    rt.launches.restype = ctypes.c_char_p
+    lib.moe_grouped_ffn_workspace_bytes.restype = lib.moe_permute_workspace_bytes.restype = c_sz
+    lib.moe_grouped_ffn_workspace_bytes.argtypes = [c_i64] + [c_int] * 4
+    lib.moe_layer_step.argtypes = [ctypes.c_char_p, ctypes.c_void_p]
+    HOOK = ctypes.CFUNCTYPE(None, c_int)
+    rt.start.argtypes = [HOOK]
+    POINTERS = ("logits x hist_pred pred_idx packed topk_idx topk_w hist hist_plan slot_expert slot_quota rank_load_pred "
+                "n_iters seg_offsets row_of_assign assign_of_row x_perm rank_load y_perm out").split()
+    MODE, DTYPE, T, D, FFN, E, K, G, S, CMAX, RELU, GATE = range(12)
+
+    def step(ints, hook=None, ws=(0, 0), **pointers):
+        """(return code, launches) of a step; pointers far apart unless given, ws: bytes missing from the workspaces"""
+        p = {n: (i + 1) << 40 for i, n in enumerate(POINTERS)}
+        p.update(pointers)
+        A = max(ints[T], 0) * max(ints[K], 1)
+        perm = lib.moe_permute_workspace_bytes(ints[T], ints[E], ints[K], ints[G], ints[S]) - ws[0]
+        ffn = lib.moe_grouped_ffn_workspace_bytes(A, ints[D], ints[FFN], ints[G] * ints[S] & 0x7fffffff, ints[DTYPE]) - ws[1]
+        args = struct.pack("@12i24Q", *ints, *[p[n] for n in POINTERS], p.get("ws_perm", 21 << 40), max(perm, 0),
+                           p.get("ws_ffn", 22 << 40), max(ffn, 0))
+        keep = HOOK(hook) if hook else HOOK()
+        rt.start(keep)
+        rc = lib.moe_layer_step(args, None)
+        got = rt.launches().decode()
+        return rc, [l.split()[0] for l in got.splitlines()]
+''')
+
+
+@pytest.fixture(scope="module")
+def child(tmp_path_factory):
+    """Runs a script behind CHILD; its output."""
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler")
+    from paper_2506_07366_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2506_07366_amd.build import build
+        build(verbose=False)
+    tmp = tmp_path_factory.mktemp("runtime")
+    (tmp / "rt.c").write_text(RUNTIME)
+    rt = str(tmp / "rt.so")
+    subprocess.run([cc, "-shared", "-fPIC", "-o", rt, str(tmp / "rt.c")], check=True)
+
+    def run(script):
+        path = tmp / "child.py"
+        path.write_text(CHILD + textwrap.dedent(script))
+        r = subprocess.run([sys.executable, str(path), rt, binding.LIB_PATH], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, f"{r.stdout}\n{r.stderr}"
+        return r.stdout
+
+    return run
+
+
+def test_options_are_read_once_per_step(child):
+    """An option that another thread sets while a step is under way is for the next one: the products are those
+    whose tables the permutation has built."""
+    out = child('''
+        TILE1, TILE2, SPLIT, GROUP_N, STREAM = range(5)
+        for ints in ([1, 1, 16, 4096, 1024, 8, 2, 8, 3, 8, 0, 0],       # streams: tables by the permutation
+                     [1, 1, 1500, 512, 2048, 8, 2, 8, 3, 8, 0, 0]):     # tiles, closing ones split
+            want = step(ints)
+            assert want[0] == 0, want
+            for option, value in ((STREAM, 0), (STREAM, 1), (STREAM, 2), (TILE1, 1), (TILE2, 2), (SPLIT, 0), (SPLIT, 1)):
+                for after in range(1, len(want[1])):
+                    hook = lambda n: n == after and lib.moe_grouped_ffn_set_option(option, value)
+                    got = step(ints, hook)
+                    lib.moe_grouped_ffn_set_option(option, -1)
+                    assert got == want, (option, value, after, got, want)
+            print(len(want[1]), "launches")
+    ''')
+    assert out.count("launches") == 2
