@@ -122,9 +122,12 @@ class MoELayer:
 
     def _one_call(self, logits, x, hist_pred, pred_idx, mode) -> bool:
         """The whole step as one C-ABI call, for inputs of the layer's own sizes; anything else is left to
-        the calls of the single steps (and to what they say about it)."""
+        the calls of the single steps (and to what they say about it), and so is a layer whose single steps
+        have been replaced, in a subclass, on the object (to time or record one, say) or on the class."""
         c = self.cfg
         if type(self) is not MoELayer or self.packed is None or mode not in (MODE_NONE, MODE_DISTRIBUTION, MODE_TOKEN):
+            return False
+        if not _STEP_NAMES.isdisjoint(self.__dict__) or _single_steps(MoELayer) != _SINGLE_STEPS:
             return False
         if c.T < 1 or logits.shape != (c.T, c.E) or x.shape != (c.T, c.d) or x.dtype != self.out.dtype:
             return False
@@ -223,3 +226,13 @@ class MoELayer:
             n_iters=int(self.n_iters.item()),
             replicas=int((self.slot_expert.cpu().numpy() >= 0).sum() - c.E),
         )
+
+
+_STEP_NAMES = frozenset(("route", "histogram", "plan", "permute", "ffn", "combine"))
+
+
+def _single_steps(cls):
+    return cls.route, cls.histogram, cls.plan, cls.permute, cls.ffn, cls.combine
+
+
+_SINGLE_STEPS = _single_steps(MoELayer)
