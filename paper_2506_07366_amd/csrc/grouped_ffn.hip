@@ -514,6 +514,8 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
                         const MTile* tiles, const int32_t* counts, int32_t* queues, int N, int K, int group_n,
                         const RowMap& rm, float* partials, hipStream_t st) {
     const bool past_caches = (size_t)E * b_stride * sizeof(bf16_t) > kCachedWeights;
+    // (the kernel multiplies by it: an option beyond the N-tiles there are means all of them)
+    if (group_n > ceil_div(N, kPackN)) group_n = ceil_div(N, kPackN);
     // the kernel uses more LDS than the default limit: raised once per kernel and device
     static std::atomic<unsigned long long> attr_set{0};  // bit per device
     const auto kern = grouped_gemm_tile_kernel<EPI>;

@@ -27,6 +27,7 @@ RUNTIME = textwrap.dedent('''
     static char log_[1 << 16];
     static void (*hook)(int);
     static int n_launches;
+    static void** last_args;
     void** __hipRegisterFatBinary(const void* data) { (void)data; return &module; }
     void __hipUnregisterFatBinary(void** m) { (void)m; }
     void __hipRegisterFunction(void** m, const void* fn, char* device, const char* name, unsigned limit, void* tid,
@@ -47,12 +48,13 @@ RUNTIME = textwrap.dedent('''
         return 0;
     }
     int hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args, size_t shared, void* stream) {
-        (void)block; (void)args; (void)shared; (void)stream;
+        (void)block; (void)shared; (void)stream;
         for (int i = 0; i < n_kernels; ++i)
             if (kernels[i].fn == fn) {
                 const size_t at = strlen(log_);
                 snprintf(log_ + at, sizeof(log_) - at, "%s %u\\n", kernels[i].name, grid.x);
             }
+        last_args = args;
         if (hook) hook(++n_launches);
         return 0;
     }
@@ -60,6 +62,7 @@ RUNTIME = textwrap.dedent('''
     int hipGetDevice(int* d) { *d = 0; return 0; }
     int hipFuncSetAttribute(const void* fn, int a, int v) { (void)fn; (void)a; (void)v; return 0; }
     int hipGetDevicePropertiesR0600(void* p, int d) { (void)p; (void)d; return 1; }
+    int int_argument(int i) { return *(int*)last_args[i]; }   /* of the launch under way */
     const char* launches(void) { return log_; }
     void start(void (*h)(int)) { log_[0] = 0; n_launches = 0; hook = h; }
 ''')
@@ -139,3 +142,18 @@ def test_options_are_read_once_per_step(child):
             print(len(want[1]), "launches")
     ''')
     assert out.count("launches") == 2
+
+
+@pytest.mark.parametrize("option", [1, 7, 8, 9, 2**16, 2**31 - 1])
+def test_n_tiles_walked_together_are_tiles_that_exist(child, option):
+    """The tile kernel multiplies the option by its M-tiles: it gets no more than there are N-tiles."""
+    out = child(f"""
+        N, GROUP = 9, 11                      # arguments of grouped_gemm_tile_kernel
+        def look(n):
+            if "grouped_gemm_tile" in rt.launches().decode().splitlines()[-1]:
+                print("tile", rt.int_argument(N), rt.int_argument(GROUP))
+        assert lib.moe_grouped_ffn_set_option(3, {option}) == 0
+        assert step([1, 1, 1500, 512, 1024, 8, 2, 8, 3, 8, 0, 0], look)[0] == 0
+    """)
+    seen = [tuple(map(int, line.split()[1:])) for line in out.splitlines() if line.startswith("tile")]
+    assert seen == [(2048, min(option, 8)), (512, min(option, 2))]
