@@ -14,7 +14,8 @@ struct MTile {
     int expert;  // expert whose weights the rows take
     int kt0;     // k-tiles [kt0, kt1) of the product belong to this entry; kt1 == 0: all of them
     int kt1;
-    int part;    // < 0: results go to the output; else fp32 partial sums go to slab `part`
+    int part;    // < 0: results go to the output (kPartAlone: from the expert's only tile of the table); else
+                 //   fp32 partial sums go to slab `part`
     int first;   // whole tiles: the expert's whole tiles are the entries [first, first + n_same)
     int n_same;
 };
@@ -22,6 +23,7 @@ struct MTile {
 struct SplitInfo {
     int list0, rows;
 };
+constexpr int kPartWhole = -1, kPartAlone = -2;
 constexpr int kGemmGrid = 256;  // persistent workgroups of a GEMM launch: 8 XCDs x 32
 constexpr int kPartRows = 256;  // rows of one slab of partial sums (the tallest tile shape)
 constexpr int kMaxParts = 4;    // parts of K of a split tile
@@ -352,7 +354,7 @@ __device__ __forceinline__ void build_tables(TableScratch<MAXSEG, MAXE, NT>& sh,
                 mt.rows = left < height ? left : height;
                 mt.expert = expert;
                 mt.kt0 = mt.kt1 = 0;
-                mt.part = -1;
+                mt.part = o_base[lo + 1] - o_base[lo] == 1 ? kPartAlone : kPartWhole;
                 mt.first = o_base[lo];
                 mt.n_same = (o_base[lo + 1] < n_whole ? o_base[lo + 1] : n_whole) - mt.first;
                 if (t < n_whole) {

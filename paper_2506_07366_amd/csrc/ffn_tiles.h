@@ -311,7 +311,7 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
             for (int r = 0; r < R; ++r) lds_landed(af[r]);
         };
         // one K loop per 32 rows of height; every one runs the same barriers
-        const bool once = past_caches && mt.part < 0 && mt.n_same == 1;
+        const bool once = past_caches && mt.part == kPartAlone;
         static_for<TM_MAX / 2>([&](auto H2) {
             constexpr int tm = 2 * decltype(H2)::value + 2;
             const std::integral_constant<int, tm> TM{};

@@ -541,6 +541,53 @@ def test_ffn_heights_chosen_from_the_batch(sizes, split, ffn_options):
         B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, -1)
 
 
+def second_table(ws, A, d, ffn, nseg):
+    """Entries (first row, rows, expert, part, first, n_same) of the second product's M-tile table, and its counts of
+    entries, whole tiles and split tiles, out of a workspace that a call has used."""
+    up = lambda n: -(-n // 256) * 256
+    head, cap = up(A * (-(-ffn // 64) * 64) * 2) + up(A * 4), -(-A // 32) + nseg
+    # the sizes say how many split tiles there is room for (four parts each, 256 fp32 rows a part)
+    split = next(n for n in range(1, 4096) if head + 2 * up((cap + 4 * n) * 32) + 256 + up(n * 8) + up(n * 4096 * d)
+                 == B.moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, B.MOE_DTYPE_BF16))
+    table = up((cap + 4 * split) * 32)
+    raw = ws.cpu().numpy()
+    entries, whole, splits = raw[head + 2 * table:][16:28].view(np.int32)
+    return raw[head + table:][:32 * entries].view(np.int32).reshape(-1, 8)[:, [0, 1, 2, 5, 6, 7]], int(whole), int(splits)
+
+
+@pytest.mark.parametrize("rows", [
+    [540, 0, 123, 1467, 1116, 382],                                   # one tile split, of an expert with two
+    [406, 753, 40, 1484, 51, 98, 638, 10, 410, 0, 281, 306]])         # the eight last ones of 24
+def test_ffn_some_tiles_split_by_the_rule(rows, ffn_options):
+    """Heights from the batch and the rule that splits the closing tiles, together: a table of whole tiles and of
+    parts, the walk over an expert's whole tiles ends in front of its split ones, and a tile that shares its
+    weights with them does not pass for the expert's only one.  Results against 64 bits."""
+    ffn_options()
+    d, ffn, E, A = 4096, 1024, len(rows), sum(rows)
+    nseg = E + 3
+    gen = torch.Generator(device="cuda").manual_seed(71)
+    W1, W3, W2 = [torch.randn((E, *shape), device="cuda", generator=gen).mul_(0.03).to(torch.bfloat16)
+                  for shape in ((d, ffn), (d, ffn), (ffn, d))]
+    x = torch.randn((A, d), device="cuda", generator=gen).to(torch.bfloat16)
+    offsets = np.concatenate([[0], np.cumsum(rows + [0, 0, 0])])
+    ws = torch.zeros(B.moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, B.MOE_DTYPE_BF16), dtype=torch.uint8, device="cuda")
+    y = B.moe_grouped_ffn(x, dev_i32(offsets), dev_i32([*range(E), -1, -1, -1]), B.moe_pack_weights(W1, W3, W2), E, ffn,
+                          workspace=ws)
+    ref = torch.cat([(torch.nn.functional.silu(v @ W1[e].double()) * (v @ W3[e].double())) @ W2[e].double()
+                     for e, v in enumerate(x.double().split(rows))])
+    assert float((y.double() - ref).abs().max()) <= TOL["bf16"] * float(ref.abs().max())
+    table, n_whole, n_split = second_table(ws, A, d, ffn, nseg)
+    assert n_whole > 0 and n_split > 0 and len(table) == n_whole + 4 * n_split
+    tiles = table[:n_whole + n_split]                                 # (the first part of every split tile)
+    covered = np.concatenate([np.arange(lo, lo + n) for lo, n in tiles[:, :2]])
+    assert np.array_equal(np.sort(covered), np.arange(A))
+    per_expert = np.bincount(tiles[:, 2], minlength=E)
+    assert any(0 < np.sum(tiles[:n_whole, 2] == e) < per_expert[e] for e in range(E))
+    for t, (_, _, e, part, first, n_same) in enumerate(table[:n_whole].tolist()):
+        assert part == (-2 if per_expert[e] == 1 else -1)
+        assert first <= t < first + n_same <= n_whole and np.all(table[first:first + n_same, 2] == e)
+
+
 @pytest.mark.parametrize("form", [1, 2])
 @pytest.mark.parametrize("d,ffn,relu", [(64, 64, False),      # one k-tile: one half / three parts of K are empty
                                         (192, 320, False),    # odd numbers of k-tiles, half a unit at the edge of N
