@@ -526,7 +526,8 @@ def test_ffn_weights_read_past_the_caches(relu, ffn_options):
     [0, 0, 0, 0, 0, 3000]])           # one expert holds everything
 def test_ffn_heights_chosen_from_the_batch(sizes, split, ffn_options):
     """Tables whose tile heights come from the rows per expert, every row present once: against the
-    oracle, whole and split along K."""
+    oracle, whole (four k-tiles are too few for the rule to split any) and all split along K.  Whole and split
+    ones in one table: test_ffn_some_tiles_split_by_the_rule."""
     ffn_options(split=split)
     B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, 0)
     try:

@@ -46,8 +46,9 @@ def test_step_equals_single_calls(T, E, k, G, S, dtype, mode):
           for s in ((E, d, ffn), (E, d, ffn), (E, ffn, d))]
     pred_idx = torch.topk(logits + 0.5 * torch.randn_like(logits), k, dim=1).indices.to(torch.int32).contiguous()
     hist_pred = torch.bincount(pred_idx.reshape(-1).long(), minlength=E).to(torch.int32)
-    for gather, weights in ((False, False), (True, False), (True, True)):
-        layer = MoELayer(cfg, fused_gather=gather, fused_weights=weights)
+    for gather, weights, act in ((False, False, "swiglu"), (True, False, "swiglu"), (True, True, "swiglu"),
+                                 (False, False, "relu")):
+        layer = MoELayer(cfg.replace(act=act), fused_gather=gather, fused_weights=weights)
         layer.set_weights(*ws)
         layer.route(logits)
         layer.histogram()
@@ -57,8 +58,8 @@ def test_step_equals_single_calls(T, E, k, G, S, dtype, mode):
         layer.combine()
         want = outputs(layer)
         plan_hist = layer.hist_plan.clone()
-        for t in (layer.hist, layer.hist_plan, layer.slot_expert, layer.slot_quota, layer.n_iters, layer.topk_idx,
-                  *(v for v in layer.perm.values() if v is not None), layer.out, layer.y_perm):
+        for t in (*(layer.perm[n] if n in layer.perm else getattr(layer, n) for n in want), layer.hist_plan, layer.y_perm,
+                  *(v for v in (layer.perm["x_perm"],) if v is not None)):
             t.fill_(-7)
         assert layer._one_call(logits, x, hist_pred, pred_idx, mode)
         got = outputs(layer)

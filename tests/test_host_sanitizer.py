@@ -16,7 +16,6 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2506_07366_amd", "csrc")
-SOURCES = ["api", "route_topk", "histogram", "plan", "permute", "grouped_ffn", "combine", "comm", "predictor"]
 
 
 def _hipcc():
@@ -31,12 +30,13 @@ def sanitized_library(tmp_path_factory):
     hipcc = _hipcc()
     if hipcc is None:
         pytest.skip("hipcc not found")
+    from paper_2506_07366_amd.build import SOURCES
     out = tmp_path_factory.mktemp("ubsan")
     flags = ["--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
              "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fsanitize-trap=undefined", "-I", os.path.join(ROOT, "include")]
     procs = []
-    for s in SOURCES:
+    for s in (name[:-len(".hip")] for name in SOURCES):
         obj = str(out / (s + ".o"))
         procs.append((s, obj, subprocess.Popen([hipcc, *flags, "-c", os.path.join(CSRC, s + ".hip"), "-o", obj],
                                                stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)))
@@ -125,6 +125,19 @@ CHILD = textwrap.dedent('''
     assert call("moe_combine", [vp, c_int, c_int, c_int, c_int, vp, vp, vp, vp], None, 1, -1, 64, 2, None, None, None, None) != OK
     assert call("moe_combine", [vp, c_int, c_int, c_int, c_int, vp, vp, vp, vp], None, 1, 16, 2**31 - 1, 2**31 - 1, None, None, None, None) != OK
     assert call("moe_grouped_ffn_set_option", [c_int, c_int], 99, 0) != OK
+    # a whole step: sizes at and beyond every limit, in fields of the right type (no pointers, no workspaces)
+    import struct
+    def step(*ints):
+        return call("moe_layer_step", [ctypes.c_char_p, vp], struct.pack("@12i24Q", *ints, *[0] * 24), None)
+    good = dict(mode=1, dtype=1, T=16, d=64, ffn=64, E=8, k=2, G=8, S=2, c_max=8, relu=0, gate=0)
+    for field in good:
+        for v in I32:
+            r = step(*{**good, field: v}.values())
+            assert r != OK or (field == "T" and v == 0), (field, v, r)
+    big = dict(T=2**31 - 1, d=2**31 - 64, ffn=2**31 - 1, E=1024, k=16, G=256, S=16)
+    for fields in itertools.chain.from_iterable(itertools.combinations(big, n) for n in (2, 3, 7)):
+        assert step(*{**good, **{f: big[f] for f in fields}}.values()) != OK, fields
+    assert call("moe_layer_step", [ctypes.c_char_p, vp], None, None) == INVALID
     for code in range(-8, 3):
         lib.moe_strerror.restype = ctypes.c_char_p
         lib.moe_strerror.argtypes = [c_int]

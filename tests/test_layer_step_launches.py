@@ -157,3 +157,66 @@ def test_n_tiles_walked_together_are_tiles_that_exist(child, option):
     """)
     seen = [tuple(map(int, line.split()[1:])) for line in out.splitlines() if line.startswith("tile")]
     assert seen == [(2048, min(option, 8)), (512, min(option, 2))]
+
+
+def test_own_outputs_as_prediction_come_in_the_order_of_the_single_calls(child):
+    """ids or counts that the step itself writes: routing, histogram (of the predicted ids too), plan, permutation, each a
+    launch of its own.  A prediction next to them shares the launches as any other does."""
+    out = child("""
+        def kinds(mode, t, e, g, s, **pointers):
+            rc, names = step([mode, 1, t, 64, 64, e, 2, g, s, 8, 0, 0], **pointers)
+            assert rc == 0
+            return [next(w for w in ("route_plan", "route", "hist", "plan", "perm", "other") if w in n or w == "other")
+                    for n in names]
+        TOPK, WEIGHT, HIST = [(POINTERS.index(n) + 1) << 40 for n in ("topk_idx", "topk_w", "hist")]
+        for shape in ((64, 16, 4, 5), (3000, 16, 4, 5), (100, 300, 32, 10)):
+            ids, counts = 2 * shape[0] * 4, shape[1] * 4
+            for at in (TOPK, TOPK - ids + 4, TOPK + ids - 4, WEIGHT, HIST + counts - 4):
+                got = kinds(2, *shape, pred_idx=at)
+                assert got[:5] == ["route", "hist", "hist", "plan", "perm"], (shape, at, got)
+            for at in (HIST, HIST - counts + 4, HIST + counts - 4, TOPK, WEIGHT + ids - 4):
+                got = kinds(1, *shape, hist_pred=at)
+                assert got[:4] == ["route", "hist", "plan", "perm"], (shape, at, got)
+            for mode, beside in ((2, dict(pred_idx=TOPK - ids)), (2, dict(pred_idx=TOPK + ids)), (1, dict(hist_pred=HIST + counts)),
+                                 (1, dict(pred_idx=TOPK)), (2, dict(hist_pred=HIST)), (0, dict(pred_idx=TOPK, hist_pred=HIST))):
+                assert kinds(mode, *shape, **beside) == kinds(mode, *shape), (shape, mode, beside)
+            print("shape", kinds(2, *shape))
+    """)
+    assert out.count("shape") == 3
+
+
+def test_arguments_are_checked_before_the_first_launch(child):
+    """What the single calls refuse is refused, with their codes, and nothing has been launched by then."""
+    child("""
+        INVALID, UNSUPPORTED, TOO_SMALL = -1, -2, -3
+        good = [1, 1, 16, 64, 64, 8, 2, 8, 2, 8, 0, 0]
+        assert step(good)[0] == 0 and len(step(good)[1]) > 3
+        def refused(code, changes={}, **kw):
+            ints = list(good)
+            for i, v in changes.items():
+                ints[i] = v
+            got = step(ints, **kw)
+            assert got == (code, []), (changes, kw, got)
+        for field, value in ((MODE, -1), (MODE, 3), (DTYPE, 2), (T, -1), (D, 0), (FFN, 0), (E, 0), (K, 0), (K, 9), (G, 0), (S, 0),
+                             (CMAX, 0), (G, 2)):                       # (two ranks of two slots do not hold 8 experts)
+            refused(INVALID, {field: value})
+        for changes in ({E: 1025, G: 256, S: 8}, {E: 17, K: 17, G: 16}, {G: 257}, {S: 17}, {G: 256, S: 9}, {D: 4}, {D: 72},
+                        {D: 63, DTYPE: 0}, {FFN: 66, DTYPE: 0}, {FFN: (1 << 22) + 1}, {D: 1 << 23}, {T: 1 << 30},
+                        {T: 1 << 25}, {T: 1 << 28, E: 9, K: 1, G: 9, D: 4, FFN: 4, DTYPE: 0}):
+            refused(UNSUPPORTED, changes)
+        for name in POINTERS:
+            if name in ("pred_idx", "hist_plan", "x_perm"):
+                continue
+            refused(INVALID, {}, **{name: 0})
+        for name in ("ws_perm", "ws_ffn"):
+            refused(INVALID, {}, **{name: 0})
+        refused(INVALID, {MODE: 2}, pred_idx=0)
+        refused(INVALID, {MODE: 2}, hist_plan=0)
+        refused(UNSUPPORTED, {RELU: 1}, x_perm=0)
+        refused(TOO_SMALL, {}, ws=(1, 0))
+        refused(TOO_SMALL, {}, ws=(0, 1))
+        assert step([0, 1, 0] + good[3:]) == (0, [])                   # no tokens: nothing to do
+        for ints, kw in (([0] + good[1:], dict(hist_pred=0, pred_idx=0, hist_plan=0)), (good, dict(pred_idx=0, hist_plan=0)),
+                         ([2] + good[1:], dict(hist_pred=0)), (good, dict(x_perm=0)), (good[:11] + [1], dict(x_perm=0))):
+            assert step(ints, **kw)[0] == 0, (ints, kw)                # what a mode does not read may be missing
+    """)
