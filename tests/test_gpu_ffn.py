@@ -199,8 +199,8 @@ def test_layer_full_size_sampled(name):
     compute one by one: all k rows of sampled tokens, the first and last row of
     every non-empty segment, and the rows either side of every tile boundary the
     kernels can use (rows are tiled per expert, over all its segments, in tiles of
-    256 or 128 rows: every multiple of 128 in every expert's row list).  The load
-    report is compared with the oracle's skewness and rank loads."""
+    some multiple of 32 rows: every multiple of 32 in every expert's row list).  The
+    load report is compared with the oracle's skewness and rank loads."""
     cfg = wl.CONFIGS[name]
     case = Case(cfg)
     Ws = host_weights(cfg)
@@ -227,7 +227,7 @@ def test_layer_full_size_sampled(name):
         if hi > lo:
             rows.update([lo, hi - 1])
     for lst in expert_row_lists(so, case.plan.slot_expert, cfg.E):
-        for b in range(128, len(lst), 128):       # every tile boundary inside the expert's rows
+        for b in range(32, len(lst), 32):         # every tile boundary inside the expert's rows
             rows.update([lst[b - 1], lst[b]])
     rows = np.array(sorted(rows), dtype=np.int64)
     aor = case.perm["assign_of_row"]

@@ -83,10 +83,12 @@ CHILD = textwrap.dedent('''
     # every entry point refuses invalid shapes before it touches a pointer or the GPU
     OK, INVALID, UNSUPPORTED = 0, -1, -2
     bad = (INVALID, UNSUPPORTED)
+    called = set()
     def call(name, argtypes, *args):
         print("call", name, [a for a in args if a is not None], flush=True)
         fn = getattr(lib, name)
         fn.argtypes, fn.restype = argtypes, c_int
+        called.add(name)
         return fn(*args)
     assert call("moe_route_topk", [vp, c_int, c_int, c_int, vp, vp, vp], None, -1, 8, 2, None, None, None) in bad
     assert call("moe_route_topk", [vp, c_int, c_int, c_int, vp, vp, vp], None, 16, 8, 9, None, None, None) in bad
@@ -122,6 +124,11 @@ CHILD = textwrap.dedent('''
     fused_t = [vp, c_int, c_int, c_int, vp, vp, c_int, c_int, c_int, vp, vp, c_int, c_int, c_int, vp, vp, vp, c_sz, vp]
     assert call("moe_grouped_ffn_fused", fused_t, None, 1, -1, 2, None, None, 64, 64, 8, None, None, 16, 0, 16, None, None, None, 0, None) != OK
     assert call("moe_grouped_ffn_fused", fused_t, None, 1, 2**31 - 1, 16, None, None, 2**31 - 64, 2**31 - 1, 8, None, None, 16, 0, 16, None, None, None, 0, None) != OK
+    assert call("moe_grouped_ffn_gather", fused_t[:5] + fused_t[6:], None, 1, -1, 2, None, 64, 64, 8, None, None, 16, 0, 16, None, None, None, 0, None) != OK
+    for E, d, ffn, dtype in itertools.product([0, 8, 2**31 - 1], [0, 63, 2**31 - 1], [0, 64, 2**31 - 1], [0, 1, 2]):
+        assert call("moe_pack_weights", [vp] * 3 + [c_int] * 4 + [vp] * 2, None, None, None, dtype, E, d, ffn, None, None) in bad
+        assert call("moe_pack_weights_relu", [vp] * 2 + [c_int] * 4 + [vp] * 2, None, None, dtype, E, d, ffn, None, None) in bad
+    assert call("moe_grouped_ffn_time_next_call", [vp], ctypes.cast((vp * 4)(), vp)) == INVALID     # no events
     assert call("moe_combine", [vp, c_int, c_int, c_int, c_int, vp, vp, vp, vp], None, 1, -1, 64, 2, None, None, None, None) != OK
     assert call("moe_combine", [vp, c_int, c_int, c_int, c_int, vp, vp, vp, vp], None, 1, 16, 2**31 - 1, 2**31 - 1, None, None, None, None) != OK
     assert call("moe_grouped_ffn_set_option", [c_int, c_int], 99, 0) != OK
@@ -138,6 +145,8 @@ CHILD = textwrap.dedent('''
     for fields in itertools.chain.from_iterable(itertools.combinations(big, n) for n in (2, 3, 7)):
         assert step(*{**good, **{f: big[f] for f in fields}}.values()) != OK, fields
     assert call("moe_layer_step", [ctypes.c_char_p, vp], None, None) == INVALID
+    missing = set(sys.argv[2:]) - called
+    assert not missing, missing
     for code in range(-8, 3):
         lib.moe_strerror.restype = ctypes.c_char_p
         lib.moe_strerror.argtypes = [c_int]
@@ -149,6 +158,9 @@ CHILD = textwrap.dedent('''
 def test_host_arithmetic_is_free_of_undefined_behaviour(sanitized_library, tmp_path):
     script = tmp_path / "child.py"
     script.write_text(CHILD)
-    r = subprocess.run([sys.executable, str(script), sanitized_library], capture_output=True, text=True, timeout=600)
+    from paper_2506_07366_amd.binding import EXPORTS
+    plain = ("moe_strerror", "moe_last_hip_error", "moe_abi_version")       # (no sizes among their arguments)
+    checked = [n for n in EXPORTS if n not in plain and not n.endswith("_bytes")]  # (size queries are swept above)
+    r = subprocess.run([sys.executable, str(script), sanitized_library, *checked], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, f"child ended with {r.returncode} (a negative code is a signal: the sanitizer's trap)\n{r.stdout[-1500:]}\n{r.stderr[-2000:]}"
     assert "argument checks ok" in r.stdout
