@@ -325,7 +325,7 @@ def main():
         "dtype": cfg.dtype, "data": "synthetic",
         "config": {"workload": describe(cfg), "T": cfg.T, "A": cfg.A, "mode": cfg.mode, "seed": cfg.seed,
                    "input_sha256": input_digests,
-                   "row_gather": "fused into the first FFN product" if args.fused_gather else "x_perm copy (six-call path)"},
+                   "row_gather": "fused into the first FFN product" if args.fused_gather else "x_perm copy"},
         "roofline": roofline,
     }
     if args.headline_only:
@@ -560,7 +560,7 @@ def main():
             fused[key] = {"ms_per_step": other_ms, "value": cfg.T / (other_ms * 1e-3), "unit": "tokens/s"}
             del other
 
-    # the same six calls replayed from a HIP graph (one capture, then replays timed like the steps
+    # the same step replayed from a HIP graph (one capture, then replays timed like the steps
     # above): what the launch gaps between the small kernels cost
     graph = layer.capture(logits, x, hist_pred=hist_pred, pred_idx=pred_idx)
     for _ in range(max(1, args.warmup)):

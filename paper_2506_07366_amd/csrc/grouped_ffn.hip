@@ -425,8 +425,11 @@ static inline size_t packed_elems2(int d, int fp) { return packed_rows((size_t)d
 // of the launch matters, and the segments are not slivers (splitting K would only add
 // traffic).  Decided from the sizes the workspace is laid out for, so that the layout and the call
 // agree; the number of experts is not among them, so a batch that streams its weights (stream_form) has
-// room for slabs that it leaves unused.  split_capacity bounds the M-tiles the table builder may split:
-// at most 5/8 of a round of tiles, each M-tile at least half a tile's worth per N-tile.
+// room for slabs that it leaves unused.  split_capacity bounds the M-tiles the table builder may split: more than 5/8 of a
+// round of tiles, and no more than there are of 128 rows.  Lower tiles can be more; where the builder's rule asks
+// for more than there is room for, which takes narrow outputs and a batch that is less than a round in all, it splits
+// none.  Room for all of them would be worse, both products, us, none split -> all: 8 experts of 512 x 1024, 1001 / 2048
+// tokens 35 -> 44 / 41 -> 59; 8 of 1024 x 4096, 1001 tokens 83 -> 98; 8 of 768 x 3072, 3000 tokens 60 -> 73.
 // mode: 0 never, 1 every tile whenever the kernels can (for tests), -1 the rule.
 static void split_plan(int64_t A, int d, int ffn, int nseg, int dtype, int mode, int* split_capacity, int* parts,
                        int* split_all) {
@@ -540,26 +543,24 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
 // The rule goes by the whole batch (A rows, E experts), not by the launched slot range, so that
 // a row gets the same bits from a launch over some slots as from one over all.  How the rows lie is
 // only known on the device, so a line has to do for all rows on one expert as well as for an equal share
-// on each.  Spread out, the streaming forms lead far beyond these lines; batches that lie on a
-// few experts fall behind once the tiles of so many rows fill the chip.  The figures are from tiles with both operands in
-// LDS and of one height; against the present ones, both products, us, tiles -> streaming: 128 experts of 4096 x 1536, 2048
-// rows on 128 / 16 / 1 750 -> 739 / 126 -> 166 / 89 -> 107; 64 of 2048 x 1408, 1536 rows on 64 / 16 / 1 190 -> 186 /
-// 80 -> 78 / 48 -> 58; 16 of 4096 x 688, 1024 rows on 16 / 1 84 -> 65 / 53 -> 48; 8 of 4096 x 14336, 128 rows on 8 / 1
-// 466 -> 425 / 126 -> 135.  As the lines were set, both products, us, tiles -> streaming:
-//   up to 16 rows per expert on average: 128 experts of 4096 x 1536, 2048 rows on all of them 807 -> 736, on
-//     16 140 -> 165, on one 102 -> 108 (1536 rows on all 128 823 -> 730, on 16 136 -> 155); 8 experts of
-//     4096 x 14336, 128 rows on 8 / 1 519 -> 421 / 162 -> 135; but not with so many experts that the tiles of A
-//     rows on one of them are more than 128 k-tiles per CU (512 experts of 4096 x 1536, first product, 6144 rows on
-//     512 / 64: 2062 -> 1917 / 288 -> 373);
-//   up to 24 where those are no more than 18 per CU and K is not short (64 experts of 2048 x 1408, 132 tiles of
-//     32 and 96 of 22, 1536 rows on 64 / 16 / 1 214 -> 186 / 85 -> 75 / 71 -> 60); with more than that too much is lost (128 experts
-//     of 4096 x 1536, 240 tiles of 64 and 320 of 24, 2560 rows on 128 / 32 / 16 820 -> 772 / 261 -> 282 / 187 ->
-//     209; 64 experts of 4096 x 4096, second product, 160 tiles of 64, 1280 rows on 16 / 8 / 4 102 -> 122 / 73 ->
-//     90 / 68 -> 84; 1024 experts of 1024 x 512, second product, 8 k-tiles, 18432 rows on 16 / 1 39 -> 46 / 40 -> 47);
-//   up to 64 where even every expert's own ragged 128 x 256 tiles would not go once round the chip (16
-//     experts of 4096 x 688, 1024 rows on 16 / 1, first product: 67 -> 43 / 61 -> 33).
-// Above 16 rows per expert a long K is left to the tiles in any case, their closing ones are computed as
-// parts of K (8 experts, K = 14336, second product, 192 rows on 1 / 2 experts: 77 / 91 against 110 / 111).
+// on each.  The lines were drawn against tiles that took longer for few rows than the present ones: what they give up for
+// batches on a few experts is now more than they gain on spread ones.  Both products, us, tiles -> streaming, rows on so
+// many experts, with the present tiles:
+//   up to 16 rows per expert on average: 128 experts of 4096 x 1536 on 128 / 16 / 1, 512 rows 721 -> 704 / 121 -> 107 /
+//     58 -> 50, 1024 rows 721 -> 718 / 125 -> 118 / 62 -> 60, 1536 rows 734 -> 727 / 131 -> 155 / 76 -> 100, 2048 rows 743 -> 737 /
+//     136 -> 165 / 91 -> 105; 64 of 2048 x 1408, 1024 rows on 64 / 16 / 1 187 -> 190 / 78 -> 67 / 43 -> 40; 8 of 4096 x 14336
+//     on 8 / 2 / 1, 64 rows 472 -> 451 / 155 -> 136 / 135 -> 112, 128 rows 466 -> 422 / 161 -> 174 / 125 -> 134; but not with
+//     so many experts that the tiles of A rows on one of them are more than 128 k-tiles per CU (512 experts of 4096 x 1536,
+//     first product, 6144 rows on 512 / 64 / 8 1875 -> 1983 / 263 -> 372 / 132 -> 218);
+//   up to 24 where those are no more than 18 per CU and K is not short (64 experts of 2048 x 1408, 132 tiles of 32 and 96 of
+//     22, 1536 rows on 64 / 16 / 1 191 -> 190 / 83 -> 80 / 47 -> 59); with more than that too much is lost (128 experts of
+//     4096 x 1536, 240 tiles of 64 and 320 of 24, 2560 rows on 128 / 32 / 16 745 -> 763 / 237 -> 282 / 144 -> 211; 64 of
+//     4096 x 4096, second product, 160 tiles of 64, 1280 rows on 16 / 8 / 4 97 -> 125 / 64 -> 90 / 64 -> 85; 1024 of
+//     1024 x 512, second product, 8 k-tiles, 18432 rows on 16 / 1 36 -> 46 / 31 -> 45);
+//   up to 64 where even every expert's own ragged 128 x 256 tiles would not go once round the chip (16 experts of 4096 x
+//     688, 1024 rows on 16 / 4 / 1 88 -> 67 / 54 -> 49 / 53 -> 49).
+// Above 16 rows per expert a long K is left to the tiles in any case, their closing ones are computed as parts of K (8
+// experts, K = 14336, second product, 192 rows on 8 / 2 / 1 189 -> 145 / 90 -> 113 / 63 -> 110).
 // Of the two, form 1 (finer units) takes what the 128-column units of form 2 would not bring round the 512
 // workgroups the chip holds, up to 16 rows per expert (8 experts, K = 14336, second product, 32 rows on 8 / 4
 // 139 against 148 / 74 against 94), and small batches of up to 4 (64 experts of 2048 x 1408, first

@@ -10,8 +10,8 @@
 // Anything else goes through the calls of the single steps, in their order; the results are the same integers
 // either way.
 // Whole steps, us, six calls (seven with predicted ids) -> one: 256 tokens of the small fp32 layer 45.0 -> 39.9 (no
-// longer bound by the host, which takes 22), one token on 128 experts 80.2 -> 74.9, 16 tokens of the Mixtral
-// shape as a graph 296 -> 289, 777 tokens with Token-to-Expert 438 -> 427.
+// longer bound by the host, which takes 22), one token on 128 experts 80.2 -> 74.9, 777 tokens with Token-to-Expert 438 ->
+// 427; batches of some 300 us and more gain less than the runs differ.
 #include "permute.h"
 #include "plan_regs.h"
 #include "route_tokens.h"
