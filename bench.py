@@ -35,8 +35,8 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 KERNEL_SOURCES = [os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2506_07366_amd", "csrc", f)
                   for f in ("grouped_ffn.hip", "ffn_tiles.h", "ffn_tables.h")]
 TRAFFIC = {
-    "cfg2_mixtral_dist": {"source_sha256": "0477f0c2a58294cad3dd01a4f666891e8c7fb544893c277cf55ebdb28ad3821e",
-                          "fetch_bytes": 5670507540, "write_bytes": 235089928,
+    "cfg2_mixtral_dist": {"source_sha256": "ebc15c27080546e48e86a8d0189408080555664ab1cb0ac9b11ef86d477348c9",
+                          "fetch_bytes": 5721937688, "write_bytes": 235192986,
                           "profile": "profiles/gemm1_cfg2_mixtral_traffic_counters.md"},
 }
 
