@@ -171,7 +171,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--config", default="cfg2_mixtral_dist")
     ap.add_argument("--tokens", type=int, default=0,
-                    help="run the config's shape at another batch size (the tables of batch sizes in DESIGN.md); "
+                    help="run the config's shape at another batch size; "
                          "the config's own size when 0")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--stages", action="store_true", help="also print per-stage timings to stderr")
