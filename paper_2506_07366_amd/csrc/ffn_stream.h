@@ -32,7 +32,8 @@
 template <int NT, int NW, int EPI>
 __global__ __launch_bounds__(NW * 64) void grouped_gemm_stream_ksplit_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ Bp, size_t b_stride, bf16_t* __restrict__ C,
-    int ldc, const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int N, int K, RowMap rm) {
+    int ldc, const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int N, int K, RowMap rm,
+    int grid, RowCopy copy) {  // workgroups of the product; ahead of them those of the copy
     constexpr bool SWIGLU = EPI == kEpiSwiglu;
     constexpr int UC = NT * 16;     // packed columns of a unit
     constexpr int PITCH = UC + 4;   // floats per row of the exchange
@@ -51,7 +52,12 @@ __global__ __launch_bounds__(NW * 64) void grouped_gemm_stream_ksplit_kernel(
     const int KT = K / kPackK;
     const int kt0 = KT * wave / NW, nk = KT * (wave + 1) / NW - kt0;
 
-    for (int u = blockIdx.x; u < total; u += gridDim.x) {
+    if constexpr (EPI != kEpiNone)
+        if (blockIdx.x < gridDim.x - grid) {
+            copy_part(copy, (int)blockIdx.x * NW + wave);
+            return;
+        }
+    for (int u = (int)blockIdx.x - (int)(gridDim.x - grid); u < total; u += grid) {
         const int entry = u / n_units, nu = u - entry * n_units;
         const MTile mt = mtiles[entry];
         const int col0 = JSTEP == 2 ? (nu >> 1) * 64 + (nu & 1) * 16 : nu * UC;
@@ -157,7 +163,8 @@ constexpr int kStreamBM = 64;  // rows of an M-tile of both forms
 template <int EPI>
 __global__ __launch_bounds__(512, 4) void grouped_gemm_stream_shared_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ Bp, size_t b_stride, bf16_t* __restrict__ C,
-    int ldc, const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int N, int K, RowMap rm) {
+    int ldc, const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int N, int K, RowMap rm,
+    int grid, RowCopy copy) {  // workgroups of the product; behind them those of the copy
     constexpr bool SWIGLU = EPI == kEpiSwiglu;
     constexpr int BM = kStreamBM, NT = 2, KS = 2, NWN = 4;
     constexpr int UC = NT * 16 * NWN;        // packed columns of a unit
@@ -184,8 +191,13 @@ __global__ __launch_bounds__(512, 4) void grouped_gemm_stream_shared_kernel(
     // workgroups), so that the M-tiles of an expert run side by side behind one L2 and share its
     // weights there (popularity 0.1, 128 experts, 256 tokens, 35 of them with 58 rows on average:
     // 345 -> 284 us).
+    if constexpr (EPI != kEpiNone)
+        if ((int)blockIdx.x >= grid) {
+            copy_part(copy, ((int)blockIdx.x - grid) * (NWN * KS) + wave);
+            return;
+        }
     const int slot = blockIdx.x >> 3;
-    for (int u = ((slot >> 4) * 8 + (blockIdx.x & 7)) * 16 + (slot & 15); u < total; u += gridDim.x) {
+    for (int u = ((slot >> 4) * 8 + (blockIdx.x & 7)) * 16 + (slot & 15); u < total; u += grid) {
         int entry = u / n_units, nu = u - entry * n_units;
         MTile mt = mtiles[entry];
         if (mt.n_same > 1) {

@@ -3,6 +3,7 @@
 #pragma once
 #include "common.h"
 #include "block_scan.h"
+#include "row_copy.h"
 
 namespace moegps {
 
@@ -143,11 +144,19 @@ __device__ __forceinline__ int even_height(int rows, int most) {
     return ((rows + n - 1) / n + kHeightStep - 1) / kHeightStep * kHeightStep;
 }
 
+// Row list, and the list of the rows' tokens, rows r being the assignments of[r], `per_token` to a token (null: not wanted).
+struct RowLists {
+    int32_t* rows;
+    int32_t* tokens;
+    const int32_t* of;
+    int per_token;
+};
+
 // Everything a builder needs to know.
 struct TableJob {
     int E, seg_begin, seg_end;
     TableSpec t1, t2;    // of the two products; tiles null: none wanted
-    int32_t* rowlist;
+    RowLists lists;
     int32_t* queues;     // claim counters to set
     int n_queues;
 };
@@ -233,7 +242,9 @@ __device__ __forceinline__ void build_tables(TableScratch<MAXSEG, MAXE, NT>& sh,
                 if (srt_base[mid] <= p) lo = mid;
                 else hi = mid - 1;
             }
-            job.rowlist[p] = srt_first[lo] + (p - srt_base[lo]);
+            const int r = srt_first[lo] + (p - srt_base[lo]);
+            job.lists.rows[p] = r;
+            if (job.lists.tokens) job.lists.tokens[p] = job.lists.of[r] / job.lists.per_token;
         }
     };
     // tables
@@ -392,11 +403,14 @@ FfnOptions ffn_options();
 
 // How much of a grouped FFN call is done: all of it; nothing but its checks and the job of its table
 // builder; or everything behind the builder, which has run (with the options that the job was made with).
+// `copy`: rows that the launch of the first product copies besides (to a place that the call does not read).
+// `tokens`: A ints for the list of the rows' tokens, with gather_rows; without it the first product looks a row up twice.
 enum FfnStage { kFfnAll, kFfnJobOnly, kFfnTablesBuilt };
 int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t* gather_rows, int gather_div,
                      const int32_t* scale_idx, const float* scale, int dtype, int64_t A, int d, int ffn, int E,
                      const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin, int seg_end,
                      const void* packed, void* y_perm, void* workspace, size_t workspace_bytes, void* stream,
-                     const FfnOptions& opt, FfnStage stage = kFfnAll, TableJob* job_out = nullptr);
+                     const FfnOptions& opt, FfnStage stage = kFfnAll, TableJob* job_out = nullptr,
+                     const RowCopy& copy = RowCopy{}, int32_t* tokens = nullptr);
 
 }  // namespace moegps

@@ -23,7 +23,11 @@
 constexpr int kTileMaxRows = 256;  // rows of the tallest tile
 constexpr int kTileGroup = 4;      // N-tiles walked side by side
 constexpr int kNonTemporal = 2;    // cache policy of a buffer load: nt
-constexpr size_t kTileLds = (size_t)3 * kTileMaxRows * kPackK * 2;  // dynamic LDS of a workgroup
+constexpr int kCopyPieces = 6;     // pieces of the row copy that a wavefront takes along with a tile
+constexpr size_t kStageLds = (size_t)3 * kTileMaxRows * kPackK * 2;
+// dynamic LDS of a workgroup: the stages, and in the first product the copy's pieces
+template <int EPI>
+constexpr size_t kTileLds = kStageLds + (EPI != kEpiNone ? 8 * kCopyPieces * kCopyPieceLds : 0);
 
 template <int EPI>
 __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
@@ -32,7 +36,8 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
     bf16_t* __restrict__ C, int ldc,                 // output [rows, SWIGLU ? N/2 : N]
     const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int32_t* __restrict__ queues,
     int N, int K, int group_n, bool past_caches, RowMap rm,
-    float* __restrict__ partials) {  // [slab][kPartRows][N] fp32 sums of entries that cover part of K (plain product only)
+    float* __restrict__ partials,  // [slab][kPartRows][N] fp32 sums of entries that cover part of K (plain product only)
+    RowCopy copy) {                // first product: rows to be copied besides, a share of them with every tile
     constexpr bool SWIGLU = EPI == kEpiSwiglu;
     constexpr int BN = kPackN, BK = kPackK, NW = 8;
     constexpr int ROW_BYTES = BK * 2;      // of an activation row in a stage
@@ -68,6 +73,9 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
     constexpr int run = kGemmGrid / 8;  // the launch is always kGemmGrid workgroups
     const int total = n_entries * n_ntiles;
     const int total_whole = n_whole * n_ntiles;
+    int copy_share = 0;  // pieces of the row copy that go with a tile
+    if constexpr (EPI != kEpiNone)
+        if (copy.x_perm) copy_share = ceil_div(copy.T * ceil_div(copy.chunks, kWave), total > 0 ? total : 1);
     __shared__ volatile int next_tile;
     // The claims are the business of wavefront 0, and every value involved is the same in
     // all its lanes, so the state lives in scalar registers (lane 0 performs the atomic, its
@@ -127,6 +135,25 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
         __builtin_amdgcn_s_barrier();  // also: every wavefront is done reading the previous tile's stages
         const int t_all = __builtin_amdgcn_readfirstlane(next_tile);
         if (t_all < 0) break;
+        // This tile's share of the row copy.  The product is bound by the matrix pipe and leaves memory idle, the copy by
+        // memory: its pieces, and where they go, are on their way to LDS while the tile is worked on and are stored behind
+        // it, in the drain of the tile's own results.  What does not fit into LDS (many tokens for few tiles) is copied here.  Whole
+        // steps, us, a launch of the copy's own -> this: 16384 tokens, top-6 of 64 experts of 2048 x 1408 1659 -> 1624,
+        // 32768, top-8 of 128 of 4096 x 1536 8791 -> 8488, 16384, top-1 of 64 of 768 x 3072 283 -> 276, 2048, top-6
+        // of 64 of 2048 x 1408 392 -> 384.  Loaded and stored at the tile's start instead (one memory round trip more per tile) 1679, 8956,
+        // 279; copied by workgroups behind those of the product, as these run out of tiles, 1665, 8707, 294.
+        int copy_first = 0, copy_n = 0;  // this wavefront's pieces
+        if constexpr (EPI != kEpiNone) {
+            if (copy.x_perm) {
+                const int all = copy.T * ceil_div(copy.chunks, kWave), first = t_all * copy_share;
+                const int end = first + copy_share < all ? first + copy_share : all;
+                const int most = copy_share < NW * kCopyPieces ? ceil_div(copy_share, NW) : kCopyPieces;
+                copy_first = first + wave * most;
+                copy_n = end - copy_first < most ? end - copy_first : most;
+                request_pieces(copy, copy_first, copy_n, smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
+                if (copy_share > NW * kCopyPieces) copy_pieces<NW>(copy, first + NW * kCopyPieces, end, wave);
+            }
+        }
         // The claim for the tile after this one is made towards the end of the K loop and looked at behind
         // it: late, so that the workgroups that are ahead take what is left.
         int ahead_q = -1, ahead_pending = 0;
@@ -193,7 +220,7 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
             constexpr int kAux = decltype(once_tag)::value ? kNonTemporal : 0;
             constexpr int D = TM <= 8 ? 4 : 3;                          // k-tiles under way
             constexpr int STAGE = (TM <= 8 ? 128 : 256) * ROW_BYTES;    // activation bytes of one of them
-            static_assert((size_t)D * STAGE <= kTileLds, "LDS of the launch");
+            static_assert((size_t)D * STAGE <= kStageLds, "LDS of the launch");
             constexpr int IA = (TM + 3) / 4;  // activation loads per wavefront and k-tile, 8 rows each
             constexpr int NB = 4 + IA;        // loads per wavefront and k-tile
             constexpr int NF = 2 * TM;
@@ -414,5 +441,7 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
                 }
             }
         }
+        if constexpr (EPI != kEpiNone)
+            if (copy_n > 0) store_pieces(copy, copy_first, copy_n, (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
     }
 }

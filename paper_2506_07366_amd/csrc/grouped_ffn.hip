@@ -196,8 +196,8 @@ constexpr int kEpiNone = 0, kEpiSwiglu = 1, kEpiRelu = 2;
 
 // Where the rows of a product live.  List position p of an M-tile is
 //   operand row  a_rows ? a_rows[p] : p, and then, with a_rows2, a_rows2[that] / a_div
-//                (the first product reads x_perm through the row list, or the token rows
-//                of x through the row list and assign_of_row);
+//                (the first product reads x_perm through the row list, or rows of x through the list
+//                of their tokens, or through the row list and assign_of_row);
 //   output row   c_rows ? c_rows[p] : p  (the second product writes y_perm through the row list);
 //   output scale scale ? scale[scale_idx[output row]] : 1  (gate weight of the row's assignment).
 struct RowMap {
@@ -208,6 +208,58 @@ struct RowMap {
     const int32_t* scale_idx;
     const float* scale;
 };
+
+// A wavefront's share of the row copy that goes with the first product.
+__device__ __forceinline__ void copy_part(const RowCopy& copy, int wv) {
+    if (copy.chunks >= 4 * kWave) copy_rows<4>(copy, wv);
+    else copy_rows<1>(copy, wv);
+}
+
+// n pieces of the row copy (row_copy.h) from number `first` on, and the rows they go to, asked for by a wavefront into
+// its LDS at `lds`, kCopyPieceLds bytes each (a piece's bytes past the end of its row and destinations past the k-th come as
+// zeros, out of the buffers' ranges) ...
+constexpr int kCopyPieceLds = kCopyPieceBytes + kWave * 4;
+__device__ __forceinline__ void request_pieces(const RowCopy& c, int first, int n, unsigned char* lds) {
+    const unsigned lane = threadIdx.x & (kWave - 1);
+    const int per_row = ceil_div(c.chunks, kWave);
+    int t = first / per_row, q = first - t * per_row;
+    for (int i = 0; i < n; ++i) {
+        const auto row = __builtin_amdgcn_make_buffer_rsrc((void*)(c.x + (size_t)t * c.chunks + q * kWave), 0,
+                                                           (c.chunks - q * kWave) * 16, 0x00027000);
+        const auto ids = __builtin_amdgcn_make_buffer_rsrc((void*)(c.row_of_assign + (size_t)t * c.k), 0, c.k * 4, 0x00027000);
+        unsigned char* at = lds + i * kCopyPieceLds;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(row, (__attribute__((address_space(3))) void*)at, 16, lane * 16, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ids, (__attribute__((address_space(3))) void*)(at + kCopyPieceBytes), 4,
+                                                 lane * 4, 0, 0, 0);
+        if (++q == per_row) {
+            q = 0;
+            ++t;
+        }
+    }
+}
+
+// ... and, once they have landed (LDS address `at`), stored to these rows, which nothing in the call reads: past the caches.
+__device__ __forceinline__ void store_pieces(const RowCopy& c, int first, int n, unsigned at) {
+    typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+    const int lane = opaque((int)threadIdx.x) & (kWave - 1);
+    const int per_row = ceil_div(c.chunks, kWave);
+    int q = first % per_row;
+    for (int i = 0; i < n; ++i, at += kCopyPieceLds) {
+        bf16x8 v;
+        int row;
+        lds_read_b128<0>(v, at + lane * 16);
+        asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(row) : "v"(at + lane * 4), "n"(kCopyPieceBytes) : "memory");
+        lds_wait<0>();
+        lds_landed(v);
+        asm volatile("" : "+v"(row));
+        u32x4* dst = (u32x4*)c.x_perm + q * kWave + lane;
+        if (q * kWave + lane < c.chunks)
+            for (int j = 0; j < c.k; ++j)
+                __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v),
+                                            dst + (size_t)__builtin_amdgcn_readlane(row, j) * c.chunks);
+        if (++q == per_row) q = 0;
+    }
+}
 
 #include "ffn_tiles.h"
 #include "ffn_stream.h"
@@ -271,7 +323,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(const float* __re
                                                                 float* __restrict__ C, int ldc,
                                                                 const MTile* __restrict__ mtiles,
                                                                 const int32_t* __restrict__ counts, int N,
-                                                                int K, RowMap rm, int relu) {
+                                                                int K, RowMap rm, int relu, int grid, RowCopy copy) {
     constexpr int BN = 64;
     constexpr int CH = MT == 2 ? 4 : 2;  // 16-deep steps per chunk
     constexpr int NB = SWIGLU ? 2 : 1;
@@ -281,7 +333,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(const float* __re
     const int n_ntiles = (N + BN - 1) / BN;
     const int total = counts[kCntEntries] * n_ntiles;
     const int n_chunks = (K + 16 * CH - 1) / (16 * CH);
-    for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    if (blockIdx.x < gridDim.x - grid) {
+        copy_part(copy, (int)blockIdx.x * (int)(blockDim.x / kWave) + wave);
+        return;
+    }
+    for (int tile = (int)blockIdx.x - (int)(gridDim.x - grid); tile < total; tile += grid) {
         const MTile mt = mtiles[tile / n_ntiles];
         const int n0 = (tile % n_ntiles) * BN + wave * 16;
         if (n0 >= N) continue;
@@ -512,10 +568,23 @@ static int num_cus() {
 // both products 33 us through the caches, 35 past them.  Above it: see the K loop of the tile kernel.
 constexpr size_t kCachedWeights = (size_t)128 << 20;
 
+// Workgroups that a row copy adds to a launch of workgroups of `threads` threads: none without one.  A wavefront moves
+// 32 KiB at least, once there are a few thousand of them.  They come first in the grid where a workgroup of the
+// product goes on to another as soon as it has run out of units: last, they are what the launch waits for (16 tokens on 8 experts of
+// 4096 x 14336, whole step 333 -> 326 us).  In the second streaming form, whose workgroups all fit on the chip at once, they come last: first,
+// they keep some of these waiting (128 tokens on 128 experts of 4096 x 1536 542 -> 533).
+static int copy_blocks(RowCopy& copy, int threads) {
+    if (!copy.x_perm || copy.T < 1) return 0;
+    const int64_t bytes = (int64_t)(copy.k + 1) * copy.chunks * 16 / copy.slices;
+    const int64_t spare = (int64_t)copy.T * copy.slices / 4096, most = ceil_div64(32768, bytes);
+    copy.per_wave = (int)(spare < 1 ? 1 : spare < most ? spare : most);
+    return (int)ceil_div64((int64_t)copy.T * copy.slices, (int64_t)copy.per_wave * (threads / kWave));
+}
+
 template <int EPI>
 static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_stride, int E, bf16_t* C, int ldc,
                         const MTile* tiles, const int32_t* counts, int32_t* queues, int N, int K, int group_n,
-                        const RowMap& rm, float* partials, hipStream_t st) {
+                        const RowMap& rm, float* partials, RowCopy copy, hipStream_t st) {
     const bool past_caches = (size_t)E * b_stride * sizeof(bf16_t) > kCachedWeights;
     // (the kernel multiplies by it: an option beyond the N-tiles there are means all of them)
     if (group_n > ceil_div(N, kPackN)) group_n = ceil_div(N, kPackN);
@@ -526,7 +595,7 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
     (void)hipGetDevice(&dev);
     const unsigned long long bit = 1ull << (dev & 63);
     if (!(attr_set.load() & bit)) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds);
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds<EPI>);
         if (e != hipSuccess) {
             set_last_hip_error(e);
             return MOE_ERR_HIP;
@@ -534,8 +603,8 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
         attr_set.fetch_or(bit);
     }
     // 32 workgroups for each of the 8 XCDs; they claim tiles from `queues` (cleared by the table builder)
-    hipLaunchKernelGGL(kern, dim3(kGemmGrid), dim3(512), kTileLds, st, A, lda, Bp, b_stride, C, ldc, tiles, counts,
-                       queues, N, K, group_n, past_caches, rm, partials);
+    hipLaunchKernelGGL(kern, dim3(kGemmGrid), dim3(512), kTileLds<EPI>, st, A, lda, Bp, b_stride, C, ldc, tiles, counts, queues, N, K,
+                       group_n, past_caches, rm, partials, copy);
     return check_launch();
 }
 
@@ -585,9 +654,11 @@ static int stream_form(int opt, int forced_tile, int64_t A, int E, int n_cols, i
 template <int EPI>
 static int launch_stream(int form, int64_t A, int E, const bf16_t* X, int lda, const bf16_t* Bp, size_t b_stride,
                          bf16_t* C, int ldc, const MTile* tiles, const int32_t* counts, int N, int K, const RowMap& rm,
-                         hipStream_t st) {
+                         RowCopy copy, hipStream_t st) {
     auto go = [&](auto kern, int grid, int threads) {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, X, lda, Bp, b_stride, C, ldc, tiles, counts, N, K, rm);
+        const int all = grid + copy_blocks(copy, threads);
+        hipLaunchKernelGGL(kern, dim3(all), dim3(threads), 0, st, X, lda, Bp, b_stride, C, ldc, tiles, counts, N, K, rm, grid,
+                           copy);
         return check_launch();
     };
     // The registers let a CU hold two workgroups of form 2; of form 1 one (<4, 8>) or two, its kernels
@@ -724,7 +795,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
                      const int32_t* scale_idx, const float* scale, int dtype, int64_t A, int d, int ffn, int E,
                      const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin, int seg_end,
                      const void* packed, void* y_perm, void* workspace, size_t workspace_bytes, void* stream,
-                     const FfnOptions& opt, FfnStage stage, TableJob* job_out) {
+                     const FfnOptions& opt, FfnStage stage, TableJob* job_out, const RowCopy& copy, int32_t* tokens) {
     const bool timed = g_time_armed && stage != kFfnJobOnly;
     if (stage != kFfnJobOnly) g_time_armed = false;  // the hook belongs to this call, whatever becomes of it
     if (dtype != MOE_DTYPE_F32 && dtype != MOE_DTYPE_BF16) return MOE_ERR_INVALID_ARG;
@@ -764,8 +835,17 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
         *rc_out = check_launch();
         return *rc_out == MOE_OK;
     };
-    RowMap rm1{ws.rowlist, gather_rows, gather_div, nullptr, nullptr, nullptr};
-    RowMap rm2{nullptr, nullptr, 1, ws.rowlist, scale_idx, scale};
+    // Forms of the first product's kernels, and how they find their rows: the streaming ones, with a handful of rows to an
+    // M-tile, look a gathered row up twice (a list of tokens costs the workgroup that builds the tables a memory round trip, one token
+    // on 128 experts 75.9 -> 76.7 us), the others once (16384 tokens on 64 experts of 768 x 3072 119 -> 113, the product alone).
+    const int fp = padded_ffn(ffn, dtype);  // hidden width the kernels see
+    const int n1 = relu ? 1 : 2;            // matrices in the first product
+    const int s1 = dtype == MOE_DTYPE_F32 ? 0 : stream_form(opt.stream, opt.tile1, A, E, n1 * fp, d / kPackK);
+    if (s1) tokens = nullptr;
+    const RowMap rm1 = tokens ? RowMap{tokens, nullptr, 1, nullptr, nullptr, nullptr}
+                              : RowMap{ws.rowlist, gather_rows, gather_div, nullptr, nullptr, nullptr};
+    const RowMap rm2{nullptr, nullptr, 1, ws.rowlist, scale_idx, scale};
+    const RowLists lists{ws.rowlist, tokens, gather_rows, gather_div};
 
     if (dtype == MOE_DTYPE_F32) {
         // 32-row tiles until 64-row ones would go twice round the CUs for the wider product
@@ -773,35 +853,33 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
         const int bm = tiles64 < 2 * kGemmGrid ? 32 : 64;
         TableSpec t1{ws.tiles1, ws.counts, nullptr, bm, ws.capacity, 0, 0, 1, 0, 0};
         TableSpec none{};
-        if (!tables(TableJob{E, seg_begin, seg_end, t1, none, ws.rowlist, nullptr, 0}, &rc)) return rc;
+        if (!tables(TableJob{E, seg_begin, seg_end, t1, none, lists, nullptr, 0}, &rc)) return rc;
         const float* w1 = (const float*)packed;
         const float* w3 = w1 + per;
         const float* w2 = relu ? w3 : w3 + per;
         const int grid = 4 * num_cus();
         auto go = [&](auto kern, const float* X, int lda, const float* b1, const float* b3, float* Cp, int ldc, int N,
-                      int K, const RowMap& rm, int is_relu) {
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, X, lda, b1, b3, (size_t)d * ffn, Cp, ldc, ws.tiles1,
-                               ws.counts, N, K, rm, is_relu);
+                      int K, const RowMap& rm, int is_relu, RowCopy cp) {
+            const int all = grid + copy_blocks(cp, 256);
+            hipLaunchKernelGGL(kern, dim3(all), dim3(256), 0, st, X, lda, b1, b3, (size_t)d * ffn, Cp, ldc, ws.tiles1,
+                               ws.counts, N, K, rm, is_relu, grid, cp);
             return check_launch();
         };
         const bool low = bm == 32;
         if (relu)
             rc = go(low ? grouped_gemm_f32_kernel<2, false> : grouped_gemm_f32_kernel<4, false>, (const float*)x_in, d,
-                    w1, nullptr, (float*)ws.h, ffn, ffn, d, rm1, 1);
+                    w1, nullptr, (float*)ws.h, ffn, ffn, d, rm1, 1, copy);
         else
             rc = go(low ? grouped_gemm_f32_kernel<2, true> : grouped_gemm_f32_kernel<4, true>, (const float*)x_in, d,
-                    w1, w3, (float*)ws.h, ffn, ffn, d, rm1, 0);
+                    w1, w3, (float*)ws.h, ffn, ffn, d, rm1, 0, copy);
         if (rc != MOE_OK) return rc;
         return go(low ? grouped_gemm_f32_kernel<2, false> : grouped_gemm_f32_kernel<4, false>, (const float*)ws.h, ffn,
-                  w2, nullptr, (float*)y_perm, d, d, ffn, rm2, 0);
+                  w2, nullptr, (float*)y_perm, d, d, ffn, rm2, 0, RowCopy{});
     }
 
-    // Batches of a few rows per expert stream their weights (stream_form); for the rest the table
-    // builder chooses the height of the tiles.
-    const int fp = padded_ffn(ffn, dtype);  // hidden width the kernels see
-    const int n1 = relu ? 1 : 2;            // matrices in the first product
+    // Batches of a few rows per expert stream their weights; for the rest the table builder chooses the height of
+    // the tiles.
     const int v1 = opt.tile1, v2 = opt.tile2;
-    const int s1 = stream_form(opt.stream, v1, A, E, n1 * fp, d / kPackK);
     const int s2 = opt.split == 1 ? 0 : stream_form(opt.stream, v2, A, E, d, fp / kPackK);
     // N-tiles walked side by side over the M-tiles of an expert: see the tile order in ffn_tiles.h
     const int group_n = opt.group_n > 0 ? opt.group_n : kTileGroup;
@@ -815,7 +893,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
                  ceil_div(n1 * fp, kPackN), 0, 0};
     TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / kPackK,
                  split ? ws.parts : 0, ceil_div(d, kPackN), ws.split_all, ws.split_capacity};
-    if (!tables(TableJob{E, seg_begin, seg_end, t1, t2, ws.rowlist, ws.queues, 16}, &rc)) return rc;
+    if (!tables(TableJob{E, seg_begin, seg_end, t1, t2, lists, ws.queues, 16}, &rc)) return rc;
     const MTile* tiles2 = own2 ? ws.tiles2 : ws.tiles1;
     const int32_t* count2 = own2 ? ws.counts + kCntStride : ws.counts;
     const bf16_t* p13 = (const bf16_t*)packed;
@@ -823,23 +901,23 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     if (timed) (void)hipEventRecord(g_time_events[0], st);
     if (s1) {
         rc = relu ? launch_stream<kEpiRelu>(s1, A, E, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h,
-                                            fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, st)
+                                            fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, copy, st)
                   : launch_stream<kEpiSwiglu>(s1, A, E, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp),
-                                              (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, st);
+                                              (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, copy, st);
     } else {
         const auto go = relu ? launch_tiles<kEpiRelu> : launch_tiles<kEpiSwiglu>;
         rc = go((const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), E, (bf16_t*)ws.h, fp, ws.tiles1, ws.counts, ws.queues,
-                n1 * fp, d, group_n, rm1, nullptr, st);
+                n1 * fp, d, group_n, rm1, nullptr, copy, st);
     }
     if (timed) (void)hipEventRecord(g_time_events[1], st);
     if (rc != MOE_OK) return rc;
     if (timed) (void)hipEventRecord(g_time_events[2], st);
     if (s2)
         rc = launch_stream<kEpiNone>(s2, A, E, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d,
-                                     tiles2, count2, d, fp, rm2, st);
+                                     tiles2, count2, d, fp, rm2, RowCopy{}, st);
     else
         rc = launch_tiles<kEpiNone>((const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), E, (bf16_t*)y_perm, d, tiles2, count2,
-                                    ws.queues + 8, d, fp, group_n, rm2, ws.partials, st);
+                                    ws.queues + 8, d, fp, group_n, rm2, ws.partials, RowCopy{}, st);
     if (rc == MOE_OK && split) {
         hipLaunchKernelGGL(add_partials_kernel, dim3(ws.split_capacity < 64 ? ws.split_capacity : 64, 32), dim3(256),
                            0, st, ws.partials, ws.splits, count2, ws.parts, (bf16_t*)y_perm, d, d, rm2);

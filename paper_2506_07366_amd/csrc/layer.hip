@@ -7,6 +7,8 @@
 //     after counting the predicted ids) while the others of the same launch route the tokens;
 //   - where the permutation is one workgroup's work it also writes the histogram, without a prediction
 //     the plan, which then is the home placement, and goes on to the tables of the grouped FFN.
+//   - the permuted rows are for the caller alone: the first product reads its rows from x, and the copy goes with its
+//     launch (ffn_tiles.h, grouped_ffn.hip).
 // Anything else goes through the calls of the single steps, in their order; the results are the same integers
 // either way.
 // Whole steps, us, six calls (seven with predicted ids) -> one: 256 tokens of the small fp32 layer 45.0 -> 39.9 (no
@@ -131,6 +133,7 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     if (!a->x_perm && (int64_t)T * a->d >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;  // 32-bit element offsets into x
     const int64_t A = (int64_t)T * k;
     if (a->workspace_perm_bytes < moe_permute_workspace_bytes(T, E, k, G, S)) return MOE_ERR_WORKSPACE_TOO_SMALL;
+    if (a->x_perm && a->dtype == MOE_DTYPE_BF16 && A * a->d >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;  // as moe_grouped_ffn
     hipStream_t st = (hipStream_t)stream;
     int rc;
     const int32_t* hp = mode == MOE_MODE_TOKEN ? a->hist_plan : mode == MOE_MODE_DISTRIBUTION ? a->hist_pred : a->hist;
@@ -149,13 +152,18 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
                                    a->n_iters, stream);
     };
     const float* gate = a->x_perm ? nullptr : a->gate_in_ffn ? a->topk_w : nullptr;
+    // The permuted rows are for the caller: the first product reads the rows of x, and they are copied beside it.
+    const RowCopy copy = a->x_perm ? row_copy(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm) : RowCopy{};
+    // The permutation's scratch, done with by then, takes the list of the rows' tokens (it is larger than A ints), unless the caller
+    // has it share memory with what the first product writes.
+    const bool scratch_free = !share_bytes(a->workspace_perm, ids, a->workspace_ffn, a->workspace_ffn_bytes) &&
+                              !(a->x_perm && share_bytes(a->workspace_perm, ids, a->x_perm, (size_t)A * a->d * dtype_size(a->dtype)));
+    int32_t* const tokens = scratch_free ? (int32_t*)a->workspace_perm : nullptr;
     const FfnOptions opt = ffn_options();  // (once: the job and the products go by the same)
     auto ffn = [&](FfnStage stage, TableJob* job) {
-        const bool gather = !a->x_perm;
-        return grouped_ffn_call(a->relu, gather ? a->x : a->x_perm, gather ? T : A, gather ? a->assign_of_row : nullptr,
-                                gather ? k : 1, gate ? a->assign_of_row : nullptr, gate, a->dtype, A, a->d, a->ffn, E,
-                                a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm, a->workspace_ffn,
-                                a->workspace_ffn_bytes, stream, opt, stage, job);
+        return grouped_ffn_call(a->relu, a->x, T, a->assign_of_row, k, gate ? a->assign_of_row : nullptr, gate, a->dtype, A,
+                                a->d, a->ffn, E, a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm,
+                                a->workspace_ffn, a->workspace_ffn_bytes, stream, opt, stage, job, copy, tokens);
     };
     TableJob job{};
     if ((rc = ffn(kFfnJobOnly, &job)) != MOE_OK) return rc;  // (checks its arguments, launches nothing)
@@ -181,13 +189,12 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
         const HomePlan home{a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters};
         rc = permute_and_count(mode, T, k, E, G, S, a->topk_idx, a->pred_idx, hp, a->slot_expert, a->slot_quota,
                                a->seg_offsets, a->row_of_assign, a->assign_of_row, a->rank_load, a->hist, home, job, st);
-        if (rc == MOE_OK && a->x_perm) rc = scatter_rows(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm, st);
     } else {
         if (!own_pred && (rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
         if (mode == MOE_MODE_NONE && (rc = plan()) != MOE_OK) return rc;
-        rc = moe_permute(mode, a->x_perm ? a->x : nullptr, a->dtype, T, a->d, E, k, G, S, a->topk_idx,
+        rc = moe_permute(mode, nullptr, a->dtype, T, a->d, E, k, G, S, a->topk_idx,
                          mode == MOE_MODE_TOKEN ? a->pred_idx : nullptr, a->hist, hp, a->slot_expert, a->slot_quota,
-                         a->seg_offsets, a->row_of_assign, a->assign_of_row, a->x_perm, a->rank_load, a->workspace_perm,
+                         a->seg_offsets, a->row_of_assign, a->assign_of_row, nullptr, a->rank_load, a->workspace_perm,
                          a->workspace_perm_bytes, stream);
     }
     if (rc != MOE_OK) return rc;

@@ -19,8 +19,4 @@ int permute_and_count(int mode, int T, int k, int E, int G, int S, const int32_t
                       int32_t* seg_offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* rank_load,
                       int32_t* hist_out, const HomePlan& home, const TableJob& job, hipStream_t st);
 
-// x_perm[row_of_assign[t*k + j], :] = x[t, :] (row bytes a multiple of 16, T >= 1).
-int scatter_rows(const void* x, int dtype, int T, int d, int k, const int32_t* row_of_assign, void* x_perm,
-                 hipStream_t st);
-
 }  // namespace moegps

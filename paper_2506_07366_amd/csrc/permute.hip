@@ -13,7 +13,8 @@
 //              same launch turn the plan into per-expert replica tables
 //   segment  : stable rank -> replica -> segment id; per-chunk segment histogram
 //   place    : seg_offsets, rank_load, row_of_assign / assign_of_row
-//   scatter  : each token row is read once and written to its k rows of x_perm
+//   scatter  : each token row is read once and written to its k rows of x_perm (a whole step leaves that to
+//              the launch of the first FFN product, row_copy.h)
 //
 // These kernels are bound by latency, each costs 4-5 us whatever it does, so a workgroup of
 // "segment" and "place" adds up the counts of the chunks before its own by itself (a few hundred
@@ -31,6 +32,7 @@
 // workgroup and one launch: the same ranks and scans, the chunk being the whole batch (one_workgroup_limit).
 #include "permute.h"
 #include "block_scan.h"
+#include "row_copy.h"
 #include <initializer_list>
 #include <mutex>
 
@@ -587,7 +589,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     int mode, int T, int k, int E, int G, int S, const int32_t* __restrict__ topk_idx,
     const int32_t* __restrict__ pred_idx, const int32_t* __restrict__ hist_true, const int32_t* __restrict__ hist_pred,
     const int32_t* __restrict__ slot_expert, const int32_t* __restrict__ slot_quota,
-    int32_t* __restrict__ seg_offsets, int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row,
+    int32_t* __restrict__ seg_offsets, int32_t* __restrict__ row_of_assign, int32_t* assign_of_row,
     int32_t* __restrict__ rank_load, int32_t* __restrict__ hist_out, HomePlan home, TableJob job) {
     // one buffer, three lives: wavefront counters of the first rank; rank and key by position
     // (token-to-expert mode looks up those of the token's predicted ids); counters of the second
@@ -763,7 +765,7 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
         row_of_assign[p] = row;
         assign_of_row[row] = p;
     }
-    if (WHOLE_STEP && job.rowlist) {
+    if (WHOLE_STEP && job.lists.rows) {
         __syncthreads();  // the counters are dead for good
         using Scratch = TableScratch<kSmallKeys, kSmallKeys, 2>;
         static_assert(sizeof(Scratch) <= sizeof(buf), "the tables' scratch takes the counters' place");
@@ -771,38 +773,9 @@ __global__ __launch_bounds__(kSmallThreads) void perm_small_kernel(
     }
 }
 
-// x_perm[row_of_assign[t*k + j], :] = x[t, :]: one wavefront per token, the row is
-// read once (16 bytes per lane per piece, UNROLL pieces in flight) and stored to its k
-// destinations.
 template <int UNROLL>
-__global__ __launch_bounds__(256) void perm_scatter_rows_kernel(const uint4* __restrict__ x,
-                                                                 uint4* __restrict__ x_perm,
-                                                                 const int32_t* __restrict__ row_of_assign, int T,
-                                                                 int k, int chunks, int slices) {
-    typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
-    const int lane = threadIdx.x & (kWave - 1);
-    // wavefront wv serves slice wv % slices of token wv / slices (several per token only for small batches)
-    const int wv = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * (unsigned)blockDim.x + threadIdx.x) / kWave));
-    const int t = wv / slices, slice = wv % slices;
-    if (t >= T) return;
-    int rows[MOE_MAX_TOPK];
-#pragma unroll
-    for (int j = 0; j < MOE_MAX_TOPK; ++j) rows[j] = j < k ? row_of_assign[(size_t)t * k + j] : 0;
-    const u32x4* src = (const u32x4*)x + (size_t)t * chunks;
-    u32x4* dst = (u32x4*)x_perm;
-    for (int c0 = lane + slice * kWave * UNROLL; c0 < chunks; c0 += kWave * UNROLL * slices) {
-        u32x4 v[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-            if (c0 + u * kWave < chunks) v[u] = src[c0 + u * kWave];
-#pragma unroll
-        for (int j = 0; j < MOE_MAX_TOPK; ++j)
-            if (j < k) {
-#pragma unroll
-                for (int u = 0; u < UNROLL; ++u)
-                    if (c0 + u * kWave < chunks) dst[(size_t)rows[j] * chunks + c0 + u * kWave] = v[u];
-            }
-    }
+__global__ __launch_bounds__(256) void perm_scatter_rows_kernel(RowCopy copy) {
+    copy_rows<UNROLL>(copy, __builtin_amdgcn_readfirstlane((int)((blockIdx.x * (unsigned)blockDim.x + threadIdx.x) / kWave)));
 }
 
 }  // namespace moegps
@@ -843,19 +816,10 @@ int permute_and_count(int mode, int T, int k, int E, int G, int S, const int32_t
     return check_launch();
 }
 
-int scatter_rows(const void* x, int dtype, int T, int d, int k, const int32_t* row_of_assign, void* x_perm,
-                 hipStream_t st) {
-    const int chunks = (int)((size_t)d * dtype_size(dtype) / 16);
-    const int unroll = chunks >= 4 * kWave ? 4 : 1;
-    // a small batch: split every row over several wavefronts until there are a few thousand
-    int slices = 1;
-    while (slices < 16 && (int64_t)T * slices < 4096 && chunks >= 2 * slices * kWave * unroll) slices *= 2;
-    auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64((int64_t)T * slices, 4)), dim3(256), 0, st, (const uint4*)x,
-                           (uint4*)x_perm, row_of_assign, T, k, chunks, slices);
-    };
-    if (unroll == 4) launch(perm_scatter_rows_kernel<4>);
-    else launch(perm_scatter_rows_kernel<1>);
+static int scatter_rows(const RowCopy& copy, hipStream_t st) {
+    const dim3 grid((unsigned)ceil_div64((int64_t)copy.T * copy.slices, 4));
+    if (row_copy_unroll(copy.chunks) == 4) hipLaunchKernelGGL(perm_scatter_rows_kernel<4>, grid, dim3(256), 0, st, copy);
+    else hipLaunchKernelGGL(perm_scatter_rows_kernel<1>, grid, dim3(256), 0, st, copy);
     return check_launch();
 }
 
@@ -920,7 +884,7 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
         }
     }
     if (nb > 0) {
-        if (x_perm && (rc = scatter_rows(x, dtype, T, d, k, row_of_assign, x_perm, st)) != MOE_OK) return rc;
+        if (x_perm && (rc = scatter_rows(row_copy(x, dtype, T, d, k, row_of_assign, x_perm), st)) != MOE_OK) return rc;
     }
     return MOE_OK;
 }

@@ -158,3 +158,62 @@ def test_step_leaves_other_inputs_to_the_single_calls():
         layer.step(logits.double(), x, hist_pred=hist)
     with pytest.raises(Exception):
         layer.step(logits, x, hist_pred=hist.long())
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype,act,stream", [
+    (1, 64, 8, 2, "bf16", "swiglu", -1),        # one token: fewer wavefronts than a workgroup has
+    (37, 2048, 8, 2, "bf16", "swiglu", 1),      # weights streamed, first form; rows shared by several wavefronts
+    (37, 2112, 8, 16 // 2, "bf16", "relu", 2),  # second form, a row that is no whole number of pieces per lane
+    (200, 4096, 16, 4, "bf16", "swiglu", 0),    # tiles
+    (5003, 192, 4, 1, "bf16", "relu", 0),       # short rows, several per wavefront, the last wavefront with fewer
+    (777, 1088, 8, 3, "bf16", "swiglu", -1),
+    (1, 4, 3, 1, "f32", "swiglu", -1),          # one piece a row
+    (515, 132, 8, 2, "f32", "relu", -1),
+])
+def test_step_copies_every_row(T, d, E, k, dtype, act, stream):
+    """x_perm of a whole step, copied beside the first product: every row, nothing behind the last one."""
+    from paper_2506_07366_amd import binding as B
+    cfg = wl.MoEConfig("copy", T=T, d=d, ffn=64, E=E, k=k, G=2, S=E, dtype=dtype, mode=0, seed=67, act=act)
+    gen = torch.Generator(device="cuda").manual_seed(68)
+    layer = MoELayer(cfg)
+    dt = layer.out.dtype
+    layer.set_weights(*[torch.randn(s, device="cuda", generator=gen).mul_(0.02).to(dt)
+                        for s in ((E, d, 64), (E, d, 64), (E, 64, d))])
+    store = torch.full((cfg.A + 8, d), -7, dtype=dt, device="cuda")
+    layer.perm["x_perm"] = store[:cfg.A]
+    logits = torch.randn((T, E), device="cuda", generator=gen)
+    x = torch.randn((T, d), device="cuda", generator=gen).to(dt)
+    B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, stream)
+    try:
+        assert layer._one_call(logits, x, None, None, 0)
+    finally:
+        B.moe_grouped_ffn_set_option(B.FFN_OPT_STREAM, -1)
+    assert torch.equal(store[:cfg.A], x[layer.perm["assign_of_row"].long() // k])
+    assert bool((store[cfg.A:] == -7).all())
+
+
+@pytest.mark.parametrize("gather", [False, True])
+@pytest.mark.parametrize("T", [200, 3000])           # one workgroup permutes, several
+def test_step_with_scratch_shared_by_its_stages(T, gather):
+    """The permutation's scratch is the FFN's, or lies in x_perm: nothing of the one is wanted once the other is written."""
+    cfg = wl.MoEConfig("shared", T=T, d=128, ffn=128, E=16, k=4, G=4, S=5, dtype="bf16", mode=1, seed=69)
+    gen = torch.Generator(device="cuda").manual_seed(70)
+    ws = [torch.randn(s, device="cuda", generator=gen).mul_(0.02).to(torch.bfloat16)
+          for s in ((16, 128, 128), (16, 128, 128), (16, 128, 128))]
+    logits = torch.randn((T, 16), device="cuda", generator=gen)
+    x = torch.randn((T, 128), device="cuda", generator=gen).to(torch.bfloat16)
+    hist = torch.bincount(torch.topk(logits, 4, dim=1).indices.reshape(-1), minlength=16).to(torch.int32)
+    got = []
+    for shared in (None, "ffn", "x_perm"):
+        layer = MoELayer(cfg, fused_gather=gather)
+        layer.set_weights(*ws)
+        if shared == "ffn":
+            layer.ws_perm = layer.ws_ffn = torch.empty(max(layer.ws_perm.numel(), layer.ws_ffn.numel()), dtype=torch.uint8,
+                                                       device="cuda")
+        elif shared == "x_perm" and not gather:
+            layer.ws_perm = layer.perm["x_perm"].view(torch.uint8).reshape(-1)
+        assert layer._one_call(logits, x, hist, None, 1)
+        got.append(outputs(layer))
+    for other in got[1:]:
+        for n, v in got[0].items():
+            assert torch.equal(other[n], v), n
