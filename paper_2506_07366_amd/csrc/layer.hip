@@ -31,6 +31,7 @@ struct PlanJob {
     const int32_t* pred_idx;
     int n_pred;
     int32_t *hist_plan, *slot_expert, *slot_quota, *rank_load_pred, *n_iters;
+    int32_t* hist;             // counts that a later launch adds to, cleared here; null: none
 };
 
 // Workgroup 0 plans, the others route.  The plan is the longer of the two up to some 30000 tokens: us of
@@ -55,6 +56,9 @@ __global__ __launch_bounds__(kRouteThreads) void route_plan_kernel(PlanJob p, co
         else route_tokens<16, 16>(block, logits, T, E, k, topk_idx, topk_w);
         return;
     }
+    if (p.hist)
+        for (int e = threadIdx.x; e < E; e += kRouteThreads) p.hist[e] = 0;
+    if (p.mode == MOE_MODE_NONE) return;  // (the plan is the home placement, made from the batch's counts)
     const int32_t* hist = p.hist_pred;
     if (!hist) {
         static_assert(kPlanMaxExperts <= kRouteThreads, "a thread per expert");
@@ -145,8 +149,10 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     const bool own_pred = pred && (share_bytes(pred, n_pred, a->topk_idx, ids) || share_bytes(pred, n_pred, a->topk_w, ids) ||
                                    share_bytes(pred, n_pred, a->hist, counts));
     const bool small = !own_pred && permute_in_one_workgroup(mode, A, E, G * S);
-    const bool together =
-        !own_pred && mode != MOE_MODE_NONE && E <= kPlanMaxExperts && S <= kPlanMaxSlots && G <= 32;
+    const bool shared = !own_pred && E <= kPlanMaxExperts && S <= kPlanMaxSlots && G <= 32;
+    // several workgroups permute and add up the histogram, which the first launch clears
+    const bool wide = shared && !small && permute_counts(T, E, k, G, S);
+    const bool together = shared && (wide || mode != MOE_MODE_NONE);
     auto plan = [&] {
         return moe_plan_duplicates(mode, hp, E, G, S, a->c_max, a->slot_expert, a->slot_quota, a->rank_load_pred,
                                    a->n_iters, stream);
@@ -177,7 +183,7 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
         if (mode == MOE_MODE_TOKEN && !count && (rc = moe_histogram(a->pred_idx, A, E, a->hist_plan, stream)) != MOE_OK)
             return rc;
         const PlanJob p{mode, E, G, S, a->c_max, count ? nullptr : hp, a->pred_idx, (int)A, a->hist_plan,
-                        a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters};
+                        a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters, wide ? a->hist : nullptr};
         if ((rc = route_and_plan(p, a->logits, T, k, a->topk_idx, a->topk_w, st)) != MOE_OK) return rc;
     } else {
         if ((rc = moe_route_topk(a->logits, T, E, k, a->topk_idx, a->topk_w, stream)) != MOE_OK) return rc;
@@ -189,6 +195,11 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
         const HomePlan home{a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters};
         rc = permute_and_count(mode, T, k, E, G, S, a->topk_idx, a->pred_idx, hp, a->slot_expert, a->slot_quota,
                                a->seg_offsets, a->row_of_assign, a->assign_of_row, a->rank_load, a->hist, home, job, st);
+    } else if (wide) {
+        const HomePlan home{a->slot_expert, a->slot_quota, a->rank_load_pred, a->n_iters};
+        rc = permute_and_count_wide(mode, T, k, E, G, S, a->topk_idx, a->pred_idx, hp, a->slot_expert, a->slot_quota,
+                                    a->seg_offsets, a->row_of_assign, a->assign_of_row, a->rank_load, a->hist, home,
+                                    a->workspace_perm, st);
     } else {
         if (!own_pred && (rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
         if (mode == MOE_MODE_NONE && (rc = plan()) != MOE_OK) return rc;

@@ -19,4 +19,12 @@ int permute_and_count(int mode, int T, int k, int E, int G, int S, const int32_t
                       int32_t* seg_offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* rank_load,
                       int32_t* hist_out, const HomePlan& home, const TableJob& job, hipStream_t st);
 
+// The same by many workgroups, for batches that permute_counts() says they count; hist_out is zero before.  (The tables are
+// a launch of their own.)
+bool permute_counts(int T, int E, int k, int G, int S);
+int permute_and_count_wide(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
+                           const int32_t* hist_pred, const int32_t* slot_expert, const int32_t* slot_quota,
+                           int32_t* seg_offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* rank_load,
+                           int32_t* hist_out, const HomePlan& home, void* workspace, hipStream_t st);
+
 }  // namespace moegps

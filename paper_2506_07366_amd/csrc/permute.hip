@@ -82,7 +82,7 @@ static PermWs perm_ws_layout(int T, int E, int k, int G, int S, char* base) {
         w.nb = T > 0 ? ceil_div(T, tokens_per_chunk(k, w.rounds)) : 0;
         size_t off = 0;
         auto take = [&](size_t bytes) {
-            char* p = base + off;
+            char* p = base ? base + off : nullptr;
             off += align_up(bytes, 256);
             return p;
         };
@@ -94,6 +94,11 @@ static PermWs perm_ws_layout(int T, int E, int k, int G, int S, char* base) {
         w.rep_hi = (int32_t*)take((size_t)E * G * 4);
         if (off <= have || w.rounds == kRounds) return w;
     }
+}
+
+// more chunks than the workgroups add up by themselves
+static inline bool perm_scanned(const PermWs& ws) {
+    return ws.nb == 0 || (ws.nb > kSelfScanChunks && ws.rounds == kRounds);
 }
 
 __device__ __forceinline__ int clamp_key(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
@@ -206,7 +211,8 @@ __device__ __forceinline__ void wave_columns_scan(int32_t* table, int nb, int nc
 }
 
 // Replicas of expert e in ascending slot id with the exclusive upper bound of each
-// replica's range of ranks, by one wavefront (every lane active).
+// replica's range of ranks, by one wavefront (every lane active).  In mode 1 without hist_true (a whole step, whose
+// histogram is being counted by the same launch) the bound is the quota up to the replica, for segment_of to scale.
 __device__ __forceinline__ void replica_table(int e, int mode, int G, int nseg, const int32_t* __restrict__ hist_true,
                                               const int32_t* __restrict__ hist_pred,
                                               const int32_t* __restrict__ slot_expert,
@@ -215,7 +221,7 @@ __device__ __forceinline__ void replica_table(int e, int mode, int G, int nseg, 
     const unsigned long long lt = (1ull << lane) - 1ull;
     long long n_true = 0, n_hat = 0;
     if (mode == MOE_MODE_DISTRIBUTION) {
-        n_true = hist_true[e];
+        if (hist_true) n_true = hist_true[e];
         n_hat = hist_pred[e];
     }
     int cnt = 0;
@@ -230,7 +236,7 @@ __device__ __forceinline__ void replica_table(int e, int mode, int G, int nseg, 
             const int pos = cnt + __popcll(m & lt);
             if (match && pos < G) {
                 long long hi = cum + incl;                                       // Q_{r+1}
-                if (mode == MOE_MODE_DISTRIBUTION) hi = (n_true * hi) / n_hat;   // floor(n_e * Q / nhat_e)
+                if (mode == MOE_MODE_DISTRIBUTION && hist_true) hi = (n_true * hi) / n_hat;  // floor(n_e * Q / nhat_e)
                 if (hi > 0x7fffffffLL) hi = 0x7fffffffLL;
                 ws.rep_slot[(size_t)e * G + pos] = sigma;
                 ws.rep_hi[(size_t)e * G + pos] = (int)hi;
@@ -243,14 +249,17 @@ __device__ __forceinline__ void replica_table(int e, int mode, int G, int nseg, 
 }
 
 // per-chunk histogram of the dispatch keys (workgroups below ws.nb) and the replica tables of the
-// plan (the workgroups above, one wavefront per expert)
+// plan (the workgroups above, one wavefront per expert); the histogram of the keys is added to hist_out, if
+// there is one (ids of no expert are ranked as the nearest one and counted for none)
 __global__ __launch_bounds__(kPermThreads) void perm_count_kernel(const int32_t* __restrict__ keys, int mode, int T,
                                                                    int k, int E, int G, int S,
                                                                    const int32_t* __restrict__ hist_true,
                                                                    const int32_t* __restrict__ hist_pred,
                                                                    const int32_t* __restrict__ slot_expert,
-                                                                   const int32_t* __restrict__ slot_quota, PermWs ws) {
+                                                                   const int32_t* __restrict__ slot_quota, PermWs ws,
+                                                                   int32_t* __restrict__ hist_out) {
     __shared__ int bins[MOE_MAX_EXPERTS];
+    __shared__ int strays[2];  // ids below 0, from E on
     if ((int)blockIdx.x >= ws.nb) {
         const int e = ((int)blockIdx.x - ws.nb) * kPermWaves + (int)threadIdx.x / kWave;
         if (e < E) replica_table(e, mode, G, G * S, hist_true, hist_pred, slot_expert, slot_quota, ws);
@@ -261,10 +270,20 @@ __global__ __launch_bounds__(kPermThreads) void perm_count_kernel(const int32_t*
     const int64_t A = (int64_t)T * k;
     const int64_t hi = lo + (int64_t)tpc * k < A ? lo + (int64_t)tpc * k : A;
     for (int e = threadIdx.x; e < E; e += blockDim.x) bins[e] = 0;
+    if (threadIdx.x < 2) strays[threadIdx.x] = 0;
     __syncthreads();
-    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) atomicAdd(&bins[clamp_key(keys[i], E)], 1);
+    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
+        const int id = keys[i];
+        atomicAdd(&bins[clamp_key(id, E)], 1);
+        if ((unsigned)id >= (unsigned)E) atomicAdd(&strays[id < 0 ? 0 : 1], 1);
+    }
     __syncthreads();
-    for (int e = threadIdx.x; e < E; e += blockDim.x) ws.bh1[(size_t)blockIdx.x * E + e] = bins[e];
+    for (int e = threadIdx.x; e < E; e += blockDim.x) {
+        const int n = bins[e];
+        ws.bh1[(size_t)blockIdx.x * E + e] = n;
+        const int counted = n - (e == 0 ? strays[0] : 0) - (e == E - 1 ? strays[1] : 0);
+        if (hist_out && counted != 0) atomicAdd(&hist_out[e], counted);
+    }
 }
 
 // chunk bases per expert (in place), one wavefront per expert column, columns dealt over the whole grid
@@ -316,28 +335,40 @@ __device__ __forceinline__ void block_column_sums(const int32_t* __restrict__ ta
 
 // Segment of an assignment to expert e that stands at place i of the plan's order for e
 // (i < 0: the assignment is outside the plan's order and goes to the home slot).
-__device__ __forceinline__ int segment_of(int e, int i, int H, int S, int G, const PermWs& ws) {
+// With hist_true the replicas' bounds are quotas Q of the predicted n_hat, and i is past floor(n Q / n_hat) exactly
+// if (i + 1) n_hat > n Q.
+__device__ __forceinline__ int segment_of(int e, int i, int H, int S, int G, const PermWs& ws,
+                                          const int32_t* __restrict__ hist_true, const int32_t* __restrict__ hist_pred) {
     int sg = home_slot_of(e, H, S);
     if (i < 0) return sg;
     const int cnt = ws.rep_cnt[e];
     if (cnt > 0) {
         int rr = 0;
-        while (rr < cnt - 1 && i >= ws.rep_hi[(size_t)e * G + rr]) ++rr;
+        if (hist_true) {
+            const long long n = hist_true[e], past = (i + 1ll) * hist_pred[e];
+            while (rr < cnt - 1 && past > n * ws.rep_hi[(size_t)e * G + rr]) ++rr;
+        } else {
+            while (rr < cnt - 1 && i >= ws.rep_hi[(size_t)e * G + rr]) ++rr;
+        }
         sg = ws.rep_slot[(size_t)e * G + rr];
     }
     return sg;
 }
 
 // segment id per assignment + per-chunk segment histogram.  SCANNED: ws.bh1 holds chunk bases, else counts.
+// In a whole step hist_true and hist_pred scale the replicas' bounds (mode 1), and in the modes whose count launch does not
+// see topk_idx its histogram is added to hist_out here.
 template <bool SCANNED>
 __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, int T, int k, int E, int G, int S,
                                                                      const int32_t* __restrict__ topk_idx,
                                                                      const int32_t* __restrict__ pred_idx,
-                                                                     PermWs ws) {
+                                                                     PermWs ws, const int32_t* __restrict__ hist_true,
+                                                                     const int32_t* __restrict__ hist_pred,
+                                                                     int32_t* __restrict__ hist_out) {
     __shared__ int wcnt[kPermWaves * MOE_MAX_EXPERTS];
     __shared__ int prank[kChunk];
     __shared__ int seg_bins[MOE_MAX_SEGMENTS];
-    __shared__ int ebase[MOE_MAX_EXPERTS];
+    __shared__ int ebase[MOE_MAX_EXPERTS];  // (its second life: counts for hist_out)
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int w = tid / kWave;
@@ -373,12 +404,17 @@ __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, in
         }
     }
     __syncthreads();
+    if (hist_out) {
+        for (int e = tid; e < E; e += kPermThreads) ebase[e] = 0;
+        __syncthreads();
+    }
 
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const int p = (w * rounds + r) * kWave + lane;
         if (!valid[r]) continue;
-        const int e = clamp_key(topk_idx[base + p], E);
+        const int id = topk_idx[base + p], e = clamp_key(id, E);
+        if (hist_out && id == e) atomicAdd(&ebase[e], 1);
         int i = -1;  // place of this assignment in the plan's order for expert e
         if (mode == MOE_MODE_DISTRIBUTION) {
             i = prank[p];
@@ -391,12 +427,15 @@ __global__ __launch_bounds__(kPermThreads) void perm_segment_kernel(int mode, in
                 }
             }
         }
-        const int sg = segment_of(e, i, H, S, G, ws);
+        const int sg = segment_of(e, i, H, S, G, ws, hist_true, hist_pred);
         ws.seg[base + p] = (uint16_t)sg;
         atomicAdd(&seg_bins[sg], 1);
     }
     __syncthreads();
     for (int s = tid; s < nseg; s += kPermThreads) ws.bh2[(size_t)blockIdx.x * nseg + s] = seg_bins[s];
+    if (hist_out)
+        for (int e = tid; e < E; e += kPermThreads)
+            if (ebase[e] > 0) atomicAdd(&hist_out[e], ebase[e]);
 }
 
 // chunk bases per segment (in place), seg_offsets, rank_load
@@ -423,14 +462,33 @@ __global__ __launch_bounds__(1024) void perm_scan2_kernel(int G, int S, PermWs w
     for (int g = tid; g < G; g += blockDim.x) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
 }
 
+// The plan of mode 0, the home placement with the batch's own counts, by a workgroup.
+__device__ __forceinline__ void home_plan(const HomePlan& home, const int32_t* hist, int E, int G, int S) {
+    const int H = ceil_div(E, G), tid = threadIdx.x, n = blockDim.x;
+    for (int s = tid; s < G * S; s += n) {
+        const int j = s % S, e = s / S * H + j;
+        const bool held = j < H && e < E;
+        home.slot_expert[s] = held ? e : -1;
+        home.slot_quota[s] = held ? hist[e] : 0;
+    }
+    for (int g = tid; g < G; g += n) {
+        int load = 0;
+        for (int e = g * H; e < (g + 1) * H && e < E; ++e) load += hist[e];
+        home.rank_load_pred[g] = load;
+    }
+    if (tid == 0) home.n_iters[0] = 0;
+}
+
 // final position of every assignment.  SCANNED: ws.bh2 holds chunk bases and seg_offsets / rank_load
-// are written; else ws.bh2 holds counts, every workgroup works the offsets out and the first writes them.
+// are written; else ws.bh2 holds counts, every workgroup works the offsets out and the first writes them, and
+// with `home` the plan of mode 0 from the histogram.
 template <bool SCANNED>
 __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, int G, int S, PermWs ws,
                                                                    int32_t* __restrict__ seg_offsets,
                                                                    int32_t* __restrict__ rank_load,
                                                                    int32_t* __restrict__ row_of_assign,
-                                                                   int32_t* __restrict__ assign_of_row) {
+                                                                   int32_t* __restrict__ assign_of_row, HomePlan home,
+                                                                   const int32_t* __restrict__ hist, int E) {
     __shared__ int wcnt[kPermWaves * kMaxKeys];
     __shared__ int first[MOE_MAX_SEGMENTS];    // first row of this chunk in the segment
     __shared__ int tot[MOE_MAX_SEGMENTS + 1];  // rows per segment -> seg_offsets
@@ -477,6 +535,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_place_kernel(int T, int k, 
         if (blockIdx.x == 0) {
             for (int s = tid; s <= nseg; s += kPermThreads) seg_offsets[s] = tot[s];
             for (int g = tid; g < G; g += kPermThreads) rank_load[g] = tot[(g + 1) * S] - tot[g * S];
+            if (home.slot_expert) home_plan(home, hist, E, G, S);
         }
     }
     chunk_stable_rank<kPermWaves, kRounds>(key, valid, nseg, wcnt, rank, nullptr, rounds);
@@ -823,6 +882,61 @@ static int scatter_rows(const RowCopy& copy, hipStream_t st) {
     return check_launch();
 }
 
+// The index steps by many workgroups.  hist_out: the histogram, zero so far, is an output (not for batches that are scanned),
+// and in mode 0 the plan, `home`.
+static int permute_wide(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
+                        const int32_t* hist_true, const int32_t* hist_pred, const int32_t* slot_expert,
+                        const int32_t* slot_quota, const PermWs& ws, int32_t* seg_offsets, int32_t* row_of_assign,
+                        int32_t* assign_of_row, int32_t* rank_load, int32_t* hist_out, const HomePlan& home,
+                        hipStream_t st) {
+    const int nb = ws.nb;
+    const bool scanned = perm_scanned(ws);
+    const bool dist = mode == MOE_MODE_DISTRIBUTION;
+    const int32_t* scale = hist_out && dist ? hist_out : nullptr;
+    int rc;
+    if (mode != MOE_MODE_NONE) {
+        const int32_t* keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
+        hipLaunchKernelGGL(perm_count_kernel, dim3(nb + ceil_div(E, kPermWaves)), dim3(kPermThreads), 0, st, keys, mode, T, k,
+                           E, G, S, hist_out ? nullptr : hist_true, hist_pred, slot_expert, slot_quota, ws,
+                           dist ? hist_out : nullptr);
+        if ((rc = check_launch()) != MOE_OK) return rc;
+        if (scanned && nb > 0) {
+            hipLaunchKernelGGL(perm_scan1_kernel, dim3(ceil_div(E, kScan1Threads / kWave)), dim3(kScan1Threads), 0, st, E, ws);
+            if ((rc = check_launch()) != MOE_OK) return rc;
+        }
+    }
+    if (nb > 0) {
+        hipLaunchKernelGGL(scanned ? perm_segment_kernel<true> : perm_segment_kernel<false>, dim3(nb), dim3(kPermThreads), 0,
+                           st, mode, T, k, E, G, S, topk_idx, pred_idx, ws, scale, scale ? hist_pred : nullptr,
+                           dist ? nullptr : hist_out);
+        if ((rc = check_launch()) != MOE_OK) return rc;
+    }
+    if (scanned) {
+        hipLaunchKernelGGL(perm_scan2_kernel, dim3(1), dim3(1024), 0, st, G, S, ws, seg_offsets, rank_load);
+        if ((rc = check_launch()) != MOE_OK) return rc;
+    }
+    if (nb > 0) {
+        hipLaunchKernelGGL(scanned ? perm_place_kernel<true> : perm_place_kernel<false>, dim3(nb), dim3(kPermThreads), 0, st, T,
+                           k, G, S, ws, seg_offsets, rank_load, row_of_assign, assign_of_row, home, hist_out, E);
+        if ((rc = check_launch()) != MOE_OK) return rc;
+    }
+    return MOE_OK;
+}
+
+bool permute_counts(int T, int E, int k, int G, int S) {
+    const PermWs ws = perm_ws_layout(T, E, k, G, S, nullptr);
+    return ws.nb > 0 && !perm_scanned(ws);
+}
+
+int permute_and_count_wide(int mode, int T, int k, int E, int G, int S, const int32_t* topk_idx, const int32_t* pred_idx,
+                           const int32_t* hist_pred, const int32_t* slot_expert, const int32_t* slot_quota,
+                           int32_t* seg_offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* rank_load,
+                           int32_t* hist_out, const HomePlan& home, void* workspace, hipStream_t st) {
+    return permute_wide(mode, T, k, E, G, S, topk_idx, pred_idx, nullptr, hist_pred, slot_expert, slot_quota,
+                        perm_ws_layout(T, E, k, G, S, (char*)workspace), seg_offsets, row_of_assign, assign_of_row, rank_load,
+                        hist_out, mode == MOE_MODE_NONE ? home : HomePlan{}, st);
+}
+
 static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E, int k, int G, int S,
                         const int32_t* topk_idx, const int32_t* pred_idx, const int32_t* hist_true,
                         const int32_t* hist_pred, const int32_t* slot_expert, const int32_t* slot_quota,
@@ -855,33 +969,9 @@ static int permute_impl(int mode, const void* x, int dtype, int T, int d, int E,
                             TableJob{}, st);
         if ((rc = check_launch()) != MOE_OK) return rc;
     } else {
-        const bool scanned = nb == 0 || (nb > kSelfScanChunks && ws.rounds == kRounds);
-        if (mode != MOE_MODE_NONE) {
-            const int32_t* keys = (mode == MOE_MODE_TOKEN) ? pred_idx : topk_idx;
-            hipLaunchKernelGGL(perm_count_kernel, dim3(nb + ceil_div(E, kPermWaves)), dim3(kPermThreads), 0, st, keys,
-                               mode, T, k, E, G, S, hist_true, hist_pred, slot_expert, slot_quota, ws);
-            if ((rc = check_launch()) != MOE_OK) return rc;
-            if (scanned && nb > 0) {
-                hipLaunchKernelGGL(perm_scan1_kernel, dim3(ceil_div(E, kScan1Threads / kWave)), dim3(kScan1Threads), 0,
-                                   st, E, ws);
-                if ((rc = check_launch()) != MOE_OK) return rc;
-            }
-        }
-        if (nb > 0) {
-            hipLaunchKernelGGL(scanned ? perm_segment_kernel<true> : perm_segment_kernel<false>, dim3(nb),
-                               dim3(kPermThreads), 0, st, mode, T, k, E, G, S, topk_idx, pred_idx, ws);
-            if ((rc = check_launch()) != MOE_OK) return rc;
-        }
-        if (scanned) {
-            hipLaunchKernelGGL(perm_scan2_kernel, dim3(1), dim3(1024), 0, st, G, S, ws, seg_offsets, rank_load);
-            if ((rc = check_launch()) != MOE_OK) return rc;
-        }
-        if (nb > 0) {
-            hipLaunchKernelGGL(scanned ? perm_place_kernel<true> : perm_place_kernel<false>, dim3(nb),
-                               dim3(kPermThreads), 0, st, T, k, G, S, ws, seg_offsets, rank_load, row_of_assign,
-                               assign_of_row);
-            if ((rc = check_launch()) != MOE_OK) return rc;
-        }
+        if ((rc = permute_wide(mode, T, k, E, G, S, topk_idx, pred_idx, hist_true, hist_pred, slot_expert, slot_quota, ws,
+                               seg_offsets, row_of_assign, assign_of_row, rank_load, nullptr, HomePlan{}, st)) != MOE_OK)
+            return rc;
     }
     if (nb > 0) {
         if (x_perm && (rc = scatter_rows(row_copy(x, dtype, T, d, k, row_of_assign, x_perm), st)) != MOE_OK) return rc;

@@ -217,3 +217,16 @@ def test_step_with_scratch_shared_by_its_stages(T, gather):
     for other in got[1:]:
         for n, v in got[0].items():
             assert torch.equal(other[n], v), n
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("T,E,k,G,S", [
+    (3073, 8, 1, 4, 3),        # just past one workgroup: 13 chunks, the last of one token
+    (1638, 256, 5, 32, 10),    # chunks of 51 tokens, 33 of them; the most experts that share the planner's launch
+    (16384, 24, 2, 12, 3),     # 128 chunks of 256 assignments
+    (16400, 24, 2, 12, 3),     # chunks of 512
+    (70001, 3, 3, 2, 3),       # chunks of 2046 with an odd last one
+])
+def test_step_permuted_by_many_workgroups(T, E, k, G, S, mode):
+    """Histogram and plan that the permuting launches make, at either side of their chunks' sizes."""
+    test_step_equals_single_calls(T, E, k, G, S, "bf16", mode)
