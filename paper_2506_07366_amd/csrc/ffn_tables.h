@@ -159,6 +159,7 @@ struct TableJob {
     RowLists lists;
     int32_t* queues;     // claim counters to set
     int n_queues;
+    int32_t* left;       // both products in one launch: what the second waits for (ffn_tiles.h); null: a launch each
 };
 
 // LDS of a builder for up to MAXSEG segments and MAXE experts that makes NT tables.
@@ -194,7 +195,8 @@ __device__ __forceinline__ void build_tables(TableScratch<MAXSEG, MAXE, NT>& sh,
     const int ns = job.seg_end - job.seg_begin;
     const bool many = E > 4 * kWave;  // experts enough that looking for groups of 64 without rows pays
     if (block == 0)
-        for (int i = tid; i < job.n_queues; i += blockDim.x) job.queues[i] = kGemmGrid / 8;  // (first tiles are claimed)
+        for (int i = tid; i < job.n_queues; i += blockDim.x)
+            job.queues[i] = job.left && i >= 8 ? 0 : kGemmGrid / 8;  // (first tiles are claimed)
     for (int e = tid; e < E; e += blockDim.x) e_segs[e] = 0;
     for (int i = tid; i < ns; i += blockDim.x) {
         const int s = job.seg_begin + i;
@@ -249,6 +251,8 @@ __device__ __forceinline__ void build_tables(TableScratch<MAXSEG, MAXE, NT>& sh,
     };
     // tables
     auto list_base = [&](int e) { return srt_base[e_segs[e]]; };  // first list position of expert e
+    if (block == 0 && job.left)
+        for (int e = tid; e < E; e += blockDim.x) job.left[e] = -((list_base(e + 1) - list_base(e)) * job.t1.n_ntiles);
     // wavefront j < NT prepares table first_table + j while the others fill in the row list
     auto spec_of = [&](int j) -> const TableSpec& { return first_table + j == 0 ? job.t1 : job.t2; };
     auto wanted = [&](int j) { return first_table + j < 2 && spec_of(j).tiles != nullptr; };

@@ -23,21 +23,54 @@
 constexpr int kTileMaxRows = 256;  // rows of the tallest tile
 constexpr int kTileGroup = 4;      // N-tiles walked side by side
 constexpr int kNonTemporal = 2;    // cache policy of a buffer load: nt
+constexpr int kThrough = 16;       // of a buffer store: sc1, written through to memory
 constexpr int kCopyPieces = 6;     // pieces of the row copy that a wavefront takes along with a tile
 constexpr size_t kStageLds = (size_t)3 * kTileMaxRows * kPackK * 2;
-// dynamic LDS of a workgroup: the stages, and in the first product the copy's pieces
+// dynamic LDS of a workgroup: the stages, in the first product the copy's pieces, the number of the next tile
 template <int EPI>
-constexpr size_t kTileLds = kStageLds + (EPI != kEpiNone ? 8 * kCopyPieces * kCopyPieceLds : 0);
+constexpr size_t kNextTileAt = kStageLds + (EPI != kEpiNone ? 8 * kCopyPieces * kCopyPieceLds : 0);
+template <int EPI>
+constexpr size_t kTileLds = kNextTileAt<EPI> + 16;
 
-template <int EPI>
-__global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
-    const bf16_t* __restrict__ A, int lda,           // activations [rows, K]
+// Both products of an FFN in one launch (grouped_ffn_tiles_kernel): a workgroup that finds no tile of the first product
+// left goes on to those of the second, and the uneven end of the first (a launch of few rounds of 256 tiles loses up to
+// a fifth of one there) fills up with them.  A tile of the second needs the hidden rows of its expert: left[e] starts at
+// -(rows of expert e) x (N-tiles of the first product), a finished tile of the first adds its rows, and at 0 all are there.
+// A workgroup that waits for that waits for tiles that others are working on: it got to the second product because every
+// tile of the first had been claimed, and a workgroup goes from a tile that it has claimed to telling so without
+// waiting for anybody.
+// The XCDs' L2 caches are not coherent with each other inside a launch, so the hidden rows are written through to memory
+// (kThrough) and the tile is told once every wavefront has seen its own stores acknowledged (at the start of the next
+// tile, where the row list is waited for anyway); no cache can hold older hidden rows, nobody in the launch reads a
+// row before it is complete, and a row is whole cache lines.
+//
+// Whether a product shares its launch with the other one of the FFN.
+constexpr int kAlone = 0, kMakesRows = 1, kWantsRows = 2;
+
+typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+
+// waits until *left is 0 (every wavefront by itself; uniform address)
+__device__ __forceinline__ void wait_rows(int32_t* left) {
+    while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0)
+        __builtin_amdgcn_s_sleep(4);
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void tell_rows(int32_t* left, int& expert, int rows) {
+    if ((threadIdx.x & 63) == 0)
+        (void)__hip_atomic_fetch_add(&left[expert], rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    expert = -1;
+}
+
+template <int EPI, int LINK>
+__device__ __forceinline__ void tile_product(
+    const bf16_t* A, int lda,                        // activations [rows, K]
     const bf16_t* __restrict__ Bp, size_t b_stride,  // packed weights [E][N-tile][k-tile][kPackN x kPackK]
-    bf16_t* __restrict__ C, int ldc,                 // output [rows, SWIGLU ? N/2 : N]
+    bf16_t* C, int ldc,                              // output [rows, SWIGLU ? N/2 : N]
     const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int32_t* __restrict__ queues,
     int N, int K, int group_n, bool past_caches, RowMap rm,
     float* __restrict__ partials,  // [slab][kPartRows][N] fp32 sums of entries that cover part of K (plain product only)
-    RowCopy copy) {                // first product: rows to be copied besides, a share of them with every tile
+    RowCopy copy,                  // first product: rows to be copied besides, a share of them with every tile
+    int32_t* left) {               // [E] what the second product waits for, see above (LINK)
     constexpr bool SWIGLU = EPI == kEpiSwiglu;
     constexpr int BN = kPackN, BK = kPackK, NW = 8;
     constexpr int ROW_BYTES = BK * 2;      // of an activation row in a stage
@@ -76,7 +109,8 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
     int copy_share = 0;  // pieces of the row copy that go with a tile
     if constexpr (EPI != kEpiNone)
         if (copy.x_perm) copy_share = ceil_div(copy.T * ceil_div(copy.chunks, kWave), total > 0 ? total : 1);
-    __shared__ volatile int next_tile;
+    volatile __attribute__((address_space(3))) int& next_tile =
+        *(volatile __attribute__((address_space(3))) int*)(__attribute__((address_space(3))) unsigned char*)(smem + kNextTileAt<EPI>);
     // The claims are the business of wavefront 0, and every value involved is the same in
     // all its lanes, so the state lives in scalar registers (lane 0 performs the atomic, its
     // result is broadcast): nothing of it occupies a vector register across the K loop
@@ -128,8 +162,10 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
         }
     };
     // The first tile of a workgroup is its own claim of its XCD's counter, made in advance (the counters
-    // start at `run`): no round trip before it, and a workgroup that starts early cannot take it.
-    if (wave == 0) next_tile = settle_claim(xcd, (int)(blockIdx.x >> 3));
+    // start at `run`): no round trip before it, and a workgroup that starts early cannot take it.  (The second product of
+    // a shared launch starts whenever a workgroup gets there, its counters start at 0.)
+    if (wave == 0) next_tile = LINK == kWantsRows ? settle_claim(-1, 0) : settle_claim(xcd, (int)(blockIdx.x >> 3));
+    int told_expert = -1, told_rows = 0;  // the tile whose results are on their way to memory
     for (;;) {
         lds_wait<0>();                 // thread 0's store of next_tile
         __builtin_amdgcn_s_barrier();  // also: every wavefront is done reading the previous tile's stages
@@ -150,7 +186,6 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
                 const int most = copy_share < NW * kCopyPieces ? ceil_div(copy_share, NW) : kCopyPieces;
                 copy_first = first + wave * most;
                 copy_n = end - copy_first < most ? end - copy_first : most;
-                request_pieces(copy, copy_first, copy_n, smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
                 if (copy_share > NW * kCopyPieces) copy_pieces<NW>(copy, first + NW * kCopyPieces, end, wave);
             }
         }
@@ -172,6 +207,7 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
         const int mt_i = m_base + rem / gw;
         const int nt_i = grp * group_n + rem % gw;
         const MTile mt = mtiles[mt_i];
+        if constexpr (LINK == kWantsRows) wait_rows(&left[mt.expert]);
         const int n0 = nt_i * BN;
         // k-tiles of this entry: all of K, or the part of it a split tile covers
         const int KT = mt.kt1 > 0 ? mt.kt1 - mt.kt0 : K / BK;
@@ -239,6 +275,9 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
                 }
                 offA[i] = ((unsigned)r * (unsigned)lda + (unsigned)((slot ^ swz(row)) * 8)) * 2u;
             }
+            if constexpr (LINK == kMakesRows) wait_vmcnt<0>();  // the previous tile's results have reached memory
+            if constexpr (EPI != kEpiNone)  // (behind the row list, whose wait would be for the pieces too)
+                request_pieces(copy, copy_first, copy_n, smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
             bf16x8 w[D][2][2], af[R];
             const unsigned lane_off = (unsigned)(lane_p * 16);
             // load l of this wavefront's NB loads of k-tile kt, into buffers b
@@ -283,6 +322,8 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
             };
             wait_vmcnt<NB*(D - 2)>();  // k-tile 0 has landed
             __builtin_amdgcn_s_barrier();
+            if constexpr (LINK == kMakesRows)  // every wavefront's results have
+                if (wave == 0 && told_expert >= 0) tell_rows(left, told_expert, told_rows);
             static_for<R>([&](auto F) { read_frag(F, std::integral_constant<int, 0>{}); });
             // k-tile kt in buffers U; LOAD: k-tile kt + D - 1 is asked for meanwhile
             auto body = [&](int kt, auto U, auto load_tag) {
@@ -365,7 +406,17 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
             unsigned qx = pack_bf16x2(v1[0], v1[1]), qy = pack_bf16x2(v1[2], v1[3]);
             lane_swap_pairs(px, qx);
             lane_swap_pairs(py, qy);
-            if (on) *(uint4*)at = make_uint4(px, py, qx, qy);
+            if constexpr (LINK == kMakesRows) {
+                // to memory, not to this XCD's L2 alone
+                const u32x4 v = {px, py, qx, qy};
+                const bf16_t* base = C + (size_t)mt.list0 * ldc;
+                const auto c_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00027000);
+                if (on)
+                    __builtin_amdgcn_raw_buffer_store_b128(v, c_rsrc, (unsigned)((const char*)at - (const char*)base), 0,
+                                                           kThrough);
+            } else if (on) {
+                *(uint4*)at = make_uint4(px, py, qx, qy);
+            }
         };
         if constexpr (SWIGLU) {
             const int col = n0 / 2 + (wave >> 1) * 32 + (wave & 1) * 16 + (g16e & 1) * 8;
@@ -443,5 +494,38 @@ __global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
         }
         if constexpr (EPI != kEpiNone)
             if (copy_n > 0) store_pieces(copy, copy_first, copy_n, (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
+        if constexpr (LINK == kMakesRows) {
+            told_expert = mt.expert;
+            told_rows = mt.rows;
+        }
     }
+    if constexpr (LINK == kMakesRows) {
+        wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        if (wave == 0 && told_expert >= 0) tell_rows(left, told_expert, told_rows);
+    }
+}
+
+template <int EPI>
+__global__ __launch_bounds__(512, 2) void grouped_gemm_tile_kernel(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ Bp, size_t b_stride, bf16_t* __restrict__ C, int ldc,
+    const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int32_t* __restrict__ queues, int N, int K,
+    int group_n, bool past_caches, RowMap rm, float* __restrict__ partials, RowCopy copy) {
+    tile_product<EPI, kAlone>(A, lda, Bp, b_stride, C, ldc, mtiles, counts, queues, N, K, group_n, past_caches, rm, partials,
+                              copy, nullptr);
+}
+
+// Both products in one launch.
+template <int EPI>
+__global__ __launch_bounds__(512, 2) void grouped_ffn_tiles_kernel(
+    const bf16_t* __restrict__ X, int d, const bf16_t* __restrict__ P13, size_t stride1, const bf16_t* __restrict__ P2,
+    size_t stride2, bf16_t* h, int fp, bf16_t* __restrict__ Y, const MTile* __restrict__ tiles1,
+    const MTile* __restrict__ tiles2, const int32_t* __restrict__ counts1, const int32_t* __restrict__ counts2,
+    int32_t* __restrict__ queues, bool past_caches1, bool past_caches2, RowMap rm1, RowMap rm2,
+    float* __restrict__ partials, RowCopy copy, int32_t* left) {
+    tile_product<EPI, kMakesRows>(X, d, P13, stride1, h, fp, tiles1, counts1, queues, EPI == kEpiSwiglu ? 2 * fp : fp, d,
+                                  kTileGroup, past_caches1, rm1, nullptr, copy, left);
+    if (counts1[kCntEntries] == 0) return;  // (no table fits offsets that claim more rows than the call has: nothing to wait for)
+    tile_product<kEpiNone, kWantsRows>(h, fp, P2, stride2, Y, d, tiles2, counts2, queues + 8, d, fp, kTileGroup, past_caches2,
+                                       rm2, partials, RowCopy{}, left);
 }

@@ -581,30 +581,61 @@ static int copy_blocks(RowCopy& copy, int threads) {
     return (int)ceil_div64((int64_t)copy.T * copy.slices, (int64_t)copy.per_wave * (threads / kWave));
 }
 
+static bool past_caches(int E, size_t b_stride) { return (size_t)E * b_stride * sizeof(bf16_t) > kCachedWeights; }
+
+// A kernel that uses more LDS than the default limit: raised once per kernel (`raised`: bit per device).
+static int raise_lds(const void* kern, size_t bytes, std::atomic<unsigned long long>& raised) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (raised.load() & bit) return MOE_OK;
+    const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) {
+        set_last_hip_error(e);
+        return MOE_ERR_HIP;
+    }
+    raised.fetch_or(bit);
+    return MOE_OK;
+}
+
 template <int EPI>
 static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_stride, int E, bf16_t* C, int ldc,
                         const MTile* tiles, const int32_t* counts, int32_t* queues, int N, int K, int group_n,
                         const RowMap& rm, float* partials, RowCopy copy, hipStream_t st) {
-    const bool past_caches = (size_t)E * b_stride * sizeof(bf16_t) > kCachedWeights;
     // (the kernel multiplies by it: an option beyond the N-tiles there are means all of them)
     if (group_n > ceil_div(N, kPackN)) group_n = ceil_div(N, kPackN);
-    // the kernel uses more LDS than the default limit: raised once per kernel and device
-    static std::atomic<unsigned long long> attr_set{0};  // bit per device
     const auto kern = grouped_gemm_tile_kernel<EPI>;
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    const unsigned long long bit = 1ull << (dev & 63);
-    if (!(attr_set.load() & bit)) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds<EPI>);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return MOE_ERR_HIP;
-        }
-        attr_set.fetch_or(bit);
-    }
+    static std::atomic<unsigned long long> raised{0};
+    if (const int rc = raise_lds((const void*)kern, kTileLds<EPI>, raised); rc != MOE_OK) return rc;
     // 32 workgroups for each of the 8 XCDs; they claim tiles from `queues` (cleared by the table builder)
     hipLaunchKernelGGL(kern, dim3(kGemmGrid), dim3(512), kTileLds<EPI>, st, A, lda, Bp, b_stride, C, ldc, tiles, counts, queues, N, K,
-                       group_n, past_caches, rm, partials, copy);
+                       group_n, past_caches(E, b_stride), rm, partials, copy);
+    return check_launch();
+}
+
+// Whether both products share a launch (ffn_tiles.h).  It saves what the uneven end of the first product costs, half a tile
+// per workgroup on average, and costs what writing the hidden rows through to memory does (2 % at 16 rounds of tiles).  Whole
+// steps, us, a launch each -> one, by the rounds of 256 tiles that the first product has at 256 rows per tile: 1.8 (64 experts of
+// 2048 x 1408, 400 tokens) 222 -> 206, 2.0 (16 of 4096 x 688, 5000) 420 -> 398, 3.5 (8 of 4096 x 14336, 400) 543 -> 536,
+// 5.5 (64 of 2048 x 1408, 4096) 555 -> 546, 5.9 (128 of 4096 x 1536, 2000) 971 -> 954, 6.6 (8 of 4096 x 14336, 1400) 937 -> 930, 7.4
+// (64 of 2048 x 1408, 6000) 674 -> 670, 8.8 (8 of 4096 x 14336, 2000) 1270 -> 1277, 10.4 (64 of 2048 x 1408, 9000) 918 -> 929.
+// Below a round there is little to fill (64 of 768 x 3072, 2000 tokens 142 -> 143), and tiles of a few k-tiles are done before the
+// hand-over is (8 of 512 x 1024, K = 512, 4096 tokens 78 -> 85).
+static bool one_launch(int64_t A, int E, int n_ntiles, int k_tiles) {
+    const int64_t tiles = (ceil_div64(A, kTallest) + (A < E ? A : E) / 2) * n_ntiles;
+    return tiles >= kGemmGrid && tiles <= 7 * kGemmGrid && k_tiles >= 12;
+}
+
+template <int EPI>
+static int launch_both(const bf16_t* X, int d, const bf16_t* P13, size_t stride1, const bf16_t* P2, size_t stride2, int E,
+                       const FfnWs& ws, int fp, bf16_t* Y, const MTile* tiles2, const int32_t* counts2, const RowMap& rm1,
+                       const RowMap& rm2, const RowCopy& copy, int32_t* left, hipStream_t st) {
+    const auto kern = grouped_ffn_tiles_kernel<EPI>;
+    static std::atomic<unsigned long long> raised{0};
+    if (const int rc = raise_lds((const void*)kern, kTileLds<EPI>, raised); rc != MOE_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3(kGemmGrid), dim3(512), kTileLds<EPI>, st, X, d, P13, stride1, P2, stride2, (bf16_t*)ws.h, fp,
+                       Y, ws.tiles1, tiles2, ws.counts, counts2, ws.queues, past_caches(E, stride1), past_caches(E, stride2),
+                       rm1, rm2, ws.partials, copy, left);
     return check_launch();
 }
 
@@ -796,7 +827,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
                      const int32_t* seg_offsets, const int32_t* slot_expert, int nseg, int seg_begin, int seg_end,
                      const void* packed, void* y_perm, void* workspace, size_t workspace_bytes, void* stream,
                      const FfnOptions& opt, FfnStage stage, TableJob* job_out, const RowCopy& copy, int32_t* tokens) {
-    const bool timed = g_time_armed && stage != kFfnJobOnly;
+    const bool armed = g_time_armed, timed = armed && stage != kFfnJobOnly;
     if (stage != kFfnJobOnly) g_time_armed = false;  // the hook belongs to this call, whatever becomes of it
     if (dtype != MOE_DTYPE_F32 && dtype != MOE_DTYPE_BF16) return MOE_ERR_INVALID_ARG;
     if (A < 0 || d < 1 || ffn < 1 || E < 1 || nseg < 1) return MOE_ERR_INVALID_ARG;
@@ -853,7 +884,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
         const int bm = tiles64 < 2 * kGemmGrid ? 32 : 64;
         TableSpec t1{ws.tiles1, ws.counts, nullptr, bm, ws.capacity, 0, 0, 1, 0, 0};
         TableSpec none{};
-        if (!tables(TableJob{E, seg_begin, seg_end, t1, none, lists, nullptr, 0}, &rc)) return rc;
+        if (!tables(TableJob{E, seg_begin, seg_end, t1, none, lists, nullptr, 0, nullptr}, &rc)) return rc;
         const float* w1 = (const float*)packed;
         const float* w3 = w1 + per;
         const float* w2 = relu ? w3 : w3 + per;
@@ -887,19 +918,33 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     // table when it has the same tile height and splits nothing
     const int bm1 = s1 ? kStreamBM : v1 >= 0 ? kShapeRows[v1] : 0;  // 0: the table builder chooses
     const int bm2 = s2 ? kStreamBM : v2 >= 0 ? kShapeRows[v2] : 0;
-    const bool split = ws.split_capacity > 0 && !s2;
+    // Both products in one launch: of the whole slot range, with nothing forced.  Where a product is to be timed, or walks its
+    // tiles as an option says, they are a launch each all the same, with the same bits: no tile of a batch of such a size is split,
+    // the second product's end is the launch's only one (split by the rule, whole steps: 64 experts of 2048 x 1408, 1000 / 4096
+    // tokens 264 -> 268 / 532 -> 546 us).  What the second product waits for lies behind the first table's tiles, of which there
+    // are less than there is room for.
+    const int64_t spare = ws.capacity - (ceil_div64(A, kMinAutoHeight) + (A < nseg ? A : nseg));
+    const bool linked = !s1 && !s2 && v1 < 0 && v2 < 0 && opt.split <= 0 && nrange == nseg &&
+                        spare * (int64_t)sizeof(MTile) >= (int64_t)E * (int64_t)sizeof(int32_t) &&
+                        one_launch(A, E, ceil_div(n1 * fp, kPackN), d / kPackK);
+    int32_t* const left = linked && !armed && opt.group_n == 0 ? (int32_t*)(ws.tiles1 + ws.capacity) - E : nullptr;
+    const bool split = ws.split_capacity > 0 && !s2 && !linked;
     const bool own2 = bm2 != bm1 || bm2 == 0 || split;
     TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / kPackK, 0,
                  ceil_div(n1 * fp, kPackN), 0, 0};
     TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / kPackK,
                  split ? ws.parts : 0, ceil_div(d, kPackN), ws.split_all, ws.split_capacity};
-    if (!tables(TableJob{E, seg_begin, seg_end, t1, t2, lists, ws.queues, 16}, &rc)) return rc;
+    if (!tables(TableJob{E, seg_begin, seg_end, t1, t2, lists, ws.queues, 16, left}, &rc)) return rc;
     const MTile* tiles2 = own2 ? ws.tiles2 : ws.tiles1;
     const int32_t* count2 = own2 ? ws.counts + kCntStride : ws.counts;
     const bf16_t* p13 = (const bf16_t*)packed;
     const bf16_t* p2 = p13 + (size_t)E * packed_elems1(n1, d, fp);
     if (timed) (void)hipEventRecord(g_time_events[0], st);
-    if (s1) {
+    if (left) {
+        const auto go = relu ? launch_both<kEpiRelu> : launch_both<kEpiSwiglu>;
+        rc = go((const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), p2, packed_elems2(d, fp), E, ws, fp, (bf16_t*)y_perm,
+                tiles2, count2, rm1, rm2, copy, left, st);
+    } else if (s1) {
         rc = relu ? launch_stream<kEpiRelu>(s1, A, E, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp), (bf16_t*)ws.h,
                                             fp, ws.tiles1, ws.counts, n1 * fp, d, rm1, copy, st)
                   : launch_stream<kEpiSwiglu>(s1, A, E, (const bf16_t*)x_in, d, p13, packed_elems1(n1, d, fp),
@@ -912,7 +957,8 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     if (timed) (void)hipEventRecord(g_time_events[1], st);
     if (rc != MOE_OK) return rc;
     if (timed) (void)hipEventRecord(g_time_events[2], st);
-    if (s2)
+    if (left) {
+    } else if (s2)
         rc = launch_stream<kEpiNone>(s2, A, E, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d,
                                      tiles2, count2, d, fp, rm2, RowCopy{}, st);
     else

@@ -161,9 +161,11 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     // The permuted rows are for the caller: the first product reads the rows of x, and they are copied beside it.
     const RowCopy copy = a->x_perm ? row_copy(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm) : RowCopy{};
     // The permutation's scratch, done with by then, takes the list of the rows' tokens (it is larger than A ints), unless the caller
-    // has it share memory with what the first product writes.
+    // has it share memory with what the launch of the first product writes.
+    const size_t rows = (size_t)A * a->d * dtype_size(a->dtype);
     const bool scratch_free = !share_bytes(a->workspace_perm, ids, a->workspace_ffn, a->workspace_ffn_bytes) &&
-                              !(a->x_perm && share_bytes(a->workspace_perm, ids, a->x_perm, (size_t)A * a->d * dtype_size(a->dtype)));
+                              !share_bytes(a->workspace_perm, ids, a->y_perm, rows) &&
+                              !(a->x_perm && share_bytes(a->workspace_perm, ids, a->x_perm, rows));
     int32_t* const tokens = scratch_free ? (int32_t*)a->workspace_perm : nullptr;
     const FfnOptions opt = ffn_options();  // (once: the job and the products go by the same)
     auto ffn = [&](FfnStage stage, TableJob* job) {

@@ -904,3 +904,70 @@ def test_layer_step_replays_from_a_hip_graph(name, mode):
         assert torch.equal(layer.topk_idx, eager.topk_idx)
         assert torch.equal(layer.perm["row_of_assign"], eager.perm["row_of_assign"])
         assert torch.equal(layer.out.view(torch.uint8), ref.view(torch.uint8)), rep
+
+
+@pytest.mark.parametrize("form", ["plain", "relu", "gather", "weights"])
+@pytest.mark.parametrize("d,ffn,sizes", [
+    (768, 1700, [4000, 0, 0, 0, 0, 0, 0, 0]),                  # one expert: the second product waits for all of the first
+    (768, 1700, [1, 300, 0, 257, 1900, 64, 65, 1413]),         # ragged, an expert without rows between, padded hidden width
+    (832, 3200, [31, 33, 700, 1, 2, 500, 129, 604]),           # 13 k-tiles, 25 N-tiles, just past a round
+    (1024, 4096, [1500, 1501, 1502, 1503, 0, 1, 1000, 993]),   # several rounds
+    (768, 3200, [200 + 7 * i for i in range(64)]),             # many experts
+])
+def test_ffn_products_in_one_launch(d, ffn, sizes, form, ffn_options):
+    """Both products in one launch against a launch each (which a given walk over the tiles asks for): the same bits, call after
+    call and replayed from a graph with other rows in between."""
+    ffn_options()
+    E, A, k = len(sizes), sum(sizes), 2
+    A -= A % k
+    sizes = [*sizes[:-1], sizes[-1] - sum(sizes) % k]
+    gen = torch.Generator(device="cuda").manual_seed(81)
+    bf = lambda *shape: torch.randn(shape, device="cuda", generator=gen).mul_(0.05).to(torch.bfloat16)
+    W1, W3, W2 = bf(E, d, ffn), bf(E, d, ffn), bf(E, ffn, d)
+    relu = form == "relu"
+    packed = B.moe_pack_weights_relu(W1, W2) if relu else B.moe_pack_weights(W1, W3, W2)
+    nseg = E + 2
+    # expert 0 in two slots, one slot empty
+    rows = [sizes[0] // 2, *sizes[1:], sizes[0] - sizes[0] // 2, 0]
+    so, se = dev_i32(np.concatenate([[0], np.cumsum(rows)])), dev_i32([*range(E), 0, -1])
+    of = torch.randperm(A, device="cuda", generator=gen).to(torch.int32)
+    gate = torch.rand((A // k, k), device="cuda", generator=gen)
+    xs = [bf(A // k if form in ("gather", "weights") else A, d) * 20 for _ in range(2)]
+    ws = torch.zeros(B.moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, B.MOE_DTYPE_BF16), dtype=torch.uint8, device="cuda")
+    y = torch.empty((A, d), dtype=torch.bfloat16, device="cuda")
+
+    def call(x):
+        if form in ("gather", "weights"):
+            B.moe_grouped_ffn_gather(x, of, k, so, se, packed, E, ffn, workspace=ws, out=y, topk_w=gate if form == "weights" else None)
+        else:
+            B.moe_grouped_ffn(x, so, se, packed, E, ffn, workspace=ws, out=y, relu=relu)
+
+    want = []
+    for x in xs:
+        ffn_options(group_n=4)
+        y.fill_(-7)
+        call(x)
+        want.append(y.clone())
+    ffn_options()
+    for i in range(12):
+        ws.fill_(255 if i % 3 == 0 else 0)
+        y.fill_(-7)
+        call(xs[i % 2])
+        assert torch.equal(y, want[i % 2]), i
+    x = xs[0].clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(x)
+    for i in range(6):
+        x.copy_(xs[i % 2])
+        y.fill_(-7)
+        graph.replay()
+        assert torch.equal(y, want[i % 2]), i
+    ref = torch.cat([(torch.relu(v @ W1[e].double()) if relu else torch.nn.functional.silu(v @ W1[e].double()) * (v @ W3[e].double()))
+                     .to(torch.bfloat16).double() @ W2[e].double()
+                     for e, v in zip([*range(E), 0], (xs[0] if form not in ("gather", "weights") else xs[0][of.long() // k])
+                                     .double().split(rows[:-1]))])
+    if form == "weights":
+        ref *= gate.reshape(-1)[of.long()].double()[:, None]
+    assert float((want[0].double() - ref).abs().max()) <= TOL["bf16"] * float(ref.abs().max())
