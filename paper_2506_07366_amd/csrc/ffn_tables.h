@@ -196,7 +196,7 @@ __device__ __forceinline__ void build_tables(TableScratch<MAXSEG, MAXE, NT>& sh,
     const bool many = E > 4 * kWave;  // experts enough that looking for groups of 64 without rows pays
     if (block == 0)
         for (int i = tid; i < job.n_queues; i += blockDim.x)
-            job.queues[i] = job.left && i >= 8 ? 0 : kGemmGrid / 8;  // (first tiles are claimed)
+            job.queues[i] = job.left ? 0 : kGemmGrid / 8;  // (a launch each: first tiles are claimed)
     for (int e = tid; e < E; e += blockDim.x) e_segs[e] = 0;
     for (int i = tid; i < ns; i += blockDim.x) {
         const int s = job.seg_begin + i;

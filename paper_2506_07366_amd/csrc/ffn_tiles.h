@@ -37,8 +37,8 @@ constexpr size_t kTileLds = kNextTileAt<EPI> + 16;
 // a fifth of one there) fills up with them.  A tile of the second needs the hidden rows of its expert: left[e] starts at
 // -(rows of expert e) x (N-tiles of the first product), a finished tile of the first adds its rows, and at 0 all are there.
 // A workgroup that waits for that waits for tiles that others are working on: it got to the second product because every
-// tile of the first had been claimed, and a workgroup goes from a tile that it has claimed to telling so without
-// waiting for anybody.
+// tile of the first had been claimed, by a workgroup that was running, and a workgroup goes from a tile that it has claimed
+// to telling so without waiting for anybody.  So a launch needs no number of its workgroups on the chip at a time.
 // The XCDs' L2 caches are not coherent with each other inside a launch, so the hidden rows are written through to memory
 // (kThrough) and the tile is told once every wavefront has seen its own stores acknowledged (at the start of the next
 // tile, where the row list is waited for anyway); no cache can hold older hidden rows, nobody in the launch reads a
@@ -162,9 +162,10 @@ __device__ __forceinline__ void tile_product(
         }
     };
     // The first tile of a workgroup is its own claim of its XCD's counter, made in advance (the counters
-    // start at `run`): no round trip before it, and a workgroup that starts early cannot take it.  (The second product of
-    // a shared launch starts whenever a workgroup gets there, its counters start at 0.)
-    if (wave == 0) next_tile = LINK == kWantsRows ? settle_claim(-1, 0) : settle_claim(xcd, (int)(blockIdx.x >> 3));
+    // start at `run`): no round trip before it, and a workgroup that starts early cannot take it.  In a shared launch
+    // workgroups wait for tiles, so only one that runs may own a tile: another launch that waits the same way, on another stream,
+    // can keep the rest of this one from starting.  Its counters start at 0.
+    if (wave == 0) next_tile = LINK == kAlone ? settle_claim(xcd, (int)(blockIdx.x >> 3)) : settle_claim(-1, 0);
     int told_expert = -1, told_rows = 0;  // the tile whose results are on their way to memory
     for (;;) {
         lds_wait<0>();                 // thread 0's store of next_tile

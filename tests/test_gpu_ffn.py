@@ -971,3 +971,30 @@ def test_ffn_products_in_one_launch(d, ffn, sizes, form, ffn_options):
     if form == "weights":
         ref *= gate.reshape(-1)[of.long()].double()[:, None]
     assert float((want[0].double() - ref).abs().max()) <= TOL["bf16"] * float(ref.abs().max())
+
+
+def test_ffn_products_in_one_launch_on_two_streams(ffn_options):
+    """Launches whose workgroups wait for each other's tiles, side by side on two streams: a tile belongs to a workgroup that
+    runs, so either launch ends whatever part of it the other leaves room for."""
+    ffn_options()
+    d, ffn, E, sizes = 1024, 2048, 8, [700, 1, 0, 900, 513, 256, 1024, 702]
+    A, nseg = sum(sizes), len(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(82)
+    bf = lambda *shape: torch.randn(shape, device="cuda", generator=gen).mul_(0.05).to(torch.bfloat16)
+    packed = B.moe_pack_weights(bf(E, d, ffn), bf(E, d, ffn), bf(E, ffn, d))
+    so, se = dev_i32(np.concatenate([[0], np.cumsum(sizes)])), dev_i32([*range(E)])
+    xs = [bf(A, d) * 20 for _ in range(2)]
+    ws = [torch.zeros(B.moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, B.MOE_DTYPE_BF16), dtype=torch.uint8, device="cuda")
+          for _ in range(2)]
+    want = [B.moe_grouped_ffn(x, so, se, packed, E, ffn, workspace=w).clone() for x, w in zip(xs, ws)]
+    ys = [[torch.empty((A, d), dtype=torch.bfloat16, device="cuda") for _ in range(8)] for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for i in range(8):
+        for j, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                B.moe_grouped_ffn(xs[j], so, se, packed, E, ffn, workspace=ws[j], out=ys[j][i])
+    torch.cuda.synchronize()
+    for j in range(2):
+        for y in ys[j]:
+            assert torch.equal(y, want[j]), j
