@@ -927,7 +927,13 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     const bool linked = !s1 && !s2 && v1 < 0 && v2 < 0 && opt.split <= 0 && nrange == nseg &&
                         spare * (int64_t)sizeof(MTile) >= (int64_t)E * (int64_t)sizeof(int32_t) &&
                         one_launch(A, E, ceil_div(n1 * fp, kPackN), d / kPackK);
-    int32_t* const left = linked && !armed && opt.group_n == 0 ? (int32_t*)(ws.tiles1 + ws.capacity) - E : nullptr;
+    // The same where the result lies on what the first product reads or copies (in place, for one): it is written while that goes on.
+    const size_t row_bytes = (size_t)d * sizeof(bf16_t), result = (size_t)A * row_bytes;
+    const bool in_place = share_bytes(y_perm, result, x_in, (size_t)rows_in * row_bytes) ||
+                          (copy.x_perm && share_bytes(y_perm, result, copy.x_perm, result)) ||
+                          (gather_rows && share_bytes(y_perm, result, gather_rows, (size_t)A * sizeof(int32_t)));
+    int32_t* const left =
+        linked && !armed && opt.group_n == 0 && !in_place ? (int32_t*)(ws.tiles1 + ws.capacity) - E : nullptr;
     const bool split = ws.split_capacity > 0 && !s2 && !linked;
     const bool own2 = bm2 != bm1 || bm2 == 0 || split;
     TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / kPackK, 0,

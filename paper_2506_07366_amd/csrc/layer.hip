@@ -106,10 +106,6 @@ static int route_and_plan(const PlanJob& p, const float* logits, int T, int k, i
     }
 }
 
-static bool share_bytes(const void* a, size_t na, const void* b, size_t nb) {
-    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
-}
-
 }  // namespace moegps
 
 extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
@@ -148,10 +144,14 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     const size_t n_pred = mode == MOE_MODE_TOKEN ? ids : counts;
     const bool own_pred = pred && (share_bytes(pred, n_pred, a->topk_idx, ids) || share_bytes(pred, n_pred, a->topk_w, ids) ||
                                    share_bytes(pred, n_pred, a->hist, counts));
-    const bool small = !own_pred && permute_in_one_workgroup(mode, A, E, G * S);
+    // x may lie in the FFN's scratch, being done with once its rows have been copied: then they are, before the FFN.
+    const size_t tokens_bytes = (size_t)T * a->d * dtype_size(a->dtype);
+    const bool copy_first = a->x_perm && share_bytes(a->x, tokens_bytes, a->workspace_ffn, a->workspace_ffn_bytes);
+    const bool small = !own_pred && !copy_first && permute_in_one_workgroup(mode, A, E, G * S);
     const bool shared = !own_pred && E <= kPlanMaxExperts && S <= kPlanMaxSlots && G <= 32;
-    // several workgroups permute and add up the histogram, which the first launch clears
-    const bool wide = shared && !small && permute_counts(T, E, k, G, S);
+    // several workgroups permute and add up the histogram, which the first launch clears (and then counts predicted ids)
+    const bool own_counts = mode == MOE_MODE_TOKEN && share_bytes(a->hist_plan, counts, a->hist, counts);
+    const bool wide = shared && !small && !copy_first && !own_counts && permute_counts(T, E, k, G, S);
     const bool together = shared && (wide || mode != MOE_MODE_NONE);
     auto plan = [&] {
         return moe_plan_duplicates(mode, hp, E, G, S, a->c_max, a->slot_expert, a->slot_quota, a->rank_load_pred,
@@ -159,16 +159,21 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     };
     const float* gate = a->x_perm ? nullptr : a->gate_in_ffn ? a->topk_w : nullptr;
     // The permuted rows are for the caller: the first product reads the rows of x, and they are copied beside it.
-    const RowCopy copy = a->x_perm ? row_copy(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm) : RowCopy{};
+    const RowCopy copy = a->x_perm && !copy_first ? row_copy(a->x, a->dtype, T, a->d, k, a->row_of_assign, a->x_perm) : RowCopy{};
     // The permutation's scratch, done with by then, takes the list of the rows' tokens (it is larger than A ints), unless the caller
     // has it share memory with what the launch of the first product writes.
     const size_t rows = (size_t)A * a->d * dtype_size(a->dtype);
     const bool scratch_free = !share_bytes(a->workspace_perm, ids, a->workspace_ffn, a->workspace_ffn_bytes) &&
                               !share_bytes(a->workspace_perm, ids, a->y_perm, rows) &&
+                              !share_bytes(a->workspace_perm, ids, a->x, tokens_bytes) &&
                               !(a->x_perm && share_bytes(a->workspace_perm, ids, a->x_perm, rows));
     int32_t* const tokens = scratch_free ? (int32_t*)a->workspace_perm : nullptr;
     const FfnOptions opt = ffn_options();  // (once: the job and the products go by the same)
     auto ffn = [&](FfnStage stage, TableJob* job) {
+        if (copy_first)
+            return grouped_ffn_call(a->relu, a->x_perm, A, nullptr, 1, nullptr, nullptr, a->dtype, A, a->d, a->ffn, E,
+                                    a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm, a->workspace_ffn,
+                                    a->workspace_ffn_bytes, stream, opt, stage, job);
         return grouped_ffn_call(a->relu, a->x, T, a->assign_of_row, k, gate ? a->assign_of_row : nullptr, gate, a->dtype, A,
                                 a->d, a->ffn, E, a->seg_offsets, a->slot_expert, G * S, 0, G * S, a->packed, a->y_perm,
                                 a->workspace_ffn, a->workspace_ffn_bytes, stream, opt, stage, job, copy, tokens);
@@ -205,10 +210,10 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     } else {
         if (!own_pred && (rc = moe_histogram(a->topk_idx, A, E, a->hist, stream)) != MOE_OK) return rc;
         if (mode == MOE_MODE_NONE && (rc = plan()) != MOE_OK) return rc;
-        rc = moe_permute(mode, nullptr, a->dtype, T, a->d, E, k, G, S, a->topk_idx,
+        rc = moe_permute(mode, copy_first ? a->x : nullptr, a->dtype, T, a->d, E, k, G, S, a->topk_idx,
                          mode == MOE_MODE_TOKEN ? a->pred_idx : nullptr, a->hist, hp, a->slot_expert, a->slot_quota,
-                         a->seg_offsets, a->row_of_assign, a->assign_of_row, nullptr, a->rank_load, a->workspace_perm,
-                         a->workspace_perm_bytes, stream);
+                         a->seg_offsets, a->row_of_assign, a->assign_of_row, copy_first ? a->x_perm : nullptr,
+                         a->rank_load, a->workspace_perm, a->workspace_perm_bytes, stream);
     }
     if (rc != MOE_OK) return rc;
     if ((rc = ffn(tables_too ? kFfnTablesBuilt : kFfnAll, nullptr)) != MOE_OK) return rc;

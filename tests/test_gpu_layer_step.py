@@ -230,3 +230,45 @@ def test_step_with_scratch_shared_by_its_stages(T, gather):
 def test_step_permuted_by_many_workgroups(T, E, k, G, S, mode):
     """Histogram and plan that the permuting launches make, at either side of their chunks' sizes."""
     test_step_equals_single_calls(T, E, k, G, S, "bf16", mode)
+
+
+@pytest.mark.parametrize("gather", [False, True])
+@pytest.mark.parametrize("T", [300, 3000])           # one workgroup permutes and streams; several, both products in one launch
+def test_step_with_buffers_that_share_memory(T, gather):
+    """y_perm on x or on x_perm, x in the FFN's scratch (with a copy of its rows), the two histograms of the Token-to-Expert
+    plan in one place: the step reads what is read late before it writes there."""
+    E, k, d, ffn = 8, 2, 1024, 2048
+    cfg = wl.MoEConfig("alias", T=T, d=d, ffn=ffn, E=E, k=k, G=4, S=3, dtype="bf16", mode=2, seed=71)
+    gen = torch.Generator(device="cuda").manual_seed(72)
+    ws = [torch.randn(s, device="cuda", generator=gen).mul_(0.02).to(torch.bfloat16)
+          for s in ((E, d, ffn), (E, d, ffn), (E, ffn, d))]
+    logits = torch.randn((T, E), device="cuda", generator=gen)
+    x = torch.randn((T, d), device="cuda", generator=gen).to(torch.bfloat16)
+    pred_idx = torch.topk(logits, k, dim=1).indices.to(torch.int32).contiguous()
+    res = {}
+    for how in ("none", "y on x", "y on x_perm", "x in scratch", "one histogram"):
+        if gather and how in ("y on x_perm", "x in scratch"):
+            continue
+        layer = MoELayer(cfg, fused_gather=gather)
+        layer.set_weights(*ws)
+        given = x.clone()
+        if how == "y on x":
+            layer.y_perm[:T].copy_(x)
+            given = layer.y_perm[:T]
+        elif how == "y on x_perm":
+            layer.y_perm = layer.perm["x_perm"]
+        elif how == "x in scratch":
+            given = layer.ws_ffn[:T * d * 2].view(torch.bfloat16).reshape(T, d)
+            given.copy_(x)
+        elif how == "one histogram":
+            layer.hist_plan = layer.hist
+        assert layer._one_call(logits, given, None, pred_idx, 2)
+        res[how] = outputs(layer)
+        if not gather and how != "y on x_perm":
+            assert torch.equal(layer.perm["x_perm"], x[layer.perm["assign_of_row"].long() // k]), how
+    for how, got in res.items():
+        for n, v in res["none"].items():
+            if how == "x in scratch" and n == "out":   # (rows in place: the same sums)
+                assert torch.allclose(got[n].float(), v.float(), rtol=1e-2, atol=1e-3), n
+            else:
+                assert torch.equal(got[n], v), (how, n)
