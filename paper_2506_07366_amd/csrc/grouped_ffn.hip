@@ -621,9 +621,17 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
 // (64 of 2048 x 1408, 6000) 674 -> 670, 8.8 (8 of 4096 x 14336, 2000) 1270 -> 1277, 10.4 (64 of 2048 x 1408, 9000) 918 -> 929.
 // Below a round there is little to fill (64 of 768 x 3072, 2000 tokens 142 -> 143), and tiles of a few k-tiles are done before the
 // hand-over is (8 of 512 x 1024, K = 512, 4096 tokens 78 -> 85).
-static bool one_launch(int64_t A, int E, int n_ntiles, int k_tiles) {
-    const int64_t tiles = (ceil_div64(A, kTallest) + (A < E ? A : E) / 2) * n_ntiles;
-    return tiles >= kGemmGrid && tiles <= 7 * kGemmGrid && k_tiles >= 12;
+// Where a launch of its own would compute the second product's closing tiles as parts of K (`parts`), a tile here is all of K: with
+// a long one it stays alone where that is more than 3/4 of all that a workgroup has to do on average.  8 experts of
+// 4096 x 14336, rows as a popularity of 0.1 / 1 / 10 has them, by that share: 1.07 (80 tokens) 251 -> 304 / 499 -> 525 / 494 ->
+// 513, 1.07 (128) 252 -> 332 / 527 -> 515 / 514 -> 522, 0.89 (256) 335 -> 354 / 535 -> 537 / 546 -> 533, 0.76 (384) 376 -> 380 /
+// 571 -> 571 / 573 -> 558, 0.59 (640) 516 -> 510 / 674 -> 667 / 652 -> 629.  Up to 48 k-tiles one launch is ahead at any share measured (64 of 768 x 3072,
+// 1.07 (2048) 119 -> 118 / 163 -> 158 at 0.1 / 10, 0.67 (8192) 177 -> 163 / 216 -> 200).
+static bool one_launch(int64_t A, int E, int n_ntiles1, int k_tiles1, int n_ntiles2, int k_tiles2, bool parts) {
+    const int64_t m_tiles = ceil_div64(A, kTallest) + (A < E ? A : E) / 2, tiles = m_tiles * n_ntiles1;
+    if (tiles < kGemmGrid || tiles > 7 * kGemmGrid || k_tiles1 < 12) return false;
+    const int64_t work = m_tiles * ((int64_t)n_ntiles1 * k_tiles1 + (int64_t)n_ntiles2 * k_tiles2);
+    return !parts || k_tiles2 < 64 || (int64_t)4 * kGemmGrid * k_tiles2 <= 3 * work;
 }
 
 template <int EPI>
@@ -872,6 +880,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     const int fp = padded_ffn(ffn, dtype);  // hidden width the kernels see
     const int n1 = relu ? 1 : 2;            // matrices in the first product
     const int s1 = dtype == MOE_DTYPE_F32 ? 0 : stream_form(opt.stream, opt.tile1, A, E, n1 * fp, d / kPackK);
+    const int s2 = dtype == MOE_DTYPE_F32 || opt.split == 1 ? 0 : stream_form(opt.stream, opt.tile2, A, E, d, fp / kPackK);
     if (s1) tokens = nullptr;
     const RowMap rm1 = tokens ? RowMap{tokens, nullptr, 1, nullptr, nullptr, nullptr}
                               : RowMap{ws.rowlist, gather_rows, gather_div, nullptr, nullptr, nullptr};
@@ -911,7 +920,6 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     // Batches of a few rows per expert stream their weights; for the rest the table builder chooses the height of
     // the tiles.
     const int v1 = opt.tile1, v2 = opt.tile2;
-    const int s2 = opt.split == 1 ? 0 : stream_form(opt.stream, v2, A, E, d, fp / kPackK);
     // N-tiles walked side by side over the M-tiles of an expert: see the tile order in ffn_tiles.h
     const int group_n = opt.group_n > 0 ? opt.group_n : kTileGroup;
     // one launch builds the row list and both tables; the second product shares the first one's
@@ -926,7 +934,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     const int64_t spare = ws.capacity - (ceil_div64(A, kMinAutoHeight) + (A < nseg ? A : nseg));
     const bool linked = !s1 && !s2 && v1 < 0 && v2 < 0 && opt.split <= 0 && nrange == nseg &&
                         spare * (int64_t)sizeof(MTile) >= (int64_t)E * (int64_t)sizeof(int32_t) &&
-                        one_launch(A, E, ceil_div(n1 * fp, kPackN), d / kPackK);
+                        one_launch(A, E, ceil_div(n1 * fp, kPackN), d / kPackK, ceil_div(d, kPackN), fp / kPackK, ws.split_capacity > 0);
     // The same where the result lies on what the first product reads or copies (in place, for one): it is written while that goes on.
     const size_t row_bytes = (size_t)d * sizeof(bf16_t), result = (size_t)A * row_bytes;
     const bool in_place = share_bytes(y_perm, result, x_in, (size_t)rows_in * row_bytes) ||

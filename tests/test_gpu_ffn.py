@@ -913,6 +913,7 @@ def test_layer_step_replays_from_a_hip_graph(name, mode):
     (832, 3200, [31, 33, 700, 1, 2, 500, 129, 604]),           # 13 k-tiles, 25 N-tiles, just past a round
     (1024, 4096, [1500, 1501, 1502, 1503, 0, 1, 1000, 993]),   # several rounds
     (768, 3200, [200 + 7 * i for i in range(64)]),             # many experts
+    (768, 5632, [700, 580]), (768, 5632, [5000, 4472]),        # 88 k-tiles in the second product: stays a launch of its own, joins
 ])
 def test_ffn_products_in_one_launch(d, ffn, sizes, form, ffn_options):
     """Both products in one launch against a launch each (which a given walk over the tiles asks for): the same bits, call after
