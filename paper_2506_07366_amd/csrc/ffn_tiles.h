@@ -24,6 +24,7 @@ constexpr int kTileMaxRows = 256;  // rows of the tallest tile
 constexpr int kTileGroup = 4;      // N-tiles walked side by side
 constexpr int kNonTemporal = 2;    // cache policy of a buffer load: nt
 constexpr int kThrough = 16;       // of a buffer store: sc1, written through to memory
+constexpr int kCacheLine = 128;    // bytes, of the vector L1 and the L2
 constexpr int kCopyPieces = 6;     // pieces of the row copy that a wavefront takes along with a tile
 constexpr size_t kStageLds = (size_t)3 * kTileMaxRows * kPackK * 2;
 // dynamic LDS of a workgroup: the stages, in the first product the copy's pieces, the number of the next tile
@@ -42,7 +43,7 @@ constexpr size_t kTileLds = kNextTileAt<EPI> + 16;
 // The XCDs' L2 caches are not coherent with each other inside a launch, so the hidden rows are written through to memory
 // (kThrough) and the tile is told once every wavefront has seen its own stores acknowledged (at the start of the next
 // tile, where the row list is waited for anyway); no cache can hold older hidden rows, nobody in the launch reads a
-// row before it is complete, and a row is whole cache lines.
+// row before it is complete, and a row is whole cache lines (the host sees to that: elsewhere a launch each).
 //
 // Whether a product shares its launch with the other one of the FFN.
 constexpr int kAlone = 0, kMakesRows = 1, kWantsRows = 2;

@@ -940,8 +940,12 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     const bool in_place = share_bytes(y_perm, result, x_in, (size_t)rows_in * row_bytes) ||
                           (copy.x_perm && share_bytes(y_perm, result, copy.x_perm, result)) ||
                           (gather_rows && share_bytes(y_perm, result, gather_rows, (size_t)A * sizeof(int32_t)));
+    // And where hidden rows share cache lines (they are multiples of 128 bytes, from the scratch's own address on, of which the ABI
+    // asks 16 bytes of alignment): a line read for a complete row would be kept with what its neighbour held before.
+    const bool own_lines = (uintptr_t)ws.h % kCacheLine == 0;
+    static_assert(kPackK * sizeof(bf16_t) % kCacheLine == 0, "a hidden row is whole lines");
     int32_t* const left =
-        linked && !armed && opt.group_n == 0 && !in_place ? (int32_t*)(ws.tiles1 + ws.capacity) - E : nullptr;
+        linked && !armed && opt.group_n == 0 && !in_place && own_lines ? (int32_t*)(ws.tiles1 + ws.capacity) - E : nullptr;
     const bool split = ws.split_capacity > 0 && !s2 && !linked;
     const bool own2 = bm2 != bm1 || bm2 == 0 || split;
     TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / kPackK, 0,

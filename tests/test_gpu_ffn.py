@@ -999,3 +999,26 @@ def test_ffn_products_in_one_launch_on_two_streams(ffn_options):
     for j in range(2):
         for y in ys[j]:
             assert torch.equal(y, want[j]), j
+
+
+@pytest.mark.parametrize("shift", [0, 16, 64, 112, 128])
+def test_ffn_scratch_at_any_sixteen_bytes(shift, ffn_options):
+    """The ABI asks 16 bytes of alignment of the scratch: hidden rows that share cache lines give the same bits."""
+    ffn_options()
+    d, ffn, E, sizes = 1024, 2048, 8, [700, 1, 0, 900, 513, 256, 1024, 702]
+    A, nseg = sum(sizes), len(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(83)
+    bf = lambda *shape: torch.randn(shape, device="cuda", generator=gen).mul_(0.05).to(torch.bfloat16)
+    packed = B.moe_pack_weights(bf(E, d, ffn), bf(E, d, ffn), bf(E, ffn, d))
+    so, se = dev_i32(np.concatenate([[0], np.cumsum(sizes)])), dev_i32([*range(E)])
+    x, other = bf(A, d) * 20, bf(A, d) * 20
+    n = B.moe_grouped_ffn_workspace_bytes(A, d, ffn, nseg, B.MOE_DTYPE_BF16)
+    store = torch.zeros(n + 256, dtype=torch.uint8, device="cuda")
+    at = -store.data_ptr() % 128 + shift
+    want = B.moe_grouped_ffn(x, so, se, packed, E, ffn, workspace=store[at:at + n]).clone()
+    ffn_options(group_n=4)   # a launch each
+    assert torch.equal(B.moe_grouped_ffn(x, so, se, packed, E, ffn, workspace=store[at:at + n]), want)
+    ffn_options()
+    for _ in range(4):
+        B.moe_grouped_ffn(other, so, se, packed, E, ffn, workspace=store[at:at + n])
+        assert torch.equal(B.moe_grouped_ffn(x, so, se, packed, E, ffn, workspace=store[at:at + n]), want)

@@ -220,3 +220,20 @@ def test_arguments_are_checked_before_the_first_launch(child):
                          ([2] + good[1:], dict(hist_pred=0)), (good, dict(x_perm=0)), (good[:11] + [1], dict(x_perm=0))):
             assert step(ints, **kw)[0] == 0, (ints, kw)                # what a mode does not read may be missing
     """)
+
+
+def test_products_share_a_launch_only_where_hidden_rows_are_whole_cache_lines(child):
+    """The hidden rows lie at the start of the FFN's scratch, of which the ABI asks 16 bytes of alignment: where a row shares a
+    128-byte line with the next one, a launch that reads finished rows beside unfinished ones is not to be had."""
+    out = child("""
+        FFN_WS = 22 << 40
+        for at in (0, 16, 32, 48, 64, 80, 96, 112, 128, 144, 192, 256, 4096 + 64):
+            for relu, x_perm in ((0, 17 << 40), (1, 17 << 40), (0, 0)):
+                rc, names = step([1, 1, 3000, 1024, 3008 if relu else 2048, 8, 2, 4, 3, 8, relu, 0], ws_ffn=FFN_WS + at, x_perm=x_perm)
+                assert rc == 0
+                products = [n for n in names if "grouped_" in n]
+                assert len(products) == (1 if at % 128 == 0 else 2), (at, relu, products)
+                assert ("grouped_ffn_tiles" in products[0]) == (at % 128 == 0), (at, products)
+                print("step")
+    """)
+    assert out.count("step") == 39
