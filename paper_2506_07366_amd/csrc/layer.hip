@@ -148,10 +148,19 @@ extern "C" int moe_layer_step(const moe_layer_step_args* a, void* stream) {
     const size_t tokens_bytes = (size_t)T * a->d * dtype_size(a->dtype);
     const bool copy_first = a->x_perm && share_bytes(a->x, tokens_bytes, a->workspace_ffn, a->workspace_ffn_bytes);
     const bool small = !own_pred && !copy_first && permute_in_one_workgroup(mode, A, E, G * S);
-    const bool shared = !own_pred && E <= kPlanMaxExperts && S <= kPlanMaxSlots && G <= 32;
+    // What the first workgroup of the routing launch writes, the plan and a cleared histogram, may lie in the logits, which the
+    // others still read: then that is left to later launches.
+    const size_t slots = (size_t)G * S * sizeof(int32_t), loads = (size_t)G * sizeof(int32_t);
+    auto in_logits = [&](const void* p, size_t n) { return share_bytes(p, n, a->logits, (size_t)T * E * sizeof(float)); };
+    const bool plan_in_logits = (mode == MOE_MODE_TOKEN && in_logits(a->hist_plan, counts)) || in_logits(a->slot_expert, slots) ||
+                                in_logits(a->slot_quota, slots) || in_logits(a->rank_load_pred, loads) ||
+                                in_logits(a->n_iters, sizeof(int32_t));
+    const bool shared = !own_pred && (mode == MOE_MODE_NONE || !plan_in_logits) && E <= kPlanMaxExperts &&
+                        S <= kPlanMaxSlots && G <= 32;
     // several workgroups permute and add up the histogram, which the first launch clears (and then counts predicted ids)
     const bool own_counts = mode == MOE_MODE_TOKEN && share_bytes(a->hist_plan, counts, a->hist, counts);
-    const bool wide = shared && !small && !copy_first && !own_counts && permute_counts(T, E, k, G, S);
+    const bool wide =
+        shared && !small && !copy_first && !own_counts && !in_logits(a->hist, counts) && permute_counts(T, E, k, G, S);
     const bool together = shared && (wide || mode != MOE_MODE_NONE);
     auto plan = [&] {
         return moe_plan_duplicates(mode, hp, E, G, S, a->c_max, a->slot_expert, a->slot_quota, a->rank_load_pred,

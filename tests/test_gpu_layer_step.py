@@ -272,3 +272,32 @@ def test_step_with_buffers_that_share_memory(T, gather):
                 assert torch.allclose(got[n].float(), v.float(), rtol=1e-2, atol=1e-3), n
             else:
                 assert torch.equal(got[n], v), (how, n)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("T", [300, 3000, 20000])
+def test_step_with_outputs_in_the_logits(T, mode):
+    """Histogram and plan on logits that are of no further use, at their start (read by the first workgroup) and their end."""
+    E, k, d = 16, 2, 64
+    cfg = wl.MoEConfig("inlog", T=T, d=d, ffn=64, E=E, k=k, G=4, S=5, dtype="bf16", mode=mode, seed=73)
+    gen = torch.Generator(device="cuda").manual_seed(74)
+    ws = [torch.randn(s, device="cuda", generator=gen).mul_(0.02).to(torch.bfloat16) for s in ((E, d, 64), (E, d, 64), (E, 64, d))]
+    logits = torch.randn((T, E), device="cuda", generator=gen)
+    x = torch.randn((T, d), device="cuda", generator=gen).to(torch.bfloat16)
+    pred_idx = torch.topk(logits + 0.5 * torch.randn((T, E), device="cuda", generator=gen), k, dim=1).indices.to(torch.int32).contiguous()
+    hist_pred = torch.bincount(pred_idx.reshape(-1).long(), minlength=E).to(torch.int32)
+    res = {}
+    for how in ("none", "hist", "hist_plan", "slot_expert", "slot_quota"):
+        for end in (False, True):
+            layer = MoELayer(cfg)
+            layer.set_weights(*ws)
+            given = logits.clone()
+            if how != "none":
+                flat = given.view(torch.int32).reshape(-1)
+                n = getattr(layer, how).numel()
+                setattr(layer, how, flat[-n:] if end else flat[:n])
+            assert layer._one_call(given, x, hist_pred, pred_idx, mode)
+            res[how, end] = outputs(layer)
+    for how, got in res.items():
+        for n, v in res["none", False].items():
+            assert torch.equal(got[n], v), (how, n)

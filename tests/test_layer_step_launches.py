@@ -237,3 +237,34 @@ def test_products_share_a_launch_only_where_hidden_rows_are_whole_cache_lines(ch
                 print("step")
     """)
     assert out.count("step") == 39
+
+
+def test_outputs_in_the_logits_are_written_once_these_are_read(child):
+    """No workgroup clears the histogram or writes the plan beside others that still route: where one of these outputs lies in the
+    logits, a later launch does."""
+    out = child("""
+        LOGITS = (POINTERS.index("logits") + 1) << 40
+        def kinds(mode, t, e, g, s, **pointers):
+            rc, names = step([mode, 1, t, 64, 64, e, 2, g, s, 8, 0, 0], **pointers)
+            assert rc == 0
+            return [next(w for w in ("route_plan", "route", "hist", "plan", "perm", "other") if w in n or w == "other") for n in names]
+        for shape in ((64, 16, 4, 5), (3000, 16, 4, 5), (20000, 16, 4, 5)):   # one workgroup permutes; several; ids counted ahead
+            t, e, g, s = shape
+            size = dict(hist=4 * e, hist_plan=4 * e, slot_expert=4 * g * s, slot_quota=4 * g * s, rank_load_pred=4 * g, n_iters=4)
+            for mode in (0, 1, 2):
+                beside = kinds(mode, *shape)
+                for name, n in size.items():
+                    for at in (LOGITS + 4 * t * e, LOGITS - n):
+                        assert kinds(mode, *shape, **{name: at}) == beside, (shape, mode, name)
+                    for at in (LOGITS, LOGITS + 4 * t * e - 4, LOGITS + 4 - n):
+                        got = kinds(mode, *shape, **{name: at})
+                        if name == "hist" and t > 1000:                  # the launch after the routing's and the plan's makes it whole
+                            assert got[:3] == {0: ["route", "hist", "plan"], 1: ["route_plan", "hist", "perm"],
+                                               2: ["hist", "route_plan", "hist"] if t > 10000 else ["route_plan", "hist", "perm"]}[mode]
+                        elif name == "hist" or mode == 0 or (name == "hist_plan" and mode != 2):
+                            assert got == beside, (shape, mode, name, got)   # not written yet, or not at all
+                        else:
+                            assert got[0] == "route" and "route_plan" not in got, (shape, mode, name, got)
+            print("shape")
+    """)
+    assert out.count("shape") == 3
