@@ -56,7 +56,15 @@ __device__ __forceinline__ void wait_rows(int32_t* left) {
         __builtin_amdgcn_s_sleep(4);
     asm volatile("" ::: "memory");
 }
+// (behind a wait for this wavefront's stores and a barrier, neither of which the compiler takes for memory accesses: the
+// stores must be ahead of them in the code, too, and the count behind)
+__device__ __forceinline__ void rows_stored() {
+    asm volatile("" ::: "memory");
+    wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+}
 __device__ __forceinline__ void tell_rows(int32_t* left, int& expert, int rows) {
+    asm volatile("" ::: "memory");
     if ((threadIdx.x & 63) == 0)
         (void)__hip_atomic_fetch_add(&left[expert], rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     expert = -1;
@@ -277,7 +285,7 @@ __device__ __forceinline__ void tile_product(
                 }
                 offA[i] = ((unsigned)r * (unsigned)lda + (unsigned)((slot ^ swz(row)) * 8)) * 2u;
             }
-            if constexpr (LINK == kMakesRows) wait_vmcnt<0>();  // the previous tile's results have reached memory
+            if constexpr (LINK == kMakesRows) rows_stored();  // the previous tile's results have reached memory
             if constexpr (EPI != kEpiNone)  // (behind the row list, whose wait would be for the pieces too)
                 request_pieces(copy, copy_first, copy_n, smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
             bf16x8 w[D][2][2], af[R];
@@ -502,7 +510,7 @@ __device__ __forceinline__ void tile_product(
         }
     }
     if constexpr (LINK == kMakesRows) {
-        wait_vmcnt<0>();
+        rows_stored();
         __builtin_amdgcn_s_barrier();
         if (wave == 0 && told_expert >= 0) tell_rows(left, told_expert, told_rows);
     }
