@@ -287,7 +287,8 @@ __device__ __forceinline__ void tile_product(
             }
             if constexpr (LINK == kMakesRows) rows_stored();  // the previous tile's results have reached memory
             if constexpr (EPI != kEpiNone)  // (behind the row list, whose wait would be for the pieces too)
-                request_pieces(copy, copy_first, copy_n, smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
+                if (copy_n > 0)
+                    request_pieces(copy, copy_first, copy_n, smem + kStageLds + wave * (kCopyPieces * kCopyPieceLds));
             bf16x8 w[D][2][2], af[R];
             const unsigned lane_off = (unsigned)(lane_p * 16);
             // load l of this wavefront's NB loads of k-tile kt, into buffers b
