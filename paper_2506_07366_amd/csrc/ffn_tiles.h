@@ -536,7 +536,7 @@ __global__ __launch_bounds__(512, 2) void grouped_ffn_tiles_kernel(
     float* __restrict__ partials, RowCopy copy, int32_t* left) {
     tile_product<EPI, kMakesRows>(X, d, P13, stride1, h, fp, tiles1, counts1, queues, EPI == kEpiSwiglu ? 2 * fp : fp, d,
                                   kTileGroup, past_caches1, rm1, nullptr, copy, left);
-    if (counts1[kCntEntries] == 0) return;  // (no table fits offsets that claim more rows than the call has: nothing to wait for)
+    if (counts1[kCntEntries] == 0) return;  // (the first table did not fit: its tiles are not made, waiting for them would not end)
     tile_product<kEpiNone, kWantsRows>(h, fp, P2, stride2, Y, d, tiles2, counts2, queues + 8, d, fp, kTileGroup, past_caches2,
                                        rm2, partials, RowCopy{}, left);
 }

@@ -932,8 +932,8 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     // tokens 264 -> 268 / 532 -> 546 us).  What the second product waits for lies behind the first table's tiles, of which there
     // are less than there is room for.
     const int64_t spare = ws.capacity - (ceil_div64(A, kMinAutoHeight) + (A < nseg ? A : nseg));
-    const bool linked = !s1 && !s2 && v1 < 0 && v2 < 0 && opt.split <= 0 && nrange == nseg &&
-                        spare * (int64_t)sizeof(MTile) >= (int64_t)E * (int64_t)sizeof(int32_t) &&
+    const int left_room = ceil_div(E * (int)sizeof(int32_t), (int)sizeof(MTile));
+    const bool linked = !s1 && !s2 && v1 < 0 && v2 < 0 && opt.split <= 0 && nrange == nseg && spare >= left_room &&
                         one_launch(A, E, ceil_div(n1 * fp, kPackN), d / kPackK, ceil_div(d, kPackN), fp / kPackK, ws.split_capacity > 0);
     // The same where the result lies on what the first product reads or copies (in place, for one): it is written while that goes on.
     const size_t row_bytes = (size_t)d * sizeof(bf16_t), result = (size_t)A * row_bytes;
@@ -944,11 +944,13 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     // asks 16 bytes of alignment): a line read for a complete row would be kept with what its neighbour held before.
     const bool own_lines = (uintptr_t)ws.h % kCacheLine == 0;
     static_assert(kPackK * sizeof(bf16_t) % kCacheLine == 0, "a hidden row is whole lines");
-    int32_t* const left =
-        linked && !armed && opt.group_n == 0 && !in_place && own_lines ? (int32_t*)(ws.tiles1 + ws.capacity) - E : nullptr;
+    const bool both = linked && !armed && opt.group_n == 0 && !in_place && own_lines;
+    // (the first table ends where the counts begin, whatever the offsets say: one that does not fit is none, and nobody waits for it)
+    const int room1 = both ? ws.capacity - left_room : ws.capacity;
+    int32_t* const left = both ? (int32_t*)(ws.tiles1 + room1) : nullptr;
     const bool split = ws.split_capacity > 0 && !s2 && !linked;
     const bool own2 = bm2 != bm1 || bm2 == 0 || split;
-    TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, ws.capacity, d / kPackK, 0,
+    TableSpec t1{ws.tiles1, ws.counts, nullptr, bm1, room1, d / kPackK, 0,
                  ceil_div(n1 * fp, kPackN), 0, 0};
     TableSpec t2{own2 ? ws.tiles2 : nullptr, ws.counts + kCntStride, ws.splits, bm2, ws.capacity, fp / kPackK,
                  split ? ws.parts : 0, ceil_div(d, kPackN), ws.split_all, ws.split_capacity};
