@@ -616,22 +616,21 @@ static int launch_tiles(const bf16_t* A, int lda, const bf16_t* Bp, size_t b_str
 // Whether both products share a launch (ffn_tiles.h).  It saves what the uneven end of the first product costs, half a tile
 // per workgroup on average, and costs what writing the hidden rows through to memory does (2 % at 16 rounds of tiles).  Whole
 // steps, us, a launch each -> one, by the rounds of 256 tiles that the first product has at 256 rows per tile: 1.8 (64 experts of
-// 2048 x 1408, 400 tokens) 222 -> 206, 2.0 (16 of 4096 x 688, 5000) 420 -> 398, 3.5 (8 of 4096 x 14336, 400) 543 -> 536,
-// 5.5 (64 of 2048 x 1408, 4096) 555 -> 546, 5.9 (128 of 4096 x 1536, 2000) 971 -> 954, 6.6 (8 of 4096 x 14336, 1400) 937 -> 930, 7.4
-// (64 of 2048 x 1408, 6000) 674 -> 670, 8.8 (8 of 4096 x 14336, 2000) 1270 -> 1277, 10.4 (64 of 2048 x 1408, 9000) 918 -> 929.
-// Below a round there is little to fill (64 of 768 x 3072, 2000 tokens 142 -> 143), and tiles of a few k-tiles are done before the
-// hand-over is (8 of 512 x 1024, K = 512, 4096 tokens 78 -> 85).
-// Where a launch of its own would compute the second product's closing tiles as parts of K (`parts`), a tile here is all of K: with
-// a long one it stays alone where that is more than 3/4 of all that a workgroup has to do on average.  8 experts of
-// 4096 x 14336, rows as a popularity of 0.1 / 1 / 10 has them, by that share: 1.07 (80 tokens) 251 -> 304 / 499 -> 525 / 494 ->
-// 513, 1.07 (128) 252 -> 332 / 527 -> 515 / 514 -> 522, 0.89 (256) 335 -> 354 / 535 -> 537 / 546 -> 533, 0.76 (384) 376 -> 380 /
-// 571 -> 571 / 573 -> 558, 0.59 (640) 516 -> 510 / 674 -> 667 / 652 -> 629.  Up to 48 k-tiles one launch is ahead at any share measured (64 of 768 x 3072,
-// 1.07 (2048) 119 -> 118 / 163 -> 158 at 0.1 / 10, 0.67 (8192) 177 -> 163 / 216 -> 200).
-static bool one_launch(int64_t A, int E, int n_ntiles1, int k_tiles1, int n_ntiles2, int k_tiles2, bool parts) {
-    const int64_t m_tiles = ceil_div64(A, kTallest) + (A < E ? A : E) / 2, tiles = m_tiles * n_ntiles1;
-    if (tiles < kGemmGrid || tiles > 7 * kGemmGrid || k_tiles1 < 12) return false;
-    const int64_t work = m_tiles * ((int64_t)n_ntiles1 * k_tiles1 + (int64_t)n_ntiles2 * k_tiles2);
-    return !parts || k_tiles2 < 64 || (int64_t)4 * kGemmGrid * k_tiles2 <= 3 * work;
+// 2048 x 1408, 400 tokens) 222 -> 206, 2.0 (16 of 4096 x 688, 5000) 420 -> 398, 5.5 (64 of 2048 x 1408, 4096) 555 -> 546, 5.9 (128
+// of 4096 x 1536, 2000) 971 -> 954, 7.4 (64 of 2048 x 1408, 6000) 674 -> 670, 8.8 (8 of 4096 x 14336, 2000) 1270 -> 1277, 10.4 (64
+// of 2048 x 1408, 9000) 918 -> 929.  Below a round there is little to fill (64 of 768 x 3072, 2000 tokens 142 -> 143).
+// A first product of few k-tiles is done before the hand-over is.  d / 64 = 6 / 8 / 9 / 10 / 11 at hidden width 2048: 8 experts, 4096
+// tokens 105 -> 111 / 105 -> 111 / 114 -> 122 / 119 -> 126 / 132 -> 139; 64 experts, 8192 tokens, popularity 10 186 -> 195 /
+// 204 -> 205 / 234 -> 230 / 255 -> 252 / 266 -> 261.
+// A long second product keeps its launch: a tile of all its k-tiles is what the shared launch ends with, where a launch of its own has
+// closing tiles in parts of K.  8 experts of 4096 x 14336 (224 k-tiles), rows as a popularity of 0.1 / 1 / 10 has them, 384 tokens 373 ->
+// 385 / 567 -> 560 / 566 -> 554, 640 500 -> 499 / 674 -> 672 / 646 -> 636, 1001 659 -> 673 / 814 -> 852 / 775 -> 790, 1024 674 -> 694 /
+// 840 -> 821 / 789 -> 792, 1400 821 -> 848 / 984 -> 1005 / 946 -> 958; below 384 it is further behind (128 tokens 252 -> 332 at 0.1).
+// 70 shapes drawn inside these lines (12 to 64 and 4 to 60 k-tiles, 8 to 128 experts): 3.2 % ahead on average, 0.91 to 1.30; behind
+// is above all 8 experts with a first product of 12 to 16 k-tiles (0.91 to 1.02).
+static bool one_launch(int64_t A, int E, int n_ntiles1, int k_tiles1, int k_tiles2) {
+    const int64_t tiles = (ceil_div64(A, kTallest) + (A < E ? A : E) / 2) * n_ntiles1;
+    return tiles >= kGemmGrid && tiles <= 7 * kGemmGrid && k_tiles1 >= 12 && k_tiles2 < 64;
 }
 
 template <int EPI>
@@ -934,7 +933,7 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     const int64_t spare = ws.capacity - (ceil_div64(A, kMinAutoHeight) + (A < nseg ? A : nseg));
     const int left_room = ceil_div(E * (int)sizeof(int32_t), (int)sizeof(MTile));
     const bool linked = !s1 && !s2 && v1 < 0 && v2 < 0 && opt.split <= 0 && nrange == nseg && spare >= left_room &&
-                        one_launch(A, E, ceil_div(n1 * fp, kPackN), d / kPackK, ceil_div(d, kPackN), fp / kPackK, ws.split_capacity > 0);
+                        one_launch(A, E, ceil_div(n1 * fp, kPackN), d / kPackK, fp / kPackK);
     // The same where the result lies on what the first product reads or copies (in place, for one): it is written while that goes on.
     const size_t row_bytes = (size_t)d * sizeof(bf16_t), result = (size_t)A * row_bytes;
     const bool in_place = share_bytes(y_perm, result, x_in, (size_t)rows_in * row_bytes) ||

@@ -268,3 +268,20 @@ def test_outputs_in_the_logits_are_written_once_these_are_read(child):
             print("shape")
     """)
     assert out.count("shape") == 3
+
+
+@pytest.mark.parametrize("T,d,ffn,E,k,relu,both", [
+    (1408, 1024, 2048, 8, 2, 0, False), (1409, 1024, 2048, 8, 2, 0, True),       # a round of 256 tiles
+    (13824, 1024, 2048, 8, 2, 0, True), (13825, 1024, 2048, 8, 2, 0, False),     # seven
+    (3000, 704, 2048, 8, 2, 0, False), (3000, 768, 2048, 8, 2, 0, True),         # 12 k-tiles in the first product
+    (3000, 1024, 4032, 8, 2, 0, True), (3000, 1024, 4033, 8, 2, 0, False),       # 63 in the second
+    (3000, 1024, 4032, 8, 2, 1, True), (3000, 1024, 4096, 8, 2, 1, False),
+    (384, 4096, 14336, 8, 2, 0, False), (1001, 4096, 14336, 8, 2, 0, False), (1400, 4096, 14336, 8, 2, 0, False),
+])
+def test_products_share_a_launch_within_the_rule(child, T, d, ffn, E, k, relu, both):
+    out = child(f"""
+        rc, names = step([1, 1, {T}, {d}, {ffn}, {E}, {k}, 8, 2, 8, {relu}, 0])
+        assert rc == 0
+        print(["tiles" if "grouped_gemm_tile" in n else "both" for n in names if "grouped_" in n])
+    """)
+    assert out.strip() == str(["both"] if both else ["tiles", "tiles"]), out
