@@ -7,7 +7,8 @@ that is already resident in HBM: route -> histogram -> duplication plan -> permu
   value      = tokens/s of the whole layer (T / time per step)
   roofline   = the dominant kernel (the gate/up + SwiGLU grouped GEMM) against the
                MI355X dense bf16 MFMA peak, its duration measured with HIP events on
-               the launch stream inside the timed region
+               the launch stream, over as many steps again behind the timed ones (with
+               events each product is a launch of its own)
   cpu_baseline = the CPU oracle timed on a bounded sample of the same workload
 """
 from __future__ import annotations
@@ -252,7 +253,16 @@ def main():
         step()
     torch.cuda.synchronize()
 
-    # events for the dominant kernel, recorded by the library on the launch stream
+    t0 = time.perf_counter()
+    for _ in range(args.steps):
+        step()
+    torch.cuda.synchronize()
+    t1 = time.perf_counter()
+    ms_per_step = (t1 - t0) * 1e3 / args.steps
+    tokens_per_s = cfg.T / (ms_per_step * 1e-3)
+
+    # The two products, between events that the library records on the launch stream.  A pass of its own: a call
+    # with events launches each product by itself, also where the steps above run both in one launch.
     bf16 = cfg.dtype == "bf16"
     evs = []
     if bf16:
@@ -262,16 +272,10 @@ def main():
                 e.record()      # creates the underlying hipEvent
             evs.append(quad)
         torch.cuda.synchronize()
-
-    t0 = time.perf_counter()
-    for i in range(args.steps):
-        if bf16:
-            B.moe_grouped_ffn_time_next_call(evs[i])
-        step()
-    torch.cuda.synchronize()
-    t1 = time.perf_counter()
-    ms_per_step = (t1 - t0) * 1e3 / args.steps
-    tokens_per_s = cfg.T / (ms_per_step * 1e-3)
+        for quad in evs:
+            B.moe_grouped_ffn_time_next_call(quad)
+            step()
+        torch.cuda.synchronize()
 
     flops1 = (2.0 if cfg.act == "relu" else 4.0) * cfg.A * cfg.d * cfg.ffn   # gate + up products (ReLU form: one)
     flops2 = 2.0 * cfg.A * cfg.d * cfg.ffn      # down product

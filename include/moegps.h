@@ -202,9 +202,12 @@ int moe_pack_weights(const void* W1, const void* W3, const void* W2, int dtype,
  * reciprocal instructions (about 1 ulp each, far below the bf16 rounding that follows).
  * With a few rows per expert a product's sums are taken as up to eight parts of the contracted
  * width, added in a fixed order in fp32.
- * When the second product has only a few tiles per workgroup, its closing tiles are summed as
- * up to four parts of the hidden width (fp32 partial sums held in the workspace, added in the
- * order of the parts, then rounded once); the result does not depend on launch order.
+ * When the second product has only a few tiles per workgroup and is a launch of its own, its closing
+ * tiles are summed as up to four parts of the hidden width (fp32 partial sums held in the workspace,
+ * added in the order of the parts, then rounded once); the result does not depend on launch order.
+ * A call over all slots whose first product is a few rounds of tiles runs both products in one launch,
+ * without such parts, if the workspace is 128-byte aligned and y_perm shares no memory with the inputs
+ * (else a launch each, with the same results).
  * bf16 needs d % 64 == 0 (any ffn: the packed weights pad the hidden width to a multiple of
  * 64 with zeros) and A * d < 2^31; f32 needs d % 4 == 0 and ffn % 4 == 0.
  * Limits: 0 <= A < 2^31, 1 <= d, ffn <= 2^22, 1 <= nseg <= MOE_MAX_SEGMENTS.  The size query
@@ -320,6 +323,9 @@ int moe_grouped_ffn_relu(const void* x_perm, int dtype, int64_t A, int d, int ff
  * stream before and after its first product (gate/up + SwiGLU) and before and
  * after its second product (down).  The hook is consumed by that one call, also when the
  * call returns early or takes the fp32 path (which records nothing).
+ * Such a call launches each product by itself, also where a call without the hook would run both in one
+ * launch (batches that are a few rounds of tiles): the results are the same, bit for bit, the time of
+ * the whole is not.
  * Pass NULL to clear it.  `events` is a HOST array of 4 handles; it is copied.
  */
 int moe_grouped_ffn_time_next_call(void* const* events);

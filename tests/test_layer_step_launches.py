@@ -59,6 +59,7 @@ RUNTIME = textwrap.dedent('''
         return 0;
     }
     int hipGetLastError(void) { return 0; }
+    int hipEventRecord(void* e, void* stream) { (void)e; (void)stream; return 0; }
     int hipGetDevice(int* d) { *d = 0; return 0; }
     int hipFuncSetAttribute(const void* fn, int a, int v) { (void)fn; (void)a; (void)v; return 0; }
     int hipGetDevicePropertiesR0600(void* p, int d) { (void)p; (void)d; return 1; }
@@ -285,3 +286,18 @@ def test_products_share_a_launch_within_the_rule(child, T, d, ffn, E, k, relu, b
         print(["tiles" if "grouped_gemm_tile" in n else "both" for n in names if "grouped_" in n])
     """)
     assert out.strip() == str(["both"] if both else ["tiles", "tiles"]), out
+
+
+def test_a_call_with_events_is_a_launch_per_product(child):
+    """... and the next one, without, runs both in one again."""
+    out = child("""
+        ints = [1, 1, 3000, 1024, 2048, 8, 2, 4, 3, 8, 0, 0]
+        events = (ctypes.c_void_p * 4)(1, 2, 3, 4)
+        for armed in (False, True, False):
+            if armed:
+                assert lib.moe_grouped_ffn_time_next_call(events) == 0
+            rc, names = step(ints)
+            assert rc == 0
+            print(sum("grouped_" in n for n in names), sum("grouped_ffn_tiles" in n for n in names))
+    """)
+    assert out.split("\n")[:3] == ["1 1", "2 0", "1 1"], out
