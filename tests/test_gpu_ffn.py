@@ -906,18 +906,24 @@ def test_layer_step_replays_from_a_hip_graph(name, mode):
         assert torch.equal(layer.out.view(torch.uint8), ref.view(torch.uint8)), rep
 
 
+# width, hidden width of the SwiGLU and of the ReLU form, rows per expert, whether both products share a launch
+# (tests/test_layer_step_launches.py holds the last against what is launched)
+ONE_LAUNCH = [
+    (768, 1700, 3400, [4000, 0, 0, 0, 0, 0, 0, 0], True),                  # one expert: the second product waits for all of the first
+    (768, 1700, 3400, [1, 300, 0, 257, 1900, 64, 65, 1413], True),         # ragged, an expert without rows between, padded hidden width
+    (832, 3200, 4000, [31, 33, 1700, 1, 2, 500, 129, 604], True),          # 13 k-tiles; 25 N-tiles; a round of tiles in the ReLU form
+    (1024, 4000, 4000, [1500, 1501, 1502, 1503, 0, 1, 1000, 993], True),   # several rounds; 63 k-tiles in the second product
+    (768, 1500, 3000, [200 + 7 * i for i in range(64)], True),             # many experts, between six and seven rounds
+    (768, 5632, 5632, [700, 580], False), (768, 5632, 5632, [5000, 4472], False),   # 88 k-tiles in the second product
+]
+
+
 @pytest.mark.parametrize("form", ["plain", "relu", "gather", "weights"])
-@pytest.mark.parametrize("d,ffn,sizes", [
-    (768, 1700, [4000, 0, 0, 0, 0, 0, 0, 0]),                  # one expert: the second product waits for all of the first
-    (768, 1700, [1, 300, 0, 257, 1900, 64, 65, 1413]),         # ragged, an expert without rows between, padded hidden width
-    (832, 3200, [31, 33, 700, 1, 2, 500, 129, 604]),           # 13 k-tiles, 25 N-tiles, just past a round
-    (1024, 4096, [1500, 1501, 1502, 1503, 0, 1, 1000, 993]),   # several rounds
-    (768, 3200, [200 + 7 * i for i in range(64)]),             # many experts
-    (768, 5632, [700, 580]), (768, 5632, [5000, 4472]),        # 88 k-tiles in the second product: stays a launch of its own, joins
-])
-def test_ffn_products_in_one_launch(d, ffn, sizes, form, ffn_options):
+@pytest.mark.parametrize("d,ffn,relu_ffn,sizes,both", ONE_LAUNCH)
+def test_ffn_products_in_one_launch(d, ffn, relu_ffn, sizes, both, form, ffn_options):
     """Both products in one launch against a launch each (which a given walk over the tiles asks for): the same bits, call after
     call and replayed from a graph with other rows in between."""
+    ffn = relu_ffn if form == "relu" else ffn
     ffn_options()
     E, A, k = len(sizes), sum(sizes), 2
     A -= A % k

@@ -301,3 +301,30 @@ def test_a_call_with_events_is_a_launch_per_product(child):
             print(sum("grouped_" in n for n in names), sum("grouped_ffn_tiles" in n for n in names))
     """)
     assert out.split("\n")[:3] == ["1 1", "2 0", "1 1"], out
+
+
+def test_shapes_of_the_shared_launch_reach_it(child):
+    """The shapes that tests/test_gpu_ffn.py holds against a launch each are of the form that they are listed as."""
+    from test_gpu_ffn import ONE_LAUNCH
+    child(f"""
+        c_p = ctypes.c_void_p
+        X, OF, GATE_W, SEG, SLOT, PACKED, Y, WS = [i << 40 for i in range(1, 9)]
+        plain = [c_p, c_int, c_i64] + [c_int] * 3 + [c_p] * 2 + [c_int] * 3 + [c_p] * 3 + [c_sz, c_p]
+        fused = [c_p] + [c_int] * 3 + [c_p] * 2 + [c_int] * 3 + [c_p] * 2 + [c_int] * 3 + [c_p] * 3 + [c_sz, c_p]
+        for f in (lib.moe_grouped_ffn, lib.moe_grouped_ffn_relu):
+            f.argtypes = plain
+        lib.moe_grouped_ffn_fused.argtypes = fused
+        for d, swiglu, relu, sizes, both in {ONE_LAUNCH}:
+            e, a = len(sizes), sum(sizes) // 2 * 2
+            for form, ffn in (("plain", swiglu), ("relu", relu), ("gather", swiglu), ("weights", swiglu)):
+                tail = (SEG, SLOT, e + 2, 0, e + 2, PACKED, Y, WS, lib.moe_grouped_ffn_workspace_bytes(a, d, ffn, e + 2, 1), None)
+                for group_n in (0, 4):
+                    assert lib.moe_grouped_ffn_set_option(3, group_n) == 0
+                    rt.start(HOOK())
+                    if form in ("plain", "relu"):
+                        rc = (lib.moe_grouped_ffn if form == "plain" else lib.moe_grouped_ffn_relu)(X, 1, a, d, ffn, e, *tail)
+                    else:
+                        rc = lib.moe_grouped_ffn_fused(X, 1, a // 2, 2, OF, GATE_W if form == "weights" else None, d, ffn, e, *tail)
+                    names = rt.launches().decode()
+                    assert rc == 0 and ("grouped_ffn_tiles" in names) == (both and group_n == 0), (d, ffn, sizes, form, rc, names)
+    """)
