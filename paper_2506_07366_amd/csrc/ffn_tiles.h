@@ -77,7 +77,7 @@ __device__ __forceinline__ void tile_product(
     bf16_t* C, int ldc,                              // output [rows, SWIGLU ? N/2 : N]
     const MTile* __restrict__ mtiles, const int32_t* __restrict__ counts, int32_t* __restrict__ queues,
     int N, int K, int group_n, bool past_caches, RowMap rm,
-    float* __restrict__ partials,  // [slab][kPartRows][N] fp32 sums of entries that cover part of K (plain product only)
+    float* __restrict__ partials,  // [slab][kPartRows][N] fp32 sums of entries that cover part of K (plain product, a launch of its own)
     RowCopy copy,                  // first product: rows to be copied besides, a share of them with every tile
     int32_t* left) {               // [E] what the second product waits for, see above (LINK)
     constexpr bool SWIGLU = EPI == kEpiSwiglu;
@@ -181,12 +181,13 @@ __device__ __forceinline__ void tile_product(
         __builtin_amdgcn_s_barrier();  // also: every wavefront is done reading the previous tile's stages
         const int t_all = __builtin_amdgcn_readfirstlane(next_tile);
         if (t_all < 0) break;
-        // This tile's share of the row copy.  The product is bound by the matrix pipe and leaves memory idle, the copy by
-        // memory: its pieces, and where they go, are on their way to LDS while the tile is worked on and are stored behind
-        // it, in the drain of the tile's own results.  What does not fit into LDS (many tokens for few tiles) is copied here.  Whole
+        // This tile's share of the row copy: its pieces, and where they go, are asked for ahead of the first k-tiles, in LDS with
+        // the first of these (loads return in order), and stored behind the tile's own results, whose drain they lengthen.  What does
+        // not fit into LDS (many tokens for few tiles) is copied here.  It saves the copy's launch and costs the tiles a part of that.  Whole
         // steps, us, a launch of the copy's own -> this: 16384 tokens, top-6 of 64 experts of 2048 x 1408 1659 -> 1624,
         // 32768, top-8 of 128 of 4096 x 1536 8791 -> 8488, 16384, top-1 of 64 of 768 x 3072 283 -> 276, 2048, top-6
-        // of 64 of 2048 x 1408 392 -> 384.  Loaded and stored at the tile's start instead (one memory round trip more per tile) 1679, 8956,
+        // of 64 of 2048 x 1408 392 -> 384; none on 8 of 4096 x 14336, 4096 tokens 2425 -> 2424, the first product 1502 -> 1525.  Loaded
+        // and stored at the tile's start instead (one memory round trip more per tile) 1679, 8956,
         // 279; copied by workgroups behind those of the product, as these run out of tiles, 1665, 8707, 294.
         int copy_first = 0, copy_n = 0;  // this wavefront's pieces
         if constexpr (EPI != kEpiNone) {
@@ -446,7 +447,7 @@ __device__ __forceinline__ void tile_product(
         } else {
             const int col0 = n0 + wave * 32;  // (N is a multiple of 64: the wavefront's columns exist or not together)
             float* slab = nullptr;
-            if constexpr (EPI == kEpiNone)
+            if constexpr (EPI == kEpiNone && LINK == kAlone)
                 if (mt.part >= 0) slab = partials + (size_t)mt.part * kPartRows * N;
             if (slab) {
 #pragma unroll
@@ -532,11 +533,11 @@ __global__ __launch_bounds__(512, 2) void grouped_ffn_tiles_kernel(
     const bf16_t* __restrict__ X, int d, const bf16_t* __restrict__ P13, size_t stride1, const bf16_t* __restrict__ P2,
     size_t stride2, bf16_t* h, int fp, bf16_t* __restrict__ Y, const MTile* __restrict__ tiles1,
     const MTile* __restrict__ tiles2, const int32_t* __restrict__ counts1, const int32_t* __restrict__ counts2,
-    int32_t* __restrict__ queues, bool past_caches1, bool past_caches2, RowMap rm1, RowMap rm2,
-    float* __restrict__ partials, RowCopy copy, int32_t* left) {
+    int32_t* __restrict__ queues, bool past_caches1, bool past_caches2, RowMap rm1, RowMap rm2, RowCopy copy,
+    int32_t* left) {
     tile_product<EPI, kMakesRows>(X, d, P13, stride1, h, fp, tiles1, counts1, queues, EPI == kEpiSwiglu ? 2 * fp : fp, d,
                                   kTileGroup, past_caches1, rm1, nullptr, copy, left);
     if (counts1[kCntEntries] == 0) return;  // (the first table did not fit: its tiles are not made, waiting for them would not end)
     tile_product<kEpiNone, kWantsRows>(h, fp, P2, stride2, Y, d, tiles2, counts2, queues + 8, d, fp, kTileGroup, past_caches2,
-                                       rm2, partials, RowCopy{}, left);
+                                       rm2, nullptr, RowCopy{}, left);
 }

@@ -642,7 +642,7 @@ static int launch_both(const bf16_t* X, int d, const bf16_t* P13, size_t stride1
     if (const int rc = raise_lds((const void*)kern, kTileLds<EPI>, raised); rc != MOE_OK) return rc;
     hipLaunchKernelGGL(kern, dim3(kGemmGrid), dim3(512), kTileLds<EPI>, st, X, d, P13, stride1, P2, stride2, (bf16_t*)ws.h, fp,
                        Y, ws.tiles1, tiles2, ws.counts, counts2, ws.queues, past_caches(E, stride1), past_caches(E, stride2),
-                       rm1, rm2, ws.partials, copy, left);
+                       rm1, rm2, copy, left);
     return check_launch();
 }
 
@@ -976,11 +976,10 @@ int grouped_ffn_call(int relu, const void* x_in, int64_t rows_in, const int32_t*
     if (timed) (void)hipEventRecord(g_time_events[1], st);
     if (rc != MOE_OK) return rc;
     if (timed) (void)hipEventRecord(g_time_events[2], st);
-    if (left) {
-    } else if (s2)
+    if (s2)
         rc = launch_stream<kEpiNone>(s2, A, E, (const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), (bf16_t*)y_perm, d,
                                      tiles2, count2, d, fp, rm2, RowCopy{}, st);
-    else
+    else if (!left)
         rc = launch_tiles<kEpiNone>((const bf16_t*)ws.h, fp, p2, packed_elems2(d, fp), E, (bf16_t*)y_perm, d, tiles2, count2,
                                     ws.queues + 8, d, fp, group_n, rm2, ws.partials, RowCopy{}, st);
     if (rc == MOE_OK && split) {

@@ -2,7 +2,7 @@
 // combine of one batch, with launches shared between the small ones.
 //
 // The index steps of a decode or prompt batch are a chain of launches of 2 to 20 us of work, 4.7 us apart at
-// least, and each is a call from the host.  Two things shorten it where the shape allows:
+// least, and each is a call from the host.  Three things shorten it where the shape allows:
 //   - under a prediction the plan does not need the routing: one workgroup makes it (under Token-to-Expert
 //     after counting the predicted ids) while the others of the same launch route the tokens;
 //   - where the permutation is one workgroup's work it also writes the histogram, without a prediction
