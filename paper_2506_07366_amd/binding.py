@@ -445,7 +445,7 @@ def moe_predictor_predict(counts: torch.Tensor, A_next: int, out: Optional[torch
 
 def moe_grouped_ffn_time_next_call(events) -> None:
     """``events``: four recorded-once ``torch.cuda.Event(enable_timing=True)``; the next
-    moe_grouped_ffn call on this thread records them around its two products."""
+    moe_grouped_ffn call on this thread records them around its two products, each a launch of its own."""
     lib = load_library()
     if events is None:
         _check(lib.moe_grouped_ffn_time_next_call(None), "moe_grouped_ffn_time_next_call")
